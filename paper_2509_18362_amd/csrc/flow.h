@@ -49,8 +49,9 @@ enum FlowPhase : int { FL_PROJH = 0, FL_PROJE, FL_QKV, FL_O, FL_GATEUP, FL_DOWN,
 
 // One matrix phase as a list of rows (run-time description): up to three matrices stacked row-wise.  PAIRED: the
 // rows of [w_gate; w_up] dealt so that a wave gets row q of both, one after the other (its j-th row is gate or up row
-// (j / 2) * nw + w for j < 2 * pair_rounds; the F % nw rows that are left over are dealt singly: gate rows to waves
-// 0 .. rem-1, up rows to waves rem .. 2 rem - 1).  Virtual row v = w + j * nw, as in every other phase.
+// (j / 2) * nw + w for j < 2 * pair_rounds; the rem = F % nw rows of each matrix that are left over are dealt singly:
+// rem gate rows, then rem up rows, numbered on from the pairs - 2 rem may exceed nw, the waves then get a second
+// round of them).  Virtual row v = w + j * nw, as in every other phase.
 struct FlowJob {
     const uint16_t *base[3];
     int seg1, seg2; // first row of the second and of the third matrix
@@ -73,8 +74,9 @@ struct FlowJob {
                 mat = j & 1;
                 r = (j >> 1) * nw + w;
             } else {
-                mat = w < rem ? 0 : 1;
-                r = pair_rounds * nw + (w < rem ? w : w - rem);
+                const int i = v - 2 * pair_rounds * nw; // 0 .. 2 rem - 1
+                mat = i < rem ? 0 : 1;
+                r = pair_rounds * nw + (i < rem ? i : i - rem);
             }
             return (mat ? base[1] : base[0]) + (size_t)r * pitch; // (no run-time index: the struct stays in registers)
         }
@@ -648,7 +650,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
                                 else
                                     st_tagged(out_t + (c_j >> 1) * nw + w, silu_mul(gate_saved, val), out_tag);
                             } else { // dealt singly: gate values, then up values, behind the pairs
-                                st_tagged(out_t + job.pair_rounds * nw + w, val, out_tag);
+                                st_tagged(out_t + c_row - job.pair_rounds * nw, val, out_tag);
                             }
                             break;
                         }

@@ -384,6 +384,22 @@ def test_single_launch_one_sequence_row_streaming(gpu, hq, hkv, hd):
         eng.close()
 
 
+@pytest.mark.parametrize("d_ffn", [1288, 3400])
+def test_single_launch_gate_and_up_rows_left_over(gpu, d_ffn):
+    """The gate and up rows beyond whole rounds of the grid's 2048 waves are dealt singly; where more than 1024 of each
+    are left over (1288 without a round of pairs, 1352 behind one) they take two rounds of the waves."""
+    binding = gpu["binding"]
+    shape = synth.HeadShape(512, 4, 2, 128, d_ffn, 2048)
+    wl = synth.Workload(f"ffn_{d_ffn}", 90 + d_ffn % 7, shape, 1, 0, 0, (512,), 3, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    act = synth.make_activations(wl, ctx=np.array([70], dtype=np.int32), capacity=192)
+    eng = binding.DraftEngine(shape, w, [synth.make_subsets(wl)[0]], 1, 192, 3)
+    for _ in range(2):
+        ref, res, caches = run_both(gpu, shape, w, w, act, [synth.make_subsets(wl)[0]], 0, 3, engine=eng)
+        check_chain(ref, res, caches, act["kv_len"], 3, need_clear=False)
+    eng.close()
+
+
 # ------------------------------------------------------------------------------------------ block of new positions
 def extend_inputs(shape, act, m_max, seed):
     """Position-major inputs of the multi-position first step: hidden states with the workload's spread, tokens."""
