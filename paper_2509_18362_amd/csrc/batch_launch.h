@@ -17,10 +17,13 @@ int batch_epilogue_grid(int phase, const DraftParams &p, int na);
 // the preparation kernel before step `step` (step == K: after the last step), all sequences
 void launch_bprep(const DraftParams &p, int step, hipStream_t st);
 
-// a matrix phase (BG_* index) over all p.B rows as one tiled matrix product (rows_gemm.h); the output head leaves
-// logits only, no candidates.  rows_gemm_serves: the phase's reduction length is a whole number of the tilings' rounds of steps
+// A matrix phase (BG_* index) over all p.B rows as one tiled matrix product (rows_gemm.h).  The output head leaves
+// rows_head_cands candidates per row, or none where the caller wants logits only.  part_floats: room of the partial
+// buffer.  rows_gemm_serves: the phase's reduction length is a whole number of steps.
 bool rows_gemm_serves(int phase, const DraftParams &p);
-void launch_rows_gemm(int phase, const DraftParams &p, int step, int cus, hipStream_t st);
+int rows_head_cands(const DraftParams &p, int cus);
+void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
+                      hipStream_t st);
 
 // matrix-core attention (attn_mfma.h): dynamic LDS, and the launch for query-group size G and head dimension HD
 size_t attn_mfma_lds_bytes(int G, int HD);

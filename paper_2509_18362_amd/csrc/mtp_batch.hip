@@ -73,29 +73,35 @@ __global__ __launch_bounds__(kBlock) void k_bprep(DraftParams p, int step) {
     phase_bprep(p, step, smem);
 }
 
-// a matrix phase over all p.B rows as one tiled matrix product (rows_gemm.h); at most 128 registers, so that two
-// workgroups of the 80 KB tiling (four of the 40 KB one) share a CU
-template <int PH>
-__global__ __launch_bounds__(kBlock, 4) void k_rows_gemm(DraftParams p, int step) {
-    extern __shared__ __align__(16) char smem[];
+// A matrix phase over all p.B rows as one tiled matrix product (rows_gemm.h).  PH: a BG_* index, or kHeadLogits for the
+// output head without candidates.  One workgroup per CU (144 KB of LDS, up to 256 registers).
+constexpr int kHeadLogits = BG_COUNT;
+template <int PH, class F>
+__device__ __forceinline__ void with_phase(int step, F f) {
     if constexpr (PH == BG_PROJ)
-        rows_gemm<64, 128, 4, BgProj>(p, [](const DraftParams &q) { return BgProj(q); }, smem);
+        f([](const DraftParams &q) { return BgProj(q); });
     else if constexpr (PH == BG_QKV)
-        rows_gemm<128, 128, 4, BgQkv>(p, [](const DraftParams &q) { return BgQkv(q); }, smem);
+        f([](const DraftParams &q) { return BgQkv(q); });
     else if constexpr (PH == BG_OPROJ)
-        rows_gemm<64, 128, 4, BgOproj>(p, [](const DraftParams &q) { return BgOproj(q); }, smem);
+        f([](const DraftParams &q) { return BgOproj(q); });
     else if constexpr (PH == BG_GATEUP)
-        rows_gemm<128, 128, 4, BgGateUp>(p, [](const DraftParams &q) { return BgGateUp(q); }, smem);
+        f([](const DraftParams &q) { return BgGateUp(q); });
     else if constexpr (PH == BG_DOWN)
-        rows_gemm<64, 128, 4, BgDown>(p, [](const DraftParams &q) { return BgDown(q); }, smem);
+        f([](const DraftParams &q) { return BgDown(q); });
     else
-        rows_gemm<128, 256, 2, BgHeadLogits>(p, [step](const DraftParams &q) { return BgHeadLogits(q, step); }, smem);
+        f([step](const DraftParams &q) { return BgHeadRows<PH == BG_LMHEAD>(q, step); });
 }
-
-// q/k/v with the small tiles: for row counts whose small tiles still fit the chip one per CU
-__global__ __launch_bounds__(kBlock, 4) void k_rows_gemm_qkv_small(DraftParams p, int step) {
+template <int PH, int WM, int WN, int TJ>
+__global__ __launch_bounds__(kBlock, 2) void k_rows_gemm(DraftParams p, int step, int KP) {
     extern __shared__ __align__(16) char smem[];
-    rows_gemm<64, 128, 4, BgQkv>(p, [](const DraftParams &q) { return BgQkv(q); }, smem);
+    with_phase<PH>(step, [&](auto make) {
+        rows_gemm<WM, WN, TJ, decltype(make(p))>(p, make, KP, smem);
+    });
+}
+template <int PH>
+__global__ __launch_bounds__(kBlock) void k_rows_epilogue(DraftParams p, int step, int KP, int RT) {
+    __shared__ float scale[16];
+    with_phase<PH>(step, [&](auto make) { rows_epilogue<decltype(make(p))>(p, make, KP, RT, scale); });
 }
 
 template <int G, int HD>
@@ -172,6 +178,47 @@ bg_kernel_t pick(int phase, int na) {
     default: return pick_na<BG_LMHEAD>(na);
     }
 }
+// the tilings of the many-row matrix products
+typedef void (*rows_kernel_t)(DraftParams, int, int);
+struct RowsTileInfo {
+    int bm, bn, lds;
+    double step_us; // one reduction step of a workgroup that has its CU to itself
+};
+template <class T>
+constexpr RowsTileInfo rows_tile_info(double step_us) {
+    return RowsTileInfo{T::BM, T::BN, T::kLds, step_us};
+}
+constexpr int kRowsTiles = 3;
+constexpr RowsTileInfo kRowsTile[kRowsTiles] = {rows_tile_info<RowsTile<4, 2, 8>>(1.3), rows_tile_info<RowsTile<2, 4, 8>>(1.3),
+                                                rows_tile_info<RowsTile<2, 4, 6>>(1.0)};
+constexpr int kRowsMinSteps = 8;           // reduction steps a part keeps at least
+constexpr double kRowsFixedUs = 8.0;       // of a workgroup besides its steps
+constexpr double kRowsEpilogueUs = 6.0;    // the launch that adds the parts
+constexpr double kRowsPartUs = 8.0 / 5e6;  // a float of the parts written and read
+template <int PH>
+rows_kernel_t pick_rows(int tile) {
+    return tile == 0 ? k_rows_gemm<PH, 4, 2, 8> : tile == 1 ? k_rows_gemm<PH, 2, 4, 8> : k_rows_gemm<PH, 2, 4, 6>;
+}
+rows_kernel_t rows_kernel(int phase, int tile) {
+    switch (phase) {
+    case BG_PROJ: return pick_rows<BG_PROJ>(tile);
+    case BG_QKV: return pick_rows<BG_QKV>(tile);
+    case BG_OPROJ: return pick_rows<BG_OPROJ>(tile);
+    case BG_GATEUP: return pick_rows<BG_GATEUP>(tile);
+    case BG_DOWN: return pick_rows<BG_DOWN>(tile);
+    case BG_LMHEAD: return pick_rows<BG_LMHEAD>(tile);
+    default: return pick_rows<kHeadLogits>(tile);
+    }
+}
+void (*rows_epilogue_kernel(int phase))(DraftParams, int, int, int) {
+    switch (phase) {
+    case BG_PROJ: return k_rows_epilogue<BG_PROJ>;
+    case BG_QKV: return k_rows_epilogue<BG_QKV>;
+    case BG_OPROJ: return k_rows_epilogue<BG_OPROJ>;
+    case BG_GATEUP: return k_rows_epilogue<BG_GATEUP>;
+    default: return k_rows_epilogue<BG_DOWN>;
+    }
+}
 int tiles_for(int nb) { return nb <= 16 ? 1 : nb <= 32 ? 2 : 4; }
 template <int PH>
 bg_kernel_t pick_epilogue_na(int na) {
@@ -235,9 +282,10 @@ void launch_attn_mfma_block(int G, int HD, const DraftParams &p, int step, int g
 
 bool batch_allow_lds(size_t lds_limit) {
     bool ok = true;
-    for (bg_kernel_t k : {k_rows_gemm<BG_GATEUP>, k_rows_gemm<BG_LMHEAD>})
-        ok = ok && hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit) ==
-                       hipSuccess;
+    for (int ph = 0; ph <= kHeadLogits; ++ph)
+        for (int t = 0; t < kRowsTiles; ++t)
+            ok = ok && hipFuncSetAttribute((const void *)rows_kernel(ph, t), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds_limit) == hipSuccess;
     for (int hd = 64; hd <= 128; hd *= 2)
         for (int g = 1; g <= 8; g *= 2)
             ok = ok && hipFuncSetAttribute((const void *)attn_mfma_kernel(g, hd, false),
@@ -262,34 +310,61 @@ void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t ld
                            p, step);
 }
 
-bool rows_gemm_serves(int phase, const DraftParams &p) {
-    const int K = phase == BG_PROJ ? 2 * p.d : phase == BG_OPROJ ? p.qd : phase == BG_DOWN ? p.F : p.d;
-    return K % (kRgRound * kRgBK) == 0;
+namespace {
+int rows_k(int phase, const DraftParams &p) { // reduction length of a phase
+    return phase == BG_PROJ ? 2 * p.d : phase == BG_OPROJ ? p.qd : phase == BG_DOWN ? p.F : p.d;
 }
-void launch_rows_gemm(int phase, const DraftParams &p, int step, int cus, hipStream_t st) {
+int rows_n(int phase, const DraftParams &p) { // weight rows, in whole tiles of sixteen
     auto rows16 = [](int rows) { return (rows + 15) / 16 * 16; };
-    auto small = [&](bg_kernel_t k, int n) {
-        hipLaunchKernelGGL(k, dim3(rows_gemm_grid<64, 128>(p.B, n)), dim3(kBlock), sizeof(RowsGemmLds<64, 128>), st, p, step);
-    };
-    auto mid = [&](bg_kernel_t k, int n) {
-        hipLaunchKernelGGL(k, dim3(rows_gemm_grid<128, 128>(p.B, n)), dim3(kBlock), sizeof(RowsGemmLds<128, 128>), st, p, step);
-    };
-    auto large = [&](bg_kernel_t k, int n) {
-        hipLaunchKernelGGL(k, dim3(rows_gemm_grid<128, 256>(p.B, n)), dim3(kBlock), sizeof(RowsGemmLds<128, 256>), st, p, step);
-    };
-    switch (phase) {
-    case BG_PROJ: small(k_rows_gemm<BG_PROJ>, p.d); break;
-    case BG_QKV:
-        // a tile count between one and two per CU costs two rounds: small tiles only while they fit one per CU
-        if (rows_gemm_grid<64, 128>(p.B, rows16(p.qkv_dim)) <= cus)
-            small(k_rows_gemm_qkv_small, rows16(p.qkv_dim));
-        else
-            mid(k_rows_gemm<BG_QKV>, rows16(p.qkv_dim));
-        break;
-    case BG_OPROJ: small(k_rows_gemm<BG_OPROJ>, p.d); break;
-    case BG_GATEUP: mid(k_rows_gemm<BG_GATEUP>, 2 * rows16(p.F)); break;
-    case BG_DOWN: small(k_rows_gemm<BG_DOWN>, p.d); break;
-    default: large(k_rows_gemm<BG_LMHEAD>, rows16(p.n)); break;
+    return phase == BG_QKV      ? rows16(p.qkv_dim)
+           : phase == BG_GATEUP ? 2 * rows16(p.F)
+           : phase >= BG_LMHEAD ? rows16(p.n)
+                                : p.d;
+}
+// The tiling and the number of reduction parts with the shortest estimated time: rounds of one workgroup per CU, each its
+// share of the steps, and the parts' sums written and read once.  The constants are this kernel's own times at 512 rows
+// (a step of 1.3 us in long reductions, 8 us from launch to first step and from last step to end).  Parts pay where a
+// phase has few tiles: 4096 weight rows at 512 rows are 32 tiles of 256 x 256 and take 84 us in eight parts, 270 in one.
+struct RowsPlan {
+    int tile, kp, mb, nb;
+};
+RowsPlan rows_plan(int phase, const DraftParams &p, int cus, size_t part_floats) {
+    const int steps = rows_k(phase, p) / kRgBK, n = rows_n(phase, p);
+    RowsPlan best{};
+    double best_us = 1e30;
+    for (int t = 0; t < kRowsTiles; ++t) {
+        const RowsTileInfo &ti = kRowsTile[t];
+        const int mb = (p.B + ti.bm - 1) / ti.bm, nb = (n + ti.bn - 1) / ti.bn;
+        for (int kp = 1; kp <= (phase >= BG_LMHEAD ? 1 : 16) && (kp == 1 || steps / kp >= kRowsMinSteps); ++kp) {
+            const double sums = (double)kp * n * mb * ti.bm; // floats of the parts
+            if (kp > 1 && sums > (double)part_floats) break;
+            const int rounds = (mb * nb * kp + cus - 1) / cus;
+            const double us = rounds * (kRowsFixedUs + (steps + kp - 1) / kp * ti.step_us) +
+                              (kp > 1 ? kRowsEpilogueUs + sums * kRowsPartUs : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                best = RowsPlan{t, kp, mb, nb};
+            }
+        }
+    }
+    return best;
+}
+} // namespace
+
+bool rows_gemm_serves(int phase, const DraftParams &p) { return rows_k(phase, p) % kRgBK == 0; }
+int rows_head_cands(const DraftParams &p, int cus) { return rows_plan(BG_LMHEAD, p, cus, 0).nb; }
+void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
+                      hipStream_t st) {
+    const RowsPlan pl = rows_plan(phase, p, cus, part_floats);
+    const int ph = phase == BG_LMHEAD && logits_only ? kHeadLogits : phase;
+    const int units = pl.nb * pl.kp; // (N block, part) pairs: the M blocks of eight neighbouring ones form one group
+    hipLaunchKernelGGL(rows_kernel(ph, pl.tile), dim3((units + 7) / 8 * 8 * pl.mb), dim3(kBlock), kRowsTile[pl.tile].lds, st,
+                       p, step, pl.kp);
+    if (pl.kp > 1) {
+        const int rt = pl.mb * kRowsTile[pl.tile].bm / 16, live = (p.B + 15) / 16;
+        const int groups = (rows_n(phase, p) / 16 / (phase == BG_GATEUP ? 2 : 1) + kWaves - 1) / kWaves;
+        hipLaunchKernelGGL(rows_epilogue_kernel(phase), dim3(live, std::max(1, std::min(groups, 8 * cus / live))), dim3(kBlock),
+                           0, st, p, step, pl.kp, rt);
     }
 }
 

@@ -360,7 +360,7 @@ struct WsLayout {
     size_t x, qkv, attn, o, gu, dn, hhat, err, cand, rope_inv, attn_part, total;
     size_t xt, qkvt, attnt, ot, gut, dnt, candt, tagged_end; // tagged hand-over vectors of the barrier-free kernel
     // batched path (max_batch above kBatchMinSeq - 1 only)
-    size_t act0, act1, ssq, part, ticket, a_lo, attn_ticket, row_len, seq_list, list_ids, list_n, list_cands;
+    size_t act0, act1, ssq, part, part_floats, ticket, a_lo, attn_ticket, row_len, seq_list, list_ids, list_n, list_cands;
     int a_stride;
 };
 
@@ -424,6 +424,7 @@ WsLayout ws_layout(const mtp_config &c) {
         // workgroup (of at most kMaxFusedGrid), unsplit ones every tile once
         size_t tiles = std::max(batch_max_tiles(c), (size_t)2 * kBatchGroupTiles * kMaxFusedGrid);
         l.part = take(tiles * (kBatchPassSeq / 16) * kBatchTileBytes);
+        l.part_floats = tiles * (kBatchPassSeq / 16) * kBatchTileBytes / 4;
         l.ticket = take((size_t)kMaxFusedGrid * 4);
     }
     l.total = off;
@@ -640,6 +641,10 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             groups.n[g] = s < 0 ? c.vocab_size : h->subset_n[s];
         }
         subset_index = seq_subset[0];
+        if (groups.count == 1) { // one list for everybody is the plain call
+            groups.count = 0;
+            seq_subset = nullptr;
+        }
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
@@ -990,16 +995,23 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         // grid is then this number for every pass of the call (workgroups without work leave "no candidate")
         p.head_grid = max_cands;
         publish_lists();
-        // Many rows: matrix phases as tiled matrix products over all rows instead of one pass of the batched core per
-        // 64.  The output head has hundreds of weight-row blocks at any row count, but its tiled form leaves no
-        // candidates: for callers that want logits only (the training loss), from 65 rows on.  The body's phases have
-        // as few as 32 blocks of weight rows and fill the chip only from four passes' worth of rows on (measured at
-        // 128 rows: 1034 us per step against 757 with two passes, at 256 rows 1350 against 1458).
-        const bool tiled = ext && ext->logits_only && B > kBatchPassSeq && !groups.count && logits_out;
-        const bool tiled_body = B >= 4 * kBatchPassSeq;
+        // More rows than one pass of the batched core: every matrix phase as a tiled matrix product over all rows.  Already
+        // with two passes' worth the second reading of the weights costs more than the tiles' padding (a block of 66 / 128
+        // / 256 / 512 positions at a 32768-row head: 394 / 446 / 550 / 849 us against 523 / 580 / 946 / 1434 in passes of
+        // 64, whose body was tiled from 256 rows on).  Several id lists in one call keep their passes for the head.
+        const bool many = B > kBatchPassSeq;
+        const bool logits_only = ext && ext->logits_only && logits_out;
+        bool many_head = many && !groups.count && rows_gemm_serves(BG_LMHEAD, p);
+        if (many_head && !logits_only) { // one candidate per row and block of weight rows
+            const int cands = rows_head_cands(p, grid);
+            if (cands <= kMaxFusedGrid)
+                p.head_grid = cands;
+            else
+                many_head = false;
+        }
         auto matrix_phase = [&](int timed_as, int ph, int step) {
-            if ((ph == BG_LMHEAD ? tiled : tiled_body) && rows_gemm_serves(ph, p)) {
-                launch_rows_gemm(ph, p, step, h->num_cus, st);
+            if (ph == BG_LMHEAD ? many_head : many && rows_gemm_serves(ph, p)) {
+                launch_rows_gemm(ph, logits_only, p, step, grid, l.part_floats, st);
                 mark_end(timed_as, step);
                 return;
             }

@@ -486,6 +486,25 @@ def test_tiny_extend_block_of_positions(gpu, tiny, ctx, ext, m_max):
     check_extend(ref, res, caches, act, ext_len)
 
 
+@pytest.mark.parametrize("d_ffn,subset", [(1056, 0), (1064, -1)])
+@pytest.mark.parametrize("rows", [65, 129, 257, 400])
+def test_many_rows_tiled_matrix_products(gpu, d_ffn, subset, rows):
+    """More than 64 rows: every phase as a tiled matrix product.  One row past one and two blocks of 128 and one of 256
+    rows, a block that is neither; reductions of an odd number of steps (1056) and, for the down projection of 1064, not
+    a whole number (the batched core then); gate/up rows and a vocabulary that end inside a tile of sixteen; the list
+    and the full head; the candidates of a row from several blocks of weight rows."""
+    shape = synth.HeadShape(512, 4, 2, 128, d_ffn, 2111)
+    wl = synth.Workload(f"rows_{d_ffn}", 95, shape, 1, 0, 0, (517,), 1, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=np.array([40], dtype=np.int32), capacity=448)
+    hid, tok = extend_inputs(shape, act, rows, 230 + rows)
+    ext_len = np.array([rows], dtype=np.int32)
+    ref, res, caches = run_extend(gpu, shape, w, w, act, [ids], subset, hid, tok, ext_len)
+    assert res["err"] == 0
+    check_extend(ref, res, caches, act, ext_len)
+
+
 def test_tiny_extend_long_capacity_matrix_core_attention(gpu, tiny):
     """A large capacity makes the splits long enough for the matrix-core attention (which merges its own splits)."""
     act = synth.make_activations(tiny["wl"], ctx=np.array([0, 31, 300, 1000], dtype=np.int32), capacity=32768)
