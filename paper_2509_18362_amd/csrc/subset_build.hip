@@ -41,38 +41,28 @@ __global__ void k_subset_clear(unsigned *counts, int V, unsigned *state, int sta
     if (i < state_words) state[i] = i == 2 ? (unsigned)n : 0u; // [2]: ids still to be found by the selection
 }
 
-// grid (slices, chunks): workgroup (s, c) counts the ids of chunk c in slice s of the stream.
-// What bounds it (measured on streams of 2^26 tokens, uniform or long-tailed alike): the LDS retires about one lane's
-// atomic per clock and CU, whatever the addresses - 109 us for 2^26 tokens over 256 CUs - and the vector instructions
-// around an atomic (range check, address, increment) come on top; reading the stream twice takes 77 us and hides behind
-// them.  Counting a stream's few hottest ids apart, per wave in scalar registers (they are what an LDS atomic is replayed
-// for when lanes share an address), was built and measured: each compare per token costs more than the replays it saves.
+// grid (slices, chunks): workgroup (s, c) counts the ids of chunk c in slice s of the stream.  The chunks' workgroups of a
+// slice are a multiple of eight apart in the launch order (subset_slices), so they run on the same compute die.
+// What bounds it: reading the stream once per chunk.  Of the second chunk's reads about half find the line in the die's L2
+// (2^26 tokens, 151680 ids: 470 MB from memory for a stream of 268 MB), and the counting hides behind that: the LDS takes
+// a wave's adds in 2 to 6 ns whatever the addresses (19 us for all of a CU's), so the loop over whole rounds does nothing
+// but form an address and an increment: no check for the slice's end, no count of ids outside the vocabulary (that is
+// what is missing from the sum of all counts), no branch around a load.  102 us (111 with those in the loop).
 __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restrict__ tokens, long long n_tokens, int V,
-                                                            unsigned *counts, unsigned *state, unsigned *partials) {
+                                                            unsigned *counts, unsigned *partials) {
     extern __shared__ unsigned bins[]; // word w: ids c0 + 2 w (low half) and c0 + 2 w + 1 (high half)
-    __shared__ unsigned invalid_wg;
     const int c0 = blockIdx.y * kChunkIds;
     const int nb = min(kChunkIds, V - c0), nw = (nb + 1) / 2, nw4 = (nw + 3) / 4 * 4; // (LDS holds kChunkIds / 2 words)
     for (int i4 = threadIdx.x * 4; i4 < nw4; i4 += kHistBlock * 4)
         *reinterpret_cast<uint4 *>(bins + i4) = uint4{0u, 0u, 0u, 0u};
-    if (threadIdx.x == 0) invalid_wg = 0u;
     __syncthreads();
     // slices of whole 16-byte groups; the last slice also takes the tail
     const long long groups = n_tokens / 4;
     const long long per = (groups + gridDim.x - 1) / gridDim.x;
     const long long g0 = min(groups, per * blockIdx.x), g1 = min(groups, g0 + per);
-    const bool count_invalid = blockIdx.y == 0;
-    unsigned invalid = 0u; // uniform: ids outside the vocabulary this WAVE has seen
-    auto popcount = [](unsigned long long m) { // kept where it is written (the compiler would collect the lane masks of
-        unsigned c;                            // a whole round first, which do not fit the scalar registers)
-        asm volatile("s_bcnt1_i32_b64 %0, %1" : "=s"(c) : "s"(m));
-        return c;
-    };
-    // one token per lane; live: the lane holds a token (all lanes of the wave call this together)
-    auto one = [&](int t, bool live) {
-        const unsigned rel = (unsigned)(t - c0);
-        if (live && rel < (unsigned)nb) atomicAdd(&bins[rel >> 1], 1u << ((rel & 1u) * 16u));
-        if (count_invalid) invalid += popcount(__builtin_amdgcn_ballot_w64(live && (unsigned)t >= (unsigned)V));
+    auto one = [&](int t) {
+        const unsigned rel = (unsigned)(t - c0); // (c0 is even)
+        if (rel < (unsigned)nb) atomicAdd(&bins[rel >> 1], 1u << ((rel & 1u) * 16u));
     };
     // moves the fields of at least `at` to the global counts (at = 1: all that is left)
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -113,41 +103,56 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
     constexpr int kUnroll = 4;                                      // 16-byte loads per thread and round
     constexpr long long kIter = (long long)kHistBlock * kUnroll;    // groups per round of the workgroup
     static_assert(kSweepBlock % (kHistBlock * kUnroll * 4) == 0, "a block of tokens is a whole number of rounds");
-    // the loads of round i + 1 are requested before round i is counted
-    auto fetch = [&](long long gb, i32x4(&v)[kUnroll]) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const long long g = gb + (long long)u * kHistBlock + threadIdx.x;
-            v[u] = g < g1 ? t4[g] : i32x4{0, 0, 0, 0};
-        }
-    };
     if (blockIdx.x == gridDim.x - 1) { // the stream's last one to three tokens, while the bins are still empty
         const long long i = groups * 4 + threadIdx.x;
-        one(i < n_tokens ? tokens[i] : 0, i < n_tokens);
+        if (i < n_tokens) one(tokens[i]);
     }
-    i32x4 v[kUnroll], vn[kUnroll];
-    fetch(g0, vn);
-    int since_sweep = 0; // tokens counted since the last sweep (uniform)
-    for (long long gb = g0; gb < g1; gb += kIter) {
+    if (g0 < g1) {
+        // the loads of round i + 1 are requested before round i is counted; past the slice's end its last group is read
+        // again (and not counted)
+        auto fetch = [&](long long gb, i32x4(&v)[kUnroll]) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) v[u] = vn[u];
-        fetch(gb + kIter, vn); // (past the slice's end: nothing is loaded)
+            for (int u = 0; u < kUnroll; ++u) v[u] = t4[min(gb + (long long)u * kHistBlock + threadIdx.x, g1 - 1)];
+        };
+        const long long rounds = (g1 - g0) / kIter; // whole ones
+        i32x4 va[kUnroll], vb[kUnroll];
+        fetch(g0, va);
+        int since_sweep = 0; // tokens counted since the last sweep (uniform)
+        auto round = [&](long long r, const i32x4(&v)[kUnroll], i32x4(&next)[kUnroll]) {
+            fetch(g0 + (r + 1) * kIter, next);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const bool live = gb + (long long)u * kHistBlock + threadIdx.x < g1;
-            one(v[u].x, live);
-            one(v[u].y, live);
-            one(v[u].z, live);
-            one(v[u].w, live);
+            for (int u = 0; u < kUnroll; ++u) {
+                one(v[u].x);
+                one(v[u].y);
+                one(v[u].z);
+                one(v[u].w);
+            }
+            since_sweep += (int)kIter * 4;
+            if (since_sweep >= kSweepBlock) {
+                sweep(kSweepAt);
+                since_sweep = 0;
+            }
+        };
+        long long r = 0;
+        for (; r + 1 < rounds; r += 2) {
+            round(r, va, vb);
+            round(r + 1, vb, va);
         }
-        since_sweep += (int)kIter * 4;
-        if (since_sweep >= kSweepBlock && gb + kIter < g1) {
-            sweep(kSweepAt);
-            since_sweep = 0;
+        if (r < rounds) {
+            round(r, va, vb);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) va[u] = vb[u];
         }
+        // what is left of the slice: less than a round, which fits what the sweeps leave room for
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            if (g0 + rounds * kIter + (long long)u * kHistBlock + threadIdx.x < g1) {
+                one(va[u].x);
+                one(va[u].y);
+                one(va[u].z);
+                one(va[u].w);
+            }
     }
-    // (the waves' counts of invalid ids meet in LDS first: same-address device atomics take ~40 ns each)
-    if ((threadIdx.x & 63) == 0 && invalid) atomicAdd(&invalid_wg, invalid);
     // What is left in the bins: with room for it, the workgroup's bins go to memory as they are (k_subset_reduce adds
     // the workgroups' copies up); without, every non-zero field is added to the global counts (up to 80 000 atomics per
     // workgroup, 19 M over the grid when every id occurs: slower than the counting itself).
@@ -159,14 +164,20 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
     } else {
         sweep(1u); // (begins with a barrier)
     }
-    if (threadIdx.x == 0 && invalid_wg) atomicAdd(&state[0], invalid_wg);
 }
 
 // counts[id] += the sum over the slices' workgroups of the id's field; thread = one word (two ids) of one chunk.
-// The final counts pass through here, so the first histogram pass of the selection (top digit) is taken along.
+// The final counts pass through here, so the first histogram pass of the selection (top digit), their sum and the copy
+// for the caller are taken along.
 constexpr int kSelBuckets0 = 2048;
+constexpr int kSumSlots = 64; // words the sum of all counts is spread over (same-address device atomics: ~40 ns each)
+__device__ __forceinline__ void add_to_sum(unsigned x, unsigned *sums) { // whole waves
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) x += __shfl_xor(x, off, 64);
+    if ((threadIdx.x & 63) == 0 && x) atomicAdd(&sums[(blockIdx.x * 4 + (threadIdx.x >> 6)) % kSumSlots], x);
+}
 __global__ __launch_bounds__(256) void k_subset_reduce(const unsigned *__restrict__ partials, int slices, int V,
-                                                       unsigned *counts, unsigned *hist0) {
+                                                       unsigned *counts, unsigned *hist0, unsigned *sums, int *counts_out) {
     __shared__ unsigned hist[kSelBuckets0];
     for (int i = threadIdx.x; i < kSelBuckets0; i += 256) hist[i] = 0u;
     __syncthreads();
@@ -187,6 +198,16 @@ __global__ __launch_bounds__(256) void k_subset_reduce(const unsigned *__restric
                 hi += x[u] >> 16;
             }
         }
+        for (; sl + 16 <= slices; sl += 16) {
+            unsigned x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = src[(size_t)(sl + u) * (kChunkIds / 2)];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                lo += x[u] & 0xffffu;
+                hi += x[u] >> 16;
+            }
+        }
         for (; sl < slices; ++sl) {
             const unsigned x = src[(size_t)sl * (kChunkIds / 2)];
             lo += x & 0xffffu;
@@ -194,11 +215,14 @@ __global__ __launch_bounds__(256) void k_subset_reduce(const unsigned *__restric
         }
         lo += counts[c0 + 2 * w]; // (the counting kernel, which may have added to these words, has finished)
         counts[c0 + 2 * w] = lo;
+        if (counts_out) counts_out[c0 + 2 * w] = (int)lo;
     }
     if (has_hi) {
         hi += counts[c0 + 2 * w + 1];
         counts[c0 + 2 * w + 1] = hi;
+        if (counts_out) counts_out[c0 + 2 * w + 1] = (int)hi;
     }
+    add_to_sum(lo + (has_hi ? hi : 0u), sums);
     // top digit: almost every id has a zero there, so those are counted per wave (one LDS atomic instead of up to 128
     // on the same word)
     const unsigned dlo = lo >> 21, dhi = hi >> 21;
@@ -221,10 +245,11 @@ constexpr int kCmpGroups = 160; // workgroups of the compaction: one round of 10
 constexpr int kSelPasses = 3, kSelBuckets = 2048;
 __host__ __device__ constexpr int sel_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
 __host__ __device__ constexpr int sel_bits(int pass) { return pass == 2 ? 10 : 11; }
-// state: [0] invalid ids, [1] T, [2] n, then r at [3]; [4 + 2 p], [5 + 2 p]: prefix and ids still needed after the walk
-// of pass p; then kSelPasses x kSelBuckets bucket counts, then per-workgroup (above, ties) totals of the compaction
+// state: [0] unused, [1] T, [2] n, then r at [3]; [4 + 2 p], [5 + 2 p]: prefix and ids still needed after the walk
+// of pass p; then kSelPasses x kSelBuckets bucket counts, then per-workgroup (above, ties) totals of the compaction, then
+// the slots of the sum of all counts
 constexpr int kStateAfter = 4, kStateHist = 16, kStateTotals = kStateHist + kSelPasses * kSelBuckets,
-              kStateWordsFull = kStateTotals + 2 * kCmpGroups;
+              kStateSums = kStateTotals + 2 * kCmpGroups, kStateWordsFull = kStateSums + kSumSlots;
 
 // inclusive scan of one value per thread over the workgroup; scratch holds one word per wave; returns the total too
 __device__ __forceinline__ unsigned block_scan(unsigned v, unsigned *scratch, unsigned &total) {
@@ -333,9 +358,21 @@ __global__ __launch_bounds__(kSelBlock) void k_subset_cmp_count(const unsigned *
     }
 }
 
+// ids outside the vocabulary: the tokens that no count has (whole workgroups; wave 0 works)
+__device__ __forceinline__ void put_invalid(const unsigned *state, long long n_tokens, int *invalid_out) {
+    static_assert(kSumSlots == 64, "one slot per lane");
+    if (!invalid_out || threadIdx.x >= 64) return;
+    unsigned x = state[kStateSums + threadIdx.x];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) x += __shfl_xor(x, off, 64);
+    if (threadIdx.x == 0) invalid_out[0] = (int)(n_tokens - (long long)x);
+}
+
 __global__ __launch_bounds__(kSelBlock) void k_subset_cmp_write(const unsigned *__restrict__ counts, int V, int n,
-                                                                const unsigned *__restrict__ state, int *ids_out) {
+                                                                const unsigned *__restrict__ state, int *ids_out,
+                                                                long long n_tokens, int *invalid_out) {
     __shared__ unsigned scratch[kSelBlock / 64];
+    if (blockIdx.x == gridDim.x - 1) put_invalid(state, n_tokens, invalid_out);
     const unsigned T = state[1], r = state[3];
     // what the workgroups before this one hold: summed by the whole workgroup
     unsigned above_before, ties_before;
@@ -363,11 +400,17 @@ __global__ __launch_bounds__(kSelBlock) void k_subset_cmp_write(const unsigned *
     }
 }
 
-__global__ void k_subset_export(const unsigned *counts, int V, const unsigned *state, int *counts_out,
+// the sum of all counts, where k_subset_reduce has not formed it
+__global__ __launch_bounds__(256) void k_subset_sum(const unsigned *__restrict__ counts, int V, unsigned *sums) {
+    unsigned x = 0u;
+    for (int v = blockIdx.x * 256 + threadIdx.x; v < V; v += gridDim.x * 256) x += counts[v];
+    add_to_sum(x, sums);
+}
+__global__ void k_subset_export(const unsigned *counts, int V, const unsigned *state, long long n_tokens, int *counts_out,
                                 int *invalid_out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (counts_out && i < V) counts_out[i] = (int)counts[i];
-    if (invalid_out && i == 0) invalid_out[0] = (int)state[0];
+    if (blockIdx.x == 0) put_invalid(state, n_tokens, invalid_out);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -377,7 +420,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // the library runs on holds its own copy at its own address until the process ends; host code reaches it only through
 // the per-device pointer below (the array's name is a host-side stand-in, not a device address).
 constexpr int kStaticMaxVocab = 262144;
-constexpr int kStateWordsFullStatic = 16 + 3 * 2048 + 2 * 160; // = kStateWordsFull (spelled out: used in the array bound)
+constexpr int kStateWordsFullStatic = 16 + 3 * 2048 + 2 * 160 + 64; // = kStateWordsFull (spelled out: used in the array bound)
 __device__ __align__(256) unsigned scratch[kStaticMaxVocab + kStateWordsFullStatic];
 static_assert(kStateWordsFullStatic == kStateWordsFull, "scratch layout");
 constexpr int kMaxDevices = 64;
@@ -414,7 +457,11 @@ int32_t subset_setup(int dev, bool want_scratch, unsigned **scratch_out) {
 
 // workgroups per chunk of the counting kernel: 256 workgroups in all (one per CU of the device this is written for),
 // fixed so that the workspace size does not depend on the device
-int subset_slices(int V) { return std::max(1, 256 / ((V + kChunkIds - 1) / kChunkIds)); }
+// (a multiple of eight: the chunks' workgroups of a slice then share a compute die, see k_subset_hist)
+int subset_slices(int V) {
+    const int s = 256 / ((V + kChunkIds - 1) / kChunkIds);
+    return s >= 8 ? s / 8 * 8 : std::max(1, s);
+}
 size_t subset_partial_words(int V) { return (size_t)subset_slices(V) * ((V + kChunkIds - 1) / kChunkIds) * (kChunkIds / 2); }
 
 // everything after the argument checks: `work` holds V counts followed by the selection state and, with_partials, by
@@ -429,19 +476,24 @@ int32_t subset_build_on(const int32_t *tokens, int64_t n_tokens, int32_t V, int3
     const int chunks = (V + kChunkIds - 1) / kChunkIds;
     const int slices = subset_slices(V);
     hipLaunchKernelGGL(k_subset_hist, dim3(slices, chunks), dim3(kHistBlock), kChunkIds * 2, st, tokens,
-                       (long long)n_tokens, V, counts, state, partials);
+                       (long long)n_tokens, V, counts, partials);
     if (partials)
         hipLaunchKernelGGL(k_subset_reduce, dim3((kChunkIds / 2 + 255) / 256, chunks), dim3(256), 0, st, partials, slices,
-                           V, counts, state + kStateHist);
+                           V, counts, state + kStateHist, state + kStateSums, counts_out);
+    else if (invalid_out)
+        hipLaunchKernelGGL(k_subset_sum, dim3(64), dim3(256), 0, st, counts, V, state + kStateSums);
     if (n > 0) {
         for (int pass = partials ? 1 : 0; pass < kSelPasses; ++pass) // (with partials, pass 0 was taken along above)
             hipLaunchKernelGGL(k_subset_sel_hist, dim3(kSelGroups), dim3(kSelBlock), 0, st, counts, V, pass, state);
         hipLaunchKernelGGL(k_subset_cmp_count, dim3(kCmpGroups), dim3(kSelBlock), 0, st, counts, V, state);
-        hipLaunchKernelGGL(k_subset_cmp_write, dim3(kCmpGroups), dim3(kSelBlock), 0, st, counts, V, n, state, ids_out);
+        hipLaunchKernelGGL(k_subset_cmp_write, dim3(kCmpGroups), dim3(kSelBlock), 0, st, counts, V, n, state, ids_out,
+                           (long long)n_tokens, invalid_out);
     }
-    if (counts_out || invalid_out)
-        hipLaunchKernelGGL(k_subset_export, dim3((V + 255) / 256), dim3(256), 0, st, counts, V, state, counts_out,
-                           invalid_out);
+    // what the kernels above have not handed out already
+    int32_t *counts_left = partials ? nullptr : counts_out, *invalid_left = n > 0 ? nullptr : invalid_out;
+    if (counts_left || invalid_left)
+        hipLaunchKernelGGL(k_subset_export, dim3(counts_left ? (V + 255) / 256 : 1), dim3(256), 0, st, counts, V, state,
+                           (long long)n_tokens, counts_left, invalid_left);
     if (hipGetLastError() != hipSuccess) return MTP_ERR_HIP;
     return MTP_OK;
 }
