@@ -17,11 +17,11 @@ int batch_epilogue_grid(int phase, const DraftParams &p, int na);
 // the preparation kernel before step `step` (step == K: after the last step), all sequences
 void launch_bprep(const DraftParams &p, int step, hipStream_t st);
 
-// A matrix phase (BG_* index) over all p.B rows as one tiled matrix product (rows_gemm.h).  The output head leaves
-// rows_head_cands candidates per row, or none where the caller wants logits only.  part_floats: room of the partial
-// buffer.  rows_gemm_serves: the phase's reduction length is a whole number of steps.
-bool rows_gemm_serves(int phase, const DraftParams &p);
-int rows_head_cands(const DraftParams &p, int cus);
+// A matrix phase (BG_* index) over the rows p.seq_lo .. p.seq_hi - 1 as one tiled matrix product (rows_gemm.h).  The output
+// head leaves rows_head_cands candidates per row, or none where the caller wants logits only.  part_floats: room of the
+// partial buffer.  rows_gemm_serves: it can (the reduction length is a whole number of steps) and it is the faster kernel.
+bool rows_gemm_serves(int phase, const DraftParams &p, int cus);
+int rows_head_cands(const DraftParams &p, int cus, size_t part_floats);
 void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
                       hipStream_t st);
 

@@ -91,16 +91,14 @@ __device__ __forceinline__ void with_phase(int step, F f) {
     else
         f([step](const DraftParams &q) { return BgHeadRows<PH == BG_LMHEAD>(q, step); });
 }
-template <int PH, int WM, int WN, int TJ>
+template <int PH, class T>
 __global__ __launch_bounds__(kBlock, 2) void k_rows_gemm(DraftParams p, int step, int KP) {
     extern __shared__ __align__(16) char smem[];
-    with_phase<PH>(step, [&](auto make) {
-        rows_gemm<WM, WN, TJ, decltype(make(p))>(p, make, KP, smem);
-    });
+    with_phase<PH>(step, [&](auto make) { rows_gemm<T, decltype(make(p))>(p, make, KP, smem); });
 }
 template <int PH>
 __global__ __launch_bounds__(kBlock) void k_rows_epilogue(DraftParams p, int step, int KP, int RT) {
-    __shared__ float scale[16];
+    __shared__ __align__(16) float scale[16 + kWaves * 16 * 2]; // the rows' norm scales, the waves' candidates
     with_phase<PH>(step, [&](auto make) { rows_epilogue<decltype(make(p))>(p, make, KP, RT, scale); });
 }
 
@@ -181,23 +179,41 @@ bg_kernel_t pick(int phase, int na) {
 // the tilings of the many-row matrix products
 typedef void (*rows_kernel_t)(DraftParams, int, int);
 struct RowsTileInfo {
-    int bm, bn, lds;
+    int bm, bn, bk, lds;
     double step_us; // one reduction step of a workgroup that has its CU to itself
 };
 template <class T>
 constexpr RowsTileInfo rows_tile_info(double step_us) {
-    return RowsTileInfo{T::BM, T::BN, T::kLds, step_us};
+    return RowsTileInfo{T::BM, T::BN, T::BK, T::kLds, step_us};
 }
-constexpr int kRowsTiles = 3;
-constexpr RowsTileInfo kRowsTile[kRowsTiles] = {rows_tile_info<RowsTile<4, 2, 8>>(1.3), rows_tile_info<RowsTile<2, 4, 8>>(1.3),
-                                                rows_tile_info<RowsTile<2, 4, 6>>(1.0)};
+typedef RowsTile<4, 4, 2, 8, 3> Rows256x256;
+typedef RowsTile<4, 2, 4, 8, 3> Rows128x512;
+typedef RowsTile<4, 2, 4, 6, 3> Rows128x384;
+typedef RowsTile<2, 2, 4, 4, 3, 64> Rows64x256;
+typedef RowsTile<2, 2, 4, 2, 4, 64> Rows64x128;
+typedef RowsTile<1, 2, 4, 2, 6, 64> Rows32x128;
+typedef RowsTile<1, 1, 8, 1, 7, 64> Rows16x128;
+constexpr int kRowsTiles = 7;
+constexpr RowsTileInfo kRowsTile[kRowsTiles] = {
+    rows_tile_info<Rows256x256>(1.3), rows_tile_info<Rows128x512>(1.3), rows_tile_info<Rows128x384>(1.0),
+    rows_tile_info<Rows64x256>(1.3), rows_tile_info<Rows64x128>(0.8), rows_tile_info<Rows32x128>(0.55),
+    rows_tile_info<Rows16x128>(0.52)};
 constexpr int kRowsMinSteps = 8;           // reduction steps a part keeps at least
-constexpr double kRowsFixedUs = 8.0;       // of a workgroup besides its steps
-constexpr double kRowsEpilogueUs = 6.0;    // the launch that adds the parts
+constexpr double kRowsFixedUs = 6.0;       // of a workgroup besides its steps
+constexpr double kRowsEpilogueUs = 7.5;    // the launch that adds the parts
 constexpr double kRowsPartUs = 8.0 / 5e6;  // a float of the parts written and read
+constexpr double kRowsReadUs = 1.0 / 5.5e6; // a byte of weights, per block of rows (the blocks after the first from L2)
 template <int PH>
 rows_kernel_t pick_rows(int tile) {
-    return tile == 0 ? k_rows_gemm<PH, 4, 2, 8> : tile == 1 ? k_rows_gemm<PH, 2, 4, 8> : k_rows_gemm<PH, 2, 4, 6>;
+    switch (tile) {
+    case 0: return k_rows_gemm<PH, Rows256x256>;
+    case 1: return k_rows_gemm<PH, Rows128x512>;
+    case 2: return k_rows_gemm<PH, Rows128x384>;
+    case 3: return k_rows_gemm<PH, Rows64x256>;
+    case 4: return k_rows_gemm<PH, Rows64x128>;
+    case 5: return k_rows_gemm<PH, Rows32x128>;
+    default: return k_rows_gemm<PH, Rows16x128>;
+    }
 }
 rows_kernel_t rows_kernel(int phase, int tile) {
     switch (phase) {
@@ -216,7 +232,9 @@ void (*rows_epilogue_kernel(int phase))(DraftParams, int, int, int) {
     case BG_QKV: return k_rows_epilogue<BG_QKV>;
     case BG_OPROJ: return k_rows_epilogue<BG_OPROJ>;
     case BG_GATEUP: return k_rows_epilogue<BG_GATEUP>;
-    default: return k_rows_epilogue<BG_DOWN>;
+    case BG_DOWN: return k_rows_epilogue<BG_DOWN>;
+    case BG_LMHEAD: return k_rows_epilogue<BG_LMHEAD>;
+    default: return k_rows_epilogue<kHeadLogits>;
     }
 }
 int tiles_for(int nb) { return nb <= 16 ? 1 : nb <= 32 ? 2 : 4; }
@@ -322,24 +340,29 @@ int rows_n(int phase, const DraftParams &p) { // weight rows, in whole tiles of 
                                 : p.d;
 }
 // The tiling and the number of reduction parts with the shortest estimated time: rounds of one workgroup per CU, each its
-// share of the steps, and the parts' sums written and read once.  The constants are this kernel's own times at 512 rows
-// (a step of 1.3 us in long reductions, 8 us from launch to first step and from last step to end).  Parts pay where a
-// phase has few tiles: 4096 weight rows at 512 rows are 32 tiles of 256 x 256 and take 84 us in eight parts, 270 in one.
+// share of the steps (or the time HBM takes for the weights, if that is longer), and the parts' sums written and read
+// once.  The constants are this kernel's own times on the 7B-shaped head: a step of a workgroup in long reductions, what a
+// workgroup takes from launch to first step and from last step to end, the launch that adds the parts.  Parts pay where
+// a phase has few tiles: 4096 weight rows at 512 rows are 32 tiles of 256 x 256 and take 84 us in eight parts, 270 in one.
 struct RowsPlan {
     int tile, kp, mb, nb;
 };
 RowsPlan rows_plan(int phase, const DraftParams &p, int cus, size_t part_floats) {
-    const int steps = rows_k(phase, p) / kRgBK, n = rows_n(phase, p);
+    const int K = rows_k(phase, p), n = rows_n(phase, p), rows = p.seq_hi - p.seq_lo;
     RowsPlan best{};
     double best_us = 1e30;
-    for (int t = 0; t < kRowsTiles; ++t) {
+    for (int t = kRowsTiles - 1; t >= 0; --t) { // (small tiles first: they stay where HBM bounds all alike)
         const RowsTileInfo &ti = kRowsTile[t];
-        const int mb = (p.B + ti.bm - 1) / ti.bm, nb = (n + ti.bn - 1) / ti.bn;
-        for (int kp = 1; kp <= (phase >= BG_LMHEAD ? 1 : 16) && (kp == 1 || steps / kp >= kRowsMinSteps); ++kp) {
+        if (K % ti.bk) continue;
+        const int steps = K / ti.bk;
+        const int mb = (rows + ti.bm - 1) / ti.bm, nb = (n + ti.bn - 1) / ti.bn;
+        const double weights_us = (double)n * K * 2 * mb * kRowsReadUs;
+        for (int kp = 1; kp <= 16 && (kp == 1 || K / 32 / kp >= kRowsMinSteps); ++kp) {
             const double sums = (double)kp * n * mb * ti.bm; // floats of the parts
             if (kp > 1 && sums > (double)part_floats) break;
+            if (phase == BG_LMHEAD && kp == 1 && nb > kMaxHeadCands) continue; // a candidate per row and N block
             const int rounds = (mb * nb * kp + cus - 1) / cus;
-            const double us = rounds * (kRowsFixedUs + (steps + kp - 1) / kp * ti.step_us) +
+            const double us = std::max(weights_us, rounds * ((steps + kp - 1) / kp * ti.step_us)) + rounds * kRowsFixedUs +
                               (kp > 1 ? kRowsEpilogueUs + sums * kRowsPartUs : 0.0);
             if (us < best_us) {
                 best_us = us;
@@ -351,8 +374,31 @@ RowsPlan rows_plan(int phase, const DraftParams &p, int cus, size_t part_floats)
 }
 } // namespace
 
-bool rows_gemm_serves(int phase, const DraftParams &p) { return rows_k(phase, p) % kRgBK == 0; }
-int rows_head_cands(const DraftParams &p, int cus) { return rows_plan(BG_LMHEAD, p, cus, 0).nb; }
+bool rows_gemm_serves(int phase, const DraftParams &p, int cus) {
+    const int K = rows_k(phase, p);
+    if (K % kRgBK) return false;
+    if (p.seq_hi - p.seq_lo > 16) return true;
+    // Up to 16 rows the batched core's plain kernel (waves split the reduction) streams large matrices as fast, and adds its
+    // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with
+    // the launch that adds the parts.  Measured at five rows (us, this kernel / that one): 4096 x 2048 11 / 14, 2048 x 6144
+    // 13 / 17, 12288 x 2048 14 / 17, 8192 x 2048 of a head 15 / 18; at sixteen rows 4096 x 4096 17 / 17.5, 6144 x 4096
+    // 21 / 19.5, 4096 x 8192 23 / 21, 22016 x 4096 40 / 35; a head that fills the chip in one part, 32768 x 4096: 53 / 59
+    // (a head of more blocks than candidates takes a larger tile: 151680 x 4096 at sixteen rows 260 / 247).
+    const int n = rows_n(phase, p);
+    return K <= 2048 || (double)n * K * 2 <= 32e6 ||
+           (phase == BG_LMHEAD && n >= Rows16x128::BN * cus && n <= Rows16x128::BN * kMaxHeadCands);
+}
+namespace {
+// workgroups per row tile of the kernel that adds the parts
+int rows_epilogue_groups(int phase, const DraftParams &p, int cus) {
+    const int live = (p.seq_hi - p.seq_lo + 15) / 16, per_wave = rows_n(phase, p) / 16 / (phase == BG_GATEUP ? 2 : 1);
+    return std::max(1, std::min({(per_wave + kWaves - 1) / kWaves, 8 * cus / live, kMaxHeadCands}));
+}
+} // namespace
+int rows_head_cands(const DraftParams &p, int cus, size_t part_floats) {
+    const RowsPlan pl = rows_plan(BG_LMHEAD, p, cus, part_floats);
+    return pl.kp > 1 ? rows_epilogue_groups(BG_LMHEAD, p, cus) : pl.nb;
+}
 void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
                       hipStream_t st) {
     const RowsPlan pl = rows_plan(phase, p, cus, part_floats);
@@ -360,12 +406,9 @@ void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int ste
     const int units = pl.nb * pl.kp; // (N block, part) pairs: the M blocks of eight neighbouring ones form one group
     hipLaunchKernelGGL(rows_kernel(ph, pl.tile), dim3((units + 7) / 8 * 8 * pl.mb), dim3(kBlock), kRowsTile[pl.tile].lds, st,
                        p, step, pl.kp);
-    if (pl.kp > 1) {
-        const int rt = pl.mb * kRowsTile[pl.tile].bm / 16, live = (p.B + 15) / 16;
-        const int groups = (rows_n(phase, p) / 16 / (phase == BG_GATEUP ? 2 : 1) + kWaves - 1) / kWaves;
-        hipLaunchKernelGGL(rows_epilogue_kernel(phase), dim3(live, std::max(1, std::min(groups, 8 * cus / live))), dim3(kBlock),
-                           0, st, p, step, pl.kp, rt);
-    }
+    if (pl.kp > 1)
+        hipLaunchKernelGGL(rows_epilogue_kernel(ph), dim3((p.seq_hi - p.seq_lo + 15) / 16, rows_epilogue_groups(phase, p, cus)), dim3(kBlock),
+                           0, st, p, step, pl.kp, pl.mb * kRowsTile[pl.tile].bm / 16);
 }
 
 void launch_bprep(const DraftParams &p, int step, hipStream_t st) {

@@ -353,7 +353,7 @@ bool config_ok(const mtp_config *c) {
 }
 
 constexpr size_t kAlign = 256;
-constexpr int kMaxFusedGrid = 1024; // workgroups of the single-launch kernel (one per CU)
+constexpr int kMaxFusedGrid = kMaxHeadCands; // workgroups of the single-launch kernel (one per CU)
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
@@ -975,70 +975,75 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         plan(BG_OPROJ, p.d / 16, 1, p.qd, na);
         plan(BG_GATEUP, (p.F + 15) / 16, 2, p.d, na);
         plan(BG_DOWN, p.d / 16, 1, p.F, na);
+        // Matrix phases as tiled matrix products over all rows (rows_gemm.h) where those are the faster kernel.  From 17 rows on
+        // they always are: three steps at a 32768-row head take 648 / 672 / 807 / 875 us at 17 / 32 / 48 / 64 sequences against
+        // 763 / 782 / 997 / 1042 on the batched core; a block of 66 / 128 / 256 / 512 positions 324 / 365 / 550 / 840 us against
+        // 523 / 580 / 946 / 1434 in passes of 64.
+        bool tiled[BG_COUNT];
+        for (int ph = 0; ph < BG_COUNT; ++ph) tiled[ph] = rows_gemm_serves(ph, p, grid);
+        const bool logits_only = ext && ext->logits_only && logits_out;
         // The output head: one plan per id list (one list: one plan), for the sequences that share the list - the kernel
         // of a pass follows from their number, and a plan for more of them splits the reduction of the list's rows over
         // workgroups that then wait for one another (24 sequences in three lists of 32768 / 16384 / 8195 rows, eight each:
-        // 68 / 49 / 51 us per step with the plan of the whole batch, 59 / 37 / 33 with their own).
+        // 68 / 49 / 51 us per step with the plan of the whole batch, 57 / 28 / 23 with their own).
         struct HeadPlan {
             int rg, kp, sep;
             size_t lds;
+            bool tiled;
         } head_plan[kMaxListGroups];
         const int n_heads = std::max(1, groups.count);
         int max_cands = 0;
+        auto head_of = [&](int g) { // the call's parameters with the rows and the list of head g
+            DraftParams q = p;
+            if (groups.count) {
+                q.seq_lo = groups.lo[g];
+                q.seq_hi = groups.hi[g];
+                q.ids = groups.ids[g];
+                q.n = groups.n[g];
+            }
+            return q;
+        };
         for (int g = 0; g < n_heads; ++g) {
-            const int na_g = tiles_of(groups.count ? groups.hi[g] - groups.lo[g] : B);
-            plan(BG_LMHEAD, ((groups.count ? groups.n[g] : p.n) + 15) / 16, 1, p.d, na_g);
-            head_plan[g] = HeadPlan{p.bg_rg[BG_LMHEAD], p.bg_kp[BG_LMHEAD], p.bg_sep[BG_LMHEAD], lds_bg[BG_LMHEAD]};
+            const DraftParams q = head_of(g);
+            const int na_g = tiles_of(q.seq_hi - q.seq_lo);
+            plan(BG_LMHEAD, (q.n + 15) / 16, 1, p.d, na_g);
+            head_plan[g] = HeadPlan{p.bg_rg[BG_LMHEAD], p.bg_kp[BG_LMHEAD], p.bg_sep[BG_LMHEAD], lds_bg[BG_LMHEAD], false};
             if (lds_bg[BG_LMHEAD] > h->lds_limit) return MTP_ERR_CONFIG;
-            const int cands = p.bg_sep[BG_LMHEAD] ? batch_epilogue_grid(BG_LMHEAD, p, na_g) : p.bg_rg[BG_LMHEAD];
+            int cands = p.bg_sep[BG_LMHEAD] ? batch_epilogue_grid(BG_LMHEAD, q, na_g) : p.bg_rg[BG_LMHEAD];
+            head_plan[g].tiled = rows_gemm_serves(BG_LMHEAD, q, grid);
+            if (head_plan[g].tiled) cands = rows_head_cands(q, grid, l.part_floats);
             if (groups.count) groups.cands[g] = cands;
             max_cands = std::max(max_cands, cands);
         }
         for (int ph = 0; ph < BG_COUNT; ++ph)
             if (lds_bg[ph] > h->lds_limit) return MTP_ERR_CONFIG;
-        // candidates of the output head: one per row group, or one per workgroup of its separate epilogue, whose
-        // grid is then this number for every pass of the call (workgroups without work leave "no candidate")
+        // candidates of the output head per sequence: one per row group of a batched launch, one per workgroup column of a
+        // tiled one
         p.head_grid = max_cands;
         publish_lists();
-        // More rows than one pass of the batched core: every matrix phase as a tiled matrix product over all rows.  Already
-        // with two passes' worth the second reading of the weights costs more than the tiles' padding (a block of 66 / 128
-        // / 256 / 512 positions at a 32768-row head: 394 / 446 / 550 / 849 us against 523 / 580 / 946 / 1434 in passes of
-        // 64, whose body was tiled from 256 rows on).  Several id lists in one call keep their passes for the head.
-        const bool many = B > kBatchPassSeq;
-        const bool logits_only = ext && ext->logits_only && logits_out;
-        bool many_head = many && !groups.count && rows_gemm_serves(BG_LMHEAD, p);
-        if (many_head && !logits_only) { // one candidate per row and block of weight rows
-            const int cands = rows_head_cands(p, grid);
-            if (cands <= kMaxFusedGrid)
-                p.head_grid = cands;
-            else
-                many_head = false;
-        }
         auto matrix_phase = [&](int timed_as, int ph, int step) {
-            if (ph == BG_LMHEAD ? many_head : many && rows_gemm_serves(ph, p)) {
-                launch_rows_gemm(ph, logits_only, p, step, grid, l.part_floats, st);
+            if (ph != BG_LMHEAD && tiled[ph]) {
+                launch_rows_gemm(ph, false, p, step, grid, l.part_floats, st);
                 mark_end(timed_as, step);
                 return;
             }
             const int runs = ph == BG_LMHEAD ? n_heads : 1; // the output head: once per id list
             for (int g = 0; g < runs; ++g) {
-                int lo = 0, hi = B;
+                DraftParams q = ph == BG_LMHEAD ? head_of(g) : p;
+                size_t lds = lds_bg[ph];
                 if (ph == BG_LMHEAD) {
-                    p.bg_rg[ph] = head_plan[g].rg;
-                    p.bg_kp[ph] = head_plan[g].kp;
-                    p.bg_sep[ph] = head_plan[g].sep;
-                    lds_bg[ph] = head_plan[g].lds;
-                    if (groups.count) {
-                        lo = groups.lo[g];
-                        hi = groups.hi[g];
-                        p.ids = groups.ids[g];
-                        p.n = groups.n[g];
+                    if (head_plan[g].tiled) {
+                        launch_rows_gemm(ph, logits_only, q, step, grid, l.part_floats, st);
+                        continue;
                     }
+                    q.bg_rg[ph] = head_plan[g].rg;
+                    q.bg_kp[ph] = head_plan[g].kp;
+                    q.bg_sep[ph] = head_plan[g].sep;
+                    lds = head_plan[g].lds;
                 }
-                for (int b0 = lo; b0 < hi; b0 += kBatchPassSeq) {
-                    p.b0 = b0;
-                    p.nb = std::min(kBatchPassSeq, hi - b0);
-                    launch_bgemv(ph, p, step, p.bg_rg[ph] * p.bg_kp[ph], lds_bg[ph], st);
+                for (q.b0 = q.seq_lo; q.b0 < q.seq_hi; q.b0 += kBatchPassSeq) {
+                    q.nb = std::min(kBatchPassSeq, q.seq_hi - q.b0);
+                    launch_bgemv(ph, q, step, q.bg_rg[ph] * q.bg_kp[ph], lds, st);
                 }
             }
             mark_end(timed_as, step);

@@ -12,8 +12,8 @@
 // from L2 (2 BM + BN) x 64 bytes per step, 24 bytes per clock and CU with 256 x 256 against 48 with 128 x 128.  Hence
 // the largest pieces the registers hold (128 accumulator registers), and where a phase has too few such tiles to fill
 // the chip the reduction is split over KP workgroups instead of making the tiles smaller.
-// Both operands go from memory straight into LDS (no registers, no store instructions): three stages, a stage requested
-// two steps before it is multiplied.  Such a load fills 1 KB of LDS in lane order, so rows cannot be padded; the 16-byte
+// Both operands go from memory straight into LDS (no registers, no store instructions): a ring of stages, three with the
+// large tiles, a stage requested two steps (with more stages, earlier) before it is multiplied.  Such a load fills 1 KB of LDS in lane order, so rows cannot be padded; the 16-byte
 // chunks of a 64-byte row are stored at position chunk ^ ((row >> 1) & 3) instead (the lane that fills a position
 // fetches the chunk that belongs there), which puts the eight rows a quarter of a read covers on different banks.
 // Measured at 512 rows of the 7B-shaped head (us; the kernel before, with 64 x 128 to 128 x 256 tiles, operands through
@@ -29,20 +29,24 @@
 
 namespace mtp {
 
-constexpr int kRgBK = 32;            // elements per reduction step
-constexpr int kRgRow = kRgBK * 2;    // bytes per LDS row
-constexpr int kRgStages = 3;
+constexpr int kRgBK = 32; // elements of the shortest reduction step
 
-// WM x WN waves (8 in all), TJ tiles of 16 weight rows per wave
-template <int WM, int WN, int TJ>
+// WM x WN waves (8 in all), each with TI row tiles x TJ weight-row tiles of sixteen; ST stages of the LDS ring
+// of BK elements of the reduction
+template <int TI_, int WM_, int WN_, int TJ_, int ST_, int BK_ = kRgBK>
 struct RowsTile {
-    static_assert(WM * WN == kWaves, "eight waves");
-    static constexpr int WAVES_N = WN, BM = 64 * WM, BN = 16 * TJ * WN;
-    static constexpr int NA = BM / 16 / kWaves, NW = BN / 16 / kWaves; // 1 KB pieces per wave and stage: hi (as many lo), weights
-    static constexpr int NL = 2 * NA + NW;
-    static constexpr int kStage = (2 * BM + BN) * kRgRow;
-    static constexpr int kLds = kRgStages * kStage;
-    static_assert(BM % (16 * kWaves) == 0 && BN % (16 * kWaves) == 0, "whole pieces per wave");
+    static_assert(WM_ * WN_ == kWaves, "eight waves");
+    static constexpr int TI = TI_, WM = WM_, WN = WN_, TJ = TJ_, ST = ST_, BK = BK_;
+    static constexpr int kRow = BK * 2, kPieceRows = 1024 / kRow, kChunks = kRow / 16; // a row's bytes, rows of a piece
+    static constexpr int BM = 16 * TI * WM, BN = 16 * TJ * WN;
+    // 1 KB pieces (whole rows) of a stage: the hi rows, the lo rows, the weight rows; a wave fetches NA of the
+    // activations' (with fewer pieces than waves some are fetched twice) and NW of the weights'
+    static constexpr int AP = 2 * BM / kPieceRows, NA = (AP + kWaves - 1) / kWaves, NW = BN / kPieceRows / kWaves, NL = NA + NW;
+    static constexpr int kStage = (2 * BM + BN) * kRow;
+    static constexpr int kLds = ST * kStage;
+    static_assert(BK == 32 || BK == 64, "the chunk order below");
+    static_assert(BN % (kPieceRows * kWaves) == 0 && (AP % kWaves == 0 || kWaves % AP == 0), "whole pieces per wave");
+    static_assert((ST - 2) * NL < 64, "the wait counts the requests of the later stages");
 };
 
 // The output head over many rows: BgHead's operands; CAND: also the best (logit, position) of every row among the
@@ -111,64 +115,80 @@ __device__ __forceinline__ u32x4 rg_rsrc(const uint16_t *base, uint32_t bytes) {
 // pin: the DraftParams of the launch (all rows); the phase object is built on a copy whose (b0, nb) name the
 // workgroup's rows, which is what the epilogues index with.  KP > 1: the workgroup's sums go to the partial buffer
 // ([part][virtual tile][row tile], k_rows_epilogue adds them up).
-template <int WM, int WN, int TJ, class Ph, class Make>
+template <class T, class Ph, class Make>
 __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phase, int KP, char *smem) {
-    using T = RowsTile<WM, WN, TJ>;
-    constexpr int NMAT = Ph::NMAT, BM = T::BM, BN = T::BN, NA = T::NA, NW = T::NW, NL = T::NL;
-    constexpr int TI = 4;
-    static_assert(TJ % NMAT == 0, "pairs of tiles stay inside a wave's piece");
+    constexpr int NMAT = Ph::NMAT, BM = T::BM, BN = T::BN, NA = T::NA, NW = T::NW, NL = T::NL, ST = T::ST;
+    constexpr int TI = T::TI, TJ = T::TJ, WN = T::WN;
+    constexpr bool kPairApart = TJ % NMAT != 0; // the tiles of a pair sit in neighbouring waves
+    static_assert(!kPairApart || (TJ == 1 && NMAT == 2 && T::WM == 1), "pairs of tiles: inside a wave's piece, or one each");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int i16 = lane & 15, g = lane >> 4;
 
     DraftParams p = pin;
     Ph ph = make_phase(p);
-    const int K = ph.K, nk = K / kRgBK;
+    constexpr int kRow = T::kRow, PR = T::kPieceRows;
+    const int K = ph.K, nk = K / T::BK;
     const int ntv = ((ph.rows + 15) / 16) * NMAT; // virtual 16-row tiles
-    const int MB = (pin.B + BM - 1) / BM, NB = (ntv * 16 + BN - 1) / BN;
+    const int R = pin.seq_hi - pin.seq_lo; // rows of the launch: all of the call's, or those that share an id list
+    const int MB = (R + BM - 1) / BM, NB = (ntv * 16 + BN - 1) / BN;
     // Workgroups are dealt to the XCDs round robin.  The M blocks of one (N block, part) read the same weights: numbered
     // eight apart they run on the same XCD at about the same time, and its L2 serves all but the first.
     const int x = blockIdx.x, grp = x / (8 * MB), r = x % (8 * MB);
     const int mblk = r / 8, unit = grp * 8 + (r & 7);
     if (unit >= NB * KP) return; // uniform
-    const int nblk = unit / KP, kp = unit % KP;
-    const int k0 = (int)((long long)kp * nk / KP), k1 = (int)((long long)(kp + 1) * nk / KP); // k1 > k0: KP <= nk
-    p.b0 = mblk * BM;
-    p.nb = min(BM, pin.B - p.b0);
+    // (said to be wave-uniform: a division runs on the vector unit, and the requests want scalar offsets)
+    const int nblk = __builtin_amdgcn_readfirstlane(unit / KP), kp = unit - nblk * KP;
+    const int k0 = __builtin_amdgcn_readfirstlane(kp * nk / KP);
+    const int k1 = __builtin_amdgcn_readfirstlane((kp + 1) * nk / KP); // k1 > k0: KP <= nk
+    // Workgroups of a call with one block of rows start at different places of their rows (and come back to the beginning):
+    // rows lie a power of two apart, and while all of them read the same 128 bytes of their rows only some of the memory
+    // channels have work (64 rows, 32768 weight rows of 8 KB: 71 us without, 63 with).  With several blocks of rows the
+    // workgroups of a die stay together instead, so that the activations they read come from their L2.
+    const int rot = MB == 1 ? __builtin_amdgcn_readfirstlane(nblk * 5 % (k1 - k0)) : 0;
+    p.b0 = pin.seq_lo + mblk * BM;
+    p.nb = min(BM, pin.seq_hi - p.b0);
 
-    // memory -> LDS: piece = sixteen rows x 64 bytes; lane l fills row l / 4, position l % 4
-    const int prow = lane >> 2, pchunk = (lane & 3) ^ ((prow >> 1) & 3);
+    // memory -> LDS: a lane fills one 16-byte position of one row of the piece, with the chunk that belongs there
+    auto chunk_order = [](int row) { return T::BK == 64 ? row & 7 : (row >> 1) & 3; };
+    const int prow = lane / T::kChunks, pchunk = (lane % T::kChunks) ^ chunk_order(prow);
     const size_t lo_bytes = p.a_lo * 2;
     u32x4 ar = rg_rsrc(ph.in, (uint32_t)(2 * lo_bytes));
-    int voff_a[NA];
+    int voff_a[NA], dst_a[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
-        voff_a[i] = (int)((size_t)min(p.b0 + 16 * (wave + kWaves * i) + prow, pin.B - 1) * p.a_stride * 2 + pchunk * 16);
+    for (int i = 0; i < NA; ++i) {
+        const int q = (wave + kWaves * i) % T::AP, lo = q >= BM / PR ? 1 : 0, row = (q - lo * (BM / PR)) * PR + prow;
+        voff_a[i] = (int)((size_t)min(p.b0 + row, pin.seq_hi - 1) * p.a_stride * 2 + (lo ? lo_bytes : 0) + pchunk * 16);
+        dst_a[i] = q * 1024; // the lo rows lie behind the hi rows
+    }
     u32x4 wr[NW];
     int voff_w[NW];
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
-        const int vt = min(nblk * (BN / 16) + wave + kWaves * i, ntv - 1);
+        const int q0 = (wave + kWaves * i) * PR; // first row of the piece in the block
+        const int vt = min(nblk * (BN / 16) + q0 / 16, ntv - 1);
         const uint16_t *base;
         int mat_rows, row0, row_end;
         ph.tile(vt, base, mat_rows, row0, row_end);
         wr[i] = rg_rsrc(base, (uint32_t)((size_t)mat_rows * K * 2));
-        int wrow = min(row0 + prow, row_end - 1);
+        int wrow = min(row0 + q0 % 16 + prow, row_end - 1);
         if (Ph::GATHER && ph.ids) wrow = ph.ids[wrow];
         voff_w[i] = (int)((size_t)wrow * K * 2 + pchunk * 16);
     }
     // an LDS address is the low half of the generic one
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem);
-    auto request = [&](int ks, int stage) { // steps past the range repeat its last one (in bounds, nobody reads them)
-        const int soff = min(ks, k1 - 1) * kRgRow;
-        const uint32_t at = lds0 + stage * T::kStage + wave * 1024;
+    // Steps past the range are requested beyond the buffers' ends (zeros, no traffic): the count of requests in flight does
+    // not depend on the step.
+    auto request = [&](int ks, int stage) {
+        const bool live = ks < k1;
+        const int kr = ks + rot >= k1 ? ks + rot - (k1 - k0) : ks + rot;
+        const int soff = live ? kr * kRow : 0;
+        const uint32_t at = lds0 + stage * T::kStage;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            rg_load_lds(ar, at + i * kWaves * 1024, voff_a[i], soff);
-            rg_load_lds(ar, at + (BM * kRgRow) + i * kWaves * 1024, voff_a[i], soff + (int)lo_bytes);
-        }
+        for (int i = 0; i < NA; ++i) rg_load_lds(ar, at + dst_a[i], live ? voff_a[i] : (int)kOobOffset, soff);
 #pragma unroll
-        for (int i = 0; i < NW; ++i) rg_load_lds(wr[i], at + 2 * (BM * kRgRow) + i * kWaves * 1024, voff_w[i], soff);
+        for (int i = 0; i < NW; ++i)
+            rg_load_lds(wr[i], at + 2 * (BM * kRow) + (wave + i * kWaves) * 1024, live ? voff_w[i] : (int)kOobOffset, soff);
     };
 
     // s_b = 1/sqrt(mean(u_b^2) + eps) of the workgroup's rows from the producer's per-tile sums of squares: kBlock / BM
@@ -177,7 +197,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     float my_scale = 0.f;
     if (Ph::SCALE >= 0 && KP == 1) {
         const int npart = p.d / 16, sub = tid & (TPR - 1);
-        const float *part = p.ssq + ((size_t)Ph::SCALE * p.max_batch + min(p.b0 + tid / TPR, pin.B - 1)) * npart;
+        const float *part = p.ssq + ((size_t)Ph::SCALE * p.max_batch + min(p.b0 + tid / TPR, pin.seq_hi - 1)) * npart;
         float sum = 0.f;
         for (int i0 = sub; i0 < npart; i0 += TPR * 8) {
             float v[8];
@@ -191,9 +211,11 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
         my_scale = 1.0f / sqrtf(sum / (float)p.d + p.eps);
     }
 
-    const int wm = wave / WN, wn = wave % WN; // the wave's piece: rows 64 wm .., weight rows 16 TJ wn ..
-    const int frag = i16 * kRgRow + ((g ^ ((i16 >> 1) & 3)) * 16);
-    const char *abase = smem + wm * 64 * kRgRow + frag, *wbase = smem + 2 * (BM * kRgRow) + wn * (16 * TJ) * kRgRow + frag;
+    const int wm = wave / WN, wn = wave % WN; // the wave's piece: rows 16 TI wm .., weight rows 16 TJ wn ..
+    int frag[T::BK / 32]; // 16-byte chunk g of half h of a row, where the order of the chunks puts it
+#pragma unroll
+    for (int h = 0; h < T::BK / 32; ++h) frag[h] = i16 * kRow + (((4 * h + g) ^ chunk_order(i16)) * 16);
+    const char *abase = smem + wm * (16 * TI) * kRow, *wbase = smem + 2 * (BM * kRow) + wn * (16 * TJ) * kRow;
     f32x4 acc[TI][TJ];
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
@@ -205,29 +227,32 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     asm volatile("s_nop 7" : "+s"(ar));
 #pragma unroll
     for (int i = 0; i < NW; ++i) asm volatile("s_nop 7" : "+s"(wr[i]));
-    request(k0, 0);
-    request(k0 + 1, 1);
+#pragma unroll
+    for (int u = 0; u < ST - 1; ++u) request(k0 + u, u);
     int stage = 0;
     for (int ks = k0; ks < k1; ++ks) {
-        // This wave's pieces of step ks have landed (those of ks + 1 may still be on their way) and its LDS reads of step
-        // ks - 1 are back; after the barrier that holds for all waves: step ks can be read, and the stage of step
-        // ks - 1 takes step ks + 2.
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(NL) : "memory");
-        request(ks + 2, stage == 0 ? kRgStages - 1 : stage - 1);
+        // This wave's pieces of step ks have landed (those of the later steps may still be on their way) and its LDS reads of
+        // step ks - 1 are back; after the barrier that holds for all waves: step ks can be read, and the stage of step
+        // ks - 1 takes step ks + ST - 1.
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((ST - 2) * NL) : "memory");
+        request(ks + ST - 1, stage == 0 ? ST - 1 : stage - 1);
         const char *as = abase + stage * T::kStage, *ws = wbase + stage * T::kStage;
-        u32x4 wf[TJ];
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) wf[tj] = *reinterpret_cast<const u32x4 *>(ws + tj * 16 * kRgRow);
+        for (int h = 0; h < T::BK / 32; ++h) {
+            u32x4 wf[TJ];
 #pragma unroll
-        for (int ti = 0; ti < TI; ++ti) {
-            const u32x4 ah = *reinterpret_cast<const u32x4 *>(as + ti * 16 * kRgRow);
-            const u32x4 al = *reinterpret_cast<const u32x4 *>(as + (BM * kRgRow) + ti * 16 * kRgRow);
+            for (int tj = 0; tj < TJ; ++tj) wf[tj] = *reinterpret_cast<const u32x4 *>(ws + frag[h] + tj * 16 * kRow);
 #pragma unroll
-            for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(ah, wf[tj], acc[ti][tj]);
+            for (int ti = 0; ti < TI; ++ti) {
+                const u32x4 ah = *reinterpret_cast<const u32x4 *>(as + frag[h] + ti * 16 * kRow);
+                const u32x4 al = *reinterpret_cast<const u32x4 *>(as + frag[h] + (BM * kRow) + ti * 16 * kRow);
 #pragma unroll
-            for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(al, wf[tj], acc[ti][tj]);
+                for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(ah, wf[tj], acc[ti][tj]);
+#pragma unroll
+                for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(al, wf[tj], acc[ti][tj]);
+            }
         }
-        stage = stage == kRgStages - 1 ? 0 : stage + 1;
+        stage = stage == ST - 1 ? 0 : stage + 1;
     }
     // the trailing requests have landed and every wave is done reading: the LDS is free
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
@@ -239,8 +264,8 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
         for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
             for (int tj = 0; tj < TJ; ++tj) {
-                const int vt = nblk * (BN / 16) + wn * TJ + tj, rt = mblk * (BM / 16) + wm * 4 + ti;
-                if (vt < ntv && rt * 16 < pin.B)
+                const int vt = nblk * (BN / 16) + wn * TJ + tj, rt = mblk * (BM / 16) + wm * TI + ti;
+                if (vt < ntv && rt * 16 < R)
                     *reinterpret_cast<f32x4 *>(p.part + ((((size_t)kp * ntv + vt) * RT + rt) * kWave + lane) * 4) = acc[ti][tj];
             }
         return;
@@ -257,7 +282,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
             unsigned long long best[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
             for (int tj = 0; tj < TJ; ++tj)
-                ph.epi_best(64 * wm + 16 * ti + 4 * g, nblk * (BN / 16) + wn * TJ + tj, i16, acc[ti][tj], scale, best);
+                ph.epi_best(16 * (TI * wm + ti) + 4 * g, nblk * (BN / 16) + wn * TJ + tj, i16, acc[ti][tj], scale, best);
             if (Ph::CANDS) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
@@ -267,7 +292,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
                         const unsigned long long o = __shfl_xor(m, off, kWave);
                         m = o > m ? o : m;
                     }
-                    if (i16 == 0) red[wn * BM + 64 * wm + 16 * ti + 4 * g + c] = m;
+                    if (i16 == 0) red[wn * BM + 16 * (TI * wm + ti) + 4 * g + c] = m;
                 }
             }
         }
@@ -280,6 +305,19 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
                 p.cand[((size_t)ph.step * p.max_batch + p.b0 + tid) * p.head_grid + nblk] = m;
             }
         }
+    } else if constexpr (kPairApart) {
+        f32x4 *half = reinterpret_cast<f32x4 *>(smem + 16 * BM); // [kWaves][TI][kWave], behind the scales
+        if (wn & 1)
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) half[(wn * TI + ti) * kWave + lane] = acc[ti][0];
+        __syncthreads();
+        const int vt = nblk * (BN / 16) + wn;
+        if (!(wn & 1) && vt < ntv)
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) {
+                const f32x4 sums[NMAT] = {acc[ti][0], half[((wn + 1) * TI + ti) * kWave + lane]};
+                ph.epi(16 * ti + 4 * g, vt, i16, sums, scale);
+            }
     } else {
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti)
@@ -290,7 +328,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
                 f32x4 sums[NMAT];
 #pragma unroll
                 for (int m = 0; m < NMAT; ++m) sums[m] = acc[ti][tj + m];
-                ph.epi(64 * wm + 16 * ti + 4 * g, vt, i16, sums, scale);
+                ph.epi(16 * (TI * wm + ti) + 4 * g, vt, i16, sums, scale);
             }
     }
 }
@@ -302,12 +340,12 @@ __device__ __forceinline__ void rows_epilogue(const DraftParams &pin, Make make_
     constexpr int NMAT = Ph::NMAT;
     DraftParams p = pin;
     const int rt = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    p.b0 = rt * 16;
-    p.nb = min(16, pin.B - p.b0);
+    p.b0 = pin.seq_lo + rt * 16;
+    p.nb = min(16, pin.seq_hi - p.b0);
     Ph ph = make_phase(p);
     if (Ph::SCALE >= 0) { // thirty-two threads per row
         const int npart = p.d / 16, sub = tid & 31;
-        const float *part = p.ssq + ((size_t)Ph::SCALE * p.max_batch + min(p.b0 + tid / 32, pin.B - 1)) * npart;
+        const float *part = p.ssq + ((size_t)Ph::SCALE * p.max_batch + min(p.b0 + tid / 32, pin.seq_hi - 1)) * npart;
         float sum = 0.f;
         for (int i0 = sub; i0 < npart; i0 += 32 * 8) {
             float v[8];
@@ -323,6 +361,7 @@ __device__ __forceinline__ void rows_epilogue(const DraftParams &pin, Make make_
     __syncthreads();
     const int ntv = ((ph.rows + 15) / 16) * NMAT;
     const size_t kstride = (size_t)ntv * RT * kWave * 4;
+    unsigned long long best[4] = {0ull, 0ull, 0ull, 0ull};
     for (int vt = (blockIdx.y * kWaves + wave) * NMAT; vt < ntv; vt += gridDim.y * kWaves * NMAT) {
         f32x4 sums[NMAT];
 #pragma unroll
@@ -339,7 +378,30 @@ __device__ __forceinline__ void rows_epilogue(const DraftParams &pin, Make make_
             }
             sums[m] = s;
         }
-        ph.epi((lane >> 4) * 4, vt, lane & 15, sums, scale);
+        if constexpr (IsHeadRows<Ph>::value)
+            ph.epi_best((lane >> 4) * 4, vt, lane & 15, sums[0], scale, best);
+        else
+            ph.epi((lane >> 4) * 4, vt, lane & 15, sums, scale);
+    }
+    if constexpr (IsHeadRows<Ph>::cands) { // one candidate per (row, blockIdx.y)
+        unsigned long long *red = reinterpret_cast<unsigned long long *>(scale + 16); // [kWaves][16]
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            unsigned long long m = best[c];
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                const unsigned long long o = __shfl_xor(m, off, kWave);
+                m = o > m ? o : m;
+            }
+            if ((lane & 15) == 0) red[wave * 16 + (lane >> 4) * 4 + c] = m;
+        }
+        __syncthreads();
+        if (tid < p.nb) {
+            unsigned long long m = 0ull;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) m = red[w * 16 + tid] > m ? red[w * 16 + tid] : m;
+            p.cand[((size_t)ph.step * p.max_batch + p.b0 + tid) * p.head_grid + blockIdx.y] = m;
+        }
     }
 }
 

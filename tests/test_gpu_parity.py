@@ -487,12 +487,13 @@ def test_tiny_extend_block_of_positions(gpu, tiny, ctx, ext, m_max):
 
 
 @pytest.mark.parametrize("d_ffn,subset", [(1056, 0), (1064, -1)])
-@pytest.mark.parametrize("rows", [65, 129, 257, 400])
+@pytest.mark.parametrize("rows", [5, 16, 17, 33, 64, 65, 129, 257, 400])
 def test_many_rows_tiled_matrix_products(gpu, d_ffn, subset, rows):
-    """More than 64 rows: every phase as a tiled matrix product.  One row past one and two blocks of 128 and one of 256
-    rows, a block that is neither; reductions of an odd number of steps (1056) and, for the down projection of 1064, not
-    a whole number (the batched core then); gate/up rows and a vocabulary that end inside a tile of sixteen; the list
-    and the full head; the candidates of a row from several blocks of weight rows."""
+    """Every phase as a tiled matrix product (small reductions take it at any number of rows).  Rows on both sides of the
+    blocks of 16, 32, 64, 128 and 256 rows, a block that is neither; reductions of an odd number of 32-element steps
+    (1056: no whole number of the small tiles' 64-element steps) and, for the down projection of 1064, not a whole
+    number (the batched core then); gate/up rows and a vocabulary that end inside a tile of sixteen; the list and the
+    full head; the candidates of a row from several blocks of weight rows."""
     shape = synth.HeadShape(512, 4, 2, 128, d_ffn, 2111)
     wl = synth.Workload(f"rows_{d_ffn}", 95, shape, 1, 0, 0, (517,), 1, 0.5, zipf_subset=False)
     w = synth.make_weights(wl)
