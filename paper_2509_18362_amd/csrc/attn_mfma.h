@@ -76,7 +76,8 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
     L &s = *reinterpret_cast<L *>(smem);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int i16 = lane & 15, g4 = lane >> 4;
-    const int T = p.split_tokens, S = p.max_splits;
+    int T = p.split_tokens;
+    const int S = p.max_splits;
     const int nseq = JP > 1 ? p.ext_B : p.B;             // sequences whose caches are read
     const int mpos = JP > 1 ? p.B / p.ext_B : 1;         // positions per sequence
     const int JG = (mpos + JP - 1) / JP;                 // groups of positions
@@ -128,6 +129,44 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
         for (int u = 0; u < nseq; ++u) n_ragged += (len_l[u] % T) != 0 ? 1 : 0;
         n_items = (n_full + n_ragged) * p.Hkv;
     }
+    // At most one item per workgroup, splits as short as that allows (p.attn_fit_min, set where every sequence and KV head
+    // can have a workgroup of its own): the host does not know the lengths, and splits sized for the capacity leave the
+    // launch waiting for its few full ones.  Lane c of every wave tries splits of attn_fit_min + c * attn_fit_step tokens
+    // (the last of the 64 covers the whole capacity), the first that gives no more items than there are workgroups is
+    // taken; lane b then knows sequence b's first item.  All waves compute the same.
+    const bool fit = !MAP && p.attn_fit_min > 0; // uniform
+    int fit_pre = 0x7fffffff;                    // lane b: splits of the sequences before b
+    if (fit) {
+        int lb = 0;
+        if (lane < nseq) {
+            if constexpr (JP == 1)
+                lb = (seq_dead(p, lane) ? 0 : p.kv_len[lane]) + step + 1;
+            else
+                for (int j = 0; j < mpos; ++j)
+                    lb = max(lb, seq_dead(p, j * nseq + lane) ? 0 : p.kv_len[j * nseq + lane] + step + 1);
+        }
+        auto splits_of = [](int len, int t, float inv) { // ceil(len / t), exactly (len < 2^23)
+            int q = (int)((float)(len + t - 1) * inv);
+            const int r = len + t - 1 - q * t;
+            return q + (r >= t ? 1 : 0) - (r < 0 ? 1 : 0);
+        };
+        const int tc = p.attn_fit_min + lane * p.attn_fit_step;
+        const float inv = 1.0f / (float)tc;
+        int total = 0;
+        for (int u = 0; u < nseq; ++u) total += splits_of(__builtin_amdgcn_readlane(lb, u), tc, inv);
+        const unsigned long long ok = __builtin_amdgcn_ballot_w64(total * p.Hkv * JG <= nvb);
+        const int c = ok ? __builtin_ctzll(ok) : kWave - 1;
+        T = __builtin_amdgcn_readlane(tc, c);
+        n_items = __builtin_amdgcn_readlane(total, c) * p.Hkv * JG;
+        const int ns = lane < nseq ? splits_of(lb, T, 1.0f / (float)T) : 0;
+        int incl = ns;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int o = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += o;
+        }
+        if (lane < nseq) fit_pre = incl - ns;
+    }
     // items 0 .. nvb-1 are the workgroups' first ones, the counter hands out those from nvb on
     auto draw = [&]() { return nvb + __hip_atomic_fetch_add(p.attn_queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     int item = vb, next_item = 0, pending = 0; // pending: thread 0's next number, asked for at the start of an item
@@ -150,6 +189,12 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
         // split-major numbering: the splits of one (sequence, KV head) land on workgroups of different XCDs, and with
         // the counter the short final splits are drawn last
         int kvh = item % p.Hkv, b = item / p.Hkv % nseq, jg = item / (p.Hkv * nseq) % JG, sp = item / (p.Hkv * nseq * JG);
+        if (fit) {
+            const int m = item / (p.Hkv * JG);
+            jg = item / p.Hkv % JG;
+            b = __popcll(__builtin_amdgcn_ballot_w64(fit_pre <= m)) - 1;
+            sp = m - __builtin_amdgcn_readlane(fit_pre, b);
+        }
         if constexpr (mapped) {
             const int m = item / p.Hkv;
             if (m < n_full) { // the m-th full split: the sequences that have split sp lead the order by length

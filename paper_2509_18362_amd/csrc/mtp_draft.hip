@@ -327,10 +327,22 @@ int max_splits_for(const mtp_config &c, int B) {
     int t = split_tokens_for(c, B);
     return (c.kv_capacity + t - 1) / t;
 }
+// Splits sized by the lengths found on the device (attn_mfma.h): calls of at most kFitMaxRows rows, no shorter than this -
+// up to four times as many as planned for, at least sixteen.
+constexpr int kFitMaxRows = 128;
+constexpr int kFitMinPlanned = 1024; // planned split length from which on it pays
+int fit_min_tokens(const mtp_config &c, int B) {
+    const int splits = std::max(4 * max_splits_for(c, B), 16);
+    return std::max(kMfmaAttnMinSplit, ((c.kv_capacity + splits - 1) / splits + 63) / 64 * 64);
+}
+int fit_max_splits(const mtp_config &c, int B) {
+    const int t = fit_min_tokens(c, B);
+    return (c.kv_capacity + t - 1) / t;
+}
 size_t attn_part_floats(const mtp_config &c) {
     size_t best = 0;
     for (int B = 1; B <= c.max_batch; ++B)
-        best = std::max(best, (size_t)B * max_splits_for(c, B));
+        best = std::max(best, (size_t)B * std::max(max_splits_for(c, B), B <= kFitMaxRows ? fit_max_splits(c, B) : 0));
     return best * c.n_q_heads * (c.head_dim + 2);
 }
 
@@ -760,16 +772,17 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     p.nb_d = fit(p.d, 2);
     p.nb_q = fit(p.qd, 1);
     p.nb_down = fit(p.F, 1);
+    const int strip_splits = std::max(p.max_splits, B <= kFitMaxRows ? fit_max_splits(c, B) : 0); // of the attention's merge
     const size_t lds_proj = gemv_lds_bytes(2 * p.d, p.nb_proj, 1), lds_d1 = gemv_lds_bytes(p.d, p.nb_d, 1),
                  lds_d2 = gemv_lds_bytes(p.d, p.nb_d, 2), lds_q = gemv_lds_bytes(p.qd, p.nb_q, 1),
                  lds_down = gemv_lds_bytes(p.F, p.nb_down, 1),
                  lds_attn = std::max(attn_lds_bytes(p.Hq / p.Hkv, p.hd),
                                      // the matrix-core kernel's tiles or the merge's strips, flags, then the item map
-                                     std::max(attn_mfma_lds_bytes(p.Hq / p.Hkv, p.hd), (size_t)kWaves * p.max_splits * 4) +
+                                     std::max(attn_mfma_lds_bytes(p.Hq / p.Hkv, p.hd), (size_t)kWaves * strip_splits * 4) +
                                          64 + 16 + attn_map_bytes(att_B, p.max_splits));
     // the matrix-core attention over a block of positions (sixteen query columns)
     const size_t lds_attn_block = std::max(attn_mfma_block_lds_bytes(p.Hq / p.Hkv, p.hd) + 64,
-                                           (size_t)kWaves * p.max_splits * 4 + 64);
+                                           (size_t)kWaves * strip_splits * 4 + 64);
     const size_t lds_max = std::max({lds_proj, lds_d2, lds_q, lds_down, lds_attn, ext ? lds_attn_block : 0});
     if (lds_max > h->lds_limit) return MTP_ERR_CONFIG;
 
@@ -784,6 +797,25 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     const int attn_grid = std::max(1, std::min(attn_items, h->num_cus * (mfma_attn ? 1 : 2)));
     // more items than workgroups: the matrix-core attention hands them out one by one (contexts differ in length)
     if (attn_items <= attn_grid) p.attn_queue = nullptr;
+    // Every (sequence, KV head) can have a compute unit of its own with some to spare, and the planned splits are long: the
+    // launch sizes its splits by the lengths it finds, one item per workgroup.  Three steps of 8 sequences of 8192 .. 32768
+    // tokens take 899 us against 983 with splits planned for the capacity, 20 of 1000 .. 2000 tokens 621 against 656, 12
+    // of 100 .. 8000 644 against 668; reading the lengths first costs 2 us per launch, which splits of 512 tokens do not
+    // earn back (5 sequences: 530 against 523), and with as many sequences as units the counter balances uneven
+    // contexts better (32 of 4096 .. 16384: 1322 against 1257).
+    const bool att_block = mfma_attn && ext && ext->m_max > 1;
+    const int att_seqs = ext ? ext->B : B, att_jp = att_block ? 16 / (p.Hq / p.Hkv) : 1;
+    const int att_groups = att_block ? (ext->m_max + att_jp - 1) / att_jp : 1;
+    const bool att_fit = mfma_attn && (!ext || att_block) && B <= kFitMaxRows && att_seqs <= kWave &&
+                     p.split_tokens >= kFitMinPlanned && 4 * att_seqs * p.Hkv * att_groups <= 3 * h->num_cus;
+    auto with_fit = [&](DraftParams pa) {
+        if (!att_fit) return pa;
+        pa.attn_fit_min = fit_min_tokens(c, B);
+        pa.attn_fit_step = std::max(64, ((c.kv_capacity - pa.attn_fit_min + 62) / 63 + 63) / 64 * 64);
+        pa.max_splits = fit_max_splits(c, B);
+        pa.attn_queue = nullptr;
+        return pa;
+    };
 
     const int tphase = h->timing >= 2 ? h->timing - 2 : -1;
     h->pev_used = 0;
@@ -883,7 +915,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     // four-position block take 40 us there and 26 us on the vector units)
     auto launch_attention_of = [&](const DraftParams &pa, int step) {
         if (mfma_attn)
-            launch_attn_mfma(pa.Hq / pa.Hkv, pa.hd, pa, step, attn_grid, lds_attn, st);
+            launch_attn_mfma(pa.Hq / pa.Hkv, pa.hd, with_fit(pa), step, att_fit ? h->num_cus : attn_grid, lds_attn, st);
         else
             hipLaunchKernelGGL(h->attn_fn, dim3(attn_grid), dim3(kBlock), lds_attn, st, pa, step);
     };
@@ -906,9 +938,9 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             // long splits: the positions of a sequence share its key/value reads (16 / G of them per item)
             const int G = pa.Hq / pa.Hkv, jp = 16 / G, jg = (ext->m_max + jp - 1) / jp;
             const int items = ext->B * pa.Hkv * pa.max_splits * jg;
-            const int grid_b = std::max(1, std::min(items, h->num_cus * 2));
+            const int grid_b = att_fit ? h->num_cus : std::max(1, std::min(items, h->num_cus * 2));
             pa.attn_queue = items > grid_b ? pa.attn_ticket + (size_t)2 * c.max_batch * c.n_kv_heads : nullptr;
-            launch_attn_mfma_block(G, pa.hd, pa, 0, grid_b, lds_attn_block, st);
+            launch_attn_mfma_block(G, pa.hd, with_fit(pa), 0, grid_b, lds_attn_block, st);
         } else {
             launch_attention_of(pa, 0);
         }

@@ -47,6 +47,8 @@ struct DraftParams {
     int max_batch;
     // launch plan
     int split_tokens, max_splits; // attention: tokens per split, splits per (sequence, KV head)
+    int attn_fit_min, attn_fit_step; // matrix-core attention: shortest splits and their increment where the launch sizes
+                                  // them by the lengths it finds (0: splits of split_tokens)
     int mfma_attn;                // the splits are long enough for the matrix-core attention
     int own_hidden;               // step 1 of this call starts from hhat (fp32, put there by the host: the head's own
                                   // output of an earlier call) instead of hidden_in (bf16, the target model's)

@@ -516,6 +516,31 @@ def test_tiny_extend_long_capacity_matrix_core_attention(gpu, tiny):
     check_extend(ref, res, caches, act, ext_len)
 
 
+@pytest.mark.parametrize("ctx,ext", [
+    ([957, 958, 959, 960, 0, 31, 1918, 1919, 5000], None),  # steps that end on, before and behind a split's last token
+    ([32700, 1], None),                                      # a nearly full cache: many splits of one sequence
+    ([0], None),
+    ([950, 0, 1915, 959, 40], [12, 12, 7, 0, 1]),            # blocks that cross a split's end, an idle sequence
+])
+def test_tiny_attention_splits_sized_by_the_lengths(gpu, tiny, ctx, ext):
+    """Few sequences in a large cache: the matrix-core attention sizes its splits by the lengths it finds (960 tokens
+    here, the shortest it may take at this capacity), one item per workgroup.  Two sequences at least, so that the draft
+    steps take the batched path; a single one in the launch-per-phase mode."""
+    act = synth.make_activations(tiny["wl"], ctx=np.array(ctx, dtype=np.int32), capacity=32768)
+    if ext is not None:
+        ext_len = np.array(ext, dtype=np.int32)
+        hid, tok = extend_inputs(tiny["shape"], act, 12, 214)
+        ref, res, caches = run_extend(gpu, tiny["shape"], tiny["w"], tiny["w"], act, [tiny["ids"]], 0, hid, tok, ext_len)
+        assert res["err"] == 0
+        check_extend(ref, res, caches, act, ext_len)
+        return
+    eng = gpu["binding"].DraftEngine(tiny["shape"], tiny["w"], [tiny["ids"]], len(ctx), 32768, 3)
+    assert gpu["binding"].mtp_set_launch_mode(eng.handle, 0) == 0
+    ref, res, caches = run_both(gpu, tiny["shape"], tiny["w"], tiny["w"], act, [tiny["ids"]], 0, 3, engine=eng)
+    check_chain(ref, res, caches, act["kv_len"], 3, need_clear=False)
+    eng.close()
+
+
 def test_tiny_extend_long_block_positions_share_the_cache_reads(gpu, tiny):
     """Twenty positions per sequence with splits of 4096 tokens: the matrix-core attention serves eight positions of
     a sequence per item (three groups, the last ragged), each position seeing the cache up to its own slot.  One block
