@@ -1,4 +1,5 @@
-// Batched weight streaming for 5..64 sequences per pass (gfx950): every weight is read from HBM once per pass.
+// Batched weight streaming for 2..64 sequences per pass (gfx950): every weight is read from HBM once per pass.  Large
+// matrices at up to 16 sequences, and what the tiled products of rows_gemm.h do not serve, run here.
 //
 // The activations of a phase arrive already split into bf16 hi + lo, written to global memory by the phase before
 // (they stay in L2), so the A operand of the 16x16x32 MFMA (16 sequences x 32 elements) is loaded straight into

@@ -44,28 +44,12 @@ __global__ __launch_bounds__(kBlock) void k_bgemv(DraftParams p, int step) {
     }
 }
 
-template <int PH, int NA>
-__global__ __launch_bounds__(kBlock) void k_bepilogue(DraftParams p, int step) {
+// (the only phase that more than 16 rows take to the batched core with its reduction split: see rows_gemm_serves)
+template <int NA>
+__global__ __launch_bounds__(kBlock) void k_bepilogue_down(DraftParams p, int step) {
     __shared__ __align__(16) char smem[kWaves * kBatchMaxSeq * 8 + kBatchMaxSeq * 4];
-    if constexpr (PH == BG_PROJ) {
-        BgProj ph(p);
-        phase_bepilogue<NA>(p, ph, p.bg_kp[PH], smem);
-    } else if constexpr (PH == BG_QKV) {
-        BgQkv ph(p);
-        phase_bepilogue<NA>(p, ph, p.bg_kp[PH], smem);
-    } else if constexpr (PH == BG_OPROJ) {
-        BgOproj ph(p);
-        phase_bepilogue<NA>(p, ph, p.bg_kp[PH], smem);
-    } else if constexpr (PH == BG_GATEUP) {
-        BgGateUp ph(p);
-        phase_bepilogue<NA>(p, ph, p.bg_kp[PH], smem);
-    } else if constexpr (PH == BG_DOWN) {
-        BgDown ph(p);
-        phase_bepilogue<NA>(p, ph, p.bg_kp[PH], smem);
-    } else {
-        BgHead ph(p, step);
-        phase_bepilogue<NA>(p, ph, p.bg_kp[PH], smem);
-    }
+    BgDown ph(p);
+    phase_bepilogue<NA>(p, ph, p.bg_kp[BG_DOWN], smem);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bprep(DraftParams p, int step) {
@@ -162,9 +146,14 @@ bg_kernel_t attn_mfma_kernel(int G, int HD, bool lpt) {
     }
     return nullptr;
 }
+// More than 16 rows take the tiled products wherever those serve: the batched core then runs the down projection of
+// reduction lengths that are no multiple of 32 and heads of more rows than the tiles have candidates for.
 template <int PH>
 bg_kernel_t pick_na(int na) {
-    return na == 1 ? k_bgemv<PH, 1> : na == 2 ? k_bgemv<PH, 2> : k_bgemv<PH, 4>;
+    if constexpr (PH == BG_DOWN || PH == BG_LMHEAD)
+        return na == 1 ? k_bgemv<PH, 1> : na == 2 ? k_bgemv<PH, 2> : k_bgemv<PH, 4>;
+    else
+        return na == 1 ? k_bgemv<PH, 1> : nullptr;
 }
 bg_kernel_t pick(int phase, int na) {
     switch (phase) {
@@ -238,30 +227,10 @@ void (*rows_epilogue_kernel(int phase))(DraftParams, int, int, int) {
     }
 }
 int tiles_for(int nb) { return nb <= 16 ? 1 : nb <= 32 ? 2 : 4; }
-template <int PH>
-bg_kernel_t pick_epilogue_na(int na) {
-    return na == 1 ? k_bepilogue<PH, 1> : na == 2 ? k_bepilogue<PH, 2> : k_bepilogue<PH, 4>;
-}
-bg_kernel_t pick_epilogue(int phase, int na) {
-    switch (phase) {
-    case BG_PROJ: return pick_epilogue_na<BG_PROJ>(na);
-    case BG_QKV: return pick_epilogue_na<BG_QKV>(na);
-    case BG_OPROJ: return pick_epilogue_na<BG_OPROJ>(na);
-    case BG_GATEUP: return pick_epilogue_na<BG_GATEUP>(na);
-    case BG_DOWN: return pick_epilogue_na<BG_DOWN>(na);
-    default: return pick_epilogue_na<BG_LMHEAD>(na);
-    }
-}
 
 } // namespace
 
 size_t bgemv_lds_bytes(int rows_per_group) { return batch_lds_bytes(rows_per_group); }
-
-int batch_epilogue_grid(int phase, const DraftParams &p, int na) {
-    const int rows = phase == BG_QKV ? p.qkv_dim : phase == BG_GATEUP ? p.F : phase == BG_LMHEAD ? p.n : p.d;
-    const int slots = (rows + 15) / 16 * na;
-    return std::min((slots + kWaves - 1) / kWaves, 1024);
-}
 
 size_t attn_mfma_lds_bytes(int G, int HD) {
     switch (HD * 16 + G) {
@@ -314,18 +283,17 @@ bool batch_allow_lds(size_t lds_limit) {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit) == hipSuccess;
     for (int ph = 0; ph < BG_COUNT; ++ph)
         for (int na = 1; na <= 4; na *= 2)
-            ok = ok && hipFuncSetAttribute((const void *)pick(ph, na), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds_limit) == hipSuccess;
+            ok = ok && (!pick(ph, na) || hipFuncSetAttribute((const void *)pick(ph, na), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                             (int)lds_limit) == hipSuccess);
     return ok;
 }
 
 void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t lds, hipStream_t st) {
     const int na = tiles_for(p.nb);
     hipLaunchKernelGGL(pick(phase, na), dim3(grid), dim3(kBlock), lds, st, p, step);
-    if (p.bg_sep[phase]) // one wave per (tile or pair of tiles, sequence tile)
-        hipLaunchKernelGGL(pick_epilogue(phase, na),
-                           dim3(phase == BG_LMHEAD ? p.head_grid : batch_epilogue_grid(phase, p, na)), dim3(kBlock), 0, st,
-                           p, step);
+    if (p.bg_sep[phase]) // (BG_DOWN) one wave per (tile, sequence tile)
+        hipLaunchKernelGGL(na == 1 ? k_bepilogue_down<1> : na == 2 ? k_bepilogue_down<2> : k_bepilogue_down<4>,
+                           dim3(std::min((p.d / 16 * na + kWaves - 1) / kWaves, 1024)), dim3(kBlock), 0, st, p, step);
 }
 
 namespace {
@@ -377,6 +345,7 @@ RowsPlan rows_plan(int phase, const DraftParams &p, int cus, size_t part_floats)
 bool rows_gemm_serves(int phase, const DraftParams &p, int cus) {
     const int K = rows_k(phase, p);
     if (K % kRgBK) return false;
+    if (phase == BG_LMHEAD && rows_n(phase, p) > Rows128x512::BN * kMaxHeadCands) return false; // no room for the candidates
     if (p.seq_hi - p.seq_lo > 16) return true;
     // Up to 16 rows the batched core's plain kernel (waves split the reduction) streams large matrices as fast, and adds its
     // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with

@@ -996,10 +996,10 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             // does (a relaxed ticket; the parts are written and read with device-coherent accesses, no cache is written
             // back or invalidated): config 3 runs 2.4 % faster than with a kernel of its own per phase.  Above 16
             // sequences a row group holds 64/NA tiles x NA sequence tiles of sums and the last workgroup becomes the
-            // bottleneck (config 5: 8.6 % slower), so there a small epilogue kernel spread over the chip adds them -
+            // bottleneck (8.6 % of a step at 64), so there a small epilogue kernel spread over the chip adds them -
             // except for the output head, whose epilogue kernel would leave four times as many argmax candidates
             // behind (measured: 122 vs 97 us at 64 sequences).
-            p.bg_sep[ph] = (kp >= 2 && ph != BG_LMHEAD && na > 1) ? 1 : 0;
+            p.bg_sep[ph] = (kp >= 2 && ph == BG_DOWN && na > 1) ? 1 : 0; // (the phases such a call may bring here)
             lds_bg[ph] = bgemv_lds_bytes(((units + rg - 1) / rg) * 16);
         };
         plan(BG_PROJ, p.d / 16, 1, 2 * p.d, na);
@@ -1041,7 +1041,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             plan(BG_LMHEAD, (q.n + 15) / 16, 1, p.d, na_g);
             head_plan[g] = HeadPlan{p.bg_rg[BG_LMHEAD], p.bg_kp[BG_LMHEAD], p.bg_sep[BG_LMHEAD], lds_bg[BG_LMHEAD], false};
             if (lds_bg[BG_LMHEAD] > h->lds_limit) return MTP_ERR_CONFIG;
-            int cands = p.bg_sep[BG_LMHEAD] ? batch_epilogue_grid(BG_LMHEAD, q, na_g) : p.bg_rg[BG_LMHEAD];
+            int cands = p.bg_rg[BG_LMHEAD];
             head_plan[g].tiled = rows_gemm_serves(BG_LMHEAD, q, grid);
             if (head_plan[g].tiled) cands = rows_head_cands(q, grid, l.part_floats);
             if (groups.count) groups.cands[g] = cands;
