@@ -653,10 +653,8 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             groups.n[g] = s < 0 ? c.vocab_size : h->subset_n[s];
         }
         subset_index = seq_subset[0];
-        if (groups.count == 1) { // one list for everybody is the plain call
-            groups.count = 0;
-            seq_subset = nullptr;
-        }
+        if (groups.count == 1) groups.count = 0; // one list for everybody: the plain call's kernels, except that a single
+                                                 // sequence keeps its launch per phase
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 

@@ -97,7 +97,8 @@ struct IsHeadRows<BgHeadRows<CAND>> {
 // One 1 KB piece from memory into LDS: lane l fetches 16 bytes at voff[l] + soff of the buffer, they land at lds + 16 l.
 // In assembler because the compiler, which cannot tell the stages of the ring apart, would wait for ALL such loads in
 // flight before the next LDS read; there are no output registers, and the counted waits of the main loop are the only
-// ones these loads need.  (One wait state between the write of m0 and its use.)
+// ones these loads need.  (One wait state between the write of m0 and its use; m0 is reserved, the compiler writes it itself
+// wherever it needs it.)
 __device__ __forceinline__ void rg_load_lds(const u32x4 &rs, uint32_t lds, int voff, int soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :
