@@ -339,10 +339,11 @@ int fit_max_splits(const mtp_config &c, int B) {
     const int t = fit_min_tokens(c, B);
     return (c.kv_capacity + t - 1) / t;
 }
+bool fit_possible(const mtp_config &c, int B) { return B <= kFitMaxRows && split_tokens_for(c, B) >= kFitMinPlanned; }
 size_t attn_part_floats(const mtp_config &c) {
     size_t best = 0;
     for (int B = 1; B <= c.max_batch; ++B)
-        best = std::max(best, (size_t)B * std::max(max_splits_for(c, B), B <= kFitMaxRows ? fit_max_splits(c, B) : 0));
+        best = std::max(best, (size_t)B * std::max(max_splits_for(c, B), fit_possible(c, B) ? fit_max_splits(c, B) : 0));
     return best * c.n_q_heads * (c.head_dim + 2);
 }
 
@@ -770,7 +771,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     p.nb_d = fit(p.d, 2);
     p.nb_q = fit(p.qd, 1);
     p.nb_down = fit(p.F, 1);
-    const int strip_splits = std::max(p.max_splits, B <= kFitMaxRows ? fit_max_splits(c, B) : 0); // of the attention's merge
+    const int strip_splits = std::max(p.max_splits, fit_possible(c, B) ? fit_max_splits(c, B) : 0); // of the attention's merge
     const size_t lds_proj = gemv_lds_bytes(2 * p.d, p.nb_proj, 1), lds_d1 = gemv_lds_bytes(p.d, p.nb_d, 1),
                  lds_d2 = gemv_lds_bytes(p.d, p.nb_d, 2), lds_q = gemv_lds_bytes(p.qd, p.nb_q, 1),
                  lds_down = gemv_lds_bytes(p.F, p.nb_down, 1),
@@ -804,8 +805,8 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     const bool att_block = mfma_attn && ext && ext->m_max > 1;
     const int att_seqs = ext ? ext->B : B, att_jp = att_block ? 16 / (p.Hq / p.Hkv) : 1;
     const int att_groups = att_block ? (ext->m_max + att_jp - 1) / att_jp : 1;
-    const bool att_fit = mfma_attn && (!ext || att_block) && B <= kFitMaxRows && att_seqs <= kWave &&
-                     p.split_tokens >= kFitMinPlanned && 4 * att_seqs * p.Hkv * att_groups <= 3 * h->num_cus;
+    const bool att_fit = mfma_attn && (!ext || att_block) && fit_possible(c, B) && att_seqs <= kWave &&
+                     4 * att_seqs * p.Hkv * att_groups <= 3 * h->num_cus;
     auto with_fit = [&](DraftParams pa) {
         if (!att_fit) return pa;
         pa.attn_fit_min = fit_min_tokens(c, B);
