@@ -44,6 +44,15 @@ struct RowsTile {
     static constexpr int AP = 2 * BM / kPieceRows, NA = (AP + kWaves - 1) / kWaves, NW = BN / kPieceRows / kWaves, NL = NA + NW;
     static constexpr int kStage = (2 * BM + BN) * kRow;
     static constexpr int kLds = ST * kStage;
+    // How the sums are rounded.  Every MFMA of a chain rounds its accumulator once, so one chain over a whole reduction is
+    // less exact than the batched core, whose waves and parts add up short ones (rms error of 2048 / 4096 products against 64
+    // bits: 1.2 to 2.2e-7 in one chain, 0.8 to 1.1e-7 there; 1 to 2 % of a draft step's error of 6e-6, most of which is the
+    // 16 bits of the activations).  So where the registers allow: the lo halves in accumulators of their own (no
+    // rounding of the large sum for them), and after every kChain steps the sums move to a second set (0: never).  Now 0.7 to
+    // 0.9e-7.  The tiles of 24 accumulators do it for the output head only, whose sums are outputs: the error of calls whose body
+    // they compute (96 to 512 rows) is that of the batched core without it, and the moves cost 0.5 % of such a call.
+    static constexpr bool kLoApart = TI * TJ <= 8;
+    static constexpr int kChain = TI * TJ <= 2 ? 2 : kLoApart ? 4 : TI * TJ <= 24 ? 16 : 0;
     static_assert(BK == 32 || BK == 64, "the chunk order below");
     static_assert(BN % (kPieceRows * kWaves) == 0 && (AP % kWaves == 0 || kWaves % AP == 0), "whole pieces per wave");
     static_assert((ST - 2) * NL < 64, "the wait counts the requests of the later stages");
@@ -120,6 +129,8 @@ template <class T, class Ph, class Make>
 __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phase, int KP, char *smem) {
     constexpr int NMAT = Ph::NMAT, BM = T::BM, BN = T::BN, NA = T::NA, NW = T::NW, NL = T::NL, ST = T::ST;
     constexpr int TI = T::TI, TJ = T::TJ, WN = T::WN;
+    constexpr bool kLoApart = T::kLoApart;
+    constexpr int kChain = kLoApart || IsHeadRows<Ph>::value ? T::kChain : 0; // (see RowsTile)
     constexpr bool kPairApart = TJ % NMAT != 0; // the tiles of a pair sit in neighbouring waves
     static_assert(!kPairApart || (TJ == 1 && NMAT == 2 && T::WM == 1), "pairs of tiles: inside a wave's piece, or one each");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -217,11 +228,27 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
 #pragma unroll
     for (int h = 0; h < T::BK / 32; ++h) frag[h] = i16 * kRow + (((4 * h + g) ^ chunk_order(i16)) * 16);
     const char *abase = smem + wm * (16 * TI) * kRow, *wbase = smem + 2 * (BM * kRow) + wn * (16 * TJ) * kRow;
-    f32x4 acc[TI][TJ];
+    // the sums of the present chain, of the chains before it, of the lo halves
+    f32x4 acc[TI][TJ], tot[kChain ? TI : 1][kChain ? TJ : 1], lo[kLoApart ? TI : 1][kLoApart ? TJ : 1];
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int tj = 0; tj < TJ; ++tj) {
+            acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kChain > 0) tot[ti][tj] = acc[ti][tj];
+            if constexpr (kLoApart) lo[ti][tj] = acc[ti][tj];
+        }
+    auto end_chain = [&]() {
+        if constexpr (kChain > 0) {
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < TJ; ++tj) {
+                    tot[ti][tj] += acc[ti][tj];
+                    acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
 
     // (a scalar register written by the vector unit needs five wait states before a load reads it; the compiler does not
     // look into the assembler of the requests)
@@ -250,10 +277,25 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
 #pragma unroll
                 for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(ah, wf[tj], acc[ti][tj]);
 #pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(al, wf[tj], acc[ti][tj]);
+                for (int tj = 0; tj < TJ; ++tj) {
+                    if constexpr (kLoApart)
+                        lo[ti][tj] = mfma16(al, wf[tj], lo[ti][tj]);
+                    else
+                        acc[ti][tj] = mfma16(al, wf[tj], acc[ti][tj]);
+                }
             }
         }
         stage = stage == ST - 1 ? 0 : stage + 1;
+        if (kChain > 0 && ((ks - k0) & (kChain - 1)) == kChain - 1) end_chain();
+    }
+    if constexpr (kChain > 0) {
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < TJ; ++tj) {
+                if constexpr (kLoApart) acc[ti][tj] += lo[ti][tj];
+                acc[ti][tj] += tot[ti][tj];
+            }
     }
     // the trailing requests have landed and every wave is done reading: the LDS is free
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");

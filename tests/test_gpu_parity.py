@@ -506,6 +506,45 @@ def test_many_rows_tiled_matrix_products(gpu, d_ffn, subset, rows):
     check_extend(ref, res, caches, act, ext_len)
 
 
+@pytest.mark.parametrize("d,rows,n", [(1024, 5, 3584), (1024, 20, 8192), (1024, 64, 3584), (2048, 20, 8192),
+                                      (2048, 64, 8192), (2048, 100, 8192), (2048, 192, 8192), (4096, 5, 3584),
+                                      (4096, 20, 8192), (4096, 40, 8192), (4096, 100, 8192), (4096, 192, 3584)])
+def test_tiled_products_add_up_as_exactly_as_the_row_streaming_kernels(gpu, d, rows, n):
+    """The output head on activations that are exact in bf16 (x = +-1 through an identity projection, no attention, no
+    MLP, gains in bf16, no epsilon), so that its logits are off by the rounding of the sums alone.  Both kernels add d
+    products in single precision; how often a large partial sum is rounded is up to the order.  The row-streaming
+    kernels split a reduction over eight waves: the tiled products, whatever their tiles and parts, stay within 1.3
+    times their error (a whole reduction in one chain of matrix instructions has 1.4 to 3 times it at these sizes)."""
+    binding = gpu["binding"]
+    rng = np.random.default_rng(31)
+    shape = synth.HeadShape(d, 4, 2, 64, 256, n, rms_eps=0.0)
+    w = {k: np.zeros(s, np.float32) for k, s in synth.weight_shapes(shape).items()}
+    for k in w:
+        if k.startswith("g_") or k == "embed":
+            w[k][:] = 1.0
+    w["w_proj"][:, :d] = np.eye(d, dtype=np.float32)
+    w["lm_head"] = rng.standard_normal((n, d)).astype(np.float32) * 0.02
+    w["g_final_norm"] = (1.0 + 0.3 * rng.standard_normal(d)).astype(np.float32)
+    w = {k: synth.f32_to_bf16_bits(v) for k, v in w.items()}
+    h = np.where(rng.random((rows, d)) < 0.5, -1.0, 1.0).astype(np.float32)
+    ref = (h * synth.bf16_bits_to_f32(w["g_final_norm"])).astype(np.float64) @ \
+        synth.bf16_bits_to_f32(w["lm_head"]).astype(np.float64).T
+    eng = binding.DraftEngine(shape, w, [], rows, 64, 1)
+
+    def error(B, mode):
+        assert binding.mtp_set_launch_mode(eng.handle, mode) == 0
+        cache = [gpu["torch"].zeros((rows, 2, 64, 64), dtype=gpu["torch"].bfloat16, device="cuda") for _ in range(2)]
+        out = eng.draft(1, -1, eng.to_device_bits(synth.f32_to_bf16_bits(h[:B])), eng.to_device_i32(np.zeros(B, np.int32)),
+                        *cache, eng.to_device_i32(np.zeros(B, np.int32)), want_logits=True)
+        assert eng.poll_error() == 0
+        diff = out["logits"][:, 0].cpu().numpy().astype(np.float64) - ref[:B]
+        return np.sqrt((diff ** 2).mean() / (ref[:B] ** 2).mean())
+
+    rows_err, tiled_err = error(4, binding.LAUNCH_ROWS), error(rows, binding.LAUNCH_AUTO)
+    eng.close()
+    assert tiled_err <= 1.3 * rows_err, (tiled_err, rows_err)
+
+
 def test_tiny_extend_long_capacity_matrix_core_attention(gpu, tiny):
     """A large capacity makes the splits long enough for the matrix-core attention (which merges its own splits)."""
     act = synth.make_activations(tiny["wl"], ctx=np.array([0, 31, 300, 1000], dtype=np.int32), capacity=32768)
