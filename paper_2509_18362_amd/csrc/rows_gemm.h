@@ -44,15 +44,16 @@ struct RowsTile {
     static constexpr int AP = 2 * BM / kPieceRows, NA = (AP + kWaves - 1) / kWaves, NW = BN / kPieceRows / kWaves, NL = NA + NW;
     static constexpr int kStage = (2 * BM + BN) * kRow;
     static constexpr int kLds = ST * kStage;
-    // How the sums are rounded.  Every MFMA of a chain rounds its accumulator once, so one chain over a whole reduction is
-    // less exact than the batched core, whose waves and parts add up short ones (rms error of 2048 / 4096 products against 64
-    // bits: 1.2 to 2.2e-7 in one chain, 0.8 to 1.1e-7 there; 1 to 2 % of a draft step's error of 6e-6, most of which is the
-    // 16 bits of the activations).  So where the registers allow: the lo halves in accumulators of their own (no
-    // rounding of the large sum for them), and after every kChain steps the sums move to a second set (0: never).  Now 0.7 to
-    // 0.9e-7.  The tiles of 24 accumulators do it for the output head only, whose sums are outputs: the error of calls whose body
-    // they compute (96 to 512 rows) is that of the batched core without it, and the moves cost 0.5 % of such a call.
-    static constexpr bool kLoApart = TI * TJ <= 8;
-    static constexpr int kChain = TI * TJ <= 2 ? 2 : kLoApart ? 4 : TI * TJ <= 24 ? 16 : 0;
+    // How the sums are rounded.  Every MFMA of a chain rounds its accumulator once, and a chain that takes the lo products
+    // along (2^-9 of the hi ones) loses their low bits in the large sum: one chain over a whole reduction is less exact than
+    // the batched core, whose waves and parts add up short ones (1 to 2 % of a draft step's error, most of which is the 16
+    // bits of the activations).  So where the registers allow, the lo halves have accumulators of their own; the smallest tiles
+    // also have one set per half step; and the sums move to another set every CHAIN steps - in the smallest tiles and, for
+    // tiles of up to 24 accumulators, in the output head, whose sums are outputs (elsewhere the error is the batched core's
+    // without that).  Costs 0.5 % of a step of a 1024-wide head, nothing measurable at 4096.
+    static constexpr bool kApart = TI * TJ <= 8;
+    static constexpr int SETS = TI * TJ <= 2 ? 2 : 1, CHAIN = TI * TJ <= 24 ? 16 : 0;
+    static_assert(SETS == 1 || BK == 64, "half steps");
     static_assert(BK == 32 || BK == 64, "the chunk order below");
     static_assert(BN % (kPieceRows * kWaves) == 0 && (AP % kWaves == 0 || kWaves % AP == 0), "whole pieces per wave");
     static_assert((ST - 2) * NL < 64, "the wait counts the requests of the later stages");
@@ -129,8 +130,9 @@ template <class T, class Ph, class Make>
 __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phase, int KP, char *smem) {
     constexpr int NMAT = Ph::NMAT, BM = T::BM, BN = T::BN, NA = T::NA, NW = T::NW, NL = T::NL, ST = T::ST;
     constexpr int TI = T::TI, TJ = T::TJ, WN = T::WN;
-    constexpr bool kLoApart = T::kLoApart;
-    constexpr int kChain = kLoApart || IsHeadRows<Ph>::value ? T::kChain : 0; // (see RowsTile)
+    constexpr bool kApart = T::kApart;
+    constexpr int SETS = T::SETS;
+    constexpr int kChain = SETS > 1 || IsHeadRows<Ph>::value ? T::CHAIN : 0; // (see RowsTile)
     constexpr bool kPairApart = TJ % NMAT != 0; // the tiles of a pair sit in neighbouring waves
     static_assert(!kPairApart || (TJ == 1 && NMAT == 2 && T::WM == 1), "pairs of tiles: inside a wave's piece, or one each");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -228,26 +230,28 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
 #pragma unroll
     for (int h = 0; h < T::BK / 32; ++h) frag[h] = i16 * kRow + (((4 * h + g) ^ chunk_order(i16)) * 16);
     const char *abase = smem + wm * (16 * TI) * kRow, *wbase = smem + 2 * (BM * kRow) + wn * (16 * TJ) * kRow;
-    // the sums of the present chain, of the chains before it, of the lo halves
-    f32x4 acc[TI][TJ], tot[kChain ? TI : 1][kChain ? TJ : 1], lo[kLoApart ? TI : 1][kLoApart ? TJ : 1];
+    // acc: the sums of the present chains; lo: of the lo halves, where they are apart; tot: of the chains before
+    f32x4 acc[SETS][TI][TJ], lo[kApart ? TI : 1][kApart ? TJ : 1], tot[kChain ? TI : 1][kChain ? TJ : 1];
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
         for (int tj = 0; tj < TJ; ++tj) {
-            acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (kChain > 0) tot[ti][tj] = acc[ti][tj];
-            if constexpr (kLoApart) lo[ti][tj] = acc[ti][tj];
-        }
-    auto end_chain = [&]() {
-        if constexpr (kChain > 0) {
 #pragma unroll
-            for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) {
-                    tot[ti][tj] += acc[ti][tj];
-                    acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
+            for (int u = 0; u < SETS; ++u) acc[u][ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kApart) lo[ti][tj] = acc[0][ti][tj];
+            if constexpr (kChain > 0) tot[ti][tj] = acc[0][ti][tj];
         }
+    auto end_chains = [&]() {
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < TJ; ++tj) {
+                f32x4 a = acc[0][ti][tj];
+                if constexpr (SETS == 2) a += acc[SETS - 1][ti][tj];
+                tot[kChain ? ti : 0][kChain ? tj : 0] += a;
+#pragma unroll
+                for (int u = 0; u < SETS; ++u) acc[u][ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
     };
 
     // (a scalar register written by the vector unit needs five wait states before a load reads it; the compiler does not
@@ -258,45 +262,48 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
 #pragma unroll
     for (int u = 0; u < ST - 1; ++u) request(k0 + u, u);
     int stage = 0;
-    for (int ks = k0; ks < k1; ++ks) {
-        // This wave's pieces of step ks have landed (those of the later steps may still be on their way) and its LDS reads of
-        // step ks - 1 are back; after the barrier that holds for all waves: step ks can be read, and the stage of step
-        // ks - 1 takes step ks + ST - 1.
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((ST - 2) * NL) : "memory");
-        request(ks + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+    // This wave's pieces of step ks have landed (those of the later steps may still be on their way) and its LDS reads of
+    // step ks - 1 are back; after the barrier that holds for all waves: step ks can be read, and the stage of step
+    // ks - 1 takes step ks + ST - 1.
+    auto await_step = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((ST - 2) * NL) : "memory"); };
+    auto multiply = [&](int stage, int h) {
         const char *as = abase + stage * T::kStage, *ws = wbase + stage * T::kStage;
+        u32x4 wf[TJ];
 #pragma unroll
-        for (int h = 0; h < T::BK / 32; ++h) {
-            u32x4 wf[TJ];
+        for (int tj = 0; tj < TJ; ++tj) wf[tj] = *reinterpret_cast<const u32x4 *>(ws + frag[h] + tj * 16 * kRow);
 #pragma unroll
-            for (int tj = 0; tj < TJ; ++tj) wf[tj] = *reinterpret_cast<const u32x4 *>(ws + frag[h] + tj * 16 * kRow);
+        for (int ti = 0; ti < TI; ++ti) {
+            const u32x4 ah = *reinterpret_cast<const u32x4 *>(as + frag[h] + ti * 16 * kRow);
+            const u32x4 al = *reinterpret_cast<const u32x4 *>(as + frag[h] + (BM * kRow) + ti * 16 * kRow);
 #pragma unroll
-            for (int ti = 0; ti < TI; ++ti) {
-                const u32x4 ah = *reinterpret_cast<const u32x4 *>(as + frag[h] + ti * 16 * kRow);
-                const u32x4 al = *reinterpret_cast<const u32x4 *>(as + frag[h] + (BM * kRow) + ti * 16 * kRow);
+            for (int tj = 0; tj < TJ; ++tj) acc[h % SETS][ti][tj] = mfma16(ah, wf[tj], acc[h % SETS][ti][tj]);
 #pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16(ah, wf[tj], acc[ti][tj]);
-#pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) {
-                    if constexpr (kLoApart)
-                        lo[ti][tj] = mfma16(al, wf[tj], lo[ti][tj]);
-                    else
-                        acc[ti][tj] = mfma16(al, wf[tj], acc[ti][tj]);
-                }
+            for (int tj = 0; tj < TJ; ++tj) {
+                f32x4 &l = kApart ? lo[kApart ? ti : 0][kApart ? tj : 0] : acc[h % SETS][ti][tj];
+                l = mfma16(al, wf[tj], l);
             }
         }
-        stage = stage == ST - 1 ? 0 : stage + 1;
-        if (kChain > 0 && ((ks - k0) & (kChain - 1)) == kChain - 1) end_chain();
-    }
-    if constexpr (kChain > 0) {
+    };
+    // (chains in an outer loop, so that the inner one stays short: with the moves behind a branch of the inner loop a draft
+    // step of a 1024-wide head took 2.5 % longer, most launches of which are 8 to 16 steps)
+    int ks = k0;
+    do {
+        const int end = kChain > 0 ? min(ks + kChain, k1) : k1;
+        for (; ks < end; ++ks) {
+            await_step();
+            request(ks + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+#pragma unroll
+            for (int h = 0; h < T::BK / 32; ++h) multiply(stage, h);
+            stage = stage == ST - 1 ? 0 : stage + 1;
+        }
+        if constexpr (kChain > 0) end_chains();
+    } while (kChain > 0 && ks < k1);
+    f32x4(&sum)[TI][TJ] = kChain > 0 ? reinterpret_cast<f32x4(&)[TI][TJ]>(tot) : acc[0];
+    if constexpr (kApart)
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-            for (int tj = 0; tj < TJ; ++tj) {
-                if constexpr (kLoApart) acc[ti][tj] += lo[ti][tj];
-                acc[ti][tj] += tot[ti][tj];
-            }
-    }
+            for (int tj = 0; tj < TJ; ++tj) sum[ti][tj] += lo[ti][tj];
     // the trailing requests have landed and every wave is done reading: the LDS is free
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
 
@@ -309,7 +316,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
             for (int tj = 0; tj < TJ; ++tj) {
                 const int vt = nblk * (BN / 16) + wn * TJ + tj, rt = mblk * (BM / 16) + wm * TI + ti;
                 if (vt < ntv && rt * 16 < R)
-                    *reinterpret_cast<f32x4 *>(p.part + ((((size_t)kp * ntv + vt) * RT + rt) * kWave + lane) * 4) = acc[ti][tj];
+                    *reinterpret_cast<f32x4 *>(p.part + ((((size_t)kp * ntv + vt) * RT + rt) * kWave + lane) * 4) = sum[ti][tj];
             }
         return;
     }
@@ -325,7 +332,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
             unsigned long long best[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
             for (int tj = 0; tj < TJ; ++tj)
-                ph.epi_best(16 * (TI * wm + ti) + 4 * g, nblk * (BN / 16) + wn * TJ + tj, i16, acc[ti][tj], scale, best);
+                ph.epi_best(16 * (TI * wm + ti) + 4 * g, nblk * (BN / 16) + wn * TJ + tj, i16, sum[ti][tj], scale, best);
             if (Ph::CANDS) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
@@ -352,13 +359,13 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
         f32x4 *half = reinterpret_cast<f32x4 *>(smem + 16 * BM); // [kWaves][TI][kWave], behind the scales
         if (wn & 1)
 #pragma unroll
-            for (int ti = 0; ti < TI; ++ti) half[(wn * TI + ti) * kWave + lane] = acc[ti][0];
+            for (int ti = 0; ti < TI; ++ti) half[(wn * TI + ti) * kWave + lane] = sum[ti][0];
         __syncthreads();
         const int vt = nblk * (BN / 16) + wn;
         if (!(wn & 1) && vt < ntv)
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti) {
-                const f32x4 sums[NMAT] = {acc[ti][0], half[((wn + 1) * TI + ti) * kWave + lane]};
+                const f32x4 sums[NMAT] = {sum[ti][0], half[((wn + 1) * TI + ti) * kWave + lane]};
                 ph.epi(16 * ti + 4 * g, vt, i16, sums, scale);
             }
     } else {
@@ -370,7 +377,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
                 if (vt >= ntv) continue; // uniform per wave
                 f32x4 sums[NMAT];
 #pragma unroll
-                for (int m = 0; m < NMAT; ++m) sums[m] = acc[ti][tj + m];
+                for (int m = 0; m < NMAT; ++m) sums[m] = sum[ti][tj + m];
                 ph.epi(16 * (TI * wm + ti) + 4 * g, vt, i16, sums, scale);
             }
     }

@@ -1,0 +1,90 @@
+// Which tiles, and how many reduction parts, a tiled matrix product (rows_gemm.h) runs with.  Host code without HIP: the
+// rules can be compiled and checked on their own.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+
+namespace mtp {
+
+constexpr int kMaxHeadCands = 1024; // candidates of the output head a sequence has room for
+constexpr int kRgBK = 32;           // elements of the shortest reduction step
+
+// One matrix phase over some rows of a call.
+struct RowsCall {
+    int K, n, rows; // reduction length, weight rows in whole tiles of sixteen, rows of activations
+    bool head;      // leaves argmax candidates: one per row and block of weight rows, or per group of the adding launch
+    bool pairs;     // gate/up: two tiles make one
+};
+struct RowsPlan {
+    int tile, kp, mb, nb; // tiling, reduction parts, blocks of rows and of weight rows
+    double us;            // estimated time
+};
+
+// the tilings of the many-row matrix products
+struct RowsTileInfo {
+    int bm, bn, bk, lds;
+    double step_us; // one reduction step of a workgroup that has its CU to itself
+};
+constexpr int kRowsTiles = 7;
+constexpr RowsTileInfo kRowsTile[kRowsTiles] = {
+    {256, 256, 32, 3 * (2 * 256 + 256) * 64, 1.3}, {128, 512, 32, 3 * (2 * 128 + 512) * 64, 1.3},
+    {128, 384, 32, 3 * (2 * 128 + 384) * 64, 1.0}, {64, 256, 64, 3 * (2 * 64 + 256) * 128, 1.3},
+    {64, 128, 64, 4 * (2 * 64 + 128) * 128, 0.8},  {32, 128, 64, 6 * (2 * 32 + 128) * 128, 0.55},
+    {16, 128, 64, 7 * (2 * 16 + 128) * 128, 0.52}};
+constexpr int kRowsHalf = 4;               // the tilings from this one on take a last step that is half a one
+constexpr int kRowsMinSteps = 8;           // reduction steps of 32 a part keeps at least
+constexpr double kRowsFixedUs = 6.0;       // of a workgroup besides its steps
+constexpr double kRowsEpilogueUs = 7.5;    // the launch that adds the parts
+constexpr double kRowsPartUs = 8.0 / 5e6;  // a float of the parts written and read
+constexpr double kRowsReadUs = 1.0 / 5.5e6; // a byte of weights, per block of rows (the blocks after the first from L2)
+
+// The tiling and the number of reduction parts with the shortest estimated time: rounds of one workgroup per CU, each its
+// share of the steps (or the time HBM takes for the weights, if that is longer), and the parts' sums written and read
+// once.  The constants are this kernel's own times on the 7B-shaped head: a step of a workgroup in long reductions, what a
+// workgroup takes from launch to first step and from last step to end, the launch that adds the parts.  Parts pay where
+// a phase has few tiles: 4096 weight rows at 512 rows are 32 tiles of 256 x 256 and take 84 us in eight parts, 270 in one.
+// part_floats: room of the partial buffer.
+inline RowsPlan rows_plan(const RowsCall &c, int cus, size_t part_floats) {
+    RowsPlan best{};
+    best.us = 1e30;
+    for (int t = kRowsTiles - 1; t >= 0; --t) { // (small tiles first: they stay where HBM bounds all alike)
+        const RowsTileInfo &ti = kRowsTile[t];
+        if (c.K % ti.bk && t < kRowsHalf) continue;
+        const int steps = (c.K + ti.bk - 1) / ti.bk;
+        const int mb = (c.rows + ti.bm - 1) / ti.bm, nb = (c.n + ti.bn - 1) / ti.bn;
+        const double weights_us = (double)c.n * c.K * 2 * mb * kRowsReadUs;
+        for (int kp = 1; kp <= 16 && (kp == 1 || c.K / 32 / kp >= kRowsMinSteps); ++kp) {
+            const double sums = (double)kp * c.n * mb * ti.bm; // floats of the parts
+            if (kp > 1 && sums > (double)part_floats) break;
+            if (c.head && kp == 1 && nb > kMaxHeadCands) continue; // a candidate per row and N block
+            const int rounds = (mb * nb * kp + cus - 1) / cus;
+            const double us = std::max(weights_us, rounds * ((steps + kp - 1) / kp * ti.step_us)) + rounds * kRowsFixedUs +
+                              (kp > 1 ? kRowsEpilogueUs + sums * kRowsPartUs : 0.0);
+            if (us < best.us) best = RowsPlan{t, kp, mb, nb, us};
+        }
+    }
+    return best;
+}
+
+// workgroups per row tile of the kernel that adds the parts
+inline int rows_epilogue_groups(const RowsCall &c, int cus) {
+    const int live = (c.rows + 15) / 16, per_wave = c.n / 16 / (c.pairs ? 2 : 1);
+    return std::max(1, std::min({(per_wave + 7) / 8, 8 * cus / live, kMaxHeadCands})); // (eight waves each)
+}
+
+// The tiled product serves the phase, and is the faster kernel.
+inline bool rows_gemm_serves(const RowsCall &c, int cus) {
+    if (c.K % kRgBK) return false;
+    if (c.head && c.n > kRowsTile[1].bn * kMaxHeadCands) return false; // no room for the candidates
+    if (c.rows > 16) return true;
+    // Up to 16 rows the batched core's plain kernel (waves split the reduction) streams large matrices as fast, and adds its
+    // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with
+    // the launch that adds the parts.  Measured at five rows (us, this kernel / that one): 4096 x 2048 11 / 14, 2048 x 6144
+    // 13 / 17, 12288 x 2048 14 / 17, 8192 x 2048 of a head 15 / 18; at sixteen rows 4096 x 4096 17 / 17.5, 6144 x 4096
+    // 21 / 19.5, 4096 x 8192 23 / 21, 22016 x 4096 40 / 35; a head that fills the chip in one part, 32768 x 4096: 53 / 59
+    // (a head of more blocks than candidates takes a larger tile: 151680 x 4096 at sixteen rows 260 / 247).
+    const int bn = kRowsTile[kRowsTiles - 1].bn;
+    return c.K <= 2048 || (double)c.n * c.K * 2 <= 32e6 || (c.head && c.n >= bn * cus && c.n <= bn * kMaxHeadCands);
+}
+
+} // namespace mtp
