@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "phases.h"
+#include "rows_plan.h"
 
 namespace mtp {
 

@@ -165,16 +165,7 @@ bg_kernel_t pick(int phase, int na) {
     default: return pick_na<BG_LMHEAD>(na);
     }
 }
-// the tilings of the many-row matrix products
 typedef void (*rows_kernel_t)(DraftParams, int, int);
-struct RowsTileInfo {
-    int bm, bn, bk, lds;
-    double step_us; // one reduction step of a workgroup that has its CU to itself
-};
-template <class T>
-constexpr RowsTileInfo rows_tile_info(double step_us) {
-    return RowsTileInfo{T::BM, T::BN, T::BK, T::kLds, step_us};
-}
 typedef RowsTile<4, 4, 2, 8, 3> Rows256x256;
 typedef RowsTile<4, 2, 4, 8, 3> Rows128x512;
 typedef RowsTile<4, 2, 4, 6, 3> Rows128x384;
@@ -182,16 +173,16 @@ typedef RowsTile<2, 2, 4, 4, 3, 64> Rows64x256;
 typedef RowsTile<2, 2, 4, 2, 4, 64> Rows64x128;
 typedef RowsTile<1, 2, 4, 2, 6, 64> Rows32x128;
 typedef RowsTile<1, 1, 8, 1, 7, 64> Rows16x128;
-constexpr int kRowsTiles = 7;
-constexpr RowsTileInfo kRowsTile[kRowsTiles] = {
-    rows_tile_info<Rows256x256>(1.3), rows_tile_info<Rows128x512>(1.3), rows_tile_info<Rows128x384>(1.0),
-    rows_tile_info<Rows64x256>(1.3), rows_tile_info<Rows64x128>(0.8), rows_tile_info<Rows32x128>(0.55),
-    rows_tile_info<Rows16x128>(0.52)};
-constexpr int kRowsMinSteps = 8;           // reduction steps a part keeps at least
-constexpr double kRowsFixedUs = 6.0;       // of a workgroup besides its steps
-constexpr double kRowsEpilogueUs = 7.5;    // the launch that adds the parts
-constexpr double kRowsPartUs = 8.0 / 5e6;  // a float of the parts written and read
-constexpr double kRowsReadUs = 1.0 / 5.5e6; // a byte of weights, per block of rows (the blocks after the first from L2)
+typedef RowsTile<2, 2, 4, 2, 4, 64, true> Rows64x128Half;
+typedef RowsTile<1, 2, 4, 2, 6, 64, true> Rows32x128Half;
+typedef RowsTile<1, 1, 8, 1, 7, 64, true> Rows16x128Half;
+template <class T>
+constexpr bool is_tile(int t) { // the plan's entry t describes T
+    return kRowsTile[t].bm == T::BM && kRowsTile[t].bn == T::BN && kRowsTile[t].bk == T::BK && kRowsTile[t].lds == T::kLds;
+}
+static_assert(is_tile<Rows256x256>(0) && is_tile<Rows128x512>(1) && is_tile<Rows128x384>(2) && is_tile<Rows64x256>(3) &&
+                  is_tile<Rows64x128>(4) && is_tile<Rows32x128>(5) && is_tile<Rows16x128>(6),
+              "the kernels below in the order of the plan's tilings");
 template <int PH>
 rows_kernel_t pick_rows(int tile) {
     switch (tile) {
@@ -204,7 +195,24 @@ rows_kernel_t pick_rows(int tile) {
     default: return k_rows_gemm<PH, Rows16x128>;
     }
 }
-rows_kernel_t rows_kernel(int phase, int tile) {
+template <int PH>
+rows_kernel_t pick_rows_half(int tile) { // reductions of an odd number of 32s, tiles with steps of 64
+    switch (tile) {
+    case 4: return k_rows_gemm<PH, Rows64x128Half>;
+    case 5: return k_rows_gemm<PH, Rows32x128Half>;
+    case 6: return k_rows_gemm<PH, Rows16x128Half>;
+    default: return nullptr;
+    }
+}
+rows_kernel_t rows_kernel(int phase, int tile, bool half) {
+    if (half) switch (phase) { // (never of the projections: 2 d and Hq * hd are multiples of 64)
+        case BG_QKV: return pick_rows_half<BG_QKV>(tile);
+        case BG_GATEUP: return pick_rows_half<BG_GATEUP>(tile);
+        case BG_DOWN: return pick_rows_half<BG_DOWN>(tile);
+        case BG_LMHEAD:
+        case kHeadLogits: return pick_rows_half<BG_LMHEAD>(tile);
+        default: return nullptr;
+        }
     switch (phase) {
     case BG_PROJ: return pick_rows<BG_PROJ>(tile);
     case BG_QKV: return pick_rows<BG_QKV>(tile);
@@ -271,8 +279,10 @@ bool batch_allow_lds(size_t lds_limit) {
     bool ok = true;
     for (int ph = 0; ph <= kHeadLogits; ++ph)
         for (int t = 0; t < kRowsTiles; ++t)
-            ok = ok && hipFuncSetAttribute((const void *)rows_kernel(ph, t), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds_limit) == hipSuccess;
+            for (bool half : {false, true})
+                ok = ok && (!rows_kernel(ph, t, half) ||
+                            hipFuncSetAttribute((const void *)rows_kernel(ph, t, half), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)lds_limit) == hipSuccess);
     for (int hd = 64; hd <= 128; hd *= 2)
         for (int g = 1; g <= 8; g *= 2)
             ok = ok && hipFuncSetAttribute((const void *)attn_mfma_kernel(g, hd, false),
@@ -297,87 +307,38 @@ void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t ld
 }
 
 namespace {
-int rows_k(int phase, const DraftParams &p) { // reduction length of a phase
-    return phase == BG_PROJ ? 2 * p.d : phase == BG_OPROJ ? p.qd : phase == BG_DOWN ? p.F : p.d;
-}
-int rows_n(int phase, const DraftParams &p) { // weight rows, in whole tiles of sixteen
+RowsCall rows_call(int phase, const DraftParams &p) {
     auto rows16 = [](int rows) { return (rows + 15) / 16 * 16; };
-    return phase == BG_QKV      ? rows16(p.qkv_dim)
-           : phase == BG_GATEUP ? 2 * rows16(p.F)
-           : phase >= BG_LMHEAD ? rows16(p.n)
-                                : p.d;
-}
-// The tiling and the number of reduction parts with the shortest estimated time: rounds of one workgroup per CU, each its
-// share of the steps (or the time HBM takes for the weights, if that is longer), and the parts' sums written and read
-// once.  The constants are this kernel's own times on the 7B-shaped head: a step of a workgroup in long reductions, what a
-// workgroup takes from launch to first step and from last step to end, the launch that adds the parts.  Parts pay where
-// a phase has few tiles: 4096 weight rows at 512 rows are 32 tiles of 256 x 256 and take 84 us in eight parts, 270 in one.
-struct RowsPlan {
-    int tile, kp, mb, nb;
-};
-RowsPlan rows_plan(int phase, const DraftParams &p, int cus, size_t part_floats) {
-    const int K = rows_k(phase, p), n = rows_n(phase, p), rows = p.seq_hi - p.seq_lo;
-    RowsPlan best{};
-    double best_us = 1e30;
-    for (int t = kRowsTiles - 1; t >= 0; --t) { // (small tiles first: they stay where HBM bounds all alike)
-        const RowsTileInfo &ti = kRowsTile[t];
-        if (K % ti.bk) continue;
-        const int steps = K / ti.bk;
-        const int mb = (rows + ti.bm - 1) / ti.bm, nb = (n + ti.bn - 1) / ti.bn;
-        const double weights_us = (double)n * K * 2 * mb * kRowsReadUs;
-        for (int kp = 1; kp <= 16 && (kp == 1 || K / 32 / kp >= kRowsMinSteps); ++kp) {
-            const double sums = (double)kp * n * mb * ti.bm; // floats of the parts
-            if (kp > 1 && sums > (double)part_floats) break;
-            if (phase == BG_LMHEAD && kp == 1 && nb > kMaxHeadCands) continue; // a candidate per row and N block
-            const int rounds = (mb * nb * kp + cus - 1) / cus;
-            const double us = std::max(weights_us, rounds * ((steps + kp - 1) / kp * ti.step_us)) + rounds * kRowsFixedUs +
-                              (kp > 1 ? kRowsEpilogueUs + sums * kRowsPartUs : 0.0);
-            if (us < best_us) {
-                best_us = us;
-                best = RowsPlan{t, kp, mb, nb};
-            }
-        }
-    }
-    return best;
+    RowsCall c;
+    c.K = phase == BG_PROJ ? 2 * p.d : phase == BG_OPROJ ? p.qd : phase == BG_DOWN ? p.F : p.d;
+    c.n = phase == BG_QKV      ? rows16(p.qkv_dim)
+          : phase == BG_GATEUP ? 2 * rows16(p.F)
+          : phase == BG_LMHEAD ? rows16(p.n)
+                               : p.d;
+    c.rows = p.seq_hi - p.seq_lo;
+    c.head = phase == BG_LMHEAD;
+    c.pairs = phase == BG_GATEUP;
+    return c;
 }
 } // namespace
 
-bool rows_gemm_serves(int phase, const DraftParams &p, int cus) {
-    const int K = rows_k(phase, p);
-    if (K % kRgBK) return false;
-    if (phase == BG_LMHEAD && rows_n(phase, p) > Rows128x512::BN * kMaxHeadCands) return false; // no room for the candidates
-    if (p.seq_hi - p.seq_lo > 16) return true;
-    // Up to 16 rows the batched core's plain kernel (waves split the reduction) streams large matrices as fast, and adds its
-    // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with
-    // the launch that adds the parts.  Measured at five rows (us, this kernel / that one): 4096 x 2048 11 / 14, 2048 x 6144
-    // 13 / 17, 12288 x 2048 14 / 17, 8192 x 2048 of a head 15 / 18; at sixteen rows 4096 x 4096 17 / 17.5, 6144 x 4096
-    // 21 / 19.5, 4096 x 8192 23 / 21, 22016 x 4096 40 / 35; a head that fills the chip in one part, 32768 x 4096: 53 / 59
-    // (a head of more blocks than candidates takes a larger tile: 151680 x 4096 at sixteen rows 260 / 247).
-    const int n = rows_n(phase, p);
-    return K <= 2048 || (double)n * K * 2 <= 32e6 ||
-           (phase == BG_LMHEAD && n >= Rows16x128::BN * cus && n <= Rows16x128::BN * kMaxHeadCands);
-}
-namespace {
-// workgroups per row tile of the kernel that adds the parts
-int rows_epilogue_groups(int phase, const DraftParams &p, int cus) {
-    const int live = (p.seq_hi - p.seq_lo + 15) / 16, per_wave = rows_n(phase, p) / 16 / (phase == BG_GATEUP ? 2 : 1);
-    return std::max(1, std::min({(per_wave + kWaves - 1) / kWaves, 8 * cus / live, kMaxHeadCands}));
-}
-} // namespace
+bool rows_gemm_serves(int phase, const DraftParams &p, int cus) { return rows_gemm_serves(rows_call(phase, p), cus); }
 int rows_head_cands(const DraftParams &p, int cus, size_t part_floats) {
-    const RowsPlan pl = rows_plan(BG_LMHEAD, p, cus, part_floats);
-    return pl.kp > 1 ? rows_epilogue_groups(BG_LMHEAD, p, cus) : pl.nb;
+    const RowsCall c = rows_call(BG_LMHEAD, p);
+    const RowsPlan pl = rows_plan(c, cus, part_floats);
+    return pl.kp > 1 ? rows_epilogue_groups(c, cus) : pl.nb;
 }
 void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
                       hipStream_t st) {
-    const RowsPlan pl = rows_plan(phase, p, cus, part_floats);
+    const RowsCall c = rows_call(phase, p);
+    const RowsPlan pl = rows_plan(c, cus, part_floats);
     const int ph = phase == BG_LMHEAD && logits_only ? kHeadLogits : phase;
     const int units = pl.nb * pl.kp; // (N block, part) pairs: the M blocks of eight neighbouring ones form one group
-    hipLaunchKernelGGL(rows_kernel(ph, pl.tile), dim3((units + 7) / 8 * 8 * pl.mb), dim3(kBlock), kRowsTile[pl.tile].lds, st,
+    hipLaunchKernelGGL(rows_kernel(ph, pl.tile, c.K % kRowsTile[pl.tile].bk != 0), dim3((units + 7) / 8 * 8 * pl.mb), dim3(kBlock), kRowsTile[pl.tile].lds, st,
                        p, step, pl.kp);
     if (pl.kp > 1)
-        hipLaunchKernelGGL(rows_epilogue_kernel(ph), dim3((p.seq_hi - p.seq_lo + 15) / 16, rows_epilogue_groups(phase, p, cus)), dim3(kBlock),
-                           0, st, p, step, pl.kp, pl.mb * kRowsTile[pl.tile].bm / 16);
+        hipLaunchKernelGGL(rows_epilogue_kernel(ph), dim3((c.rows + 15) / 16, rows_epilogue_groups(c, cus)), dim3(kBlock), 0, st,
+                           p, step, pl.kp, pl.mb * kRowsTile[pl.tile].bm / 16);
 }
 
 void launch_bprep(const DraftParams &p, int step, hipStream_t st) {

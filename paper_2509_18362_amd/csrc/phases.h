@@ -85,7 +85,6 @@ enum : int { kErrKvOverflow = 1, kErrTokenRange = 2, kErrBarrierTimeout = 4 };
 // matrix phases of the batched path, and the vectors whose sums of squares travel with them
 enum : int { BG_PROJ = 0, BG_QKV, BG_OPROJ, BG_GATEUP, BG_DOWN, BG_LMHEAD, BG_COUNT };
 enum : int { SSQ_X = 0, SSQ_X1, SSQ_X2, SSQ_COUNT };
-constexpr int kMaxHeadCands = 1024; // candidates of the output head a sequence has room for
 
 // ---------------------------------------------------------------------------------------------------
 // tagged hand-over elements

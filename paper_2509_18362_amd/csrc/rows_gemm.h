@@ -26,14 +26,14 @@
 // 16 x 16 tile).
 #pragma once
 #include "batch.h"
+#include "rows_plan.h"
 
 namespace mtp {
 
-constexpr int kRgBK = 32; // elements of the shortest reduction step
-
 // WM x WN waves (8 in all), each with TI row tiles x TJ weight-row tiles of sixteen; ST stages of the LDS ring
 // of BK elements of the reduction
-template <int TI_, int WM_, int WN_, int TJ_, int ST_, int BK_ = kRgBK>
+// (HALF: the last step is half a one)
+template <int TI_, int WM_, int WN_, int TJ_, int ST_, int BK_ = kRgBK, bool HALF_ = false>
 struct RowsTile {
     static_assert(WM_ * WN_ == kWaves, "eight waves");
     static constexpr int TI = TI_, WM = WM_, WN = WN_, TJ = TJ_, ST = ST_, BK = BK_;
@@ -54,7 +54,9 @@ struct RowsTile {
     static constexpr bool kApart = TI * TJ <= 8;
     static constexpr int SETS = TI * TJ <= 2 ? 2 : 1, CHAIN = TI * TJ <= 24 ? 16 : 0;
     static_assert(SETS == 1 || BK == 64, "half steps");
+    static constexpr bool HALF = HALF_;
     static_assert(BK == 32 || BK == 64, "the chunk order below");
+    static_assert(!HALF || BK == 64, "half a step");
     static_assert(BN % (kPieceRows * kWaves) == 0 && (AP % kWaves == 0 || kWaves % AP == 0), "whole pieces per wave");
     static_assert((ST - 2) * NL < 64, "the wait counts the requests of the later stages");
 };
@@ -142,7 +144,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     DraftParams p = pin;
     Ph ph = make_phase(p);
     constexpr int kRow = T::kRow, PR = T::kPieceRows;
-    const int K = ph.K, nk = K / T::BK;
+    const int K = ph.K, nk = (K + (T::HALF ? 32 : 0)) / T::BK;
     const int ntv = ((ph.rows + 15) / 16) * NMAT; // virtual 16-row tiles
     const int R = pin.seq_hi - pin.seq_lo; // rows of the launch: all of the call's, or those that share an id list
     const int MB = (R + BM - 1) / BM, NB = (ntv * 16 + BN - 1) / BN;
@@ -159,7 +161,11 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     // rows lie a power of two apart, and while all of them read the same 128 bytes of their rows only some of the memory
     // channels have work (64 rows, 32768 weight rows of 8 KB: 71 us without, 63 with).  With several blocks of rows the
     // workgroups of a die stay together instead, so that the activations they read come from their L2.
-    const int rot = MB == 1 ? __builtin_amdgcn_readfirstlane(nblk * 5 % (k1 - k0)) : 0;
+    // (HALF: a reduction of an odd number of 32s in steps of 64.  The half step keeps its place at the end, kw ends the whole
+    // ones; what its second half brings lies behind the rows' ends and is not multiplied.  Kernels of its own, because the
+    // few instructions cost every other width 1 to 2 % of a short step.)
+    const int kw = T::HALF && k1 == nk ? k1 - 1 : k1;
+    const int rot = MB == 1 && (!T::HALF || kw > k0) ? __builtin_amdgcn_readfirstlane(nblk * 5 % (kw - k0)) : 0;
     p.b0 = pin.seq_lo + mblk * BM;
     p.nb = min(BM, pin.seq_hi - p.b0);
 
@@ -195,7 +201,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     // not depend on the step.
     auto request = [&](int ks, int stage) {
         const bool live = ks < k1;
-        const int kr = ks + rot >= k1 ? ks + rot - (k1 - k0) : ks + rot;
+        const int kr = T::HALF && ks >= kw ? ks : ks + rot >= kw ? ks + rot - (kw - k0) : ks + rot;
         const int soff = live ? kr * kRow : 0;
         const uint32_t at = lds0 + stage * T::kStage;
 #pragma unroll
@@ -288,7 +294,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     // step of a 1024-wide head took 2.5 % longer, most launches of which are 8 to 16 steps)
     int ks = k0;
     do {
-        const int end = kChain > 0 ? min(ks + kChain, k1) : k1;
+        const int end = kChain > 0 ? min(ks + kChain, kw) : kw;
         for (; ks < end; ++ks) {
             await_step();
             request(ks + ST - 1, stage == 0 ? ST - 1 : stage - 1);
@@ -296,8 +302,12 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
             for (int h = 0; h < T::BK / 32; ++h) multiply(stage, h);
             stage = stage == ST - 1 ? 0 : stage + 1;
         }
+        if (T::HALF && ks == kw && kw < k1) { // the half step (requested with the others)
+            await_step();
+            multiply(stage, 0);
+        }
         if constexpr (kChain > 0) end_chains();
-    } while (kChain > 0 && ks < k1);
+    } while (kChain > 0 && ks < kw);
     f32x4(&sum)[TI][TJ] = kChain > 0 ? reinterpret_cast<f32x4(&)[TI][TJ]>(tot) : acc[0];
     if constexpr (kApart)
 #pragma unroll

@@ -1,0 +1,17 @@
+// Prints what the tiled matrix products would do with a phase: reads lines "K n rows head pairs cus part_floats" from
+// standard input, writes "serves tile_rows tile_weight_rows parts microseconds" for each.
+#include <cstdio>
+
+#include "../../paper_2509_18362_amd/csrc/rows_plan.h"
+
+int main() {
+    int K, n, rows, head, pairs, cus;
+    unsigned long long part_floats;
+    while (std::scanf("%d %d %d %d %d %d %llu", &K, &n, &rows, &head, &pairs, &cus, &part_floats) == 7) {
+        const mtp::RowsCall c{K, n, rows, head != 0, pairs != 0};
+        const mtp::RowsPlan p = mtp::rows_plan(c, cus, (size_t)part_floats);
+        const mtp::RowsTileInfo &t = mtp::kRowsTile[p.tile];
+        std::printf("%d %d %d %d %.3f\n", mtp::rows_gemm_serves(c, cus) ? 1 : 0, t.bm, t.bn, p.kp, p.us);
+    }
+    return 0;
+}

@@ -547,6 +547,23 @@ def test_tiled_products_add_up_as_exactly_as_the_batched_core(gpu, d, rows, n):
     assert err <= 1.9e-7, err
 
 
+@pytest.mark.parametrize("rows", [5, 17, 33, 64, 100, 200])
+def test_widths_that_end_inside_a_reduction_step(gpu, rows):
+    """d = 544 and d_ffn = 1056: every reduction but the output projection's is 32 modulo 64, the tiles for few rows walk
+    it in steps of 64 (the weights behind a row's end are the next row's, the activations the next phase's)."""
+    shape = synth.HeadShape(544, 4, 2, 128, 1056, 2111)
+    wl = synth.Workload("width_544", 96, shape, 1, 0, 0, (517,), 1, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=np.array([40], dtype=np.int32), capacity=256)
+    hid, tok = extend_inputs(shape, act, rows, 330 + rows)
+    ext_len = np.array([rows], dtype=np.int32)
+    for subset in (0, -1):
+        ref, res, caches = run_extend(gpu, shape, w, w, act, [ids], subset, hid, tok, ext_len)
+        assert res["err"] == 0
+        check_extend(ref, res, caches, act, ext_len)
+
+
 def test_tiny_extend_long_capacity_matrix_core_attention(gpu, tiny):
     """A large capacity makes the splits long enough for the matrix-core attention (which merges its own splits)."""
     act = synth.make_activations(tiny["wl"], ctx=np.array([0, 31, 300, 1000], dtype=np.int32), capacity=32768)
