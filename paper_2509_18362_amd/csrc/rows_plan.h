@@ -31,6 +31,7 @@ constexpr RowsTileInfo kRowsTile[kRowsTiles] = {
     {128, 384, 32, 3 * (2 * 128 + 384) * 64, 1.0}, {64, 256, 64, 3 * (2 * 64 + 256) * 128, 1.3},
     {64, 128, 64, 4 * (2 * 64 + 128) * 128, 0.8},  {32, 128, 64, 6 * (2 * 32 + 128) * 128, 0.55},
     {16, 128, 64, 7 * (2 * 16 + 128) * 128, 0.52}};
+constexpr int kRowsFew = 16;              // rows up to which the batched core's plain kernel is an alternative
 constexpr int kRowsHalf = 4;               // the tilings from this one on take a last step that is half a one
 constexpr int kRowsMinSteps = 8;           // reduction steps of 32 a part keeps at least
 constexpr double kRowsFixedUs = 6.0;       // of a workgroup besides its steps
@@ -50,8 +51,14 @@ inline RowsPlan rows_plan(const RowsCall &c, int cus, size_t part_floats) {
     for (int t = kRowsTiles - 1; t >= 0; --t) { // (small tiles first: they stay where HBM bounds all alike)
         const RowsTileInfo &ti = kRowsTile[t];
         if (c.K % ti.bk && t < kRowsHalf) continue;
+        // Few rows: no tiles of many times as many (their products with rows that are not there cost more than the estimate
+        // says: 75841 x 3072 in tiles of 128 rows 18 us behind the batched core).  Where blocks of 128 weight rows would take a
+        // second round, blocks of 256 (36000 x 4096 at sixteen rows: 5 us ahead of the batched core, in 282 narrow blocks for 256
+        // CUs 7 behind it).
+        const int nb = (c.n + ti.bn - 1) / ti.bn;
+        if (c.rows <= kRowsFew && (ti.bm > 64 || (ti.bn == 128 && nb > cus && c.K % 64 == 0))) continue;
         const int steps = (c.K + ti.bk - 1) / ti.bk;
-        const int mb = (c.rows + ti.bm - 1) / ti.bm, nb = (c.n + ti.bn - 1) / ti.bn;
+        const int mb = (c.rows + ti.bm - 1) / ti.bm;
         const double weights_us = (double)c.n * c.K * 2 * mb * kRowsReadUs;
         for (int kp = 1; kp <= 16 && (kp == 1 || c.K / 32 / kp >= kRowsMinSteps); ++kp) {
             const double sums = (double)kp * c.n * mb * ti.bm; // floats of the parts
@@ -76,15 +83,25 @@ inline int rows_epilogue_groups(const RowsCall &c, int cus) {
 inline bool rows_gemm_serves(const RowsCall &c, int cus) {
     if (c.K % kRgBK) return false;
     if (c.head && c.n > kRowsTile[1].bn * kMaxHeadCands) return false; // no room for the candidates
-    if (c.rows > 16) return true;
+    if (c.rows > kRowsFew) return true;
     // Up to 16 rows the batched core's plain kernel (waves split the reduction) streams large matrices as fast, and adds its
     // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with
-    // the launch that adds the parts.  Measured at five rows (us, this kernel / that one): 4096 x 2048 11 / 14, 2048 x 6144
-    // 13 / 17, 12288 x 2048 14 / 17, 8192 x 2048 of a head 15 / 18; at sixteen rows 4096 x 4096 17 / 17.5, 6144 x 4096
-    // 21 / 19.5, 4096 x 8192 23 / 21, 22016 x 4096 40 / 35; a head that fills the chip in one part, 32768 x 4096: 53 / 59
-    // (a head of more blocks than candidates takes a larger tile: 151680 x 4096 at sixteen rows 260 / 247).
-    const int bn = kRowsTile[kRowsTiles - 1].bn;
-    return c.K <= 2048 || (double)c.n * c.K * 2 <= 32e6 || (c.head && c.n >= bn * cus && c.n <= bn * kMaxHeadCands);
+    // the launch that adds the parts.  Both kernels go in rounds of one workgroup per CU: this one is ahead while its
+    // workgroups fit one round and where further rounds are nearly full.  Gain of the tiled product over the batched core, us
+    // per step of whole drafts at 2, 5 and 16 rows, K = 512 .. 8192:
+    //   blocks of 128 in one round: K <= 2048 or up to 32 MB +1.3 .. +7; larger heads +1.6 .. +7.6 where nine tenths of the
+    //   round are there, -1.5 .. +4 from half of it (16384 x 3072) on;
+    //   blocks of 256: one round (33000 .. 65536 rows) +0.7 .. +17; two full ones (131072) +5 .. +36; 0.58 of two (75841) +2 at
+    //   K = 512, else -11 .. +4; 0.75 of two (98304) -3 .. +9 up to K = 2048, from 3072 on -14 .. +14; 0.77 of three (151680) -1 ..
+    //   +8 up to K = 2048, -7 .. -25 from 3072 on.
+    const bool small = c.K <= 2048 || (double)c.n * c.K * 2 <= 32e6, half = c.K % 64 != 0;
+    if (!small && !c.head) return false;
+    const int narrow = (c.n + 127) / 128, wide = (c.n + 255) / 256; // blocks of the two tiles that such calls take
+    if (narrow <= cus) return small || 10 * narrow >= 9 * cus;
+    if (half) return small && narrow <= kMaxHeadCands; // (no wide tile: 1056 x 33000 .. 65536 +7 .. +10)
+    if (wide > kMaxHeadCands) return false;
+    const int slots = (wide + cus - 1) / cus * cus;
+    return wide <= cus || (small ? c.K <= 512 || 4 * wide >= 3 * slots : 10 * wide >= 9 * slots);
 }
 
 } // namespace mtp

@@ -35,3 +35,36 @@ def test_a_reduction_of_an_odd_number_of_32s_gets_the_tiles_of_its_neighbours(pl
     odd, even = plan([dict(K=K, n=n, rows=rows), dict(K=K + 32, n=n, rows=rows)])
     assert odd["bm"] <= max(16, 2 * rows)
     assert odd["us"] <= even["us"] * 1.001
+
+
+HEADS = [1024, 4096, 8195, 16384, 24576, 29500, 30336, 32768, 32769, 33000, 36000, 40000, 49152, 65536, 65537, 75841,
+         98304, 118000, 131072, 151680, 262144, 400000]
+
+
+@pytest.mark.parametrize("rows", [2, 5, 16])
+@pytest.mark.parametrize("K", [256, 512, 544, 1024, 1056, 2048, 2080, 3072, 4096, 4128, 5120, 8192])
+def test_few_rows_take_the_tiles_only_where_their_rounds_are_full(plan, rows, K):
+    """Up to 16 rows the batched core is the alternative.  The tiled product is ahead in one round of workgroups and where
+    further rounds are nearly full, never in tiles of many times the rows: a head of 36000 x 4096 in 282 blocks for 256 units
+    was 7 us slower per step, one of 75841 x 3072 in tiles of 128 rows 18 us."""
+    for n, p in zip(HEADS, plan([dict(K=K, n=n, rows=rows, head=1) for n in HEADS])):
+        if not p["serves"]:
+            continue
+        blocks = -(-n // p["bn"])
+        assert p["us"] < 1e29 and blocks >= 1 and p["parts"] >= 1  # there is a plan
+        assert p["bm"] <= 64, (n, p)
+        assert p["parts"] > 1 or blocks <= 1024
+        slots = -(-blocks // CUS) * CUS
+        assert blocks <= CUS or K <= 512 or K % 64 or blocks >= 0.75 * slots, (n, p)
+        if K > 2048 and n * K * 2 > 32e6:  # large heads: a nearly full round, in whichever tile
+            assert blocks > 0.9 * slots - 1 or (p["bn"] == 256 and blocks > 0.5 * slots), (n, p)
+
+
+@pytest.mark.parametrize("rows,K,n,expect", [
+    (16, 4096, 32768, 16), (16, 4096, 30336, 16), (16, 4096, 33000, 64), (5, 4096, 40000, 64), (2, 4096, 65536, 64),
+    (16, 4096, 131072, 64), (16, 4096, 75841, 0), (16, 4096, 98304, 0), (2, 4096, 151680, 0), (16, 3072, 75841, 0),
+    (5, 1024, 75841, 0), (5, 1024, 151680, 64), (5, 512, 75841, 64), (16, 2048, 36000, 64), (5, 1056, 65536, 16)])
+def test_route_of_heads_at_few_rows(plan, rows, K, n, expect):
+    """The tile's rows, or 0 for the batched core, on both sides of the measured lines."""
+    p = plan([dict(K=K, n=n, rows=rows, head=1)])[0]
+    assert (p["bm"] if p["serves"] else 0) == expect, p
