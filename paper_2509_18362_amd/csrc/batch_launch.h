@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "../../include/mtp_draft.h"
 #include "phases.h"
 #include "rows_plan.h"
 
@@ -9,8 +10,9 @@ namespace mtp {
 
 // dynamic LDS of a batched matrix phase whose row groups hold at most `rows_per_group` rows
 size_t bgemv_lds_bytes(int rows_per_group);
-// raises the dynamic-LDS limit of every batched kernel; false if a call failed
-bool batch_allow_lds(size_t lds_limit);
+// raises the dynamic-LDS limit of the batched and matrix-core attention kernels that calls of a handle with this configuration
+// can take; false if a call failed
+bool batch_allow_lds(size_t lds_limit, const mtp_config &c);
 // one batched matrix phase (BG_* index) for the sequences [p.b0, p.b0 + p.nb)
 void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t lds, hipStream_t st);
 // the preparation kernel before step `step` (step == K: after the last step), all sequences

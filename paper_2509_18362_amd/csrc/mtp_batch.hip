@@ -275,26 +275,23 @@ void launch_attn_mfma_block(int G, int HD, const DraftParams &p, int step, int g
     hipLaunchKernelGGL(attn_mfma_block_kernel(G, HD), dim3(grid), dim3(kBlock), lds, st, p, step);
 }
 
-bool batch_allow_lds(size_t lds_limit) {
+bool batch_allow_lds(size_t lds_limit, const mtp_config &c) {
     bool ok = true;
+    auto allow = [&](const void *kernel) {
+        ok = ok && (!kernel || hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit) == hipSuccess);
+    };
+    const int G = c.n_q_heads / c.n_kv_heads;
+    for (bool lpt : {false, true}) allow((const void *)attn_mfma_kernel(G, c.head_dim, lpt));
+    allow((const void *)attn_mfma_block_kernel(G, c.head_dim));
+    if (c.max_batch < 2) return ok; // one sequence: the row-streaming kernels
     for (int ph = 0; ph <= kHeadLogits; ++ph)
-        for (int t = 0; t < kRowsTiles; ++t)
-            for (bool half : {false, true})
-                ok = ok && (!rows_kernel(ph, t, half) ||
-                            hipFuncSetAttribute((const void *)rows_kernel(ph, t, half), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                (int)lds_limit) == hipSuccess);
-    for (int hd = 64; hd <= 128; hd *= 2)
-        for (int g = 1; g <= 8; g *= 2)
-            ok = ok && hipFuncSetAttribute((const void *)attn_mfma_kernel(g, hd, false),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit) == hipSuccess &&
-                 hipFuncSetAttribute((const void *)attn_mfma_kernel(g, hd, true),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit) == hipSuccess &&
-                 hipFuncSetAttribute((const void *)attn_mfma_block_kernel(g, hd),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit) == hipSuccess;
+        for (int t = 0; t < kRowsTiles; ++t) {
+            if (c.max_batch <= kRowsFew && kRowsTile[t].bm > 64) continue; // (rows_plan)
+            allow((const void *)rows_kernel(ph, t, false));
+            if (c.d_model % 64 || c.d_ffn % 64) allow((const void *)rows_kernel(ph, t, true));
+        }
     for (int ph = 0; ph < BG_COUNT; ++ph)
-        for (int na = 1; na <= 4; na *= 2)
-            ok = ok && (!pick(ph, na) || hipFuncSetAttribute((const void *)pick(ph, na), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                             (int)lds_limit) == hipSuccess);
+        for (int na = 1; na <= tiles_for(c.max_batch); na *= 2) allow((const void *)pick(ph, na));
     return ok;
 }
 

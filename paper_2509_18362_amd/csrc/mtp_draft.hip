@@ -339,7 +339,13 @@ int fit_max_splits(const mtp_config &c, int B) {
     const int t = fit_min_tokens(c, B);
     return (c.kv_capacity + t - 1) / t;
 }
-bool fit_possible(const mtp_config &c, int B) { return B <= kFitMaxRows && split_tokens_for(c, B) >= kFitMinPlanned; }
+// What a call of B rows can be at most: as many (sequence, KV head, group of 16 / G positions) items as make up three
+// quarters of the compute units (256 on the device this is written for: the workspace's size does not depend on it).
+constexpr int kFitUnits = 256;
+bool fit_possible(const mtp_config &c, int B) {
+    const int per_item = 16 / (c.n_q_heads / c.n_kv_heads);
+    return B <= kFitMaxRows && 4 * B * c.n_kv_heads <= 3 * kFitUnits * per_item && split_tokens_for(c, B) >= kFitMinPlanned;
+}
 size_t attn_part_floats(const mtp_config &c) {
     size_t best = 0;
     for (int B = 1; B <= c.max_batch; ++B)
@@ -590,7 +596,7 @@ int32_t mtp_draft_init(mtp_handle **out, const mtp_config *cfg, const mtp_weight
                {(const void *)h->flow_fn, "k_flow"}};
     for (const auto &f : fns)
         if (ok) run(hipFuncSetAttribute(f.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_limit), f.name);
-    if (ok && !batch_allow_lds(h->lds_limit)) {
+    if (ok && !batch_allow_lds(h->lds_limit, *cfg)) {
         fprintf(stderr, "mtp_draft_init: raising the LDS limit of the batched and matrix-core attention kernels failed\n");
         ok = false;
     }
@@ -806,7 +812,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     const int att_seqs = ext ? ext->B : B, att_jp = att_block ? 16 / (p.Hq / p.Hkv) : 1;
     const int att_groups = att_block ? (ext->m_max + att_jp - 1) / att_jp : 1;
     const bool att_fit = mfma_attn && (!ext || att_block) && fit_possible(c, B) && att_seqs <= kWave &&
-                     4 * att_seqs * p.Hkv * att_groups <= 3 * h->num_cus;
+                     4 * att_seqs * p.Hkv * att_groups <= 3 * std::min(h->num_cus, kFitUnits);
     auto with_fit = [&](DraftParams pa) {
         if (!att_fit) return pa;
         pa.attn_fit_min = fit_min_tokens(c, B);

@@ -32,6 +32,20 @@ def test_status_strings():
     assert b.mtp_status_string(-99) == "unknown status"
 
 
+def test_workspace_holds_length_sized_splits_only_for_calls_that_can_have_them():
+    """Attention splits sized by the lengths (up to four times the planned ones) need an item per compute unit to spare:
+    with 8 query heads per KV head and 8 KV heads no call of more than 48 rows has that.  The rows beyond cost what they
+    cost at a capacity whose splits are never sized so, and the planned partials of a split or two."""
+    shape = synth.HeadShape(4096, 64, 8, 128, 11008, 32000)
+
+    def size(rows, cap):
+        return b.mtp_workspace_bytes(b.make_config(shape, rows, cap, 3))
+
+    plain = size(128, 1024) - size(48, 1024)
+    planned_partials = 128 * 8 * 64 * (128 + 2) * 4  # eight splits of 4096 tokens for 128 rows
+    assert size(128, 32768) - size(48, 32768) <= plain + planned_partials
+
+
 def test_workspace_bytes_and_config_validation():
     cfg = b.make_config(synth.SEVEN_B, 1, 2112, 3)
     n1 = b.mtp_workspace_bytes(cfg)
