@@ -773,17 +773,16 @@ struct BgHead : BgBase {
 };
 
 // The epilogue of a matrix phase as a kernel of its own: one wave per slot (tile or pair of tiles, sequence tile), any
-// grid; phases that keep state per workgroup (the output head's candidates) finish per workgroup of THIS kernel.
+// grid; for phases that keep no state per workgroup.
 template <int NA, class Ph>
 __device__ __forceinline__ void phase_bepilogue(const DraftParams &p, Ph &ph, int KP, char *smem) {
     constexpr int NMAT = Ph::NMAT;
-    float *scale_lds = reinterpret_cast<float *>(smem + kWaves * kBatchMaxSeq * 8); // behind finish()'s scratch
+    float *scale_lds = reinterpret_cast<float *>(smem);
     if (Ph::SCALE >= 0) batch_scales(p, Ph::SCALE, scale_lds);
     __syncthreads();
     const int ntv = (ph.rows + 15) / 16 * NMAT, nslots = ntv / NMAT * NA;
     for (int id = blockIdx.x * kWaves + threadIdx.x / kWave; id < nslots; id += gridDim.x * kWaves)
         bg_slot_epilogue<NA>(p, ph, KP, ntv, (id / NA) * NMAT, id % NA, scale_lds);
-    ph.finish(blockIdx.x, smem);
 }
 
 // ---------------------------------------------------------------------------------------------------

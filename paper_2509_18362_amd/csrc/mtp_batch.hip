@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kBlock) void k_bgemv(DraftParams p, int step) {
 // (the only phase that more than 16 rows take to the batched core with its reduction split: see rows_gemm_serves)
 template <int NA>
 __global__ __launch_bounds__(kBlock) void k_bepilogue_down(DraftParams p, int step) {
-    __shared__ __align__(16) char smem[kWaves * kBatchMaxSeq * 8 + kBatchMaxSeq * 4];
+    __shared__ __align__(16) char smem[kBatchMaxSeq * 4];
     BgDown ph(p);
     phase_bepilogue<NA>(p, ph, p.bg_kp[BG_DOWN], smem);
 }
@@ -57,8 +57,9 @@ __global__ __launch_bounds__(kBlock) void k_bprep(DraftParams p, int step) {
     phase_bprep(p, step, smem);
 }
 
-// A matrix phase over all p.B rows as one tiled matrix product (rows_gemm.h).  PH: a BG_* index, or kHeadLogits for the
-// output head without candidates.  One workgroup per CU (144 KB of LDS, up to 256 registers).
+// A matrix phase over the rows p.seq_lo .. p.seq_hi - 1 (all of a call's, or those that share an id list) as one tiled matrix
+// product (rows_gemm.h).  PH: a BG_* index, or kHeadLogits for the output head without candidates.  One workgroup per CU (120
+// to 147 KB of LDS, up to 256 registers).
 constexpr int kHeadLogits = BG_COUNT;
 template <int PH, class F>
 __device__ __forceinline__ void with_phase(int step, F f) {

@@ -627,8 +627,8 @@ struct ExtendCall {
     int B, m_max;           // real sequences, positions per sequence (rows = m_max * B)
     const int32_t *ext_len; // device [B]
     int32_t *kv_len;        // device [B], the real lengths (advanced at the end)
-    bool logits_only = false; // the caller wants logits and no drafts (the training loss): many rows take the
-                              // tiled matrix product for the output head
+    bool logits_only = false; // the caller wants logits and no drafts (the training loss): a tiled output head leaves no
+                              // candidates
 };
 
 // B sequences (or rows), K steps; arguments checked by the callers
@@ -999,12 +999,12 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             p.bg_kp[ph] = kp;
             // Split reductions: who adds the parts.  Up to 16 sequences the last workgroup of a row group to arrive
             // does (a relaxed ticket; the parts are written and read with device-coherent accesses, no cache is written
-            // back or invalidated): config 3 runs 2.4 % faster than with a kernel of its own per phase.  Above 16
-            // sequences a row group holds 64/NA tiles x NA sequence tiles of sums and the last workgroup becomes the
-            // bottleneck (8.6 % of a step at 64), so there a small epilogue kernel spread over the chip adds them -
-            // except for the output head, whose epilogue kernel would leave four times as many argmax candidates
-            // behind (measured: 122 vs 97 us at 64 sequences).
-            p.bg_sep[ph] = (kp >= 2 && ph == BG_DOWN && na > 1) ? 1 : 0; // (the phases such a call may bring here)
+            // back or invalidated): sixteen sequences run 2.4 % faster than with a kernel of its own per phase.  Above 16 only
+            // two kinds of phase come here: the down projection of a width that is no multiple of 32, whose row groups hold 64/NA
+            // tiles x NA sequence tiles of sums, too many for one workgroup to add (8.6 % of a step at 64): a small
+            // epilogue kernel spread over the chip does; and heads of more rows than the tiled products have candidates for,
+            // which are not split so far that it matters.
+            p.bg_sep[ph] = (kp >= 2 && ph == BG_DOWN && na > 1) ? 1 : 0;
             lds_bg[ph] = bgemv_lds_bytes(((units + rg - 1) / rg) * 16);
         };
         plan(BG_PROJ, p.d / 16, 1, 2 * p.d, na);
@@ -1024,7 +1024,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         // workgroups that then wait for one another (24 sequences in three lists of 32768 / 16384 / 8195 rows, eight each:
         // 68 / 49 / 51 us per step with the plan of the whole batch, 57 / 28 / 23 with their own).
         struct HeadPlan {
-            int rg, kp, sep;
+            int rg, kp;
             size_t lds;
             bool tiled;
         } head_plan[kMaxListGroups];
@@ -1044,7 +1044,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             const DraftParams q = head_of(g);
             const int na_g = tiles_of(q.seq_hi - q.seq_lo);
             plan(BG_LMHEAD, (q.n + 15) / 16, 1, p.d, na_g);
-            head_plan[g] = HeadPlan{p.bg_rg[BG_LMHEAD], p.bg_kp[BG_LMHEAD], p.bg_sep[BG_LMHEAD], lds_bg[BG_LMHEAD], false};
+            head_plan[g] = HeadPlan{p.bg_rg[BG_LMHEAD], p.bg_kp[BG_LMHEAD], lds_bg[BG_LMHEAD], false};
             if (lds_bg[BG_LMHEAD] > h->lds_limit) return MTP_ERR_CONFIG;
             int cands = p.bg_rg[BG_LMHEAD];
             head_plan[g].tiled = rows_gemm_serves(BG_LMHEAD, q, grid);
@@ -1075,7 +1075,6 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
                     }
                     q.bg_rg[ph] = head_plan[g].rg;
                     q.bg_kp[ph] = head_plan[g].kp;
-                    q.bg_sep[ph] = head_plan[g].sep;
                     lds = head_plan[g].lds;
                 }
                 for (q.b0 = q.seq_lo; q.b0 < q.seq_hi; q.b0 += kBatchPassSeq) {

@@ -1,19 +1,21 @@
-// The matrix phases over many rows at once (gfx950): one LDS-tiled matrix product on the matrix cores per phase, for
-// calls with more rows than one pass of the batched core (batch.h) serves: a prompt-sized block of positions, a large
-// batch, the teacher-forced forward of Sec. 2.1, Eq. (1).  The batched core streams every weight once per 64 rows; here
-// a weight tile is read once per block of BM rows and the blocks of one weight tile share an L2.
+// The matrix phases as LDS-tiled matrix products on the matrix cores (gfx950), one per phase: every call of more than 16 rows
+// (a batch, the confirmed positions of one, a prompt, the teacher-forced forward of Sec. 2.1, Eq. (1)) and, from two rows
+// on, the phases in which they are ahead of the batched core (batch.h; rows_gemm_serves in rows_plan.h).  The batched core
+// streams every weight once per 64 rows; here a weight tile is read once per block of BM rows (16 to 256) and the blocks of one
+// weight tile share an L2.
 //
-// A workgroup owns BM rows x BN weight rows of the result and walks the reduction in steps of 32 elements.  Activations
+// A workgroup owns BM rows x BN weight rows of the result and walks the reduction in steps of 32 or 64 elements.  Activations
 // are the bf16 hi + lo halves the producing phase left (the float value to 16 bits of mantissa): two MFMAs per weight
-// fragment.  Eight waves, each with a 64 x (16 TJ) piece in accumulators.
-// What bounds it: LDS reads.  A step of a wave's piece reads 2 x 64 rows of activations (both halves) and 16 TJ weight
-// rows of 64 bytes for 8 TJ MFMAs, so a CU needs 2048 (2 x 64 + 16 TJ) / (64 x 16 TJ) bytes per clock at the matrix
-// cores' full rate: 64 with TJ = 8, 160 with the 64 x 32 pieces this kernel had before, of the 128 the LDS delivers; and
-// from L2 (2 BM + BN) x 64 bytes per step, 24 bytes per clock and CU with 256 x 256 against 48 with 128 x 128.  Hence
-// the largest pieces the registers hold (128 accumulator registers), and where a phase has too few such tiles to fill
-// the chip the reduction is split over KP workgroups instead of making the tiles smaller.
+// fragment.  Eight waves, each with a (16 TI) x (16 TJ) piece in accumulators.
+// What bounds it: at few rows reading the weights, at many (pieces of 64 rows) LDS reads.  A step of a wave's piece reads 2 x
+// 64 rows of activations (both halves) and 16 TJ weight rows of 64 bytes for 8 TJ MFMAs, so a CU needs
+// 2048 (2 x 64 + 16 TJ) / (64 x 16 TJ) bytes per clock at the matrix cores' full rate: 64 with TJ = 8, 160 with TJ = 2, of
+// the 128 the LDS delivers; and from L2 (2 BM + BN) x 64 bytes per step, 24 bytes per clock and CU with 256 x 256 against 48
+// with 128 x 128.  Hence the largest pieces the registers hold (128 accumulator registers), and where a phase has too few
+// such tiles to fill the chip the reduction is split over KP workgroups instead of making the tiles smaller.
 // Both operands go from memory straight into LDS (no registers, no store instructions): a ring of stages, three with the
-// large tiles, a stage requested two steps (with more stages, earlier) before it is multiplied.  Such a load fills 1 KB of LDS in lane order, so rows cannot be padded; the 16-byte
+// large tiles, a stage requested two steps (with more stages, earlier) before it is multiplied.  Such a load fills 1 KB of LDS
+// in lane order, so rows cannot be padded; the 16-byte
 // chunks of a 64-byte row are stored at position chunk ^ ((row >> 1) & 3) instead (the lane that fills a position
 // fetches the chunk that belongs there), which puts the eight rows a quarter of a read covers on different banks.
 // Measured at 512 rows of the 7B-shaped head (us; the kernel before, with 64 x 128 to 128 x 256 tiles, operands through
@@ -30,9 +32,8 @@
 
 namespace mtp {
 
-// WM x WN waves (8 in all), each with TI row tiles x TJ weight-row tiles of sixteen; ST stages of the LDS ring
-// of BK elements of the reduction
-// (HALF: the last step is half a one)
+// WM x WN waves (8 in all), each with TI row tiles x TJ weight-row tiles of sixteen; ST stages of the LDS ring of BK elements
+// of the reduction (HALF: the last step is half a one).
 template <int TI_, int WM_, int WN_, int TJ_, int ST_, int BK_ = kRgBK, bool HALF_ = false>
 struct RowsTile {
     static_assert(WM_ * WN_ == kWaves, "eight waves");
