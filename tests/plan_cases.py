@@ -1,0 +1,25 @@
+"""Shapes of the GPU tests of the tiled matrix products and the tiles they are there for (rows, weight rows, in several parts):
+test_rows_plan.py checks that the plan still takes them, test_gpu_parity.py runs them."""
+
+# d_model, vocabulary, rows: the output head's tile
+HEAD_TILES = [
+    (256, 2111, 5, (16, 128, False)),
+    (2048, 2111, 5, (16, 128, True)),
+    (256, 16000, 17, (32, 128, False)),
+    (2048, 2111, 17, (32, 128, True)),
+    (256, 8000, 130, (64, 128, False)),
+    (2048, 4000, 40, (64, 128, True)),
+    (256, 33000, 5, (64, 256, False)),    # few rows, more than a round of narrow blocks
+    (256, 66000, 17, (128, 384, False)),
+    (2048, 33000, 100, (128, 384, True)),
+    (256, 131072, 17, (128, 512, False)),
+    (256, 131072, 130, (256, 256, False)),
+]
+
+# d_model, d_ffn, rows: the tiles of the 2d -> d projection, gate/up and the down projection (query heads of 128, d / 128 of them)
+BODY_TILES = [
+    (2048, 6144, 17, ((32, 128, True), (32, 128, False), (32, 128, True))),
+    (2048, 6144, 33, ((64, 128, True), (32, 128, False), (64, 128, True))),
+    (2048, 6144, 400, ((64, 256, True), (128, 384, False), (128, 384, True))),
+    (2048, 16384, 400, ((64, 256, True), (256, 256, False), (256, 256, True))),
+]

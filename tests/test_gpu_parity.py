@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 
 from paper_2509_18362_amd import synth
+from plan_cases import BODY_TILES, HEAD_TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -161,10 +162,10 @@ def test_tiny_many_long_contexts_items_handed_out(gpu, tiny):
 
 @pytest.mark.parametrize("B", [17, 20, 40, 70, 130, 300])
 def test_tiny_wide_batches(gpu, tiny, B):
-    """Batches above 16 take the core whose waves split the tiles (two or four sequence tiles, the last one ragged);
-    70 sequences are two weight passes (64 + 6), 130 are three (64 + 64 + 2); from 256 on the body's matrix phases are
-    tiled matrix products over all sequences (300: a ragged last block of 64).  The tiny head has a reduction length (d_ffn = 688) that is not a
-    multiple of the 64-element double step, and row counts that leave most tile slots of a block empty."""
+    """Batches above 16 take tiled matrix products over all sequences, except for the down projection: the tiny head's
+    reduction length there (d_ffn = 688) is no multiple of 32, which keeps it on the core whose waves split the tiles (two
+    or four sequence tiles, the last one ragged; 70 sequences are two weight passes, 64 + 6, 130 three, 64 + 64 + 2), with
+    row counts that leave most tile slots of a block empty."""
     wl = tiny["wl"]
     rng = np.random.default_rng(100 + B)
     ctx = rng.integers(0, 120, size=B).astype(np.int32)
@@ -489,11 +490,11 @@ def test_tiny_extend_block_of_positions(gpu, tiny, ctx, ext, m_max):
 @pytest.mark.parametrize("d_ffn,subset", [(1056, 0), (1064, -1)])
 @pytest.mark.parametrize("rows", [5, 16, 17, 33, 64, 65, 129, 257, 400])
 def test_many_rows_tiled_matrix_products(gpu, d_ffn, subset, rows):
-    """Every phase as a tiled matrix product (small reductions take it at any number of rows).  Rows on both sides of the
-    blocks of 16, 32, 64, 128 and 256 rows, a block that is neither; reductions of an odd number of 32-element steps
-    (1056: no whole number of the small tiles' 64-element steps) and, for the down projection of 1064, not a whole
-    number (the batched core then); gate/up rows and a vocabulary that end inside a tile of sixteen; the list and the
-    full head; the candidates of a row from several blocks of weight rows."""
+    """Every phase as a tiled matrix product (small reductions take it at any number of rows), here in the tiles of 16 rows
+    and, from 257 rows on, of 32 (gate/up and the head): one block to twenty-five, full and ragged last ones.  The down
+    projection of 1056 ends in half a step, that of 1064 in less than that (the batched core then); gate/up rows and a
+    vocabulary that end inside a tile of sixteen; the list and the full head; the candidates of a row from several
+    blocks of weight rows.  The other tiles: the two tests below."""
     shape = synth.HeadShape(512, 4, 2, 128, d_ffn, 2111)
     wl = synth.Workload(f"rows_{d_ffn}", 95, shape, 1, 0, 0, (517,), 1, 0.5, zipf_subset=False)
     w = synth.make_weights(wl)
@@ -564,6 +565,52 @@ def test_widths_that_end_inside_a_reduction_step(gpu, rows):
         check_extend(ref, res, caches, act, ext_len)
 
 
+def run_block_of_one_sequence(gpu, shape, rows, seed):
+    """A block of `rows` positions of one sequence with a short context, full vocabulary, against the oracle."""
+    wl = synth.Workload(f"block_{shape.d_model}_{rows}", 97, shape, 1, 0, 0, (min(517, shape.vocab_size),), 1, 0.5,
+                        zipf_subset=False)
+    w = synth.make_weights(wl)
+    act = synth.make_activations(wl, ctx=np.array([40], dtype=np.int32), capacity=-(-(rows + 40) // 64) * 64)
+    hid, tok = extend_inputs(shape, act, rows, seed)
+    ext_len = np.array([rows], dtype=np.int32)
+    ref, res, caches = run_extend(gpu, shape, w, w, act, [synth.make_subsets(wl)[0]], -1, hid, tok, ext_len)
+    assert res["err"] == 0
+    check_extend(ref, res, caches, act, ext_len)
+
+
+@pytest.mark.parametrize("d,vocab,rows", [c[:3] for c in HEAD_TILES])
+def test_drafts_from_every_tile_of_the_output_head(gpu, d, vocab, rows):
+    """The head's candidates from each of the tiles, in one part (one candidate per block of weight rows) and in several (one
+    per group of the launch that adds the parts): drafts and logits.  test_rows_plan.py holds the tile of each case."""
+    run_block_of_one_sequence(gpu, synth.HeadShape(d, 4, 2, 64, 256, vocab), rows, 400 + rows)
+
+
+@pytest.mark.parametrize("d,d_ffn,rows", [c[:3] for c in BODY_TILES])
+def test_body_phases_in_the_larger_tiles(gpu, d, d_ffn, rows):
+    """The projections, gate/up and down in tiles of 32 to 256 rows, whole and split (their tiles: test_rows_plan.py)."""
+    run_block_of_one_sequence(gpu, synth.HeadShape(d, d // 128, d // 256, 128, d_ffn, 2111), rows, 500 + rows)
+
+
+@pytest.fixture(scope="module")
+def huge_vocab():
+    """More output-head rows than the tiled products have room for candidates (1024 blocks of 512), a ragged last tile."""
+    shape = synth.HeadShape(256, 4, 2, 64, 256, 524309)
+    wl = synth.Workload("huge_vocab", 98, shape, 1, 0, 0, (517,), 1, 0.5, zipf_subset=False)
+    return wl, synth.make_weights(wl)
+
+
+@pytest.mark.parametrize("rows", [20, 40])
+def test_heads_beyond_the_tiles_candidates_stay_on_the_batched_core(gpu, huge_vocab, rows):
+    """Two and four sequence tiles of the core whose waves split the weight tiles."""
+    wl, w = huge_vocab
+    act = synth.make_activations(wl, ctx=np.array([9], dtype=np.int32), capacity=64)
+    hid, tok = extend_inputs(wl.shape, act, rows, 600 + rows)
+    ext_len = np.array([rows], dtype=np.int32)
+    ref, res, caches = run_extend(gpu, wl.shape, w, w, act, [synth.make_subsets(wl)[0]], -1, hid, tok, ext_len)
+    assert res["err"] == 0
+    check_extend(ref, res, caches, act, ext_len)
+
+
 def test_tiny_extend_long_capacity_matrix_core_attention(gpu, tiny):
     """A large capacity makes the splits long enough for the matrix-core attention (which merges its own splits)."""
     act = synth.make_activations(tiny["wl"], ctx=np.array([0, 31, 300, 1000], dtype=np.int32), capacity=32768)
@@ -574,17 +621,50 @@ def test_tiny_extend_long_capacity_matrix_core_attention(gpu, tiny):
     check_extend(ref, res, caches, act, ext_len)
 
 
-@pytest.mark.parametrize("ctx,ext", [
-    ([957, 958, 959, 960, 0, 31, 1918, 1919, 5000], None),  # steps that end on, before and behind a split's last token
-    ([32700, 1], None),                                      # a nearly full cache: many splits of one sequence
-    ([0], None),
-    ([950, 0, 1915, 959, 40], [12, 12, 7, 0, 1]),            # blocks that cross a split's end, an idle sequence
+def length_sized_splits(cap, rows, kv_heads, lens, groups=1, units=256):
+    """Tokens per split where the attention sizes its splits by the lengths it finds (restated from the plan: splits for the
+    capacity, from 1024 tokens on; at most four times as many, in 64 candidate lengths, the first that gives no more
+    items than there are compute units), and which candidate that is; (0, 0) where splits stay as planned."""
+    def up64(x):
+        return (x + 63) // 64 * 64
+    planned = min(up64(max(-(-cap * rows * kv_heads // 256), 128)), 4096)
+    if planned < 1024:
+        return 0, 0
+    first = max(256, up64(-(-cap // max(4 * -(-cap // planned), 16))))
+    step = max(64, up64((cap - first + 62) // 63))
+    for lane in range(64):
+        t = first + lane * step
+        if sum(-(-n // t) for n in lens) * kv_heads * groups <= units:
+            return t, lane
+    raise AssertionError("the last candidate covers the capacity")
+
+
+@pytest.mark.parametrize("ctx,ext,tokens,lane", [
+    # nine sequences, the shortest splits: steps that end on, before and behind a split's last token
+    ([573, 574, 575, 576, 0, 31, 1150, 1151, 5000], None, 576, 0),
+    # too many items for the shortest: a longer candidate; caches that the last step fills, ends at its multiples
+    ([32765, 32765, 32765, 1085, 1086, 1087, 2174, 3262, 20670], None, 1088, 1),
+    # four: the shortest splits there are
+    ([253, 254, 255, 256], None, 256, 0),
+    ([32765, 32765, 830, 2495], None, 832, 1),
+    # one and two sequences: as planned
+    ([32700, 1], None, 0, 0),
+    ([0], None, 0, 0),
+    # blocks of positions that cross a split's end, an idle sequence
+    ([1015, 0, 2041, 1023, 40], [12, 12, 7, 0, 1], 1024, 0),
+    # the same with a longer candidate, and blocks that fill their cache
+    ([32756, 32756, 32000, 2043, 40], [12, 12, 12, 12, 1], 2048, 2),
 ])
-def test_tiny_attention_splits_sized_by_the_lengths(gpu, tiny, ctx, ext):
-    """Few sequences in a large cache: the matrix-core attention sizes its splits by the lengths it finds (960 tokens
-    here, the shortest it may take at this capacity), one item per workgroup.  Two sequences at least, so that the draft
-    steps take the batched path; a single one in the launch-per-phase mode."""
-    act = synth.make_activations(tiny["wl"], ctx=np.array(ctx, dtype=np.int32), capacity=32768)
+def test_tiny_attention_splits_sized_by_the_lengths(gpu, tiny, ctx, ext, tokens, lane):
+    """Few sequences in a large cache: the matrix-core attention sizes its splits by the lengths it finds, one item per
+    workgroup.  Two sequences at least, so that the draft steps take the batched path; a single one in the
+    launch-per-phase mode."""
+    cap, kv_heads, K = 32768, tiny["shape"].n_kv_heads, 3
+    for step in range(1 if ext else K):
+        lens = [c + (e if ext else step + 1) for c, e in zip(ctx, ext or ctx) if not ext or e]
+        rows, groups = (len(ctx) * 12, 2) if ext else (len(ctx), 1)  # (8 of a block's 12 positions beside 2 query heads)
+        assert length_sized_splits(cap, rows, kv_heads, lens, groups) == (tokens, lane)
+    act = synth.make_activations(tiny["wl"], ctx=np.array(ctx, dtype=np.int32), capacity=cap)
     if ext is not None:
         ext_len = np.array(ext, dtype=np.int32)
         hid, tok = extend_inputs(tiny["shape"], act, 12, 214)
@@ -592,10 +672,10 @@ def test_tiny_attention_splits_sized_by_the_lengths(gpu, tiny, ctx, ext):
         assert res["err"] == 0
         check_extend(ref, res, caches, act, ext_len)
         return
-    eng = gpu["binding"].DraftEngine(tiny["shape"], tiny["w"], [tiny["ids"]], len(ctx), 32768, 3)
+    eng = gpu["binding"].DraftEngine(tiny["shape"], tiny["w"], [tiny["ids"]], len(ctx), cap, K)
     assert gpu["binding"].mtp_set_launch_mode(eng.handle, 0) == 0
-    ref, res, caches = run_both(gpu, tiny["shape"], tiny["w"], tiny["w"], act, [tiny["ids"]], 0, 3, engine=eng)
-    check_chain(ref, res, caches, act["kv_len"], 3, need_clear=False)
+    ref, res, caches = run_both(gpu, tiny["shape"], tiny["w"], tiny["w"], act, [tiny["ids"]], 0, K, engine=eng)
+    check_chain(ref, res, caches, act["kv_len"], K, need_clear=False)
     eng.close()
 
 
@@ -973,10 +1053,9 @@ def test_7b_extend_four_positions(gpu, big):
 
 @pytest.mark.parametrize("n_pos,K", [(24, 2), (80, 2), (260, 1)])
 def test_7b_teacher_forced_loss(gpu, big, n_pos, K):
-    """The 7B-shaped head, full 151680-id vocabulary: the cross-entropies and the loss.  24 positions run the
-    output head on the batched core, 80 (more than one pass of it) as the tiled matrix product, with a ragged block
-    of positions and a ragged last block of vocabulary rows; from 256 positions on the body's matrix phases are tiled
-    matrix products too."""
+    """The 7B-shaped head, full 151680-id vocabulary: the cross-entropies and the loss.  Every phase is a tiled matrix
+    product over all positions (tiles of 32 to 128 rows at 24 and 80 positions, split reductions in the body), the
+    head's without candidates, with a ragged block of positions and a ragged last block of vocabulary rows."""
     torch, Oracle, binding, orc_mod = gpu["torch"], gpu["Oracle"], gpu["binding"], gpu["orc"]
     shape = big["shape"]
     rng = np.random.default_rng(330)

@@ -4,6 +4,8 @@ import subprocess
 
 import pytest
 
+from plan_cases import BODY_TILES, HEAD_TILES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CUS = 256
 PART_FLOATS = 16384 * 4 * 256  # the smallest room for partial sums a workspace has
@@ -68,3 +70,22 @@ def test_route_of_heads_at_few_rows(plan, rows, K, n, expect):
     """The tile's rows, or 0 for the batched core, on both sides of the measured lines."""
     p = plan([dict(K=K, n=n, rows=rows, head=1)])[0]
     assert (p["bm"] if p["serves"] else 0) == expect, p
+
+
+@pytest.mark.parametrize("d,vocab,rows,tile", HEAD_TILES)
+def test_tiles_of_the_output_heads_that_run_on_the_gpu(plan, d, vocab, rows, tile):
+    """Changed constants do not silently drop a tile, or the split head, from test_gpu_parity.py."""
+    p = plan([dict(K=d, n=vocab, rows=rows, head=1)])[0]
+    assert p["serves"] and (p["bm"], p["bn"], p["parts"] > 1) == tile, p
+
+
+@pytest.mark.parametrize("d,d_ffn,rows,tiles", BODY_TILES)
+def test_tiles_of_the_body_phases_that_run_on_the_gpu(plan, d, d_ffn, rows, tiles):
+    got = plan([dict(K=2 * d, n=d, rows=rows), dict(K=d, n=2 * d_ffn, rows=rows, pairs=1), dict(K=d_ffn, n=d, rows=rows)])
+    assert all(p["serves"] for p in got)
+    assert tuple((p["bm"], p["bn"], p["parts"] > 1) for p in got) == tiles, got
+
+
+def test_every_tile_has_a_gpu_test():
+    ran = {t[:2] for *_, t in HEAD_TILES} | {t[:2] for *_, ts in BODY_TILES for t in ts}
+    assert ran == {(256, 256), (128, 512), (128, 384), (64, 256), (64, 128), (32, 128), (16, 128)}
