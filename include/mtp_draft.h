@@ -219,7 +219,7 @@ int32_t mtp_draft_continue(mtp_handle *h, int32_t B, int32_t K, int32_t subset_i
  * model's hidden state, h^k the head's own output of step k.  Inside a step a position attends the step's own keys of
  * positions <= i.  CE_k = mean over the positions of logsumexp(z) - z[label]; loss = sum_k alpha_k CE_k with
  * alpha_k = beta^(k-1) / sum_j beta^(j-1).  Each step is the block-of-positions pipeline of mtp_draft_extend from an
- * empty cache (every weight read once per 64 positions), followed by a cross-entropy kernel.
+ * empty cache (every weight read once per block of up to 256 positions), followed by a cross-entropy kernel.
  *   n_pos        positions i = 1 .. n_pos (= T - K of the paper); n_pos <= max_batch and <= kv_capacity of
  *                mtp_draft_init (else MTP_ERR_BATCH);  K: 1 .. 16;  beta > 0
  *   hidden_in    device [n_pos][d] bf16          the main model's hidden states
@@ -255,10 +255,10 @@ float mtp_last_draft_ms(mtp_handle *h);
  * How mtp_draft_steps enqueues its work.
  *   2 (default) automatic: mode 1 where it applies, mode 0 otherwise (also when the single launch is refused).
  *   0           one launch per phase.  One sequence: the row-streaming kernels, 7 launches per step plus one to publish
- *               the last draft id.  Two or more (also the rows of a block of positions): the batched kernels (every
- *               weight read once per pass of up to 64 sequences), one preparation launch per step, and one epilogue
- *               launch after each matrix phase whose reduction is split over workgroups (above 16 sequences).
- *               Matrices of 2 GiB or more: as mode 3.
+ *               the last draft id.  Two or more (also the rows of a block of positions): the batched kernels (from 17
+ *               rows on, and in smaller matrices from two on, a tiled matrix product per phase), one preparation launch
+ *               per step, and one launch more after a matrix phase whose reduction is split over workgroups and added
+ *               up apart.  Matrices of 2 GiB or more: as mode 3.
  *   1           one sequence whose reduction lengths (d_model, n_q_heads * head_dim, d_ffn) are all at least 512: one
  *               launch of one workgroup per compute unit runs all phases of all K steps; its workgroups hand their
  *               results over element by element (every element carries a tag naming the call, step and phase that
