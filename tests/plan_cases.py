@@ -14,6 +14,10 @@ HEAD_TILES = [
     (2048, 33000, 100, (128, 384, True)),
     (256, 131072, 17, (128, 512, False)),
     (256, 131072, 130, (256, 256, False)),
+    # reductions of an odd number of 32s, the half step in the last of several parts
+    (2080, 2111, 5, (16, 128, True)),
+    (2080, 2111, 17, (32, 128, True)),
+    (2080, 4000, 40, (64, 128, True)),
 ]
 
 # d_model, d_ffn, rows: the tiles of the 2d -> d projection, gate/up and the down projection (query heads of 128, d / 128 of them)
@@ -21,5 +25,6 @@ BODY_TILES = [
     (2048, 6144, 17, ((32, 128, True), (32, 128, False), (32, 128, True))),
     (2048, 6144, 33, ((64, 128, True), (32, 128, False), (64, 128, True))),
     (2048, 6144, 400, ((64, 256, True), (128, 384, False), (128, 384, True))),
+    (2080, 6176, 17, ((32, 128, True), (32, 128, True), (32, 128, True))),  # half steps, but for the projection
     (2048, 16384, 400, ((64, 256, True), (256, 256, False), (256, 256, True))),
 ]
