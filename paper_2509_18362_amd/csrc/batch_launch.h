@@ -26,6 +26,10 @@ int rows_head_cands(const DraftParams &p, int cus, size_t part_floats);
 void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
                       hipStream_t st);
 
+// the kernel of a phase and a tiling whose last reduction step is half a one (mtp_rows_half.hip); null: not needed
+typedef void (*rows_kernel_t)(DraftParams, int, int);
+rows_kernel_t rows_half_kernel(int phase, int tile);
+
 // matrix-core attention (attn_mfma.h): dynamic LDS, and the launch for query-group size G and head dimension HD
 size_t attn_mfma_lds_bytes(int G, int HD);
 void launch_attn_mfma(int G, int HD, const DraftParams &p, int step, int grid, size_t lds, hipStream_t st);

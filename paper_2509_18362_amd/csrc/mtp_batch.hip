@@ -6,7 +6,7 @@
 #include "attn_mfma.h"
 #include "batch.h"
 #include "batch_launch.h"
-#include "rows_gemm.h"
+#include "rows_kernels.h"
 
 namespace mtp {
 namespace {
@@ -57,30 +57,6 @@ __global__ __launch_bounds__(kBlock) void k_bprep(DraftParams p, int step) {
     phase_bprep(p, step, smem);
 }
 
-// A matrix phase over the rows p.seq_lo .. p.seq_hi - 1 (all of a call's, or those that share an id list) as one tiled matrix
-// product (rows_gemm.h).  PH: a BG_* index, or kHeadLogits for the output head without candidates.  One workgroup per CU (120
-// to 147 KB of LDS, up to 256 registers).
-constexpr int kHeadLogits = BG_COUNT;
-template <int PH, class F>
-__device__ __forceinline__ void with_phase(int step, F f) {
-    if constexpr (PH == BG_PROJ)
-        f([](const DraftParams &q) { return BgProj(q); });
-    else if constexpr (PH == BG_QKV)
-        f([](const DraftParams &q) { return BgQkv(q); });
-    else if constexpr (PH == BG_OPROJ)
-        f([](const DraftParams &q) { return BgOproj(q); });
-    else if constexpr (PH == BG_GATEUP)
-        f([](const DraftParams &q) { return BgGateUp(q); });
-    else if constexpr (PH == BG_DOWN)
-        f([](const DraftParams &q) { return BgDown(q); });
-    else
-        f([step](const DraftParams &q) { return BgHeadRows<PH == BG_LMHEAD>(q, step); });
-}
-template <int PH, class T>
-__global__ __launch_bounds__(kBlock, 2) void k_rows_gemm(DraftParams p, int step, int KP) {
-    extern __shared__ __align__(16) char smem[];
-    with_phase<PH>(step, [&](auto make) { rows_gemm<T, decltype(make(p))>(p, make, KP, smem); });
-}
 template <int PH>
 __global__ __launch_bounds__(kBlock) void k_rows_epilogue(DraftParams p, int step, int KP, int RT) {
     __shared__ __align__(16) float scale[16 + kWaves * 16 * 2]; // the rows' norm scales, the waves' candidates
@@ -166,7 +142,6 @@ bg_kernel_t pick(int phase, int na) {
     default: return pick_na<BG_LMHEAD>(na);
     }
 }
-typedef void (*rows_kernel_t)(DraftParams, int, int);
 typedef RowsTile<4, 4, 2, 8, 3> Rows256x256;
 typedef RowsTile<4, 2, 4, 8, 3> Rows128x512;
 typedef RowsTile<4, 2, 4, 6, 3> Rows128x384;
@@ -174,9 +149,6 @@ typedef RowsTile<2, 2, 4, 4, 3, 64> Rows64x256;
 typedef RowsTile<2, 2, 4, 2, 4, 64> Rows64x128;
 typedef RowsTile<1, 2, 4, 2, 6, 64> Rows32x128;
 typedef RowsTile<1, 1, 8, 1, 7, 64> Rows16x128;
-typedef RowsTile<2, 2, 4, 2, 4, 64, true> Rows64x128Half;
-typedef RowsTile<1, 2, 4, 2, 6, 64, true> Rows32x128Half;
-typedef RowsTile<1, 1, 8, 1, 7, 64, true> Rows16x128Half;
 template <class T>
 constexpr bool is_tile(int t) { // the plan's entry t describes T
     return kRowsTile[t].bm == T::BM && kRowsTile[t].bn == T::BN && kRowsTile[t].bk == T::BK && kRowsTile[t].lds == T::kLds;
@@ -196,24 +168,8 @@ rows_kernel_t pick_rows(int tile) {
     default: return k_rows_gemm<PH, Rows16x128>;
     }
 }
-template <int PH>
-rows_kernel_t pick_rows_half(int tile) { // reductions of an odd number of 32s, tiles with steps of 64
-    switch (tile) {
-    case 4: return k_rows_gemm<PH, Rows64x128Half>;
-    case 5: return k_rows_gemm<PH, Rows32x128Half>;
-    case 6: return k_rows_gemm<PH, Rows16x128Half>;
-    default: return nullptr;
-    }
-}
 rows_kernel_t rows_kernel(int phase, int tile, bool half) {
-    if (half) switch (phase) { // (never of the projections: 2 d and Hq * hd are multiples of 64)
-        case BG_QKV: return pick_rows_half<BG_QKV>(tile);
-        case BG_GATEUP: return pick_rows_half<BG_GATEUP>(tile);
-        case BG_DOWN: return pick_rows_half<BG_DOWN>(tile);
-        case BG_LMHEAD:
-        case kHeadLogits: return pick_rows_half<BG_LMHEAD>(tile);
-        default: return nullptr;
-        }
+    if (half) return rows_half_kernel(phase, tile);
     switch (phase) {
     case BG_PROJ: return pick_rows<BG_PROJ>(tile);
     case BG_QKV: return pick_rows<BG_QKV>(tile);
