@@ -1,7 +1,7 @@
 // The tiled matrix products whose reduction ends in half a step (widths of an odd number of 32s, tiles with steps of 64) for
-// gfx950.  A code object of their own: loaded behind the others' code they leave its place alone, which identical kernels turned
-// out to depend on (with these among them the matrix-core attention took 46 us instead of 41 at thirty sequences of 500 .. 1000
-// tokens of a 2048-wide head, and batches of 40 to 64 sequences 0.6 % longer).
+// gfx950.  In a code object of their own they leave the place of the other kernels' code alone, which identical kernels turned out
+// to depend on: with these among them three steps of a 4096-wide head took 639 us instead of 632 at forty sequences, 703 instead
+// of 698 at sixty-four.
 #include <hip/hip_runtime.h>
 
 #include "batch_launch.h"
