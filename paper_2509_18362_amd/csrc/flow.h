@@ -116,16 +116,18 @@ __device__ __forceinline__ FlowJob flow_job(const DraftParams &p, int ph, int nw
     return j;
 }
 
-// a wave's share of a job: rows wr0, wr0 + nw, ...; chunks of eight 1 KiB loads, a chunk never straddles rows; the
+// a wave's share of a job: rows wr0, wr0 + nw, ...; chunks of CL 1 KiB loads (eight, or four or two where rows are shorter:
+// a half-empty chunk requests, reads and multiplies zeros), a chunk never straddles rows; the
 // chunk count is padded to an odd number of at least three (a phase's first three chunks sit in register slot 0,
 // register slot 1 and the LDS slot, the rest alternate between the register slots)
 struct FlowGeom {
     int nblk, cpr, nrows, nreal, nchunks, wr_last;
 };
+template <int CL>
 __device__ __forceinline__ FlowGeom flow_geom(const FlowJob &j, int wr0, int nw) {
     FlowGeom g;
     g.nblk = (j.K + 511) / 512;
-    g.cpr = (g.nblk + kChunkLoads - 1) / kChunkLoads;
+    g.cpr = (g.nblk + CL - 1) / CL;
     g.nrows = wr0 < j.rows ? (j.rows - wr0 + nw - 1) / nw : 0;
     g.nreal = g.nrows * g.cpr;
     g.nchunks = max(3, g.nreal | 1);
@@ -154,16 +156,17 @@ __device__ __forceinline__ void flow_load_begin(FlowLoad &L, const FlowJob &j, c
 // Request the cursor's next chunk into a ring slot.  Past the wave's last chunk (padding, or no next phase) the
 // request goes to a zero-length buffer: it returns zeros and moves no data, so the ring is refilled without a branch
 // around any load and the compiler can count the loads in flight.
-__device__ __forceinline__ void flow_issue(FlowLoad &L, u32x4 (&buf)[kChunkLoads], int lane) {
+template <int CL>
+__device__ __forceinline__ void flow_issue(FlowLoad &L, u32x4 (&buf)[CL], int lane) {
     const bool live = L.n < L.g.nreal;
     const int v = live ? min(L.row, L.g.wr_last) : 0;
     const int jr = live ? L.jr : 0;
     const row_rsrc rs = make_row_rsrc(L.j.rowptr(v, jr, L.rid), live ? L.j.K * 2 : 0); // wave-uniform
     // The block's offset travels in the per-lane offset, which the buffer's range check covers: whatever lies beyond the
     // row (the tail of its last block, the empty slots of its last chunk) reads as zeros and moves no data.
-    const int voff = lane * 16 + L.c * (kChunkLoads * 1024);
+    const int voff = lane * 16 + L.c * (CL * 1024);
 #pragma unroll
-    for (int u = 0; u < kChunkLoads; ++u) buf[u] = row_load16<true>(rs, voff + u * 1024, 0);
+    for (int u = 0; u < CL; ++u) buf[u] = row_load16<true>(rs, voff + u * 1024, 0);
     ++L.n;
     if (++L.c == L.g.cpr) {
         L.c = 0;
@@ -173,18 +176,19 @@ __device__ __forceinline__ void flow_issue(FlowLoad &L, u32x4 (&buf)[kChunkLoads
     }
 }
 
-// The same request into the wave's LDS slot (8 KiB: eight loads of 1 KiB, each lane's 16 bytes where a register load
+// The same request into the wave's LDS slot (8 KiB: up to eight loads of 1 KiB, each lane's 16 bytes where a register load
 // would have put them).  The compiler counts these loads like the others but does not wait for them before LDS reads:
 // the reader does (flow_wait_lds_slot).
 constexpr int kLdsSlotBytes = kChunkLoads * 1024;
+template <int CL>
 __device__ __forceinline__ void flow_issue_lds(FlowLoad &L, char *slot, int lane) {
     const bool live = L.n < L.g.nreal;
     const int v = live ? min(L.row, L.g.wr_last) : 0;
     const int jr = live ? L.jr : 0;
     const row_rsrc rs = make_row_rsrc(L.j.rowptr(v, jr, L.rid), live ? L.j.K * 2 : 0); // wave-uniform
-    const int voff = lane * 16 + L.c * (kChunkLoads * 1024);
+    const int voff = lane * 16 + L.c * (CL * 1024);
 #pragma unroll
-    for (int u = 0; u < kChunkLoads; ++u)
+    for (int u = 0; u < CL; ++u)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(slot + u * 1024), 16,
                                                  voff + u * 1024, 0, 0, 2);
     ++L.n;
@@ -195,9 +199,10 @@ __device__ __forceinline__ void flow_issue_lds(FlowLoad &L, char *slot, int lane
         L.rid = L.j.row_id(L.row);
     }
 }
-// The LDS slot's chunk was requested before the two register chunks that follow it in the stream (sixteen loads) and
-// loads complete in order: once at most sixteen requests are outstanding it has landed.
-__device__ __forceinline__ void flow_wait_lds_slot() { asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); }
+// The LDS slot's chunk was requested before the two register chunks that follow it in the stream and
+// loads complete in order: once at most those (2 CL) requests are outstanding it has landed.
+template <int CL>
+__device__ __forceinline__ void flow_wait_lds_slot() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CL) : "memory"); }
 
 // ---- polling -----------------------------------------------------------------------------------------------
 __device__ __forceinline__ row_rsrc make_vec_rsrc(const void *base, size_t bytes) {
@@ -358,7 +363,7 @@ __host__ __device__ inline size_t flow_tail_bytes(int d, int nvb) {
 // ---------------------------------------------------------------------------------------------------
 // the kernel body
 // ---------------------------------------------------------------------------------------------------
-template <int G, int HD>
+template <int G, int HD, int CL>
 __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
     const int vb = blockIdx.x, nvb = gridDim.x, d = p.d, F = p.F;
     const int lane = threadIdx.x & (kWave - 1);
@@ -398,7 +403,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
         return (int)id;
     };
 
-    u32x4 ring[2][kChunkLoads];
+    u32x4 ring[2][CL];
     FlowLoad L;
     L.id = FL_NONE;
     bool slot_late = false; // the LDS slot's chunk of the phase that begins has not been requested yet
@@ -407,7 +412,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
 #pragma unroll 1
         for (int ph = FL_PROJH; ph <= FL_HEAD; ++ph) {
             const FlowJob job = flow_job(p, ph, nw);
-            const FlowGeom g = flow_geom(job, wr0, nw);
+            const FlowGeom g = flow_geom<CL>(job, wr0, nw);
             const int kpad = flow_kpad(job.K);
             uint16_t *act_hi = reinterpret_cast<uint16_t *>(smem), *act_lo = act_hi + kpad;
             const int sec = ph == FL_PROJH ? 7 : ph == FL_PROJE ? 0 : ph == FL_QKV ? 1 : ph + 0; // O..HEAD are 3..6
@@ -415,7 +420,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
                 flow_load_begin(L, job, g, ph, wr0);
                 flow_issue(L, ring[0], lane);
                 flow_issue(L, ring[1], lane);
-                flow_issue_lds(L, slot, lane);
+                flow_issue_lds<CL>(L, slot, lane);
             }
             stamp(step, sec, kTraceRequested);
             flow_barrier(); // every wave has finished with the activations of the phase before
@@ -588,7 +593,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
                 }
             }
             if (slot_late) { // the third chunk requested ahead for this phase (see the end of a phase)
-                flow_issue_lds(L, slot, lane);
+                flow_issue_lds<CL>(L, slot, lane);
                 slot_late = false;
             }
             flow_barrier();
@@ -612,9 +617,9 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
             // one chunk: eight blocks of the row against the staged activations; w(u) = the chunk's u-th 1 KiB
             auto consume = [&](auto w) {
 #pragma unroll
-                for (int u = 0; u < kChunkLoads; ++u) {
+                for (int u = 0; u < CL; ++u) {
                     // slots past the row's last block hold zero weights: they re-read the last block's activations
-                    const int e0 = min(c_c * kChunkLoads + u, g.nblk - 1) * 512 + lane * 8;
+                    const int e0 = min(c_c * CL + u, g.nblk - 1) * 512 + lane * 8;
                     const u32x4 ah = *reinterpret_cast<const u32x4 *>(act_hi + e0);
                     const u32x4 al = *reinterpret_cast<const u32x4 *>(act_lo + e0);
                     const u32x4 wv = w(u);
@@ -626,7 +631,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
             auto advance_cursor = [&]() {
                 if (L.n >= L.g.nchunks && L.id == ph && next != FL_NONE) {
                     const FlowJob nj = flow_job(p, next, nw);
-                    flow_load_begin(L, nj, flow_geom(nj, wr0, nw), next, wr0);
+                    flow_load_begin(L, nj, flow_geom<CL>(nj, wr0, nw), next, wr0);
                 }
             };
             auto row_end = [&](int n) {
@@ -695,7 +700,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
                     }
                 }
                 if (n0 == 0) {
-                    flow_wait_lds_slot();
+                    flow_wait_lds_slot<CL>();
                     consume([&](int u) { return *reinterpret_cast<const u32x4 *>(slot + u * 1024 + lane * 16); });
                     row_end(2);
                 }

@@ -52,13 +52,13 @@ __global__ __launch_bounds__(kBlock) void k_lmhead(DraftParams p, int step) {
     phase_lmhead(p, step, blockIdx.x, gridDim.x, smem);
 }
 __global__ void k_finalize(DraftParams p) { phase_finalize(p, blockIdx.x, gridDim.x); }
-template <int G, int HD>
+template <int G, int HD, int CL>
 __global__ __launch_bounds__(kBlock) void k_flow(DraftParams) {
     extern __shared__ __align__(16) char smem[];
     // the attention phase is called out of line and takes the parameters by reference: point it at the
     // kernel-argument segment (the struct is the only argument, at offset 0) instead of a per-lane stack copy
     const DraftParams *p = (const DraftParams *)__builtin_amdgcn_kernarg_segment_ptr();
-    flow_steps<G, HD>(*p, smem);
+    flow_steps<G, HD, CL>(*p, smem);
 }
 
 // Sequential acceptance up to the first mismatch and the draft-cache length after it (Sec. 2.3 "Verification phase").
@@ -280,23 +280,33 @@ phase_kernel_t attn_kernel(int G, int HD) {
     return nullptr;
 }
 typedef void (*fused_kernel_t)(DraftParams);
-fused_kernel_t flow_kernel(int G, int HD) {
+template <int CL>
+fused_kernel_t flow_kernel_of(int G, int HD) {
     if (HD == 128) {
         switch (G) {
-        case 1: return k_flow<1, 128>;
-        case 2: return k_flow<2, 128>;
-        case 4: return k_flow<4, 128>;
-        case 8: return k_flow<8, 128>;
+        case 1: return k_flow<1, 128, CL>;
+        case 2: return k_flow<2, 128, CL>;
+        case 4: return k_flow<4, 128, CL>;
+        case 8: return k_flow<8, 128, CL>;
         }
     } else if (HD == 64) {
         switch (G) {
-        case 1: return k_flow<1, 64>;
-        case 2: return k_flow<2, 64>;
-        case 4: return k_flow<4, 64>;
-        case 8: return k_flow<8, 64>;
+        case 1: return k_flow<1, 64, CL>;
+        case 2: return k_flow<2, 64, CL>;
+        case 4: return k_flow<4, 64, CL>;
+        case 8: return k_flow<8, 64, CL>;
         }
     }
     return nullptr;
+}
+// Loads of 1 KiB per chunk of a row: what one row of most phases fills (half-empty chunks request and multiply zeros).  Three
+// steps, us, with chunks of 2 / 4 / 8: 256 wide 136 / 143 / 166, 2048 wide (d_ffn 6144, 65536 rows) 345 / 305 / 339; 4096 wide
+// takes 8.
+fused_kernel_t flow_kernel(const mtp_config &c) {
+    const int G = c.n_q_heads / c.n_kv_heads, widest = std::max(c.d_model, c.n_q_heads * c.head_dim);
+    if (widest <= 1024) return flow_kernel_of<2>(G, c.head_dim);
+    if (widest <= 2048) return flow_kernel_of<4>(G, c.head_dim);
+    return flow_kernel_of<8>(G, c.head_dim);
 }
 // the matrix-core attention's item map: lengths and two orders of the sequences, full splits below each split index
 size_t attn_map_bytes(int B, int max_splits) { return ((size_t)3 * B + max_splits + 2) * 4; }
@@ -373,6 +383,8 @@ bool config_ok(const mtp_config *c) {
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxFusedGrid = kMaxHeadCands; // workgroups of the single-launch kernel (one per CU)
+constexpr size_t kFlowSmallBytes = 8 << 20;  // weights of a step that a quarter of the compute units read fast enough
+constexpr int kFlowRoundBytes = 160 * 128;   // tokens x head dimension of one round of its attention (phase_attn, U = 5)
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
@@ -576,7 +588,7 @@ int32_t mtp_draft_init(mtp_handle **out, const mtp_config *cfg, const mtp_weight
     h->num_cus = cus;
     h->lds_limit = (size_t)lds;
     h->attn_fn = attn_kernel(cfg->n_q_heads / cfg->n_kv_heads, cfg->head_dim);
-    h->flow_fn = flow_kernel(cfg->n_q_heads / cfg->n_kv_heads, cfg->head_dim);
+    h->flow_fn = flow_kernel(*cfg);
     h->flow_tags = 0;
     h->flow_lds_ok = 0;
     h->mode = 2;
@@ -824,7 +836,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
 
     const int tphase = h->timing >= 2 ? h->timing - 2 : -1;
     h->pev_used = 0;
-    // One sequence and every reduction at least 512 long: all phases of all K steps in ONE launch whose workgroups hand
+    // One sequence: all phases of all K steps in ONE launch whose workgroups hand
     // their results over as tagged elements (flow.h).  Its workgroups wait for one another, so all of them must be
     // resident at once: one per CU (the launch's LDS and registers leave no room for a second, and init has checked
     // that one fits).  A cooperative launch would have the runtime verify that, but it leaves a 20 us gap between
@@ -834,7 +846,13 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     // Its tags count calls on the host, so a call that is being captured into a HIP graph - whose replays would all
     // carry the tags of the captured call - takes one launch per phase instead (those kernels keep no state across
     // calls on the host).
-    const bool rows = B == 1 && p.d >= 512 && p.qd >= 512 && p.F >= 512;
+    // Heads with shorter reductions take a quarter of the units, where that is enough to read their weights: the process's
+    // four hardware queues can then run four such calls side by side, with every workgroup resident (256 wide, 4096 rows, three
+    // steps: 129 us with 64 workgroups, 128 with 256, 159 with a launch per phase).
+    const bool wide = p.d >= 512 && p.qd >= 512 && p.F >= 512;
+    const size_t step_bytes = 2 * ((size_t)p.d * (2 * p.d + p.qkv_dim + p.qd + 3 * (size_t)p.F) + (size_t)p.n * p.d);
+    const bool small = !wide && step_bytes <= kFlowSmallBytes;
+    const bool rows = B == 1 && (wide || small);
     bool capturing = false;
     if (st != nullptr) { // (the legacy default stream cannot be captured, and asking about it disturbs other captures)
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -845,7 +863,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         capturing = cap != hipStreamCaptureStatusNone;
     }
     if ((h->mode == 1 || h->mode == 2) && rows && tphase < 0 && !ext && !seq_subset && !capturing) {
-        const int fgrid = std::min(h->num_cus, kMaxFusedGrid);
+        const int fgrid = small ? std::max(1, h->num_cus / 4) : std::min(h->num_cus, kMaxFusedGrid);
         size_t region = std::max(flow_gemv_region(p.d, p.qd, p.F), lds_attn);
         region = (region + 255) / 256 * 256;
         const size_t lds_flow = region + flow_tail_bytes(p.d, fgrid);
@@ -872,7 +890,11 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             {
                 const int parts = p.Hq / p.Hkv >= 2 ? 2 : 1; // kFlowAttnParts
                 const long long want = ((long long)c.kv_capacity * p.Hkv * parts + fgrid - 1) / fgrid;
-                const long long t = std::min<long long>(std::max<long long>(plan_tokens, (want + 31) / 32 * 32), kMaxSplitTokens);
+                long long t = std::min<long long>(std::max<long long>(plan_tokens, (want + 31) / 32 * 32), kMaxSplitTokens);
+                // A capacity of at most two rounds is one split: nothing to merge saves 2 us per step (capacity 192 at head
+                // dimension 64: 136 -> 128 us per three steps, 640: 136 -> 134, 960: 136 -> 140; 256 at 128: 189 -> 183, 512:
+                // 190 -> 191).
+                if (c.kv_capacity <= 2 * kFlowRoundBytes / p.hd) t = (c.kv_capacity + 31) / 32 * 32;
                 p.split_tokens = (int)t;
                 p.max_splits = (int)((c.kv_capacity + t - 1) / t);
             }

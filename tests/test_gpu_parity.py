@@ -401,6 +401,25 @@ def test_single_launch_gate_and_up_rows_left_over(gpu, d_ffn):
     eng.close()
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(256, 4, 4, 64, 256), (288, 2, 1, 128, 1000), (480, 8, 2, 64, 2048),
+                                               (1024, 8, 4, 128, 520), (1056, 10, 5, 128, 4104), (2048, 16, 8, 128, 2600)])
+@pytest.mark.parametrize("ctx,cap", [(0, 64), (250, 256), (300, 320), (317, 352), (700, 768)])
+def test_single_launch_short_rows(gpu, d, hq, hkv, hd, d_ffn, ctx, cap):
+    """Rows of one 512-element block or less, chunks of two, four and eight blocks, reductions that end inside a block;
+    capacities of one split (two rounds of the attention) and of several."""
+    binding = gpu["binding"]
+    shape = synth.HeadShape(d, hq, hkv, hd, d_ffn, 2048)
+    wl = synth.Workload(f"short_{d}", 110 + d % 97, shape, 1, 0, 0, (520,), 3, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=np.array([ctx], dtype=np.int32), capacity=cap)
+    eng = binding.DraftEngine(shape, w, [ids], 1, cap, 3)
+    for _ in range(2):
+        ref, res, caches = run_both(gpu, shape, w, w, act, [ids], 0, 3, engine=eng)
+        check_chain(ref, res, caches, act["kv_len"], 3, need_clear=False)
+    eng.close()
+
+
 # ------------------------------------------------------------------------------------------ block of new positions
 def extend_inputs(shape, act, m_max, seed):
     """Position-major inputs of the multi-position first step: hidden states with the workload's spread, tokens."""
