@@ -19,7 +19,7 @@ HIPCC_FLAGS = [
 ]
 
 
-SOURCES = ["mtp_draft.hip", "mtp_batch.hip", "mtp_rows_half.hip", "subset_build.hip"]
+SOURCES = ["mtp_draft.hip", "mtp_batch.hip", "mtp_few.hip", "mtp_rows_half.hip", "subset_build.hip"]
 
 
 def _run(cmd, verbose):

@@ -543,7 +543,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
                 if (p.attn_split) {
                     uint16_t h, l;
                     split_bf16(r, h, l);
-                    const size_t at = (size_t)row * p.a_stride + (size_t)hq * HD + dd;
+                    const size_t at = act_index(p, row, hq * HD + dd);
                     p.attn_split[at] = h;
                     p.attn_split[p.a_lo + at] = l;
                 }

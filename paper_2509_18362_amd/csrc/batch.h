@@ -1,17 +1,10 @@
-// Batched weight streaming for 2..64 sequences per pass (gfx950): every weight is read from HBM once per pass.  Large
-// matrices at up to 16 sequences, and what the tiled products of rows_gemm.h do not serve, run here.
+// The phases of a draft step over several rows (sequences, or positions of a block), gfx950: their operands and epilogues (the
+// Bg* structs), used by every batched kernel - few rows (few_rows.h), tiled products (rows_gemm.h) and, in this file, a core
+// that streams every weight once per pass of 17..64 rows, for what the tiled products do not serve (a down projection whose
+// reduction length is no multiple of 32, heads of more rows than the tiles have candidates for).
 //
-// The activations of a phase arrive already split into bf16 hi + lo, written to global memory by the phase before
-// (they stay in L2), so the A operand of the 16x16x32 MFMA (16 sequences x 32 elements) is loaded straight into
-// registers and reused for every weight tile the wave holds at that depth: no LDS staging, no barrier until a group
-// of tiles is complete.  A wave keeps eight accumulators: 8/NA weight tiles (16 rows each) times NA sequence tiles.
-//
-// Work split of a phase over the grid: RG row groups times KP reduction parts.  Phases with many rows per workgroup
-// (gate/up, the output head) use KP = 1; phases with one 16-row tile per workgroup would reload all activations for
-// 16 rows, so they put eight tiles into a row group and split the reduction over KP workgroups instead.  Inside a
-// workgroup the eight waves split the workgroup's reduction range; their sums meet in LDS, the workgroup's sums go
-// to a partial buffer in global memory, and the LAST workgroup of a row group to arrive (a ticket counter) adds the
-// KP partials in a fixed order and runs the phase's epilogue.  With KP = 1 the same code runs without the ticket.
+// The activations of a phase arrive already split into bf16 hi + lo, written to global memory by the phase before (they
+// stay in L2).  The core's work split: RG row groups times KP reduction parts.
 //
 // RMSNorm (Sec. 2.1) costs no pass over the activations here: the producer writes gain * u (split) and the sum of
 // squares of its rows, and because W (s g*u) = s W (g*u), the consumer multiplies its results by
@@ -27,16 +20,8 @@ constexpr int kBatchMaxSeq = 64;  // sequences per pass
 // load returns zeros and moves no data.  Adding the wave-uniform offset (a few MiB at most) cannot wrap it around.
 constexpr uint32_t kOobOffset = 0x80000000u;
 
-
-template <int NA>
-struct BatchShape {
-    static constexpr int TG = kBatchAcc / NA;   // weight tiles per group
-    static constexpr int D = 2;                 // items (one double depth step of a group) in flight per wave
-    static constexpr int NL = 2 * TG + 4 * NA;  // 16-byte loads per lane per item
-};
-
-// partial sums of the waves (or, for wide batches, the two activation buffers, which are smaller), the
-// transposition strips, the norm scales, the ids of the row group
+// the two activation buffers (and the candidates of the head's workgroup afterwards), the transposition strips, the norm
+// scales, the ids of the row group
 __host__ __device__ inline size_t batch_lds_bytes(int max_rows_per_wg) {
     return (size_t)kWaves * kBatchAcc * kWave * 16 + (size_t)kWaves * 2 * 2304 + kBatchMaxSeq * 4 +
            (size_t)max_rows_per_wg * 4 + 256;
@@ -166,7 +151,13 @@ __device__ __forceinline__ void bg_tail(const DraftParams &p, Ph &ph, int KP, in
 }
 
 // ---------------------------------------------------------------------------------------------------
-// the core.  Ph supplies:
+// the core (NA = 2 or 4 sequence tiles).  The waves split the TILES of a block (8/NA tiles per wave, 64/NA per block) and walk
+// the reduction range together: the activations of a double step (NA*16 sequences x 64 elements, hi and lo) are fetched once
+// per workgroup - each thread brings NA/2 pieces along with its weights - parked in one of two LDS buffers and read from there
+// by all waves.  One barrier per step (it does not wait for loads in flight); no reduction across waves.  The sums go to a
+// partial buffer in global memory; with KP > 1 the LAST workgroup of a row group to arrive (a ticket counter) adds the KP
+// parts in a fixed order and runs the phase's epilogue, with KP = 1 the same code runs without the ticket.
+// Ph supplies:
 //   NMAT (1, or 2 = adjacent tiles form (gate, up) pairs), STREAM (non-temporal weight loads), GATHER (rows through
 //   the id list), SCALE (SSQ_* kind whose scale the epilogue needs, or -1),
 //   K, rows (per matrix), in (hi array of the input activations),
@@ -175,197 +166,6 @@ __device__ __forceinline__ void bg_tail(const DraftParams &p, Ph &ph, int KP, in
 //   epi(bf, vt, j, sums[NMAT], scale_lds): results of sequences b0+bf .. +3 (components of the f32x4) for row j of
 //   virtual tile vt (NMAT = 2: vt is the gate tile), run by all 64 lanes of a wave together,
 //   finish(rg, smem): after the last epilogue of the row group (all threads).
-// ---------------------------------------------------------------------------------------------------
-template <int NA, class Ph>
-__device__ __forceinline__ void bgemv(const DraftParams &p, Ph &ph, int RG, int KP, char *smem) {
-    using S = BatchShape<NA>;
-    constexpr int NMAT = Ph::NMAT, TG = S::TG, D = S::D, NL = S::NL;
-    const int wg = blockIdx.x;
-    if (wg >= RG * KP) return;
-    const int kp = wg % KP, rg = wg / KP;
-    const int lane = threadIdx.x & (kWave - 1), g = lane >> 4;
-    // said explicitly to be wave-uniform: offsets and descriptors derived from it then stay in scalar registers
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const int K = ph.K;
-    const int units = (ph.rows + 15) / 16;
-    const int u0 = (int)((long long)rg * units / RG), u1 = (int)((long long)(rg + 1) * units / RG);
-    const int vt0 = u0 * NMAT, nvt = (u1 - u0) * NMAT, ntv = units * NMAT;
-    const int ngroups = (nvt + TG - 1) / TG;
-    // The reduction runs in double steps of 64 elements (128 bytes of a row): lane (j, g) holds bytes 32g .. 32g+32 of
-    // the piece, of row j (weights) or sequence j (activations); its first 16 bytes feed one MFMA, the other 16 the
-    // next - any assignment of elements to MFMA depth slots is fine as long as both operands use the same one.  Two
-    // loads of a lane are neighbours, so a wave always consumes whole 128-byte lines.  Double steps are dealt to the
-    // waves round robin: at any time the eight waves read eight neighbouring pieces of every row, 1 KiB in a row.
-    const int nks = (K + 63) / 64;
-    const int ksA = (int)((long long)kp * nks / KP), ksB = (int)((long long)(kp + 1) * nks / KP);
-    const int per = max((ksB - ksA + kWaves - 1) / kWaves, 1); // items per group, the same for every wave
-
-    f32x4 *partial = reinterpret_cast<f32x4 *>(smem);                           // [kWaves][kBatchAcc][kWave]
-    char *strips = reinterpret_cast<char *>(partial + kWaves * kBatchAcc * kWave); // [kWaves][2] transposition strips
-    float *scale_lds = reinterpret_cast<float *>(strips + kWaves * 2 * kStripBytes); // [kBatchMaxSeq]
-    int *ids_lds = reinterpret_cast<int *>(scale_lds + kBatchMaxSeq);           // [rows of this row group]
-    if (Ph::GATHER) {
-        const int r0 = u0 * 16, nr = (u1 - u0) * 16;
-        for (int i = threadIdx.x; i < nr; i += kBlock) {
-            int pos = min(r0 + i, ph.rows - 1);
-            ids_lds[i] = ph.ids ? ph.ids[pos] : pos;
-        }
-        __syncthreads();
-    }
-
-    // activations: one descriptor over the hi and lo arrays; lane (j, g) reads sequence at*16 + j
-    const size_t lo_bytes = p.a_lo * 2;
-    const row_rsrc ar = make_row_rsrc(ph.in, (int)(2 * lo_bytes));
-    // a lane fetches sequence at*16 + lane/8 [+ 8], bytes 16 (lane % 8) of the 128-byte piece
-    int voff_a[NA][2];
-#pragma unroll
-    for (int at = 0; at < NA; ++at)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            voff_a[at][h] = (int)((size_t)min(p.b0 + at * 16 + (lane >> 3) + 8 * h, p.B - 1) * p.a_stride * 2 + (lane & 7) * 16);
-
-    row_rsrc wr[TG];
-    int voff_w[TG][2];
-    auto setup_group = [&](int grp) {
-#pragma unroll
-        for (int ts = 0; ts < TG; ++ts) {
-            const int t = grp * TG + ts;
-            const uint16_t *base;
-            int mat_rows, row0, row_end;
-            ph.tile(vt0 + min(t, nvt - 1), base, mat_rows, row0, row_end);
-            wr[ts] = make_row_rsrc(base, (int)((size_t)mat_rows * K * 2));
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int jr = (lane >> 3) + 8 * h, r = row0 + jr;
-                const bool ok = t < nvt && r < row_end;
-                const int phys = Ph::GATHER ? ids_lds[(min(t, nvt - 1) / NMAT) * 16 + jr] : r;
-                voff_w[ts][h] = ok ? (int)((size_t)phys * K * 2 + (lane & 7) * 16) : (int)kOobOffset;
-            }
-        }
-    };
-    // The ring is refilled without any branch: a conditional load would leave the compiler unable to count the loads
-    // in flight, and it would then wait for all of them before every use.  Items past the end of a group are
-    // requested beyond the buffers' ends instead (zeros, no traffic) and contribute nothing.
-    u32x4 ring[D][NL];
-    auto issue = [&](u32x4(&slot)[NL], int idx) { // item idx of the current group
-        const int ks = min(ksA + idx * kWaves + wave, nks - 1);
-        const int soff = min(ks * 64, K - 64) * 2; // the last, ragged step is shifted left to stay inside the row
-        const bool live = idx < per;
-#pragma unroll
-        for (int ts = 0; ts < TG; ++ts)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                slot[2 * ts + h] = row_load16<Ph::STREAM>(wr[ts], live ? voff_w[ts][h] : (int)kOobOffset, soff);
-#pragma unroll
-        for (int at = 0; at < NA; ++at)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int vo = live ? voff_a[at][h] : (int)kOobOffset;
-                slot[2 * TG + 4 * at + h] = row_load16<false>(ar, vo, soff);
-                slot[2 * TG + 4 * at + 2 + h] = row_load16<false>(ar, vo, soff + (int)lo_bytes);
-            }
-    };
-    f32x4 acc[kBatchAcc];
-#pragma unroll
-    for (int a = 0; a < kBatchAcc; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-    char *strip0 = strips + (size_t)wave * 2 * kStripBytes, *strip1 = strip0 + kStripBytes;
-    float *part = p.part;
-    // The norm scales for the epilogue (visible after the first group's barrier): BEFORE the weight requests.  Loads of a
-    // wave return in order, so behind forty weight loads per wave these few values arrived a trip through the busy
-    // memory system later each.
-    if (Ph::SCALE >= 0 && !p.bg_sep[Ph::WHICH]) batch_scales(p, Ph::SCALE, scale_lds);
-    for (int grp = 0; grp < ngroups; ++grp) {
-        setup_group(grp);
-        // One item ahead: the request for item i + 1 goes out when item i is about to be multiplied.  (Two items ahead -
-        // both slots requested at the start, each refilled as it is used up - put 80 MiB of requests into the memory
-        // system at once over the chip; the waves that came last then got their first data 20 us into the kernel and
-        // every workgroup waited for them at its barrier.)
-        issue(ring[0], 0);
-        for (int n0 = 0; n0 < per; n0 += D) {
-#pragma unroll
-            for (int s = 0; s < D; ++s) {
-                const int idx = n0 + s;
-                issue(ring[(s + 1) % D], idx + 1);
-                const int ksn = ksA + idx * kWaves + wave;
-                const int ks = min(ksn, nks - 1);
-                const int koff = min(ks * 64, K - 64);
-                // 8-element pieces that were already counted by the step before (ragged end), or all pieces of a
-                // step beyond the workgroup's range or the group's end, contribute zeros
-                const int cut = (idx < per && ksn < ksB) ? (ks * 64 - koff) / 8 : 8;
-                const uint32_t keep0 = g * 2 < cut ? 0u : 0xFFFFFFFFu, keep1 = g * 2 + 1 < cut ? 0u : 0xFFFFFFFFu;
-                // the activations of the step, through the strips into operand layout
-                u32x4 ah[NA][2], al[NA][2];
-#pragma unroll
-                for (int at = 0; at < NA; ++at) {
-                    strip_park(strip0, ring[s][2 * TG + 4 * at], ring[s][2 * TG + 4 * at + 1]);
-                    strip_park(strip1, ring[s][2 * TG + 4 * at + 2], ring[s][2 * TG + 4 * at + 3]);
-                    strip_fetch(strip0, ah[at][0], ah[at][1]);
-                    strip_fetch(strip1, al[at][0], al[at][1]);
-                    ah[at][0] &= keep0;
-                    al[at][0] &= keep0;
-                    ah[at][1] &= keep1;
-                    al[at][1] &= keep1;
-                }
-                // the weight tiles, one strip ahead of the MFMAs
-                strip_park(strip0, ring[s][0], ring[s][1]);
-#pragma unroll
-                for (int ts = 0; ts < TG; ++ts) {
-                    char *cur = (ts & 1) ? strip1 : strip0, *nxt = (ts & 1) ? strip0 : strip1;
-                    u32x4 w0, w1;
-                    strip_fetch(cur, w0, w1);
-                    if (ts + 1 < TG) strip_park(nxt, ring[s][2 * ts + 2], ring[s][2 * ts + 3]);
-#pragma unroll
-                    for (int at = 0; at < NA; ++at) {
-                        f32x4 a = acc[ts * NA + at];
-                        a = mfma16(ah[at][0], w0, a);
-                        a = mfma16(al[at][0], w0, a);
-                        a = mfma16(ah[at][1], w1, a);
-                        a = mfma16(al[at][1], w1, a);
-                        acc[ts * NA + at] = a;
-                    }
-                }
-            }
-        }
-        // group complete: meet the other waves in LDS, hand the sums to the partial buffer
-        f32x4 *pb = partial;
-        __syncthreads(); // the previous group's sums have been read; also drains the ring's trailing requests
-#pragma unroll
-        for (int a = 0; a < kBatchAcc; ++a) {
-            pb[(wave * kBatchAcc + a) * kWave + lane] = acc[a];
-            acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        __syncthreads();
-        {
-            const int a = wave; // this thread adds accumulator `wave`, element `lane`, of all waves
-            f32x4 sum = pb[a * kWave + lane];
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) sum += pb[(w * kBatchAcc + a) * kWave + lane];
-            const int ts = a / NA, at = a % NA, t = grp * TG + ts;
-            if (t < nvt)
-                st_part(part + ((((size_t)kp * ntv + vt0 + t) * NA + at) * kWave + lane) * 4, sum,
-                        KP > 1 && !p.bg_sep[Ph::WHICH]);
-        }
-    }
-
-    if (p.bg_sep[Ph::WHICH]) return; // the epilogue runs as a kernel of its own (see bgemv_lds)
-    bg_tail<NA>(p, ph, KP, rg, ntv, vt0, reinterpret_cast<char *>(partial), scale_lds, [&](auto f) {
-        constexpr int NQ = kBatchAcc / NMAT; // (tile or pair, sequence tile) slots with an epilogue: one per wave
-        if (wave < NQ)
-            for (int grp = 0; grp < ngroups; ++grp) {
-                const int t = grp * TG + (wave / NA) * NMAT;
-                if (t < nvt) f(t, wave % NA);
-            }
-    });
-}
-
-// ---------------------------------------------------------------------------------------------------
-// the core for 17..64 sequences (NA = 2 or 4 sequence tiles).  With the waves splitting the reduction, every wave
-// would fetch 2*NA KiB of activations per KiB of weights from L2; here the waves split the TILES of a block instead
-// (8/NA tiles per wave, 64/NA per block) and walk the reduction range together: the activations of a double step
-// (NA*16 sequences x 64 elements, hi and lo) are fetched once per workgroup - each thread brings NA/2 pieces along
-// with its weights - parked in one of two LDS buffers and read from there by all waves.  One barrier per step (it does
-// not wait for loads in flight); no reduction across waves.  Everything else (row groups x reduction parts, partial
-// buffer, ticket, epilogues) is as above.
 // ---------------------------------------------------------------------------------------------------
 template <int NA, class Ph>
 __device__ __forceinline__ void bgemv_lds(const DraftParams &p, Ph &ph, int RG, int KP, char *smem) {
@@ -441,7 +241,7 @@ __device__ __forceinline__ void bgemv_lds(const DraftParams &p, Ph &ph, int RG, 
             }
         }
     };
-    // branch-free refill, as in the core above: steps past the end of the range are requested beyond the buffers' ends
+    // branch-free refill, as everywhere: steps past the end of the range are requested beyond the buffers' ends
     u32x4 ring[D][NL];
     auto issue = [&](u32x4(&slot)[NL], int idx) { // step idx of the current block
         const int ks = min(ksA + idx, nks - 1);
@@ -460,11 +260,15 @@ __device__ __forceinline__ void bgemv_lds(const DraftParams &p, Ph &ph, int RG, 
     for (int a = 0; a < kBatchAcc; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
     char *strip0 = strips + (size_t)wave * 2 * kStripBytes, *strip1 = strip0 + kStripBytes;
     float *part = p.part;
-    // (before the weight requests, see bgemv; visible after the first step's barrier)
+    // The norm scales for the epilogue (visible after the first step's barrier): BEFORE the weight requests.  Loads of a wave
+    // return in order: behind forty weight loads per wave these few values would each arrive a trip through the busy memory
+    // system later.
     if (Ph::SCALE >= 0 && !p.bg_sep[Ph::WHICH]) batch_scales(p, Ph::SCALE, scale_lds);
     for (int blk = 0; blk < nblocks; ++blk) {
         setup_block(blk);
-        issue(ring[0], 0); // one step ahead, as in bgemv
+        // One step ahead: the request for step i + 1 goes out when step i is about to be multiplied (two ahead put 80 MiB of
+        // requests into the memory system at once; the waves that came last got their first data 20 us into the kernel)
+        issue(ring[0], 0);
         for (int n0 = 0; n0 < steps; n0 += D) {
 #pragma unroll
             for (int s = 0; s < D; ++s) {
@@ -554,6 +358,21 @@ struct BgBase {
     const int *ids = nullptr;
     __device__ BgBase(const DraftParams &p_, int K_, int rows_, const uint16_t *in_) : p(p_), K(K_), rows(rows_), in(in_) {}
     __device__ __forceinline__ void finish(int, char *) {}
+    // What an epilogue reads besides the sums, so that a caller can ask for it before they are known (pre, then epi with it).
+    struct Pre {};
+    __device__ __forceinline__ Pre pre(int, int, int) const { return Pre{}; }
+    // gain of the row, and the row's residual in the four sequences of this lane
+    struct RowPre {
+        uint16_t gn;
+        float res[4];
+    };
+    __device__ __forceinline__ RowPre row_pre(const uint16_t *gain, const float *res, int bf, int row) const {
+        RowPre r;
+        r.gn = gain[row];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) r.res[c] = res ? res[(size_t)min(p.b0 + bf + c, p.B - 1) * p.d + row] : 0.f;
+        return r;
+    }
     // sum over the sixteen rows of a tile of v*v, for the four sequences of this lane; lanes with j == 0 store it
     __device__ __forceinline__ void store_ssq(int kind, int bf, int vt, int j, const float (&v)[4]) const {
 #pragma unroll
@@ -575,17 +394,22 @@ struct BgProj : BgBase {
         mat_rows = row_end = p.d;
         row0 = vt * 16;
     }
-    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *) const {
+    typedef RowPre Pre;
+    __device__ __forceinline__ Pre pre(int bf, int vt, int j) const { return row_pre(p.g_attn, nullptr, bf, vt * 16 + j); }
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale) const {
+        epi(bf, vt, j, s, scale, pre(bf, vt, j));
+    }
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *, const Pre &pr) const {
         const int row = vt * 16 + j;
         const float v[4] = {s[0].x, s[0].y, s[0].z, s[0].w};
-        const float gn = bf16_to_f32(p.g_attn[row]);
+        const float gn = bf16_to_f32(pr.gn);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int bl = bf + c;
             if (bl < p.nb) {
                 const size_t b = p.b0 + bl;
                 p.x[b * p.d + row] = v[c];
-                store_split(p.act[1], p.a_lo, b * p.a_stride + row, gn * v[c]);
+                store_split(p.act[1], p.a_lo, act_index(p, b, row), gn * v[c]);
             }
         }
         store_ssq(SSQ_X, bf, vt, j, v);
@@ -614,7 +438,7 @@ struct BgQkv : BgBase {
         }
         row_end = mat_rows;
     }
-    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale) const {
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale, Pre = Pre{}) const {
         const int row = vt * 16 + j;
         const float v[4] = {s[0].x, s[0].y, s[0].z, s[0].w};
 #pragma unroll
@@ -634,18 +458,23 @@ struct BgOproj : BgBase {
         mat_rows = row_end = p.d;
         row0 = vt * 16;
     }
-    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *) const {
+    typedef RowPre Pre;
+    __device__ __forceinline__ Pre pre(int bf, int vt, int j) const { return row_pre(p.g_mlp, p.x, bf, vt * 16 + j); }
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale) const {
+        epi(bf, vt, j, s, scale, pre(bf, vt, j));
+    }
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *, const Pre &pr) const {
         const int row = vt * 16 + j;
         float v[4] = {s[0].x, s[0].y, s[0].z, s[0].w};
-        const float gn = bf16_to_f32(p.g_mlp[row]);
+        const float gn = bf16_to_f32(pr.gn);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int bl = bf + c;
             if (bl < p.nb) {
                 const size_t b = p.b0 + bl;
-                v[c] += p.x[b * p.d + row];
+                v[c] += pr.res[c];
                 p.o[b * p.d + row] = v[c];
-                store_split(p.act[1], p.a_lo, b * p.a_stride + row, gn * v[c]);
+                store_split(p.act[1], p.a_lo, act_index(p, b, row), gn * v[c]);
             } else {
                 v[c] = 0.f;
             }
@@ -665,7 +494,7 @@ struct BgGateUp : BgBase {
         mat_rows = row_end = p.F;
         row0 = (vt >> 1) * 16;
     }
-    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[2], const float *scale) const {
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[2], const float *scale, Pre = Pre{}) const {
         const int row = (vt >> 1) * 16 + j;
         const float gv[4] = {s[0].x, s[0].y, s[0].z, s[0].w}, uv[4] = {s[1].x, s[1].y, s[1].z, s[1].w};
 #pragma unroll
@@ -673,7 +502,7 @@ struct BgGateUp : BgBase {
             const int bl = bf + c;
             if (bl < p.nb && row < p.F) {
                 const float gs = gv[c] * scale[bl], us = uv[c] * scale[bl];
-                store_split(p.act[0], p.a_lo, (size_t)(p.b0 + bl) * p.a_stride + row, (gs / (1.0f + expf(-gs))) * us);
+                store_split(p.act[0], p.a_lo, act_index(p, p.b0 + bl, row), (gs / (1.0f + expf(-gs))) * us);
             }
         }
     }
@@ -688,18 +517,23 @@ struct BgDown : BgBase {
         mat_rows = row_end = p.d;
         row0 = vt * 16;
     }
-    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *) const {
+    typedef RowPre Pre;
+    __device__ __forceinline__ Pre pre(int bf, int vt, int j) const { return row_pre(p.g_final, p.o, bf, vt * 16 + j); }
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale) const {
+        epi(bf, vt, j, s, scale, pre(bf, vt, j));
+    }
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *, const Pre &pr) const {
         const int row = vt * 16 + j;
         float v[4] = {s[0].x, s[0].y, s[0].z, s[0].w};
-        const float gn = bf16_to_f32(p.g_final[row]);
+        const float gn = bf16_to_f32(pr.gn);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int bl = bf + c;
             if (bl < p.nb) {
                 const size_t b = p.b0 + bl;
-                v[c] += p.o[b * p.d + row];
+                v[c] += pr.res[c];
                 p.dn[b * p.d + row] = v[c];
-                store_split(p.act[1], p.a_lo, b * p.a_stride + row, gn * v[c]);
+                store_split(p.act[1], p.a_lo, act_index(p, b, row), gn * v[c]);
             } else {
                 v[c] = 0.f;
             }
@@ -723,7 +557,7 @@ struct BgHead : BgBase {
         row_end = p.n;
         row0 = vt * 16;
     }
-    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale) {
+    __device__ __forceinline__ void epi(int bf, int vt, int j, const f32x4 (&s)[1], const float *scale, Pre = Pre{}) {
         const int pos = vt * 16 + j;
         const float v[4] = {s[0].x, s[0].y, s[0].z, s[0].w};
         const int at = bf >> 4;
@@ -794,14 +628,13 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     const int b = blockIdx.x, d = p.d, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     float *ra = reinterpret_cast<float *>(smem), *rb = ra + kWaves, *rc = rb + kWaves; // [kWaves] each
     unsigned long long *rk = reinterpret_cast<unsigned long long *>(smem + 128);       // [kWaves]
-    uint16_t *hi = p.act[0] + (size_t)b * p.a_stride;
-    uint16_t *lo = hi + p.a_lo;
+    uint16_t *hi = p.act[0], *lo = hi + p.a_lo;
     if (step == 0 && tid == 0 && seq_overflows(p, b)) atomicOr(p.err, kErrKvOverflow);
 
     // Everything that can be asked for before the previous step's winner is known is asked for first, and the sums
     // of squares travel through ONE reduction together with the winner: the kernel is a chain of memory round trips
     // and barriers on sixteen to sixty-four CUs, not a bandwidth problem.
-    auto split_store = [&](uint16_t *dh, uint16_t *dl, int e, const float (&o)[4]) {
+    auto split_store = [&](uint16_t *dh, uint16_t *dl, size_t e, const float (&o)[4]) {
         uint16_t h[4], l[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) split_bf16(o[q], h[q], l[q]);
@@ -942,7 +775,7 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
                 load_bf16x4(p.g_h, e, gh);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) o[q] = gh[q] * (h[q] * inv2);
-                split_store(hi, lo, e, o);
+                split_store(hi, lo, act_index(p, b, e), o);
             }
         }
     }
@@ -967,7 +800,7 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
             load_bf16x4(p.g_e, e, ge);
 #pragma unroll
             for (int q = 0; q < 4; ++q) o[q] = ge[q] * (ev[it][q] * inve);
-            split_store(hi + d, lo + d, e, o);
+            split_store(hi, lo, act_index(p, b, d + e), o);
         }
     }
 }

@@ -15,6 +15,13 @@ size_t bgemv_lds_bytes(int rows_per_group);
 bool batch_allow_lds(size_t lds_limit, const mtp_config &c);
 // one batched matrix phase (BG_* index) for the sequences [p.b0, p.b0 + p.nb)
 void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t lds, hipStream_t st);
+// A matrix phase of the rows [p.b0, p.b0 + p.nb), at most sixteen (few_rows.h), on few_groups workgroups; the output head
+// leaves as many candidates per row.
+constexpr int kFewRows = 16, kFewPacked = 8; // (up to eight rows: hi and lo halves in one operand)
+constexpr int kFewNarrow = 2048;             // 9..16 rows: widths up to which tiles are faster
+int few_groups(int phase, const DraftParams &p, int cus);
+bool few_allow_lds(size_t lds_limit);
+void launch_few(int phase, const DraftParams &p, int step, int cus, hipStream_t st);
 // the preparation kernel before step `step` (step == K: after the last step), all sequences
 void launch_bprep(const DraftParams &p, int step, hipStream_t st);
 

@@ -11,40 +11,19 @@
 namespace mtp {
 namespace {
 
-// up to 16 sequences: the waves split the reduction; more: they split the tiles and share the activations in LDS
-template <int NA, class Ph>
-__device__ __forceinline__ void run_phase(const DraftParams &p, Ph &ph, int which, char *smem) {
-    if constexpr (NA == 1)
-        bgemv<1>(p, ph, p.bg_rg[which], p.bg_kp[which], smem);
-    else
-        bgemv_lds<NA>(p, ph, p.bg_rg[which], p.bg_kp[which], smem);
-}
-
 template <int PH, int NA>
 __global__ __launch_bounds__(kBlock) void k_bgemv(DraftParams p, int step) {
     extern __shared__ __align__(16) char smem[];
-    if constexpr (PH == BG_PROJ) {
-        BgProj ph(p);
-        run_phase<NA>(p, ph, PH, smem);
-    } else if constexpr (PH == BG_QKV) {
-        BgQkv ph(p);
-        run_phase<NA>(p, ph, PH, smem);
-    } else if constexpr (PH == BG_OPROJ) {
-        BgOproj ph(p);
-        run_phase<NA>(p, ph, PH, smem);
-    } else if constexpr (PH == BG_GATEUP) {
-        BgGateUp ph(p);
-        run_phase<NA>(p, ph, PH, smem);
-    } else if constexpr (PH == BG_DOWN) {
+    if constexpr (PH == BG_DOWN) {
         BgDown ph(p);
-        run_phase<NA>(p, ph, PH, smem);
+        bgemv_lds<NA>(p, ph, p.bg_rg[PH], p.bg_kp[PH], smem);
     } else {
         BgHead ph(p, step);
-        run_phase<NA>(p, ph, PH, smem);
+        bgemv_lds<NA>(p, ph, p.bg_rg[PH], p.bg_kp[PH], smem);
     }
 }
 
-// (the only phase that more than 16 rows take to the batched core with its reduction split: see rows_gemm_serves)
+// (the only phase that comes to the batched core with its reduction split)
 template <int NA>
 __global__ __launch_bounds__(kBlock) void k_bepilogue_down(DraftParams p, int step) {
     __shared__ __align__(16) char smem[kBatchMaxSeq * 4];
@@ -123,24 +102,12 @@ bg_kernel_t attn_mfma_kernel(int G, int HD, bool lpt) {
     }
     return nullptr;
 }
-// More than 16 rows take the tiled products wherever those serve: the batched core then runs the down projection of
-// reduction lengths that are no multiple of 32 and heads of more rows than the tiles have candidates for.
-template <int PH>
-bg_kernel_t pick_na(int na) {
-    if constexpr (PH == BG_DOWN || PH == BG_LMHEAD)
-        return na == 1 ? k_bgemv<PH, 1> : na == 2 ? k_bgemv<PH, 2> : k_bgemv<PH, 4>;
-    else
-        return na == 1 ? k_bgemv<PH, 1> : nullptr;
-}
+// What the tiled products do not serve: the down projection of reduction lengths that are no multiple of 32 and heads of more
+// rows than the tiles have candidates for.
+constexpr int kCorePhases[] = {BG_DOWN, BG_LMHEAD};
 bg_kernel_t pick(int phase, int na) {
-    switch (phase) {
-    case BG_PROJ: return pick_na<BG_PROJ>(na);
-    case BG_QKV: return pick_na<BG_QKV>(na);
-    case BG_OPROJ: return pick_na<BG_OPROJ>(na);
-    case BG_GATEUP: return pick_na<BG_GATEUP>(na);
-    case BG_DOWN: return pick_na<BG_DOWN>(na);
-    default: return pick_na<BG_LMHEAD>(na);
-    }
+    if (phase == BG_DOWN) return na == 2 ? k_bgemv<BG_DOWN, 2> : k_bgemv<BG_DOWN, 4>;
+    return na == 2 ? k_bgemv<BG_LMHEAD, 2> : k_bgemv<BG_LMHEAD, 4>;
 }
 typedef RowsTile<4, 4, 2, 8, 3> Rows256x256;
 typedef RowsTile<4, 2, 4, 8, 3> Rows128x512;
@@ -191,7 +158,7 @@ void (*rows_epilogue_kernel(int phase))(DraftParams, int, int, int) {
     default: return k_rows_epilogue<kHeadLogits>;
     }
 }
-int tiles_for(int nb) { return nb <= 16 ? 1 : nb <= 32 ? 2 : 4; }
+int tiles_for(int nb) { return nb <= 32 ? 2 : 4; }
 
 } // namespace
 
@@ -241,14 +208,15 @@ bool batch_allow_lds(size_t lds_limit, const mtp_config &c) {
     for (bool lpt : {false, true}) allow((const void *)attn_mfma_kernel(G, c.head_dim, lpt));
     allow((const void *)attn_mfma_block_kernel(G, c.head_dim));
     if (c.max_batch < 2) return ok; // one sequence: the row-streaming kernels
+    ok = ok && few_allow_lds(lds_limit);
     for (int ph = 0; ph <= kHeadLogits; ++ph)
         for (int t = 0; t < kRowsTiles; ++t) {
             if (c.max_batch <= kRowsFew && kRowsTile[t].bm > 64) continue; // (rows_plan)
             allow((const void *)rows_kernel(ph, t, false));
             if (c.d_model % 64 || c.d_ffn % 64) allow((const void *)rows_kernel(ph, t, true));
         }
-    for (int ph = 0; ph < BG_COUNT; ++ph)
-        for (int na = 1; na <= tiles_for(c.max_batch); na *= 2) allow((const void *)pick(ph, na));
+    for (int ph : kCorePhases)
+        for (int na : {2, 4}) allow((const void *)pick(ph, na));
     return ok;
 }
 
@@ -256,7 +224,7 @@ void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t ld
     const int na = tiles_for(p.nb);
     hipLaunchKernelGGL(pick(phase, na), dim3(grid), dim3(kBlock), lds, st, p, step);
     if (p.bg_sep[phase]) // (BG_DOWN) one wave per (tile, sequence tile)
-        hipLaunchKernelGGL(na == 1 ? k_bepilogue_down<1> : na == 2 ? k_bepilogue_down<2> : k_bepilogue_down<4>,
+        hipLaunchKernelGGL(na == 2 ? k_bepilogue_down<2> : k_bepilogue_down<4>,
                            dim3(std::min((p.d / 16 * na + kWaves - 1) / kWaves, 1024)), dim3(kBlock), 0, st, p, step);
 }
 

@@ -447,7 +447,7 @@ WsLayout ws_layout(const mtp_config &c) {
     if (c.max_batch >= kBatchMinSeq) {
         size_t kmax = std::max({2 * d, qd, (size_t)c.d_ffn});
         l.a_stride = (int)((kmax + 31) / 32 * 32);
-        l.a_lo = mb * (size_t)l.a_stride;
+        l.a_lo = std::max(mb, (size_t)kFewRows) * (size_t)l.a_stride;
         l.act0 = take(2 * l.a_lo * 2);
         l.act1 = take(2 * l.a_lo * 2);
         l.ssq = take((size_t)3 * mb * (d / 16) * 4);
@@ -995,60 +995,51 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         p.ssq = reinterpret_cast<float *>(ws + l.ssq);
         p.part = reinterpret_cast<float *>(ws + l.part);
         p.ticket = reinterpret_cast<int *>(ws + l.ticket);
-        size_t lds_bg[BG_COUNT];
-        // units: 16-row tiles (gate/up: pairs of tiles); kdim: reduction length
-        // One plan per call: passes of one call share it (a last, smaller pass runs a little off its optimum).
-        // Up to 16 sequences a workgroup's waves split the reduction and a row group holds eight tiles; above, its
-        // waves split the 64/NA tiles of a block.  A phase with fewer tiles than that per workgroup splits the
-        // reduction over KP workgroups, each keeping at least four double steps.
-        auto tiles_of = [](int n) { return n <= 16 ? 1 : n <= 32 ? 2 : 4; };
-        const int na = tiles_of(B);
-        auto plan = [&](int ph, int units, int nmat, int kdim, int na) {
-            // tiles a row group should hold: eight up to 16 sequences (one group of a wave), a full block of 64/NA above
-            const int block_tiles = na == 1 ? kBatchGroupTiles : kWaves * (kBatchGroupTiles / na);
-            const int nks = (kdim + 63) / 64; // double depth steps
-            const long long ntv = (long long)units * nmat;
-            int rg, kp = 1;
-            if (na == 1 && ntv >= 4ll * grid) {
-                rg = std::min(grid, units);
-            } else {
-                kp = (int)std::max(1ll, std::min<long long>((long long)grid * block_tiles / ntv,
-                                                             na == 1 ? nks / kWaves : nks / 4));
-                kp = std::max(1, std::min(kp, grid));
-                rg = std::max(1, std::min(grid / kp, units));
-            }
+        // Rows up to which the phases take the few-rows kernel (few_rows.h).  With the activations in operand order it serves every
+        // phase.  Two steps against the kernels before it (batched core, tiles), us: 4096 wide 2 / 8 / 16 rows 336 / 355 / 365
+        // -> 285 / 310 / 345 (16853-row head), 751 / 773 / 792 -> 658 / 690 / 737 (full); 2048 wide 181 / 200 / 209 -> 168 /
+        // 190 / 218.  From nine rows on every workgroup reads twice its weights in activations: narrow matrices (few tiles, so
+        // few workgroups) are then faster in tiles, split over workgroups, and what the tiles do not serve takes the
+        // few-rows kernel with row-major activations.
+        const bool few = B <= kFewPacked || (B <= kFewRows && c.d_model > kFewNarrow);
+        p.act_bytes = (int)std::min<size_t>(4 * l.a_lo, INT32_MAX);
+        if (few) {
+            const bool packed = B <= kFewPacked;
+            p.act_frag = packed ? 2 * B : B;
+            if (packed) p.a_lo = 8 * (size_t)B;
+        }
+        // Every other phase: tiled matrix products over all rows (rows_gemm.h), three steps at a 32768-row head 648 / 672 / 807 /
+        // 875 us at 17 / 32 / 48 / 64 sequences against 763 / 782 / 997 / 1042 on the batched core; a block of 66 / 128 / 256 / 512
+        // positions 324 / 365 / 550 / 840 us against 523 / 580 / 946 / 1434 in passes of 64.
+        enum { ON_FEW, ON_TILES, ON_CORE };
+        auto route = [&](int ph, const DraftParams &q) {
+            const bool up_to_16 = q.seq_hi - q.seq_lo <= kFewRows;
+            if (few || (up_to_16 && !rows_gemm_serves(ph, q, grid))) return ON_FEW;
+            return rows_gemm_serves(ph, q, grid) ? ON_TILES : ON_CORE;
+        };
+        // The batched core (more than 16 rows only): units of 16-row tiles over row groups, a phase with fewer tiles than a full
+        // block of 64/NA per workgroup splits its reduction over KP workgroups, each keeping at least four double steps.  One plan
+        // per call: passes share it (a last, smaller pass runs a little off its optimum).
+        size_t lds_bg[BG_COUNT] = {};
+        auto plan = [&](int ph, int units, int kdim, int rows) {
+            const int block_tiles = kWaves * (kBatchGroupTiles / (rows <= 32 ? 2 : 4)), nks = (kdim + 63) / 64;
+            const int kp = (int)std::max(1ll, std::min<long long>({(long long)grid * block_tiles / units, nks / 4, grid}));
+            const int rg = std::max(1, std::min(grid / kp, units));
             p.bg_rg[ph] = rg;
             p.bg_kp[ph] = kp;
-            // Split reductions: who adds the parts.  Up to 16 sequences the last workgroup of a row group to arrive
-            // does (a relaxed ticket; the parts are written and read with device-coherent accesses, no cache is written
-            // back or invalidated): sixteen sequences run 2.4 % faster than with a kernel of its own per phase.  Above 16 only
-            // two kinds of phase come here: the down projection of a width that is no multiple of 32, whose row groups hold 64/NA
-            // tiles x NA sequence tiles of sums, too many for one workgroup to add (8.6 % of a step at 64): a small
-            // epilogue kernel spread over the chip does; and heads of more rows than the tiled products have candidates for,
-            // which are not split so far that it matters.
-            p.bg_sep[ph] = (kp >= 2 && ph == BG_DOWN && na > 1) ? 1 : 0;
+            // Who adds the parts: the last workgroup of a row group to arrive, except in the down projection, whose row groups
+            // hold 64/NA tiles x NA sequence tiles of sums, too many for one workgroup to add (8.6 % of a step at 64
+            // sequences): a small epilogue kernel spread over the chip.
+            p.bg_sep[ph] = (kp >= 2 && ph == BG_DOWN) ? 1 : 0;
             lds_bg[ph] = bgemv_lds_bytes(((units + rg - 1) / rg) * 16);
         };
-        plan(BG_PROJ, p.d / 16, 1, 2 * p.d, na);
-        plan(BG_QKV, p.qkv_dim / 16, 1, p.d, na);
-        plan(BG_OPROJ, p.d / 16, 1, p.qd, na);
-        plan(BG_GATEUP, (p.F + 15) / 16, 2, p.d, na);
-        plan(BG_DOWN, p.d / 16, 1, p.F, na);
-        // Matrix phases as tiled matrix products over all rows (rows_gemm.h) where those are the faster kernel.  From 17 rows on
-        // they always are: three steps at a 32768-row head take 648 / 672 / 807 / 875 us at 17 / 32 / 48 / 64 sequences against
-        // 763 / 782 / 997 / 1042 on the batched core; a block of 66 / 128 / 256 / 512 positions 324 / 365 / 550 / 840 us against
-        // 523 / 580 / 946 / 1434 in passes of 64.
-        bool tiled[BG_COUNT];
-        for (int ph = 0; ph < BG_COUNT; ++ph) tiled[ph] = rows_gemm_serves(ph, p, grid);
+        if (route(BG_DOWN, p) == ON_CORE) plan(BG_DOWN, p.d / 16, p.F, B);
         const bool logits_only = ext && ext->logits_only && logits_out;
-        // The output head: one plan per id list (one list: one plan), for the sequences that share the list - the kernel
-        // of a pass follows from their number, and a plan for more of them splits the reduction of the list's rows over
-        // workgroups that then wait for one another (24 sequences in three lists of 32768 / 16384 / 8195 rows, eight each:
-        // 68 / 49 / 51 us per step with the plan of the whole batch, 57 / 28 / 23 with their own).
+        // The output head: one plan per id list (one list: one plan), for the sequences that share the list
         struct HeadPlan {
             int rg, kp;
             size_t lds;
-            bool tiled;
+            int on;
         } head_plan[kMaxListGroups];
         const int n_heads = std::max(1, groups.count);
         int max_cands = 0;
@@ -1064,37 +1055,46 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         };
         for (int g = 0; g < n_heads; ++g) {
             const DraftParams q = head_of(g);
-            const int na_g = tiles_of(q.seq_hi - q.seq_lo);
-            plan(BG_LMHEAD, (q.n + 15) / 16, 1, p.d, na_g);
-            head_plan[g] = HeadPlan{p.bg_rg[BG_LMHEAD], p.bg_kp[BG_LMHEAD], lds_bg[BG_LMHEAD], false};
-            if (lds_bg[BG_LMHEAD] > h->lds_limit) return MTP_ERR_CONFIG;
-            int cands = p.bg_rg[BG_LMHEAD];
-            head_plan[g].tiled = rows_gemm_serves(BG_LMHEAD, q, grid);
-            if (head_plan[g].tiled) cands = rows_head_cands(q, grid, l.part_floats);
+            HeadPlan &hp = head_plan[g];
+            hp.on = route(BG_LMHEAD, q);
+            int cands = 0;
+            if (hp.on == ON_FEW) {
+                cands = few_groups(BG_LMHEAD, q, grid);
+            } else if (hp.on == ON_TILES) {
+                cands = rows_head_cands(q, grid, l.part_floats);
+            } else {
+                plan(BG_LMHEAD, (q.n + 15) / 16, p.d, q.seq_hi - q.seq_lo);
+                hp.rg = p.bg_rg[BG_LMHEAD];
+                hp.kp = p.bg_kp[BG_LMHEAD];
+                hp.lds = lds_bg[BG_LMHEAD];
+                if (hp.lds > h->lds_limit) return MTP_ERR_CONFIG;
+                cands = hp.rg;
+            }
             if (groups.count) groups.cands[g] = cands;
             max_cands = std::max(max_cands, cands);
         }
-        for (int ph = 0; ph < BG_COUNT; ++ph)
-            if (lds_bg[ph] > h->lds_limit) return MTP_ERR_CONFIG;
+        if (lds_bg[BG_DOWN] > h->lds_limit) return MTP_ERR_CONFIG;
         // candidates of the output head per sequence: one per row group of a batched launch, one per workgroup column of a
         // tiled one
         p.head_grid = max_cands;
         publish_lists();
         auto matrix_phase = [&](int timed_as, int ph, int step) {
-            if (ph != BG_LMHEAD && tiled[ph]) {
-                launch_rows_gemm(ph, false, p, step, grid, l.part_floats, st);
-                mark_end(timed_as, step);
-                return;
-            }
             const int runs = ph == BG_LMHEAD ? n_heads : 1; // the output head: once per id list
             for (int g = 0; g < runs; ++g) {
                 DraftParams q = ph == BG_LMHEAD ? head_of(g) : p;
+                const int on = ph == BG_LMHEAD ? head_plan[g].on : route(ph, q);
+                if (on == ON_FEW) {
+                    q.b0 = q.seq_lo;
+                    q.nb = q.seq_hi - q.seq_lo;
+                    launch_few(ph, q, step, grid, st);
+                    continue;
+                }
+                if (on == ON_TILES) {
+                    launch_rows_gemm(ph, logits_only && ph == BG_LMHEAD, q, step, grid, l.part_floats, st);
+                    continue;
+                }
                 size_t lds = lds_bg[ph];
                 if (ph == BG_LMHEAD) {
-                    if (head_plan[g].tiled) {
-                        launch_rows_gemm(ph, logits_only, q, step, grid, l.part_floats, st);
-                        continue;
-                    }
                     q.bg_rg[ph] = head_plan[g].rg;
                     q.bg_kp[ph] = head_plan[g].kp;
                     lds = head_plan[g].lds;

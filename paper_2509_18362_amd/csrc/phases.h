@@ -62,6 +62,9 @@ struct DraftParams {
     uint16_t *act[2];    // two [max_batch][a_stride] hi arrays, each followed (a_lo elements later) by its lo array
     size_t a_lo;
     int a_stride;
+    int act_frag;        // rows of a block if the activations lie in operand order, [element / 8][act_frag rows][8] (few_rows.h;
+                         // up to eight rows: each block the hi rows, then the lo rows); 0: row-major
+    int act_bytes;       // of one of the two act buffers
     uint16_t *attn_split; // where the attention phases also leave their result split (nullptr: they do not)
     float *ssq;          // [3][max_batch][d/16] sums of squares over 16-row tiles of x, x1, x2
     float *part;         // partial sums of the row groups, [KP][tiles][sequence tiles][64] x 4 floats
@@ -80,6 +83,11 @@ struct DraftParams {
     int bg_rg[6], bg_kp[6]; // row groups and reduction parts of the six matrix phases
     int bg_sep[6];          // 1: the phase's epilogue runs as a kernel of its own
 };
+
+// element e of row b in the hi (or lo) array of split activations; eight elements from a multiple of eight on are neighbours
+__device__ __forceinline__ size_t act_index(const DraftParams &p, size_t b, int e) {
+    return p.act_frag ? ((size_t)(e >> 3) * p.act_frag + b) * 8 + (e & 7) : b * p.a_stride + e;
+}
 
 enum : int { kErrKvOverflow = 1, kErrTokenRange = 2, kErrBarrierTimeout = 4 };
 // matrix phases of the batched path, and the vectors whose sums of squares travel with them
@@ -914,7 +922,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
         if (p.attn_split) {
             uint16_t h, l;
             split_bf16(r, h, l);
-            const size_t at = (size_t)b * p.a_stride + (size_t)hq * HD + dd;
+            const size_t at = act_index(p, b, hq * HD + dd);
             p.attn_split[at] = h;
             p.attn_split[p.a_lo + at] = l;
         }
@@ -1270,7 +1278,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
                 if (!TAGGED && p.attn_split) {
                     uint16_t h, l;
                     split_bf16(r, h, l);
-                    const size_t at = (size_t)b * p.a_stride + (size_t)hq * HD + dd;
+                    const size_t at = act_index(p, b, hq * HD + dd);
                     p.attn_split[at] = h;
                     p.attn_split[p.a_lo + at] = l;
                 }

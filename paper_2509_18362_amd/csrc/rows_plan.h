@@ -84,7 +84,9 @@ inline bool rows_gemm_serves(const RowsCall &c, int cus) {
     if (c.K % kRgBK) return false;
     if (c.head && c.n > kRowsTile[1].bn * kMaxHeadCands) return false; // no room for the candidates
     if (c.rows > kRowsFew) return true;
-    // Up to 16 rows the batched core's plain kernel (waves split the reduction) streams large matrices as fast, and adds its
+    // Up to 16 rows (9 to 16 of narrow heads, and the lists of a larger batch: the others take few_rows.h without asking) the
+    // line was drawn against a core whose waves split the reduction, with reduction parts; few_rows.h, which has taken its
+    // place, is the faster one of the two.  That core streamed large matrices as fast as the tiles, and added its
     // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with
     // the launch that adds the parts.  Both kernels go in rounds of one workgroup per CU: this one is ahead while its
     // workgroups fit one round and where further rounds are nearly full.  Gain of the tiled product over the batched core, us
