@@ -41,7 +41,6 @@ struct AttnMfmaLds {
     static constexpr int NC = G * JP;          // query columns: (position, head of the group)
     static_assert(NC <= 16, "the columns of one MFMA tile");
     float q[NC][HD];
-    float cs[JP][HD / 2], sn[JP][HD / 2];
     float knew[HD], vnew[HD];
     float acc[NSTREAM][NC][HD];
     float ml[NSTREAM][NC][2];
@@ -270,70 +269,99 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
         // the same row: next to no traffic).  Behind a branch the compiler cannot count the loads in flight and waits
         // for ALL of them wherever it waits for any: the wait for V then also waited for the keys of the next
         // iteration, requested a moment before, and an iteration lasted a whole trip to memory.
+        // The inputs of the prologue - query, the new key and value, biases, rotary frequency - are asked for BEFORE the cache
+        // rows: loads of a wave return in order, and behind the 128 KB of cache rows per CU each of the three dependent
+        // stages (frequency, query, key) waited for HBM: 7.5 us from the first request to the main loop, now TODO.
+        // A thread turns the pair (jj, jj + HD/2) of up to NP query columns; threads 256.. also the new key's pair, threads
+        // 384.. the new value's element.
+        constexpr int NP = (NC * HD / 2 + kBlock - 1) / kBlock;
+        static_assert(kBlock % (HD / 2) == 0 && kWave * 6 + HD <= kBlock, "thread roles");
+        const int jj = tid % (HD / 2);
+        const double inv_freq = p.rope_inv[jj];
+        const bool has_k = last && tid >= kWave * 4 && tid < kWave * 4 + HD / 2;
+        const bool has_v = last && tid >= kWave * 6 && tid < kWave * 6 + HD;
+        float qa[NP], qb[NP], ka = 0.f, kb = 0.f, vraw = 0.f;
+        uint16_t bqa[NP], bqb[NP], bka = 0, bkb = 0, bv = 0;
+#pragma unroll
+        for (int r = 0; r < NP; ++r) {
+            const int c = (tid + r * kBlock) / (HD / 2), jp = c / G, hq = kvh * G + c % G;
+            bqa[r] = bqb[r] = 0;
+            qa[r] = qb[r] = 0.f;
+            if (c < NC) {
+                // the row the column's query comes from (a position past the block: any row, the column is not used)
+                const int row = JP > 1 ? min(jg * JP + jp, mpos - 1) * nseq + b : b;
+                const float *src = p.qkv + (size_t)row * p.qkv_dim + (size_t)hq * HD;
+                qa[r] = ld_f32<COH>(src + jj);
+                qb[r] = ld_f32<COH>(src + jj + HD / 2);
+                if (p.b_q) {
+                    bqa[r] = p.b_q[hq * HD + jj];
+                    bqb[r] = p.b_q[hq * HD + jj + HD / 2];
+                }
+            }
+        }
+        if (has_k) {
+            const float *src = qkv + p.qd + (size_t)kvh * HD;
+            ka = ld_f32<COH>(src + jj);
+            kb = ld_f32<COH>(src + jj + HD / 2);
+            if (p.b_k) {
+                bka = p.b_k[kvh * HD + jj];
+                bkb = p.b_k[kvh * HD + jj + HD / 2];
+            }
+        }
+        if (has_v) {
+            const int e = tid - kWave * 6;
+            vraw = ld_f32<COH>(qkv + p.qd + p.kvd + (size_t)kvh * HD + e);
+            if (p.b_v) bv = p.b_v[kvh * HD + e];
+        }
         load_iter(wave);
         if (first_item) {
             before_q();
             first_item = false;
         }
 
-        __syncthreads(); // LDS of the previous item is free
-        for (int idx = tid; idx < JP * (HD / 2); idx += kBlock) {
-            const int jp = idx / (HD / 2), e = idx % (HD / 2);
-            int pos = pnew; // JP == 1
-            if constexpr (JP > 1) {
-                pos = 0;
-#pragma unroll
-                for (int u = 0; u < JP; ++u) pos = u == jp ? max(lenj[u] - 1, 0) : pos;
-            }
-            rope_cos_sin(pos, p.rope_inv[e], s.cs[jp][e], s.sn[jp][e]);
-        }
+        lds_barrier(); // LDS of the previous item is free
         if constexpr (JP > 1) {
 #pragma unroll
             for (int u = 0; u < JP; ++u)
                 if (tid == u) s.len[u] = lenj[u];
         }
-        __syncthreads();
-        for (int idx = tid; idx < NC * HD / 2; idx += kBlock) {
-            const int c = idx / (HD / 2), jj = idx % (HD / 2), jp = c / G, gq = c % G;
-            // the row the column's query comes from (a position past the block: any row, the column is not used)
-            const int row = JP > 1 ? min(jg * JP + jp, mpos - 1) * nseq + b : b;
-            const float *src = p.qkv + (size_t)row * p.qkv_dim + (size_t)(kvh * G + gq) * HD;
-            float a = ld_f32<COH>(src + jj), bb = ld_f32<COH>(src + jj + HD / 2), cs = s.cs[jp][jj], sn = s.sn[jp][jj];
-            if (p.b_q) {
-                a += bf16_to_f32(p.b_q[(kvh * G + gq) * HD + jj]);
-                bb += bf16_to_f32(p.b_q[(kvh * G + gq) * HD + jj + HD / 2]);
+        float cs0 = 1.f, sn0 = 0.f; // of the new position (JP == 1)
+        if constexpr (JP == 1) rope_cos_sin(pnew, inv_freq, cs0, sn0);
+#pragma unroll
+        for (int r = 0; r < NP; ++r) {
+            const int c = (tid + r * kBlock) / (HD / 2);
+            float cs = cs0, sn = sn0;
+            if constexpr (JP > 1) {
+                int pos = 0;
+#pragma unroll
+                for (int u = 0; u < JP; ++u) pos = u == c / G ? max(lenj[u] - 1, 0) : pos;
+                rope_cos_sin(pos, inv_freq, cs, sn);
             }
-            s.q[c][jj] = (a * cs - bb * sn) * scale;
-            s.q[c][jj + HD / 2] = (bb * cs + a * sn) * scale;
+            if (c < NC) {
+                const float a = qa[r] + bf16_to_f32(bqa[r]), bb = qb[r] + bf16_to_f32(bqb[r]);
+                s.q[c][jj] = (a * cs - bb * sn) * scale;
+                s.q[c][jj + HD / 2] = (bb * cs + a * sn) * scale;
+            }
         }
-        if (last) {
+        if (has_k) {
             uint16_t *kdst = p.k_cache + (((size_t)b * p.Hkv + kvh) * p.cap + pnew) * HD;
-            uint16_t *vdst = p.v_cache + (((size_t)b * p.Hkv + kvh) * p.cap + pnew) * HD;
-            if (tid >= kWave * 4 && tid < kWave * 4 + HD / 2) {
-                int e = tid - kWave * 4;
-                const float *src = qkv + p.qd + (size_t)kvh * HD;
-                float a = ld_f32<COH>(src + e), bb = ld_f32<COH>(src + e + HD / 2), cs = s.cs[0][e], sn = s.sn[0][e];
-                if (p.b_k) {
-                    a += bf16_to_f32(p.b_k[kvh * HD + e]);
-                    bb += bf16_to_f32(p.b_k[kvh * HD + e + HD / 2]);
-                }
-                uint16_t r0 = f32_to_bf16(a * cs - bb * sn), r1 = f32_to_bf16(bb * cs + a * sn);
-                s.knew[e] = bf16_to_f32(r0);
-                s.knew[e + HD / 2] = bf16_to_f32(r1);
-                if (!dead) {
-                    st_u16<COH>(kdst + e, r0);
-                    st_u16<COH>(kdst + e + HD / 2, r1);
-                }
-            } else if (tid >= kWave * 6 && tid < kWave * 6 + HD) {
-                int e = tid - kWave * 6;
-                float vraw = ld_f32<COH>(qkv + p.qd + p.kvd + (size_t)kvh * HD + e);
-                if (p.b_v) vraw += bf16_to_f32(p.b_v[kvh * HD + e]);
-                uint16_t r = f32_to_bf16(vraw);
-                s.vnew[e] = bf16_to_f32(r);
-                if (!dead) st_u16<COH>(vdst + e, r);
+            const float a = ka + bf16_to_f32(bka), bb = kb + bf16_to_f32(bkb);
+            const uint16_t r0 = f32_to_bf16(a * cs0 - bb * sn0), r1 = f32_to_bf16(bb * cs0 + a * sn0);
+            s.knew[jj] = bf16_to_f32(r0);
+            s.knew[jj + HD / 2] = bf16_to_f32(r1);
+            if (!dead) {
+                st_u16<COH>(kdst + jj, r0);
+                st_u16<COH>(kdst + jj + HD / 2, r1);
             }
         }
-        __syncthreads();
+        if (has_v) {
+            uint16_t *vdst = p.v_cache + (((size_t)b * p.Hkv + kvh) * p.cap + pnew) * HD;
+            const int e = tid - kWave * 6;
+            const uint16_t r = f32_to_bf16(vraw + bf16_to_f32(bv));
+            s.vnew[e] = bf16_to_f32(r);
+            if (!dead) st_u16<COH>(vdst + e, r);
+        }
+        lds_barrier();
 
         // the query operand: column i16 = (position, query head), depth slot g4 holds elements g4*HD/4 + 8u .. +8 for step u
         u32x4 qh[NS], ql[NS];
@@ -588,10 +616,12 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
                 }
                 __syncthreads();
                 // s.len and s.last sit behind the tiles, the strips of the merge at the front of the LDS
-                for (int jp = 0; jp < JP; ++jp)
-                    if (s.last[jp] && wave < G)
-                        merge_head<HD, true, COH>(p, (jg * JP + jp) * nseq + b, kvh * G + wave, (s.len[jp] + T - 1) / T,
+                for (int c = wave; c < NC; c += kWaves) { // a column (position, head) per wave
+                    const int jp = c / G;
+                    if (s.last[jp])
+                        merge_head<HD, true, COH>(p, (jg * JP + jp) * nseq + b, kvh * G + c % G, (s.len[jp] + T - 1) / T,
                                                   reinterpret_cast<float *>(smem) + (size_t)wave * S);
+                }
             }
             __syncthreads(); // the strips and the flag are free again before the next item touches the LDS
         }

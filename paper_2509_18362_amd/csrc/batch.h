@@ -629,11 +629,20 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     float *ra = reinterpret_cast<float *>(smem), *rb = ra + kWaves, *rc = rb + kWaves; // [kWaves] each
     unsigned long long *rk = reinterpret_cast<unsigned long long *>(smem + 128);       // [kWaves]
     uint16_t *hi = p.act[0], *lo = hi + p.a_lo;
-    if (step == 0 && tid == 0 && seq_overflows(p, b)) atomicOr(p.err, kErrKvOverflow);
+    if (step == 0 && tid == 0) {
+        int L = 0;
+        if (p.ext_len) // a block of new positions: this row's length, for every launch that follows
+            p.row_len[b] = L = ext_row_len(b, p.ext_B, p.ext_m, p.cap, p.ext_kv_len, p.ext_len);
+        else
+            L = p.kv_len[b];
+        if (L != kRowInactive && (L < 0 || L + p.K > p.cap)) atomicOr(p.err, kErrKvOverflow);
+    }
+    if (step == p.K && p.ext_len && tid == 0 && b < p.ext_B) ext_advance(b, p.ext_m, p.cap, p.ext_kv_len, p.ext_len);
 
-    // Everything that can be asked for before the previous step's winner is known is asked for first, and the sums
-    // of squares travel through ONE reduction together with the winner: the kernel is a chain of memory round trips
-    // and barriers on sixteen to sixty-four CUs, not a bandwidth problem.
+    // Everything that can be asked for before the previous step's winner is known is asked for first, the gains too, and the
+    // sums of squares travel through ONE reduction together with the winner: the kernel is a chain of memory round trips
+    // and barriers on a few CUs, not a bandwidth problem.  The winner's embedding row is asked for as soon as its id is known, and
+    // the hidden half is formed while it travels (TODO).
     auto split_store = [&](uint16_t *dh, uint16_t *dl, size_t e, const float (&o)[4]) {
         uint16_t h[4], l[4];
 #pragma unroll
@@ -671,6 +680,7 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     const bool from_x2 = step > 0, src_float = from_x2 || p.own_hidden;
     const float *xf = from_x2 ? p.dn + (size_t)b * d : p.hhat + (size_t)b * d;
     float x[kMaxNormIter][4], ev[kMaxNormIter][4];
+    u32x2 gf[kMaxNormIter], gh[kMaxNormIter], ge[kMaxNormIter]; // gains, four bf16 each
     float sx = 0.f, sg = 0.f, se = 0.f;
 #pragma unroll
     for (int it = 0; it < kMaxNormIter; ++it) {
@@ -685,43 +695,57 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
             } else {
                 load_bf16x4(p.hidden_in + (size_t)b * d, e, x[it]);
             }
+            gf[it] = *reinterpret_cast<const u32x2 *>(p.g_final + e);
+            gh[it] = *reinterpret_cast<const u32x2 *>(p.g_h + e);
+            ge[it] = *reinterpret_cast<const u32x2 *>(p.g_e + e);
         }
     }
+    auto gain4 = [](const u32x2 &g, float (&v)[4]) {
+        v[0] = lo_half(g.x);
+        v[1] = hi_half(g.x);
+        v[2] = lo_half(g.y);
+        v[3] = hi_half(g.y);
+    };
     // the token whose embedding forms the other half, where it does not depend on the winner
     const bool early_tok = step < p.K && (step == 0 || p.forced != nullptr);
     int tok = 0;
-    if (early_tok) tok = checked(step == 0 ? p.token_in[b] : p.forced[(size_t)b * (p.K - 1) + step - 1]);
     auto load_embed = [&]() {
-        float s = 0.f;
 #pragma unroll
         for (int it = 0; it < kMaxNormIter; ++it) {
             const int e = (it * kBlock + tid) * 4;
-            if (e < d) {
-                load_bf16x4(p.embed + (size_t)tok * d, e, ev[it]);
+            if (e < d) load_bf16x4(p.embed + (size_t)tok * d, e, ev[it]);
+        }
+    };
+    auto embed_sum = [&]() {
+        float s = 0.f;
+#pragma unroll
+        for (int it = 0; it < kMaxNormIter; ++it)
+            if ((it * kBlock + tid) * 4 < d)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) s += ev[it][q] * ev[it][q];
-            }
-        }
-        return s;
+        return wave_sum(s);
     };
-    if (early_tok) se = load_embed();
+    if (early_tok) {
+        tok = checked(step == 0 ? p.token_in[b] : p.forced[(size_t)b * (p.K - 1) + step - 1]);
+        load_embed();
+    }
 #pragma unroll
     for (int it = 0; it < kMaxNormIter; ++it) {
         const int e = (it * kBlock + tid) * 4;
         if (e < d) {
-            float gf[4] = {1.f, 1.f, 1.f, 1.f};
-            if (from_x2) load_bf16x4(p.g_final, e, gf);
+            float g[4] = {1.f, 1.f, 1.f, 1.f};
+            if (from_x2) gain4(gf[it], g);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 sx += x[it][q] * x[it][q];
-                sg += (gf[q] * x[it][q]) * (gf[q] * x[it][q]);
+                sg += (g[q] * x[it][q]) * (g[q] * x[it][q]);
             }
         }
     }
     // one reduction: three sums and the winner
     sx = wave_sum(sx);
     sg = wave_sum(sg);
-    se = wave_sum(se);
+    if (early_tok) se = embed_sum();
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
         const unsigned long long o = __shfl_xor(best, off, kWave);
@@ -733,7 +757,7 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
         rc[wave] = se;
         rk[wave] = best;
     }
-    __syncthreads();
+    lds_barrier();
     sx = sg = se = 0.f;
     best = 0ull;
 #pragma unroll
@@ -743,10 +767,13 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
         se += rc[w];
         best = rk[w] > best ? rk[w] : best;
     }
-    int did = 0;
     if (from_x2) {
-        did = key_token(p, b, best);
+        const int did = key_token(p, b, best);
         if (tid == 0) p.draft_out[(size_t)b * p.K + step - 1] = seq_dead(p, b) ? -1 : did;
+        if (step < p.K && !early_tok) { // the winner is the next input token
+            tok = checked(did);
+            load_embed();
+        }
     }
     // h_hat = g_final * (x2 * inv1); its own mean square is inv1^2 * mean((g_final x2)^2) up to rounding, which saves a
     // second reduction
@@ -757,12 +784,11 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     for (int it = 0; it < kMaxNormIter; ++it) {
         const int e = (it * kBlock + tid) * 4;
         if (e < d) {
-            float h[4];
+            float h[4], g[4];
             if (from_x2) {
-                float gf[4];
-                load_bf16x4(p.g_final, e, gf);
+                gain4(gf[it], g);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) h[q] = gf[q] * (x[it][q] * inv1);
+                for (int q = 0; q < 4; ++q) h[q] = g[q] * (x[it][q] * inv1);
                 const f32x4 w = {h[0], h[1], h[2], h[3]};
                 *reinterpret_cast<f32x4 *>(p.hhat + (size_t)b * d + e) = w;
                 if (ho) *reinterpret_cast<f32x4 *>(ho + e) = w;
@@ -771,22 +797,20 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
                 for (int q = 0; q < 4; ++q) h[q] = x[it][q];
             }
             if (step < p.K) {
-                float gh[4], o[4];
-                load_bf16x4(p.g_h, e, gh);
+                float o[4];
+                gain4(gh[it], g);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) o[q] = gh[q] * (h[q] * inv2);
+                for (int q = 0; q < 4; ++q) o[q] = g[q] * (h[q] * inv2);
                 split_store(hi, lo, act_index(p, b, e), o);
             }
         }
     }
     if (step >= p.K) return;
-    if (!early_tok) { // the winner is the next input token
-        tok = checked(did);
-        se = load_embed();
-        se = wave_sum(se);
-        __syncthreads(); // rc has been read by everyone
+    if (!early_tok) {
+        se = embed_sum();
+        lds_barrier(); // rc has been read by everyone
         if (lane == 0) rc[wave] = se;
-        __syncthreads();
+        lds_barrier();
         se = 0.f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) se += rc[w];
@@ -796,10 +820,10 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     for (int it = 0; it < kMaxNormIter; ++it) {
         const int e = (it * kBlock + tid) * 4;
         if (e < d) {
-            float ge[4], o[4];
-            load_bf16x4(p.g_e, e, ge);
+            float g[4], o[4];
+            gain4(ge[it], g);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = ge[q] * (ev[it][q] * inve);
+            for (int q = 0; q < 4; ++q) o[q] = g[q] * (ev[it][q] * inve);
             split_store(hi, lo, act_index(p, b, d + e), o);
         }
     }

@@ -81,16 +81,10 @@ __global__ void k_accept(int B, int K, const int *draft, const int *target, int 
     }
 }
 
-// Several new positions per sequence: the cache length each (position, sequence) row starts from.  A sequence whose
-// block does not fit (or whose length is invalid) gets -1 in every row, which the first phase reports; rows beyond
-// a sequence's new positions are marked inactive.
+// (with the row-streaming kernels; the batched path does both in its preparation launches)
 __global__ void k_extend_prep(int B, int m_max, int cap, const int *kv_len, const int *ext_len, int *row_len) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= B * m_max) return;
-    const int b = r % B, j = r / B;
-    const int L = kv_len[b], m = ext_len[b];
-    const bool bad = L < 0 || m < 0 || m > m_max || L + m > cap;
-    row_len[r] = bad ? -1 : (j < m ? L + j : kRowInactive);
+    if (r < B * m_max) row_len[r] = ext_row_len(r, B, m_max, cap, kv_len, ext_len);
 }
 // A block of new positions: bias, rotary embedding and the bf16 cache append of EVERY row's key and value (the work the
 // attention's last split does for the one new position of an ordinary step), so that one attention launch can serve
@@ -124,9 +118,7 @@ __global__ void k_extend_append(DraftParams p) {
 
 __global__ void k_extend_finish(int B, int m_max, int cap, int *kv_len, const int *ext_len) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const int L = kv_len[b], m = ext_len[b];
-    if (L >= 0 && m >= 0 && m <= m_max && L + m <= cap) kv_len[b] = L + m;
+    if (b < B) ext_advance(b, m_max, cap, kv_len, ext_len);
 }
 
 // One id list per group of adjacent sequences: the tables the kernels look a sequence's list up in.
@@ -761,10 +753,12 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     p.split_tokens = split_tokens_for(c, att_B);
     p.max_splits = max_splits_for(c, att_B);
     if (ext) { // per-row cache lengths for the matrix phases
-        int *row_len = reinterpret_cast<int *>(ws + l.row_len);
-        hipLaunchKernelGGL(k_extend_prep, dim3((B + 255) / 256), dim3(256), 0, st, ext->B, ext->m_max, c.kv_capacity,
-                           ext->kv_len, ext->ext_len, row_len);
-        p.kv_len = row_len;
+        p.row_len = reinterpret_cast<int *>(ws + l.row_len);
+        p.kv_len = p.row_len;
+        p.ext_B = ext->B;
+        p.ext_m = ext->m_max;
+        p.ext_len = ext->ext_len;
+        p.ext_kv_len = ext->kv_len;
     }
 
     auto publish_lists = [&]() { // the groups' tables, once their candidate counts are known
@@ -1125,9 +1119,6 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             matrix_phase(PH_LMHEAD, BG_LMHEAD, step);
         }
         launch_bprep(p, K, st);
-        if (ext)
-            hipLaunchKernelGGL(k_extend_finish, dim3((ext->B + 63) / 64), dim3(64), 0, st, ext->B, ext->m_max,
-                               c.kv_capacity, ext->kv_len, ext->ext_len);
         if (h->timing == 1) {
             (void)hipEventRecord(h->ev[1], st);
             h->ev_recorded = true;
@@ -1137,6 +1128,9 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     }
     for (int g = 0; g < groups.count; ++g) groups.cands[g] = grid; // every launch leaves one candidate per workgroup
     publish_lists();
+    if (ext)
+        hipLaunchKernelGGL(k_extend_prep, dim3((B + 255) / 256), dim3(256), 0, st, ext->B, ext->m_max, c.kv_capacity,
+                           ext->kv_len, ext->ext_len, p.row_len);
     for (int step = 0; step < K; ++step) {
         launch(PH_PROJ, k_proj, grid, lds_proj, step);
         launch(PH_QKV, k_qkv, grid, lds_d1, step);

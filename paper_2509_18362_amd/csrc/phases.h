@@ -57,6 +57,9 @@ struct DraftParams {
     // kernel appends every row's key and value before the attention, which then runs once over all rows: a row's
     // cache is that of sequence row % ext_B, and its own position is read from the cache like the others.
     int kv_appended, ext_B;
+    const int *ext_len;          // batched path, a block of new positions: new positions per sequence (null: not a block); the first
+    int *ext_kv_len, *row_len;   // preparation launch forms the rows' lengths (row_len = kv_len of the other launches) from
+    int ext_m;                   // the sequences' (ext_kv_len), the last one advances those
     int nb_proj, nb_d, nb_q, nb_down; // sequences staged in LDS per pass, by reduction length (2d, d, Hq*hd, F)
     // batched path (two or more sequences): activations travel between the phases as bf16 hi + lo in global memory
     uint16_t *act[2];    // two [max_batch][a_stride] hi arrays, each followed (a_lo elements later) by its lo array
@@ -87,6 +90,19 @@ struct DraftParams {
 // element e of row b in the hi (or lo) array of split activations; eight elements from a multiple of eight on are neighbours
 __device__ __forceinline__ size_t act_index(const DraftParams &p, size_t b, int e) {
     return p.act_frag ? ((size_t)(e >> 3) * p.act_frag + b) * 8 + (e & 7) : b * p.a_stride + e;
+}
+
+constexpr int kRowInactive = -0x40000000; // kv_len of a (position, sequence) row beyond the sequence's new positions
+// The cache length row r of a block of new positions starts from.  A sequence whose block does not fit (or whose length is
+// invalid) gets -1 in every row, which the first phase reports; rows beyond a sequence's new positions are marked inactive.
+__device__ __forceinline__ int ext_row_len(int r, int B, int m_max, int cap, const int *kv_len, const int *ext_len) {
+    const int b = r % B, j = r / B, L = kv_len[b], m = ext_len[b];
+    const bool bad = L < 0 || m < 0 || m > m_max || L + m > cap;
+    return bad ? -1 : (j < m ? L + j : kRowInactive);
+}
+__device__ __forceinline__ void ext_advance(int b, int m_max, int cap, int *kv_len, const int *ext_len) {
+    const int L = kv_len[b], m = ext_len[b];
+    if (L >= 0 && m >= 0 && m <= m_max && L + m <= cap) kv_len[b] = L + m;
 }
 
 enum : int { kErrKvOverflow = 1, kErrTokenRange = 2, kErrBarrierTimeout = 4 };
@@ -155,7 +171,6 @@ __device__ __forceinline__ void ld_tagged2(const DraftParams &p, const unsigned 
 // ---------------------------------------------------------------------------------------------------
 // per-sequence state helpers
 // ---------------------------------------------------------------------------------------------------
-constexpr int kRowInactive = -0x40000000; // kv_len of a (position, sequence) row beyond the sequence's new positions
 __device__ __forceinline__ bool seq_dead(const DraftParams &p, int b) {
     int L = p.kv_len[b];
     return L < 0 || L + p.K > p.cap;
