@@ -41,6 +41,7 @@ struct AttnMfmaLds {
     static constexpr int NC = G * JP;          // query columns: (position, head of the group)
     static_assert(NC <= 16, "the columns of one MFMA tile");
     float q[NC][HD];
+    alignas(16) uint16_t qs[2][NC][HD + 8]; // the query times log2(e), split into bf16 hi and lo (rows apart in the banks)
     float knew[HD], vnew[HD];
     float acc[NSTREAM][NC][HD];
     float ml[NSTREAM][NC][2];
@@ -269,9 +270,8 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
         // the same row: next to no traffic).  Behind a branch the compiler cannot count the loads in flight and waits
         // for ALL of them wherever it waits for any: the wait for V then also waited for the keys of the next
         // iteration, requested a moment before, and an iteration lasted a whole trip to memory.
-        // The inputs of the prologue - query, the new key and value, biases, rotary frequency - are asked for BEFORE the cache
-        // rows: loads of a wave return in order, and behind the 128 KB of cache rows per CU each of the three dependent
-        // stages (frequency, query, key) waited for HBM: 7.5 us from the first request to the main loop, now TODO.
+        // The inputs of the prologue - query, the new key and value, biases, rotary frequency - are asked for before the cache
+        // rows (loads of a wave return in order) and stay with the thread that uses them.
         // A thread turns the pair (jj, jj + HD/2) of up to NP query columns; threads 256.. also the new key's pair, threads
         // 384.. the new value's element.
         constexpr int NP = (NC * HD / 2 + kBlock - 1) / kBlock;
@@ -339,8 +339,11 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
             }
             if (c < NC) {
                 const float a = qa[r] + bf16_to_f32(bqa[r]), bb = qb[r] + bf16_to_f32(bqb[r]);
-                s.q[c][jj] = (a * cs - bb * sn) * scale;
-                s.q[c][jj + HD / 2] = (bb * cs + a * sn) * scale;
+                const float q0 = (a * cs - bb * sn) * scale, q1 = (bb * cs + a * sn) * scale;
+                s.q[c][jj] = q0;
+                s.q[c][jj + HD / 2] = q1;
+                split_bf16(q0 * kLog2e, s.qs[0][c][jj], s.qs[1][c][jj]);
+                split_bf16(q1 * kLog2e, s.qs[0][c][jj + HD / 2], s.qs[1][c][jj + HD / 2]);
             }
         }
         if (has_k) {
@@ -367,19 +370,12 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
         u32x4 qh[NS], ql[NS];
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
-            uint32_t h[4] = {0u, 0u, 0u, 0u}, l[4] = {0u, 0u, 0u, 0u};
-            if (i16 < NC) {
-                const float *src = &s.q[i16 < NC ? i16 : 0][g4 * (HD / 4) + u * 8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    uint16_t hh, ll;
-                    split_bf16(src[e] * kLog2e, hh, ll);
-                    h[e >> 1] |= (uint32_t)hh << ((e & 1) * 16);
-                    l[e >> 1] |= (uint32_t)ll << ((e & 1) * 16);
-                }
-            }
-            qh[u] = u32x4{h[0], h[1], h[2], h[3]};
-            ql[u] = u32x4{l[0], l[1], l[2], l[3]};
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const int col = i16 < NC ? i16 : 0, at = g4 * (HD / 4) + u * 8;
+            const u32x4 h = *reinterpret_cast<const u32x4 *>(&s.qs[0][col][at]);
+            const u32x4 l = *reinterpret_cast<const u32x4 *>(&s.qs[1][col][at]);
+            qh[u] = i16 < NC ? h : zero;
+            ql[u] = i16 < NC ? l : zero;
         }
 
         // tokens of the split this lane's column sees: all of them, or up to its own position's end
