@@ -18,12 +18,12 @@
 // in lane order, so rows cannot be padded; the 16-byte
 // chunks of a 64-byte row are stored at position chunk ^ ((row >> 1) & 3) instead (the lane that fills a position
 // fetches the chunk that belongs there), which puts the eight rows a quarter of a read covers on different banks.
-// Measured at 512 rows of the 7B-shaped head (us; the kernel before, with 64 x 128 to 128 x 256 tiles, operands through
-// registers and no split, in brackets): 2d -> d 68 + 16 for the sum of eight parts [111], q/k/v 55 + 14 [139], output
-// projection 45 + 16 [68], gate/up 183 [264], down 87 + 22 [154], head of 151680 rows 1210 [1221], of 32768 rows 263 with
-// candidates [670: eight passes of the batched core].  The large ones run at 1.05 PFLOP/s of MFMAs, where a plain library
-// product of the same size reaches 1.1 (the chip holds about 2 GHz then); reading the next step's fragments ahead of the
-// barrier, in two orders, changed nothing.
+// With large tiles the two halves of the workgroup take turns, one reading its operands from LDS while the other multiplies.
+// Measured at 512 rows of the 7B-shaped head (us; in brackets with all eight waves in step): 2d -> d 61 [66], q/k/v 48 [52],
+// output projection 39 [43], gate/up 161 [181], down 76 [84], head of 151680 rows 1097 [1222], each split phase + 14 to 19 for
+// the sum of its parts; the head of 32768 rows with candidates at 509 rows 252 [280].  The large ones now run at 1.16 PFLOP/s of
+// MFMAs, 1.25 while every CU has a tile (1186 tiles of 256 x 256 are 4.6 rounds); a plain library product of 8192 cubed
+// reaches 1.22.
 // The phases and their epilogues are the batched core's (the Bg* structs: same operands, same result layout of a
 // 16 x 16 tile).
 #pragma once
@@ -294,6 +294,53 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     // (chains in an outer loop, so that the inner one stays short: with the moves behind a branch of the inner loop a draft
     // step of a 1024-wide head took 2.5 % longer, most launches of which are 8 to 16 steps)
     int ks = k0;
+    // Large pieces in turns: the four waves of one half of the workgroup (one per SIMD) read their operands of a step while the
+    // other four multiply, then the halves change places.  In step with one another all eight read first (128 KB a step, 1000
+    // cycles of the LDS) and the matrix cores waited for most of it.  The second half runs one barrier behind.  A step is
+    // read by the first half in interval 2 ks and by the second in 2 ks + 1; its stage is requested again from interval
+    // 2 ks + 2 on, and a wave has waited for its own pieces of a step before the barrier that opens the step's first interval.
+    constexpr bool kTurns = T::BK == 32 && TI * TJ >= 24 && kChain == 0 && ST == 3;
+    if constexpr (kTurns) {
+        const bool second = wave >= kWaves / 2; // uniform
+        auto landed = [&]() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NL) : "memory"); }; // all but the newest step
+        auto turn = [&]() {
+            asm volatile("s_barrier" : : : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        landed();
+        turn();
+        if (second) turn();
+        for (; ks < kw; ++ks) {
+            const char *as = abase + stage * T::kStage + frag[0], *ws = wbase + stage * T::kStage + frag[0];
+            request(ks + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+            u32x4 wf[TJ], ah[TI], al[TI];
+#pragma unroll
+            for (int tj = 0; tj < TJ; ++tj) wf[tj] = *reinterpret_cast<const u32x4 *>(ws + tj * 16 * kRow);
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) {
+                ah[ti] = *reinterpret_cast<const u32x4 *>(as + ti * 16 * kRow);
+                al[ti] = *reinterpret_cast<const u32x4 *>(as + (BM * kRow) + ti * 16 * kRow);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+            if (second) landed();
+            __builtin_amdgcn_sched_barrier(0);
+            turn();
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) {
+#pragma unroll
+                for (int tj = 0; tj < TJ; ++tj) acc[0][ti][tj] = mfma16(ah[ti], wf[tj], acc[0][ti][tj]);
+#pragma unroll
+                for (int tj = 0; tj < TJ; ++tj) acc[0][ti][tj] = mfma16(al[ti], wf[tj], acc[0][ti][tj]);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!second) landed();
+            turn();
+            stage = stage == ST - 1 ? 0 : stage + 1;
+        }
+        if (!second) turn();
+    } else
     do {
         const int end = kChain > 0 ? min(ks + kChain, kw) : kw;
         for (; ks < end; ++ks) {
