@@ -206,20 +206,22 @@ __global__ __launch_bounds__(kCeBlock) void k_train_row_ce(const float *__restri
         for (int w = 0; w < kCeWaves; ++w) M = fmaxf(M, red_m[w]);
 #pragma unroll
         for (int w = 0; w < kCeWaves; ++w) tot += red_m[w] == -INFINITY ? 0.f : red_s[w] * expf(red_m[w] - M);
-        row_loss[blockIdx.x] = M + logf(tot) - z[label];
+        // in double: the sum's own error is far below a float of M + log(tot)
+        row_loss[blockIdx.x] = (float)((double)M + log((double)tot) - (double)z[label]);
     }
 }
 // mean over the positions in a fixed order (one workgroup), and after the last step the weighted total of Eq. (1)
 __global__ __launch_bounds__(256) void k_train_step_mean(const float *row_loss, int n_pos, float *loss_out, int k, int K,
                                                          float beta) {
-    __shared__ float red[256 / kWave];
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n_pos; i += 256) s += row_loss[i];
-    s = wave_sum(s);
+    __shared__ double red[256 / kWave];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < n_pos; i += 256) s += (double)row_loss[i];
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) s += __shfl_xor(s, off, kWave);
     if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
     __syncthreads();
     if (threadIdx.x != 0) return;
-    loss_out[k] = ((red[0] + red[1]) + (red[2] + red[3])) / (float)n_pos;
+    loss_out[k] = (float)(((red[0] + red[1]) + (red[2] + red[3])) / (double)n_pos);
     if (k == K - 1) { // Eq. (2): alpha_j = beta^(j-1) / sum_i beta^(i-1)
         float wsum = 0.f, acc = 0.f, w = 1.f;
         for (int j = 0; j < K; ++j) {

@@ -325,7 +325,6 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
             if (second) landed();
             __builtin_amdgcn_sched_barrier(0);
             turn();
-            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti) {
 #pragma unroll
@@ -333,7 +332,6 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
 #pragma unroll
                 for (int tj = 0; tj < TJ; ++tj) acc[0][ti][tj] = mfma16(al[ti], wf[tj], acc[0][ti][tj]);
             }
-            __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
             if (!second) landed();
             turn();
