@@ -256,16 +256,17 @@ float mtp_last_draft_ms(mtp_handle *h);
  *   2 (default) automatic: mode 1 where it applies, mode 0 otherwise (also when the single launch is refused).
  *   0           one launch per phase.  One sequence: the row-streaming kernels, 7 launches per step plus one to publish
  *               the last draft id.  Two or more (also the rows of a block of positions): the batched kernels (from 17
- *               rows on, and in smaller matrices from two on, a tiled matrix product per phase), one preparation launch
+ *               rows on, and in narrow heads from nine on, a tiled matrix product per phase), one preparation launch
  *               per step, and one launch more after a matrix phase whose reduction is split over workgroups and added
  *               up apart.  Matrices of 2 GiB or more: as mode 3.
- *   1           one sequence whose reduction lengths (d_model, n_q_heads * head_dim, d_ffn) are all at least 512: one
- *               launch of one workgroup per compute unit runs all phases of all K steps; its workgroups hand their
- *               results over element by element (every element carries a tag naming the call, step and phase that
- *               produced it, consumers poll for it), there are no grid barriers.  The workgroups wait for one another,
- *               so the launch needs every compute unit of the device to itself: do not overlap it with other kernels
- *               (other streams, other processes); a wait that does not end within ~2 s gives up and sets
- *               MTP_ERR_TIMEOUT.  Every other call: as mode 0.
+ *   1           one sequence whose reduction lengths (d_model, n_q_heads * head_dim, d_ffn) are all at least 512, or that has a
+ *               shorter one and reads at most 8 MiB of weights per step: one launch runs all phases of all K steps, on one
+ *               workgroup per compute unit in the first case, on a quarter of the units in the second; its workgroups hand
+ *               their results over element by element (every element carries a tag naming the call, step and phase that
+ *               produced it, consumers poll for it), there are no grid barriers.  The workgroups wait for one another, so all
+ *               of them must find room on the device: do not overlap the first kind with other kernels (other streams,
+ *               other processes), nor more than four calls of the second kind with one another; a wait that does not end
+ *               within ~2 s gives up and sets MTP_ERR_TIMEOUT (mode 0 has no such waits).  Every other call: as mode 0.
  *   3           as mode 0, with the row-streaming kernels for up to four sequences (slower from the second
  *               sequence on; the form the library itself falls back to for matrices of 2 GiB or more).
  * Other values return MTP_ERR_MODE.  HIP-graph capture: mtp_draft_steps, mtp_draft_steps_lists, mtp_draft_extend,
