@@ -263,18 +263,20 @@ float mtp_last_draft_ms(mtp_handle *h);
  *               shorter one and reads at most 8 MiB of weights per step: one launch runs all phases of all K steps, on one
  *               workgroup per compute unit in the first case, on a quarter of the units in the second; its workgroups hand
  *               their results over element by element (every element carries a tag naming the call, step and phase that
- *               produced it, consumers poll for it), there are no grid barriers.  The workgroups wait for one another, so all
- *               of them must find room on the device: do not overlap the first kind with other kernels (other streams,
- *               other processes), nor more than four calls of the second kind with one another; a wait that does not end
- *               within ~2 s gives up and sets MTP_ERR_TIMEOUT (mode 0 has no such waits).  Every other call: as mode 0.
+ *               produced it, consumers poll for it), there are no grid barriers.  The workgroups of the first kind wait for one
+ *               another, so all of them must find room on the device: do not overlap it with other kernels (other streams,
+ *               other processes); a wait that does not end within ~2 s gives up and sets MTP_ERR_TIMEOUT (mode 0 has no such
+ *               waits).  The second kind may overlap anything: its workgroups wait for one another only once all of them are
+ *               on the device, and where that takes more than 0.3 ms one of them does the call by itself, with the same
+ *               bits (slower: about 0.2 ms per step and MB of weights).  Every other call: as mode 0.
  *   3           as mode 0, with the row-streaming kernels for up to four sequences (slower from the second
  *               sequence on; the form the library itself falls back to for matrices of 2 GiB or more).
  * Other values return MTP_ERR_MODE.  HIP-graph capture: mtp_draft_steps, mtp_draft_steps_lists, mtp_draft_extend,
  * mtp_draft_continue and mtp_accept only enqueue kernels (no memset or copy nodes except mtp_draft_continue's one
  * device-to-device copy, no synchronisation, no allocation) and may be captured on a non-default stream with timing
  * off; a captured call always takes one launch per phase (the single-launch kernel's tags count calls on the host,
- * which replays do not).  Results agree between the modes to rounding (one sequence: bit for bit between
- * modes 0 and 3; the single-launch kernel adds the two halves of the projection separately).
+ * which replays do not), and so does mtp_draft_steps_lists.  Results agree between the modes to rounding (one sequence:
+ * bit for bit between modes 0 and 3; the single-launch kernel adds the two halves of the projection separately).
  */
 int32_t mtp_set_launch_mode(mtp_handle *h, int32_t mode);
 
@@ -297,6 +299,13 @@ int32_t mtp_stream_probe(const void *buffer, size_t bytes, void *out8, void *hip
  */
 size_t mtp_phase_trace_bytes(const mtp_config *cfg);
 int32_t mtp_set_phase_trace(mtp_handle *h, void *device_buffer);
+
+/*
+ * Diagnostics for the single launch of heads with a reduction length below 512 (mtp_set_launch_mode): how long its workgroups
+ * wait for all of them to be on the device before one does the call alone, in 100 MHz ticks (30000 after
+ * mtp_draft_init; 0: always alone).  Negative: MTP_ERR_CONFIG.
+ */
+int32_t mtp_set_admission_ticks(mtp_handle *h, int64_t ticks);
 
 /*
  * The high-frequency id list of one language from a token stream (Sec. 2.2: the subsets come from token statistics

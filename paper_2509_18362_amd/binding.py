@@ -33,6 +33,7 @@ EXPORTS = ["mtp_status_string", "mtp_workspace_bytes", "mtp_draft_init", "mtp_dr
            "mtp_train_workspace_bytes", "mtp_train_loss",
            "mtp_accept",
            "mtp_poll_error", "mtp_set_timing", "mtp_last_draft_ms", "mtp_set_launch_mode", "mtp_set_phase_trace",
+           "mtp_set_admission_ticks",
            "mtp_phase_trace_bytes", "mtp_stream_probe",
            "mtp_draft_destroy"]
 LAUNCH_PER_PHASE, LAUNCH_SINGLE, LAUNCH_AUTO, LAUNCH_ROWS = 0, 1, 2, 3
@@ -106,6 +107,8 @@ _lib.mtp_phase_trace_bytes.restype = C.c_size_t
 _lib.mtp_phase_trace_bytes.argtypes = [C.POINTER(mtp_config)]
 _lib.mtp_set_phase_trace.restype = C.c_int32
 _lib.mtp_set_phase_trace.argtypes = [C.c_void_p, C.c_void_p]
+_lib.mtp_set_admission_ticks.restype = C.c_int32
+_lib.mtp_set_admission_ticks.argtypes = [C.c_void_p, C.c_int64]
 _lib.mtp_draft_destroy.restype = None
 _lib.mtp_draft_destroy.argtypes = [C.c_void_p]
 
@@ -246,6 +249,10 @@ TRACE_POINTS = ["requested", "released", "staged", "done"]
 
 def mtp_set_phase_trace(handle, device_buffer) -> int:
     return int(_lib.mtp_set_phase_trace(handle, _addr(device_buffer)))
+
+
+def mtp_set_admission_ticks(handle, ticks: int) -> int:
+    return int(_lib.mtp_set_admission_ticks(handle, ticks))
 
 
 def mtp_draft_destroy(handle) -> None:

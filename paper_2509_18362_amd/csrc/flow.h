@@ -361,11 +361,56 @@ __host__ __device__ inline size_t flow_tail_bytes(int d, int nvb) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// the kernel body
+// Whether the launch's workgroups may wait for one another (p.admit set: heads that do not take every compute unit, whose calls
+// may overlap other kernels).  Workgroups that wait hold their compute units; two launches that each have part of the units
+// would wait for good.  So every workgroup first counts itself in and waits until all are there: from then on nothing that they
+// wait for depends on another launch.  If that takes too long, ONE workgroup (the one whose flag gets in) does the whole call
+// by itself, as a launch of one workgroup would, and the others leave: no wait depends on more than one resident workgroup.
+// p.admit[0]: arrivals, and kAdmitAlone once the others are to leave; one word decides, so that all of them decide alike.  The
+// calls of a handle take two words in turn and clear each other's (a call's last workgroups may arrive long after its result is
+// complete, but before the next call starts).  Every workgroup arrives exactly once.
+// admit_ticks: the longest wait (100 MHz), 0: never all of them (the first to arrive does the call).
+// ---------------------------------------------------------------------------------------------------
+enum : int { kAdmitLeave = 0, kAdmitAll = 1, kAdmitOne = 2 };
+constexpr unsigned kAdmitAlone = 0x80000000u;
+__device__ __forceinline__ int flow_admit(const DraftParams &p, int *flag) {
+    if (threadIdx.x == 0) {
+        auto seen = [&]() { return __hip_atomic_load(p.admit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        const long long t0 = wall_clock64();
+        const unsigned all = gridDim.x, before = __hip_atomic_fetch_add(p.admit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (blockIdx.x == 0) __hip_atomic_store(p.admit_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int state = -1;
+        unsigned w = before + 1u;
+        if (p.admit_ticks == 0 && before == 0u) {
+            __hip_atomic_fetch_or(p.admit, kAdmitAlone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            state = kAdmitOne;
+        }
+        while (state < 0) {
+            if (w & kAdmitAlone)
+                state = kAdmitLeave;
+            else if (p.admit_ticks != 0 && w == all)
+                state = kAdmitAll;
+            else if (p.admit_ticks != 0 && wall_clock64() - t0 > p.admit_ticks) {
+                if (__hip_atomic_compare_exchange_strong(p.admit, &w, w | kAdmitAlone, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT))
+                    state = kAdmitOne; // (else w is what another workgroup has made of it)
+            } else
+                w = seen();
+        }
+        *flag = state;
+    }
+    __syncthreads();
+    const int state = __builtin_amdgcn_readfirstlane(*flag);
+    __syncthreads(); // the flag's place is used for other things from here on
+    return state;
+}
+
+// ---------------------------------------------------------------------------------------------------
+// the kernel body, workgroup vb of nvb
 // ---------------------------------------------------------------------------------------------------
 template <int G, int HD, int CL>
-__device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem) {
-    const int vb = blockIdx.x, nvb = gridDim.x, d = p.d, F = p.F;
+__device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int vb, int nvb) {
+    const int d = p.d, F = p.F;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int nw = nvb * kWaves, wr0 = vb * kWaves + wave;

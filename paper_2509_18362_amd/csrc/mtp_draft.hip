@@ -58,7 +58,13 @@ __global__ __launch_bounds__(kBlock) void k_flow(DraftParams) {
     // the attention phase is called out of line and takes the parameters by reference: point it at the
     // kernel-argument segment (the struct is the only argument, at offset 0) instead of a per-lane stack copy
     const DraftParams *p = (const DraftParams *)__builtin_amdgcn_kernarg_segment_ptr();
-    flow_steps<G, HD, CL>(*p, smem);
+    int vb = blockIdx.x, nvb = gridDim.x;
+    if (p->admit) {
+        const int admitted = flow_admit(*p, reinterpret_cast<int *>(smem));
+        if (admitted == kAdmitLeave) return;
+        if (admitted == kAdmitOne) vb = 0, nvb = 1;
+    }
+    flow_steps<G, HD, CL>(*p, smem, vb, nvb);
 }
 
 // Sequential acceptance up to the first mismatch and the draft-cache length after it (Sec. 2.3 "Verification phase").
@@ -385,11 +391,12 @@ bool config_ok(const mtp_config *c) {
 constexpr size_t kAlign = 256;
 constexpr int kMaxFusedGrid = kMaxHeadCands; // workgroups of the single-launch kernel (one per CU)
 constexpr size_t kFlowSmallBytes = 8 << 20;  // weights of a step that a quarter of the compute units read fast enough
+constexpr long long kAdmitTicks = 30000;     // 0.3 ms until one workgroup of such a call does it alone (flow_admit)
 constexpr int kFlowRoundBytes = 160 * 128;   // tokens x head dimension of one round of its attention (phase_attn, U = 5)
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
-    size_t x, qkv, attn, o, gu, dn, hhat, err, cand, rope_inv, attn_part, total;
+    size_t x, qkv, attn, o, gu, dn, hhat, err, admit, cand, rope_inv, attn_part, total;
     size_t xt, qkvt, attnt, ot, gut, dnt, candt, tagged_end; // tagged hand-over vectors of the barrier-free kernel
     // batched path (max_batch above kBatchMinSeq - 1 only)
     size_t act0, act1, ssq, part, part_floats, ticket, a_lo, attn_ticket, row_len, seq_list, list_ids, list_n, list_cands;
@@ -426,7 +433,8 @@ WsLayout ws_layout(const mtp_config &c) {
     l.gu = take(mb * (size_t)c.d_ffn * 2 * 4);
     l.dn = take(mb * d * 4);
     l.hhat = take(mb * d * 4);
-    l.err = take(4);
+    l.err = take(192); // (the admission words lie 128 bytes behind the error word)
+    l.admit = l.err + 128;
     l.cand = take((size_t)c.max_draft_steps * mb * kMaxFusedGrid * 8);
     l.rope_inv = take((size_t)c.head_dim / 2 * 8);
     l.attn_part = take(attn_part_floats(c) * 4);
@@ -479,6 +487,8 @@ struct mtp_handle {
     phase_kernel_t attn_fn;
     fused_kernel_t flow_fn;        // one sequence: all phases of all steps in one launch
     unsigned long long flow_tags;  // hand-over tags given to earlier calls of that kernel
+    unsigned admit_calls;          // calls of that kernel whose workgroups waited for all of them first
+    long long admit_ticks;         // the longest such wait
     size_t flow_lds_ok;            // largest LDS size for which a workgroup of that kernel was seen to fit a CU
     int mode;                    // 0: one launch per phase, 1: single launch for the whole call
     long long *trace;             // optional device buffer for phase time stamps
@@ -591,6 +601,8 @@ int32_t mtp_draft_init(mtp_handle **out, const mtp_config *cfg, const mtp_weight
     h->attn_fn = attn_kernel(cfg->n_q_heads / cfg->n_kv_heads, cfg->head_dim);
     h->flow_fn = flow_kernel(*cfg);
     h->flow_tags = 0;
+    h->admit_calls = 0;
+    h->admit_ticks = kAdmitTicks;
     h->flow_lds_ok = 0;
     h->mode = 2;
     h->trace = nullptr;
@@ -849,9 +861,9 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     // Its tags count calls on the host, so a call that is being captured into a HIP graph - whose replays would all
     // carry the tags of the captured call - takes one launch per phase instead (those kernels keep no state across
     // calls on the host).
-    // Heads with shorter reductions take a quarter of the units, where that is enough to read their weights: the process's
-    // four hardware queues can then run four such calls side by side, with every workgroup resident (256 wide, 4096 rows, three
-    // steps: 129 us with 64 workgroups, 128 with 256, 159 with a launch per phase).
+    // Heads with shorter reductions take a quarter of the units, where that is enough to read their weights (256 wide, 4096 rows,
+    // three steps: 129 us with 64 workgroups, 128 with 256, 159 with a launch per phase).  Their calls may overlap others, so
+    // their workgroups make sure that all of them are there before they wait for one another's results (flow_admit).
     const bool wide = p.d >= 512 && p.qd >= 512 && p.F >= 512;
     const size_t step_bytes = 2 * ((size_t)p.d * (2 * p.d + p.qkv_dim + p.qd + 3 * (size_t)p.F) + (size_t)p.n * p.d);
     const bool small = !wide && step_bytes <= kFlowSmallBytes;
@@ -869,7 +881,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         const int fgrid = small ? std::max(1, h->num_cus / 4) : std::min(h->num_cus, kMaxFusedGrid);
         size_t region = std::max(flow_gemv_region(p.d, p.qd, p.F), lds_attn);
         region = (region + 255) / 256 * 256;
-        const size_t lds_flow = region + flow_tail_bytes(p.d, fgrid);
+        const size_t lds_flow = region + std::max(flow_tail_bytes(p.d, fgrid), small ? flow_tail_bytes(p.d, 1) : 0);
         bool fits = lds_flow <= h->lds_limit;
         if (fits && lds_flow > h->flow_lds_ok) { // once per LDS size: a workgroup of this kernel fits a compute unit
             int per_cu = 0;
@@ -911,12 +923,19 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
                 h->flow_tags = 0;
             }
             p.tag_base = (unsigned)h->flow_tags;
+            if (small) {
+                unsigned *word = reinterpret_cast<unsigned *>(ws + l.admit);
+                p.admit = word + 8 * (h->admit_calls & 1);
+                p.admit_next = word + 8 * (~h->admit_calls & 1);
+                p.admit_ticks = h->admit_ticks;
+            }
             void *args[] = {(void *)&p};
             if (h->timing == 1) (void)hipEventRecord(h->ev[0], st);
             const bool launched = hipLaunchKernel((const void *)h->flow_fn, dim3(fgrid), dim3(kBlock), args,
                                                   (unsigned)lds_flow, st) == hipSuccess;
             if (launched) {
                 h->flow_tags += 8ull * (unsigned long long)K;
+                if (small) ++h->admit_calls;
                 if (h->timing == 1) {
                     (void)hipEventRecord(h->ev[1], st);
                     h->ev_recorded = true;
@@ -1363,6 +1382,13 @@ int32_t mtp_set_launch_mode(mtp_handle *h, int32_t mode) {
 size_t mtp_phase_trace_bytes(const mtp_config *cfg) {
     if (!config_ok(cfg)) return 0;
     return (size_t)cfg->max_draft_steps * kTraceSections * kTracePoints * kMaxFusedGrid * sizeof(long long);
+}
+
+int32_t mtp_set_admission_ticks(mtp_handle *h, int64_t ticks) {
+    if (!h) return MTP_ERR_NULL;
+    if (ticks < 0) return MTP_ERR_CONFIG;
+    h->admit_ticks = ticks;
+    return MTP_OK;
 }
 
 int32_t mtp_set_phase_trace(mtp_handle *h, void *device_buffer) {

@@ -44,6 +44,9 @@ struct DraftParams {
     int logit_stride;                // floats per (sequence, step) in logits_out: n, or the largest n of the lists
     int fused_gemv_bytes;     // single-launch kernel: bytes of LDS shared by the staged activations and the attention
     long long bar_timeout;    // wall-clock ticks a workgroup may wait for a hand-over before giving up
+    unsigned *admit, *admit_next; // single-launch kernel whose workgroups first wait for all of them (flow_admit): this call's
+                                  // word and the next one's; null: they do not
+    long long admit_ticks;        // the longest that may take
     long long *trace;         // optional wall-clock stamps (100 MHz) of every workgroup of the single-launch kernel
     int max_batch;
     // launch plan

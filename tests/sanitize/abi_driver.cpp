@@ -71,6 +71,7 @@ int main() {
     CHECK(mtp_set_timing(nullptr, 1) < 0);
     CHECK(mtp_set_launch_mode(nullptr, 0) < 0);
     CHECK(mtp_set_phase_trace(nullptr, nullptr) < 0);
+    CHECK(mtp_set_admission_ticks(nullptr, 1) < 0);
     CHECK(mtp_last_draft_ms(nullptr) < 0.f);
     CHECK(mtp_subset_build(nullptr, 16, 100, 10, ws, 1 << 20, out, out, nullptr, nullptr) < 0);
     CHECK(mtp_subset_build_static(nullptr, 16, 100, 10, out, out, nullptr, nullptr) < 0);

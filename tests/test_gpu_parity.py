@@ -420,6 +420,66 @@ def test_single_launch_short_rows(gpu, d, hq, hkv, hd, d_ffn, ctx, cap):
     eng.close()
 
 
+def narrow_engine(gpu, d, hq, hkv, hd, d_ffn, ctx, cap, seed):
+    """A one-sequence engine of a head with a reduction below 512, and its call on a stream (outputs on the device)."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    shape = synth.HeadShape(d, hq, hkv, hd, d_ffn, 2048)
+    wl = synth.Workload(f"narrow_{d}_{seed}", 130 + seed, shape, 1, 0, 0, (520,), 3, 0.5, zipf_subset=False)
+    act = synth.make_activations(wl, ctx=np.array([ctx], dtype=np.int32), capacity=cap)
+    eng = binding.DraftEngine(shape, synth.make_weights(wl), [synth.make_subsets(wl)[0]], 1, cap, 3)
+    hid, tok, kv = eng.to_device_bits(act["hidden_in"]), eng.to_device_i32(act["token_in"]), eng.to_device_i32(act["kv_len"])
+    k0, v0 = eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"])
+    torch.cuda.synchronize()
+
+    def call(stream=0):
+        kc, vc = k0.clone(), v0.clone()
+        out = eng.draft(3, 0, hid, tok, kc, vc, kv, want_logits=True, want_hidden=True, stream=stream)
+        return [out["draft"], out["logits"], out["hidden"], kc, vc]
+
+    return eng, call
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(256, 4, 2, 64, 688), (480, 8, 2, 64, 1280), (1024, 4, 4, 128, 264)])
+@pytest.mark.parametrize("ctx,cap", [(0, 64), (700, 768)])
+def test_narrow_single_launch_gives_the_same_bits_alone(gpu, d, hq, hkv, hd, d_ffn, ctx, cap):
+    """A narrow head's single launch whose workgroups are not all there in time is done by one of them: the same rows, splits
+    and sums, so the same bits; before and after calls of all workgroups (the two admission words take turns)."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    eng, call = narrow_engine(gpu, d, hq, hkv, hd, d_ffn, ctx, cap, 1)
+    want = call()
+    for ticks in (30000, 0, 0, 0, 30000, 1, 1, 30000, 0, 30000):
+        assert binding.mtp_set_admission_ticks(eng.handle, ticks) == 0
+        got = call()
+        torch.cuda.synchronize()
+        assert eng.poll_error() == 0
+        assert all(torch.equal(a, b) for a, b in zip(want, got)), ticks
+    assert binding.mtp_set_admission_ticks(eng.handle, -1) == -3
+    eng.close()
+
+
+def test_narrow_single_launches_overlap_each_other_and_a_wide_one(gpu):
+    """More calls in flight than the device has room for at a time, and one that wants every compute unit: nobody's wait
+    depends on another call's, and everybody's result is that of a call by itself."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    shapes = [(256, 4, 2, 64, 688), (480, 8, 2, 64, 1280), (1024, 4, 4, 128, 264), (256, 4, 2, 64, 688), (320, 4, 4, 128, 1024),
+              (256, 2, 1, 128, 512), (1024, 8, 8, 128, 1024)]  # (the last: no reduction below 512)
+    engines = [narrow_engine(gpu, *s, 300, 768, 2 + i) for i, s in enumerate(shapes)]
+    want = [call() for _, call in engines]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in engines]
+    got = []
+    for turn in range(4):
+        for (eng, call), st in zip(engines, streams):
+            with torch.cuda.stream(st):
+                got.append(call(st.cuda_stream))
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        assert all(torch.equal(a, b) for a, b in zip(want[i % len(engines)], g)), i
+    for eng, _ in engines:
+        assert eng.poll_error() == 0
+        eng.close()
+
+
 # ------------------------------------------------------------------------------------------ block of new positions
 def extend_inputs(shape, act, m_max, seed):
     """Position-major inputs of the multi-position first step: hidden states with the workload's spread, tokens."""
