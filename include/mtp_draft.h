@@ -292,7 +292,8 @@ int32_t mtp_stream_probe(const void *buffer, size_t bytes, void *out8, void *hip
 /*
  * Diagnostics for the single-launch kernel of one sequence: device_buffer (device, int64, mtp_phase_trace_bytes(cfg)
  * bytes, or NULL to stop) receives 100 MHz wall-clock stamps of EVERY workgroup, laid out
- * [step][section 0..7][point 0..3][workgroup 0..W-1] with W = the device's compute-unit count: sections are the phases
+ * [step][section 0..7][point 0..3][workgroup 0..W-1] with W = the device's compute-unit count (a launch of fewer
+ * workgroups leaves the places of the others alone): sections are the phases
  * of a draft step in order (0 projection, 1 q/k/v, 2 attention, 3 output projection, 4 gate/up, 5 down, 6 output head,
  * 7 unused); points: 0 the section's first weights have been requested, 1 its input is available (the hand-over from
  * the phase before has completed), 2 the input is staged in LDS, 3 its results are stored.

@@ -424,7 +424,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
 
     auto stamp = [&](int step, int sec, int pt) {
         if (p.trace && threadIdx.x == 0)
-            p.trace[(((size_t)step * kTraceSections + sec) * kTracePoints + pt) * nvb + vb] = wall_clock64();
+            p.trace[(((size_t)step * kTraceSections + sec) * kTracePoints + pt) * p.trace_wgs + vb] = wall_clock64();
     };
     if (vb == 0 && threadIdx.x == 0 && seq_dead(p, 0)) atomicOr(p.err, kErrKvOverflow);
 

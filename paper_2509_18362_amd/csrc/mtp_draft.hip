@@ -760,6 +760,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     p.candt = reinterpret_cast<unsigned long long *>(ws + l.candt);
     p.bar_timeout = 200000000ll; // 2 s of the 100 MHz wall clock
     p.trace = h->trace;
+    p.trace_wgs = std::min(h->num_cus, kMaxFusedGrid);
     p.max_batch = c.max_batch;
     p.seq_lo = 0;
     p.seq_hi = B;

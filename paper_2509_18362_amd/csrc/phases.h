@@ -48,6 +48,7 @@ struct DraftParams {
                                   // word and the next one's; null: they do not
     long long admit_ticks;        // the longest that may take
     long long *trace;         // optional wall-clock stamps (100 MHz) of every workgroup of the single-launch kernel
+    int trace_wgs;            // workgroups a section has room for in it (the device's compute units)
     int max_batch;
     // launch plan
     int split_tokens, max_splits; // attention: tokens per split, splits per (sequence, KV head)

@@ -457,6 +457,21 @@ def test_narrow_single_launch_gives_the_same_bits_alone(gpu, d, hq, hkv, hd, d_f
     eng.close()
 
 
+def test_phase_trace_of_a_launch_on_a_quarter_of_the_units(gpu):
+    """Stamps lie [step][section][point][compute units], also where the launch has fewer workgroups."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    eng, call = narrow_engine(gpu, 256, 4, 2, 64, 688, 100, 192, 9)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    buf = torch.zeros(binding.mtp_phase_trace_bytes(eng.cfg) // 8, dtype=torch.int64, device="cuda:0")
+    assert binding.mtp_set_phase_trace(eng.handle, buf) == 0
+    call()
+    torch.cuda.synchronize()
+    n = 3 * len(binding.TRACE_SECTIONS) * len(binding.TRACE_POINTS)
+    t = buf[:n * cus].view(n, cus).cpu()
+    assert (t[:, :cus // 4] > 0).all() and (t[:, cus // 4:] == 0).all() and (buf[n * cus:] == 0).all().item()
+    eng.close()
+
+
 def test_narrow_single_launches_overlap_each_other_and_a_wide_one(gpu):
     """More calls in flight than the device has room for at a time, and one that wants every compute unit: nobody's wait
     depends on another call's, and everybody's result is that of a call by itself."""
