@@ -260,8 +260,9 @@ float mtp_last_draft_ms(mtp_handle *h);
  *               per step, and one launch more after a matrix phase whose reduction is split over workgroups and added
  *               up apart.  Matrices of 2 GiB or more: as mode 3.
  *   1           one sequence whose reduction lengths (d_model, n_q_heads * head_dim, d_ffn) are all at least 512, or that has a
- *               shorter one and reads at most 8 MiB of weights per step: one launch runs all phases of all K steps, on one
- *               workgroup per compute unit in the first case, on a quarter of the units in the second; its workgroups hand
+ *               shorter one and reads at most 5 MiB of weights per step, with at most 8 MiB of keys and values up to
+ *               kv_capacity: one launch runs all phases of all K steps, on one workgroup per compute unit in the first case, on
+ *               a quarter of the units in the second; its workgroups hand
  *               their results over element by element (every element carries a tag naming the call, step and phase that
  *               produced it, consumers poll for it), there are no grid barriers.  The workgroups of the first kind wait for one
  *               another, so all of them must find room on the device: do not overlap it with other kernels (other streams,

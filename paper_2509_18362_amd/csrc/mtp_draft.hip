@@ -390,7 +390,6 @@ bool config_ok(const mtp_config *c) {
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxFusedGrid = kMaxHeadCands; // workgroups of the single-launch kernel (one per CU)
-constexpr size_t kFlowSmallBytes = 8 << 20;  // weights of a step that a quarter of the compute units read fast enough
 constexpr long long kAdmitTicks = 30000;     // 0.3 ms until one workgroup of such a call does it alone (flow_admit)
 constexpr int kFlowRoundBytes = 160 * 128;   // tokens x head dimension of one round of its attention (phase_attn, U = 5)
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -867,7 +866,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     // their workgroups make sure that all of them are there before they wait for one another's results (flow_admit).
     const bool wide = p.d >= 512 && p.qd >= 512 && p.F >= 512;
     const size_t step_bytes = 2 * ((size_t)p.d * (2 * p.d + p.qkv_dim + p.qd + 3 * (size_t)p.F) + (size_t)p.n * p.d);
-    const bool small = !wide && step_bytes <= kFlowSmallBytes;
+    const bool small = !wide && flow_narrow_serves(step_bytes, (size_t)4 * p.kvd * p.cap);
     const bool rows = B == 1 && (wide || small);
     bool capturing = false;
     if (st != nullptr) { // (the legacy default stream cannot be captured, and asking about it disturbs other captures)

@@ -1,5 +1,5 @@
-// Which tiles, and how many reduction parts, a tiled matrix product (rows_gemm.h) runs with.  Host code without HIP: the
-// rules can be compiled and checked on their own.
+// Rules that choose a call's kernels: which tiles, and how many reduction parts, a tiled matrix product (rows_gemm.h) runs with,
+// and where one sequence takes a single launch.  Host code without HIP: the rules can be compiled and checked on their own.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -104,6 +104,17 @@ inline bool rows_gemm_serves(const RowsCall &c, int cus) {
     if (wide > kMaxHeadCands) return false;
     const int slots = (wide + cus - 1) / cus * cus;
     return wide <= cus || (small ? c.K <= 512 || 4 * wide >= 3 * slots : 10 * wide >= 9 * slots);
+}
+
+// One sequence of a head with a reduction below 512: the single launch on a quarter of the compute units (flow.h), or one launch
+// per phase on all of them.  step_bytes: weights of a step, kv_bytes: keys and values up to the capacity (the lengths are on the
+// device).  What a launch per phase loses to its gaps a quarter of the units loses to reading more.  Three steps, us, single launch
+// / launch per phase: 2.6 MiB of weights 131 / 159, 3.8 146-158 / 152-161, 4.6 161 / 169, 5.3 157-166 / 156-164, 5.8 165-176 /
+// 160-168, 7.8 175-181 / 165-169; with 3.8 MiB of weights and 8 MiB of keys and values 166 / 174, 16 MiB 180 / 190 or (4.5 MiB,
+// 16 query heads) 194 / 188, 32 MiB 344 / 212.
+constexpr size_t kFlowNarrowBytes = 5 << 20, kFlowNarrowKvBytes = 8 << 20;
+inline bool flow_narrow_serves(size_t step_bytes, size_t kv_bytes) {
+    return step_bytes <= kFlowNarrowBytes && kv_bytes <= kFlowNarrowKvBytes;
 }
 
 } // namespace mtp

@@ -439,7 +439,8 @@ def narrow_engine(gpu, d, hq, hkv, hd, d_ffn, ctx, cap, seed):
     return eng, call
 
 
-@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(256, 4, 2, 64, 688), (480, 8, 2, 64, 1280), (1024, 4, 4, 128, 264)])
+@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(256, 4, 2, 64, 688), (480, 4, 1, 64, 776), (256, 16, 4, 128, 256),
+                                               (256, 40, 10, 64, 256)])  # (chunks of 2, 2, 4 and 8 KiB)
 @pytest.mark.parametrize("ctx,cap", [(0, 64), (700, 768)])
 def test_narrow_single_launch_gives_the_same_bits_alone(gpu, d, hq, hkv, hd, d_ffn, ctx, cap):
     """A narrow head's single launch whose workgroups are not all there in time is done by one of them: the same rows, splits
@@ -476,7 +477,7 @@ def test_narrow_single_launches_overlap_each_other_and_a_wide_one(gpu):
     """More calls in flight than the device has room for at a time, and one that wants every compute unit: nobody's wait
     depends on another call's, and everybody's result is that of a call by itself."""
     torch, binding = gpu["torch"], gpu["binding"]
-    shapes = [(256, 4, 2, 64, 688), (480, 8, 2, 64, 1280), (1024, 4, 4, 128, 264), (256, 4, 2, 64, 688), (320, 4, 4, 128, 1024),
+    shapes = [(256, 4, 2, 64, 688), (480, 4, 1, 64, 776), (256, 16, 4, 128, 256), (256, 4, 2, 64, 688), (320, 4, 4, 128, 1024),
               (256, 2, 1, 128, 512), (1024, 8, 8, 128, 1024)]  # (the last: no reduction below 512)
     engines = [narrow_engine(gpu, *s, 300, 768, 2 + i) for i, s in enumerate(shapes)]
     want = [call() for _, call in engines]

@@ -12,10 +12,16 @@ PART_FLOATS = 16384 * 4 * 256  # the smallest room for partial sums a workspace 
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def driver(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("plan") / "rows_plan")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(ROOT, "tests", "plan", "rows_plan_driver.cpp"),
                     "-o", exe], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def plan(driver):
+    exe = driver
 
     def ask(calls):
         lines = "\n".join("%d %d %d %d %d %d %d" % (c["K"], -(-c["n"] // 16) * 16, c["rows"], c.get("head", 0),
@@ -89,3 +95,22 @@ def test_tiles_of_the_body_phases_that_run_on_the_gpu(plan, d, d_ffn, rows, tile
 def test_every_tile_has_a_gpu_test():
     ran = {t[:2] for *_, t in HEAD_TILES} | {t[:2] for *_, ts in BODY_TILES for t in ts}
     assert ran == {(256, 256), (128, 512), (128, 384), (64, 256), (64, 128), (32, 128), (16, 128)}
+
+
+# d_model, query heads, KV heads, head dimension, d_ffn, rows of the output head, capacity: three steps of one sequence were slower
+# on a quarter of the units than with a launch per phase (False), or faster (True)
+NARROW = [
+    (256, 4, 2, 64, 688, 1024, 192, True), (256, 4, 2, 64, 688, 4096, 16384, True), (256, 4, 4, 64, 688, 4096, 1024, True),
+    (256, 4, 2, 64, 688, 6144, 1024, True), (384, 3, 3, 128, 1024, 1024, 384, True),
+    (256, 4, 4, 64, 688, 8192, 128, False), (320, 5, 5, 64, 864, 4096, 1024, False), (480, 8, 2, 64, 1280, 3072, 192, False),
+    (256, 16, 4, 64, 688, 1024, 32832, False), (256, 16, 4, 64, 688, 4096, 16448, False),
+    (256, 16, 16, 64, 688, 1024, 16448, False), (320, 5, 5, 64, 864, 1024, 32832, False),
+]
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn,n,cap,single", NARROW)
+def test_narrow_heads_take_the_single_launch_where_it_is_ahead(driver, d, hq, hkv, hd, d_ffn, n, cap, single):
+    """The rule against both sides' times: by the weights of a step and the keys and values that a context can grow to."""
+    step = 2 * (d * (2 * d + (hq + 2 * hkv) * hd + hq * hd + 3 * d_ffn) + n * d)
+    out = subprocess.run([driver, "narrow"], input=f"{step} {4 * hkv * hd * cap}", capture_output=True, text=True, check=True)
+    assert out.stdout.split() == [str(int(single))], (step, 4 * hkv * hd * cap)
