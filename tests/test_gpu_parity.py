@@ -702,9 +702,6 @@ FEW_ROWS_SHAPES = [
 @pytest.mark.parametrize("rows", [2, 8, 9, 16])
 def test_few_rows_every_tile_count(gpu, d, hq, hkv, d_ffn, vocab, rows):
     """2 to 16 rows, full vocabulary and a list of odd size: hi and lo halves in one operand (up to 8 rows) and in two."""
-    if (d, rows) == (256, 2) and vocab == 2111:
-        pytest.skip("this case faulted in a build whose host side left workspace pointers unset (every call of two or more rows "
-                    "did); the cause is mended, the case has not been run since")
     shape = synth.HeadShape(d, hq, hkv, 128, d_ffn, vocab)
     wl = synth.Workload(f"few_{d}_{d_ffn}", 99, shape, 1, 0, 0, (vocab // 2 + 1,), 1, 0.5, zipf_subset=False)
     w = synth.make_weights(wl)
