@@ -13,12 +13,12 @@ size_t bgemv_lds_bytes(int rows_per_group);
 // raises the dynamic-LDS limit of the batched and matrix-core attention kernels that calls of a handle with this configuration
 // can take; false if a call failed
 bool batch_allow_lds(size_t lds_limit, const mtp_config &c);
+// the kernel of a matrix phase (BG_* index) over the rows p.seq_lo .. p.seq_hi - 1 (rows_plan.h)
+RowsRoute rows_route(int phase, const DraftParams &p, bool all_few, int cus);
 // one batched matrix phase (BG_* index) for the sequences [p.b0, p.b0 + p.nb)
 void launch_bgemv(int phase, const DraftParams &p, int step, int grid, size_t lds, hipStream_t st);
 // A matrix phase of the rows [p.b0, p.b0 + p.nb), at most sixteen (few_rows.h), on few_groups workgroups; the output head
 // leaves as many candidates per row.
-constexpr int kFewRows = 16, kFewPacked = 8; // (up to eight rows: hi and lo halves in one operand)
-constexpr int kFewNarrow = 2048;             // 9..16 rows: widths up to which tiles are faster
 int few_groups(int phase, const DraftParams &p, int cus);
 bool few_allow_lds(size_t lds_limit);
 void launch_few(int phase, const DraftParams &p, int step, int cus, hipStream_t st);
@@ -27,8 +27,7 @@ void launch_bprep(const DraftParams &p, int step, hipStream_t st);
 
 // A matrix phase (BG_* index) over the rows p.seq_lo .. p.seq_hi - 1 as one tiled matrix product (rows_gemm.h).  The output
 // head leaves rows_head_cands candidates per row, or none where the caller wants logits only.  part_floats: room of the
-// partial buffer.  rows_gemm_serves: it can (the reduction length is a whole number of steps) and it is the faster kernel.
-bool rows_gemm_serves(int phase, const DraftParams &p, int cus);
+// partial buffer.
 int rows_head_cands(const DraftParams &p, int cus, size_t part_floats);
 void launch_rows_gemm(int phase, bool logits_only, const DraftParams &p, int step, int cus, size_t part_floats,
                       hipStream_t st);

@@ -244,7 +244,7 @@ RowsCall rows_call(int phase, const DraftParams &p) {
 }
 } // namespace
 
-bool rows_gemm_serves(int phase, const DraftParams &p, int cus) { return rows_gemm_serves(rows_call(phase, p), cus); }
+RowsRoute rows_route(int phase, const DraftParams &p, bool all_few, int cus) { return rows_route(rows_call(phase, p), all_few, cus); }
 int rows_head_cands(const DraftParams &p, int cus, size_t part_floats) {
     const RowsCall c = rows_call(BG_LMHEAD, p);
     const RowsPlan pl = rows_plan(c, cus, part_floats);

@@ -1017,13 +1017,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         p.ssq = reinterpret_cast<float *>(ws + l.ssq);
         p.part = reinterpret_cast<float *>(ws + l.part);
         p.ticket = reinterpret_cast<int *>(ws + l.ticket);
-        // Rows up to which the phases take the few-rows kernel (few_rows.h).  With the activations in operand order it serves every
-        // phase.  Two steps against the kernels before it (batched core, tiles), us: 4096 wide 2 / 8 / 16 rows 336 / 355 / 365
-        // -> 285 / 310 / 345 (16853-row head), 751 / 773 / 792 -> 658 / 690 / 737 (full); 2048 wide 181 / 200 / 209 -> 168 /
-        // 190 / 218.  From nine rows on every workgroup reads twice its weights in activations: narrow matrices (few tiles, so
-        // few workgroups) are then faster in tiles, split over workgroups, and what the tiles do not serve takes the
-        // few-rows kernel with row-major activations.
-        const bool few = B <= kFewPacked || (B <= kFewRows && c.d_model > kFewNarrow);
+        const bool few = rows_all_few(B, c.d_model); // every phase on few_rows.h, activations in operand order
         p.act_bytes = (int)std::min<size_t>(4 * l.a_lo, INT32_MAX);
         if (few) {
             const bool packed = B <= kFewPacked;
@@ -1033,12 +1027,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         // Every other phase: tiled matrix products over all rows (rows_gemm.h), three steps at a 32768-row head 648 / 672 / 807 /
         // 875 us at 17 / 32 / 48 / 64 sequences against 763 / 782 / 997 / 1042 on the batched core; a block of 66 / 128 / 256 / 512
         // positions 324 / 365 / 550 / 840 us against 523 / 580 / 946 / 1434 in passes of 64.
-        enum { ON_FEW, ON_TILES, ON_CORE };
-        auto route = [&](int ph, const DraftParams &q) {
-            const bool up_to_16 = q.seq_hi - q.seq_lo <= kFewRows;
-            if (few || (up_to_16 && !rows_gemm_serves(ph, q, grid))) return ON_FEW;
-            return rows_gemm_serves(ph, q, grid) ? ON_TILES : ON_CORE;
-        };
+        auto route = [&](int ph, const DraftParams &q) { return rows_route(ph, q, few, grid); };
         // The batched core (more than 16 rows only): units of 16-row tiles over row groups, a phase with fewer tiles than a full
         // block of 64/NA per workgroup splits its reduction over KP workgroups, each keeping at least four double steps.  One plan
         // per call: passes share it (a last, smaller pass runs a little off its optimum).
@@ -1055,13 +1044,13 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             p.bg_sep[ph] = (kp >= 2 && ph == BG_DOWN) ? 1 : 0;
             lds_bg[ph] = bgemv_lds_bytes(((units + rg - 1) / rg) * 16);
         };
-        if (route(BG_DOWN, p) == ON_CORE) plan(BG_DOWN, p.d / 16, p.F, B);
+        if (route(BG_DOWN, p) == kOnCore) plan(BG_DOWN, p.d / 16, p.F, B);
         const bool logits_only = ext && ext->logits_only && logits_out;
         // The output head: one plan per id list (one list: one plan), for the sequences that share the list
         struct HeadPlan {
             int rg, kp;
             size_t lds;
-            int on;
+            RowsRoute on;
         } head_plan[kMaxListGroups];
         const int n_heads = std::max(1, groups.count);
         int max_cands = 0;
@@ -1080,9 +1069,9 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             HeadPlan &hp = head_plan[g];
             hp.on = route(BG_LMHEAD, q);
             int cands = 0;
-            if (hp.on == ON_FEW) {
+            if (hp.on == kOnFew) {
                 cands = few_groups(BG_LMHEAD, q, grid);
-            } else if (hp.on == ON_TILES) {
+            } else if (hp.on == kOnTiles) {
                 cands = rows_head_cands(q, grid, l.part_floats);
             } else {
                 plan(BG_LMHEAD, (q.n + 15) / 16, p.d, q.seq_hi - q.seq_lo);
@@ -1104,14 +1093,14 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             const int runs = ph == BG_LMHEAD ? n_heads : 1; // the output head: once per id list
             for (int g = 0; g < runs; ++g) {
                 DraftParams q = ph == BG_LMHEAD ? head_of(g) : p;
-                const int on = ph == BG_LMHEAD ? head_plan[g].on : route(ph, q);
-                if (on == ON_FEW) {
+                const RowsRoute on = ph == BG_LMHEAD ? head_plan[g].on : route(ph, q);
+                if (on == kOnFew) {
                     q.b0 = q.seq_lo;
                     q.nb = q.seq_hi - q.seq_lo;
                     launch_few(ph, q, step, grid, st);
                     continue;
                 }
-                if (on == ON_TILES) {
+                if (on == kOnTiles) {
                     launch_rows_gemm(ph, logits_only && ph == BG_LMHEAD, q, step, grid, l.part_floats, st);
                     continue;
                 }

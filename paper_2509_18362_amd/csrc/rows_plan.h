@@ -1,5 +1,6 @@
-// Rules that choose a call's kernels: which tiles, and how many reduction parts, a tiled matrix product (rows_gemm.h) runs with,
-// and where one sequence takes a single launch.  Host code without HIP: the rules can be compiled and checked on their own.
+// Rules that choose a call's kernels: which kernel a matrix phase of several rows takes, which tiles, and how many reduction
+// parts, a tiled matrix product (rows_gemm.h) runs with, and where one sequence takes a single launch.  Host code without HIP:
+// the rules can be compiled and checked on their own.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -31,7 +32,7 @@ constexpr RowsTileInfo kRowsTile[kRowsTiles] = {
     {128, 384, 32, 3 * (2 * 128 + 384) * 64, 1.0}, {64, 256, 64, 3 * (2 * 64 + 256) * 128, 1.3},
     {64, 128, 64, 4 * (2 * 64 + 128) * 128, 0.8},  {32, 128, 64, 6 * (2 * 32 + 128) * 128, 0.55},
     {16, 128, 64, 7 * (2 * 16 + 128) * 128, 0.52}};
-constexpr int kRowsFew = 16;              // rows up to which the batched core's plain kernel is an alternative
+constexpr int kRowsFew = 16;              // rows up to which few_rows.h is an alternative
 constexpr int kRowsHalf = 4;               // the tilings from this one on take a last step that is half a one
 constexpr int kRowsMinSteps = 8;           // reduction steps of 32 a part keeps at least
 constexpr double kRowsFixedUs = 6.0;       // of a workgroup besides its steps
@@ -104,6 +105,29 @@ inline bool rows_gemm_serves(const RowsCall &c, int cus) {
     if (wide > kMaxHeadCands) return false;
     const int slots = (wide + cus - 1) / cus * cus;
     return wide <= cus || (small ? c.K <= 512 || 4 * wide >= 3 * slots : 10 * wide >= 9 * slots);
+}
+
+// Kernels of the matrix phases of a call of `rows` rows (sequences, or positions of a block) of a head d wide.
+enum RowsRoute : int { kOnFew, kOnTiles, kOnCore };
+constexpr int kFewRows = 16, kFewPacked = 8; // few_rows.h: rows of a launch at most; up to eight, hi and lo halves in one operand
+constexpr int kFewFrom = 384;                // 2..8 rows: widths from which on all phases take it
+constexpr int kFewNarrow = 2048;             // 9..16 rows: widths up to which tiles are faster
+// The whole call on few_rows.h, its activations in operand order.  Two steps against the kernels before it (batched core, tiles),
+// us: 4096 wide 2 / 8 / 16 rows 336 / 355 / 365 -> 285 / 310 / 345 (16853-row head), 751 / 773 / 792 -> 658 / 690 / 737 (full); 2048
+// wide 181 / 200 / 209 -> 168 / 190 / 218.  From nine rows on every workgroup reads twice its weights in activations: narrow matrices
+// (few tiles, so few workgroups) are then faster in tiles, split over workgroups.  Below 384 wide a phase is one or two chunks of
+// few_rows.h and the tiles are ahead: 256 wide, 2 / 8 rows 106 / 110 there and 102 / 107 in tiles (1024-row head), 109 / 115 and
+// 103 / 109 (32768 rows), 122 / 128 and 113 / 120 (65536); 320 wide 113 / 120 and 108 / 116 (32768), within 1 % elsewhere; 384
+// wide 106 / 113 and 108 / 116 (1024), 115 / 123 and 113 / 124 (32768).
+inline bool rows_all_few(int rows, int d) {
+    return rows <= kFewPacked ? d >= kFewFrom : rows <= kFewRows && d > kFewNarrow;
+}
+// A phase of the call (the output head: of the rows that share an id list).  What the tiles do not serve, or not as fast, takes
+// few_rows.h with row-major activations up to sixteen rows, the batched core above.
+inline RowsRoute rows_route(const RowsCall &c, bool all_few, int cus) {
+    if (all_few) return kOnFew;
+    if (rows_gemm_serves(c, cus)) return kOnTiles;
+    return c.rows <= kFewRows ? kOnFew : kOnCore;
 }
 
 // One sequence of a head with a reduction below 512: the single launch on a quarter of the compute units (flow.h), or one launch

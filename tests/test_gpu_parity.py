@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 from paper_2509_18362_amd import synth
-from plan_cases import BODY_TILES, HEAD_TILES
+from plan_cases import BODY_TILES, HEAD_TILES, LIST_GROUPS
 
 pytestmark = pytest.mark.gpu
 
@@ -583,11 +583,11 @@ def test_tiny_extend_block_of_positions(gpu, tiny, ctx, ext, m_max):
 
 
 @pytest.mark.parametrize("d_ffn,subset", [(1056, 0), (1064, -1)])
-@pytest.mark.parametrize("rows", [5, 16, 17, 33, 64, 65, 129, 257, 400])
+@pytest.mark.parametrize("rows", [5, 9, 16, 17, 33, 64, 65, 129, 257, 400])
 def test_many_rows_tiled_matrix_products(gpu, d_ffn, subset, rows):
-    """Every phase as a tiled matrix product (small reductions take it at any number of rows), here in the tiles of 16 rows
-    and, from 257 rows on, of 32 (gate/up and the head): one block to twenty-five, full and ragged last ones.  The down
-    projection of 1056 ends in half a step, that of 1064 in less than that (the batched core then); gate/up rows and a
+    """Every phase as a tiled matrix product (small reductions take it from nine rows on; five: few_rows.h), here in the tiles of 16
+    rows and, from 257 rows on, of 32 (gate/up and the head): one block to twenty-five, full and ragged last ones.  The down
+    projection of 1056 ends in half a step, that of 1064 in less than that (few_rows.h or the batched core then); gate/up rows and a
     vocabulary that end inside a tile of sixteen; the list and the full head; the candidates of a row from several
     blocks of weight rows.  The other tiles: the two tests below."""
     shape = synth.HeadShape(512, 4, 2, 128, d_ffn, 2111)
@@ -602,7 +602,7 @@ def test_many_rows_tiled_matrix_products(gpu, d_ffn, subset, rows):
     check_extend(ref, res, caches, act, ext_len)
 
 
-@pytest.mark.parametrize("d,rows,n", [(1024, 5, 3584), (1024, 20, 8192), (1024, 64, 3584), (2048, 20, 8192),
+@pytest.mark.parametrize("d,rows,n", [(1024, 5, 3584), (1024, 12, 3584), (2048, 16, 8192), (1024, 20, 8192), (1024, 64, 3584), (2048, 20, 8192),
                                       (2048, 100, 8192), (2048, 192, 8192), (4096, 5, 3584), (4096, 20, 8192),
                                       (4096, 40, 8192), (4096, 100, 8192), (4096, 192, 3584)])
 def test_tiled_products_add_up_as_exactly_as_the_batched_core(gpu, d, rows, n):
@@ -643,10 +643,10 @@ def test_tiled_products_add_up_as_exactly_as_the_batched_core(gpu, d, rows, n):
     assert err <= 1.9e-7, err
 
 
-@pytest.mark.parametrize("rows", [5, 17, 33, 64, 100, 200])
+@pytest.mark.parametrize("rows", [5, 12, 17, 33, 64, 100, 200])
 def test_widths_that_end_inside_a_reduction_step(gpu, rows):
-    """d = 544 and d_ffn = 1056: every reduction but the output projection's is 32 modulo 64, the tiles for few rows walk
-    it in steps of 64 (the weights behind a row's end are the next row's, the activations the next phase's)."""
+    """d = 544 and d_ffn = 1056: every reduction but the output projection's is 32 modulo 64, the tiles for few rows (from nine on
+    here) walk it in steps of 64 (the weights behind a row's end are the next row's, the activations the next phase's)."""
     shape = synth.HeadShape(544, 4, 2, 128, 1056, 2111)
     wl = synth.Workload("width_544", 96, shape, 1, 0, 0, (517,), 1, 0.5, zipf_subset=False)
     w = synth.make_weights(wl)
@@ -682,17 +682,22 @@ def test_drafts_from_every_tile_of_the_output_head(gpu, d, vocab, rows):
 
 @pytest.mark.parametrize("d,d_ffn,rows", [c[:3] for c in BODY_TILES])
 def test_body_phases_in_the_larger_tiles(gpu, d, d_ffn, rows):
-    """The projections, gate/up and down in tiles of 32 to 256 rows, whole and split (their tiles: test_rows_plan.py)."""
+    """The projections, gate/up and down in tiles of 16 to 256 rows, whole and split (their tiles: test_rows_plan.py)."""
     run_block_of_one_sequence(gpu, synth.HeadShape(d, d // 128, d // 256, 128, d_ffn, 2111), rows, 500 + rows)
 
 
 # d_model, query / KV heads of 128, d_ffn, vocabulary: weight tiles per workgroup of the phases (256 workgroups at most)
 FEW_ROWS_SHAPES = [
-    (256, 2, 1, 264, 2111),      # one chunk of the reduction and less (264 = 256 + 8), idle waves, one tile
-    (288, 4, 1, 1000, 8000),     # reductions that end inside a chunk; head: two tiles
+    (384, 2, 1, 264, 2111),      # two chunks of the reduction (264 = 256 + 8) to three, idle waves, one tile
+    (416, 2, 2, 1000, 8000),     # reductions that end inside a chunk; head: two tiles
+    (384, 4, 4, 8200, 24000),    # gate/up: three pairs (six tiles); head: six
+    (384, 2, 2, 16400, 70000),   # gate/up: five pairs (two groups); head: eighteen tiles, three groups, the last ragged
+    # narrower: the down projection (reductions that are no multiple of 32) with row-major activations, the rest in tiles
+    (256, 2, 1, 264, 2111),
+    (288, 4, 1, 1000, 8000),
     (544, 4, 2, 4104, 16000),    # gate/up: two pairs in one workgroup, one in the others; head: four tiles
-    (256, 4, 4, 8200, 24000),    # gate/up: three pairs (six tiles); head: six
-    (256, 2, 2, 16400, 70000),   # gate/up: five pairs (two groups); head: eighteen tiles, three groups, the last ragged
+    (256, 4, 4, 8200, 24000),
+    (256, 2, 2, 16400, 70000),
     (2304, 4, 1, 1032, 33000),   # 9..16 rows in operand order; head: nine tiles
     (4128, 33, 33, 264, 2111),   # projections: two tiles; q/k/v: four
 ]
@@ -723,9 +728,10 @@ def huge_vocab():
     return wl, synth.make_weights(wl)
 
 
-@pytest.mark.parametrize("rows", [20, 40])
+@pytest.mark.parametrize("rows", [3, 16, 20, 40])
 def test_heads_beyond_the_tiles_candidates_stay_on_the_batched_core(gpu, huge_vocab, rows):
-    """Two and four sequence tiles of the core whose waves split the weight tiles."""
+    """Two and four sequence tiles of the core whose waves split the weight tiles; up to sixteen rows few_rows.h, with row-major
+    activations."""
     wl, w = huge_vocab
     act = synth.make_activations(wl, ctx=np.array([9], dtype=np.int32), capacity=64)
     hid, tok = extend_inputs(wl.shape, act, rows, 600 + rows)
@@ -908,24 +914,11 @@ def test_tiny_extend_then_continue(gpu, tiny):
 
 
 # ------------------------------------------------------------------------------------------ one id list per sequence
-@pytest.mark.parametrize("ctx,seq_subset", [
-    ([100, 0, 64], [0, 1, -1]),                                   # row-streaming phases, three lists
-    ([10, 20, 150, 64], [1, 1, 0, 0]),
-    ([0, 1, 63, 64, 150, 7, 99], [0, 0, 0, 1, 1, -1, -1]),        # batched phases
-    (list(range(3, 123, 6)), [2] * 9 + [0] * 6 + [1] * 5),        # twenty sequences, two sequence tiles
-    ([(7 * i) % 150 for i in range(270)], [1] * 100 + [-1] * 90 + [0] * 80),  # 270: tiled body phases, passes per list
-])
-def test_tiny_one_list_per_sequence(gpu, tiny, ctx, seq_subset):
-    """Several id lists in one batch (several languages): every sequence against the oracle run with its own list
-    - logits over its own rows, drafts mapped through its own list, caches - K = 3 with the oracle's drafts forced."""
+def check_lists(gpu, shape, w, lists, act, seq_subset, K):
+    """A call with one list per sequence against the oracle run sequence by sequence, with its drafts forced.  Returns the engine."""
     torch, Oracle, binding = gpu["torch"], gpu["Oracle"], gpu["binding"]
-    shape, K = tiny["shape"], 3
-    rng = np.random.default_rng(11)
-    lists = [tiny["ids"], np.sort(rng.choice(shape.vocab_size, 300, replace=False)).astype(np.int32),
-             np.sort(rng.choice(shape.vocab_size, 37, replace=False)).astype(np.int32)]
-    act = synth.make_activations(tiny["wl"], ctx=np.array(ctx, dtype=np.int32), capacity=192)
-    B = len(ctx)
-    orc = Oracle(shape, tiny["w"], 192, "f32")
+    B, cap = len(seq_subset), act["kv_capacity"]
+    orc = Oracle(shape, w, cap, "f32")
     refs, okc, ovc = [], act["k_cache"].copy(), act["v_cache"].copy()
     forced = np.zeros((B, K - 1), np.int32)
     for b in range(B):
@@ -934,7 +927,7 @@ def test_tiny_one_list_per_sequence(gpu, tiny, ctx, seq_subset):
                       act["kv_len"][b:b + 1], ids)
         refs.append(r)
         forced[b] = r["draft"][0, :K - 1]
-    eng = binding.DraftEngine(shape, tiny["w"], lists, B, 192, K)
+    eng = binding.DraftEngine(shape, w, lists, B, cap, K)
     dkc, dvc = eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"])
     out = eng.draft_lists(K, seq_subset, eng.to_device_bits(act["hidden_in"]), eng.to_device_i32(act["token_in"]),
                           dkc, dvc, eng.to_device_i32(act["kv_len"]), forced=eng.to_device_i32(forced),
@@ -956,6 +949,28 @@ def test_tiny_one_list_per_sequence(gpu, tiny, ctx, seq_subset):
         assert appended_entries_close(kc[b][:, L:L + K], okc[b][:, L:L + K], recursive_from=1)
         assert np.array_equal(kc[b][:, :L], okc[b][:, :L])
     assert some_clear
+    return eng
+
+
+@pytest.mark.parametrize("ctx,seq_subset", [
+    ([100, 0, 64], [0, 1, -1]),                                   # row-streaming phases, three lists
+    ([10, 20, 150, 64], [1, 1, 0, 0]),
+    ([0, 1, 63, 64, 150, 7, 99], [0, 0, 0, 1, 1, -1, -1]),        # batched phases
+    (list(range(3, 123, 6)), [2] * 9 + [0] * 6 + [1] * 5),        # twenty sequences, two sequence tiles
+    ([(7 * i) % 150 for i in range(270)], [1] * 100 + [-1] * 90 + [0] * 80),  # 270: tiled body phases, passes per list
+])
+def test_tiny_one_list_per_sequence(gpu, tiny, ctx, seq_subset):
+    """Several id lists in one batch (several languages): every sequence against the oracle run with its own list
+    - logits over its own rows, drafts mapped through its own list, caches - K = 3 with the oracle's drafts forced."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    shape, K = tiny["shape"], 3
+    rng = np.random.default_rng(11)
+    lists = [tiny["ids"], np.sort(rng.choice(shape.vocab_size, 300, replace=False)).astype(np.int32),
+             np.sort(rng.choice(shape.vocab_size, 37, replace=False)).astype(np.int32)]
+    act = synth.make_activations(tiny["wl"], ctx=np.array(ctx, dtype=np.int32), capacity=192)
+    B = len(ctx)
+    eng = check_lists(gpu, shape, tiny["w"], lists, act, seq_subset, K)
+    dkc, dvc = eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"])
     # one list for everybody through the same entry point equals the plain call bit for bit
     same = eng.draft_lists(K, [0] * B, eng.to_device_bits(act["hidden_in"]), eng.to_device_i32(act["token_in"]),
                            eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"]),
@@ -972,6 +987,21 @@ def test_tiny_one_list_per_sequence(gpu, tiny, ctx, seq_subset):
         st = binding.mtp_draft_steps_lists(eng.handle, B, K, bad, dkc, dkc, dkc, dvc, dkc, None, dkc)
         assert st == -6
     eng.close()
+
+
+@pytest.mark.parametrize("d,groups", LIST_GROUPS)
+def test_lists_of_a_larger_batch_read_row_major_activations(gpu, d, groups):
+    """Few sequences per list in a batch of many, lists that the tiles do not serve as fast: few_rows.h on activations that the tiles
+    of the other phases left row by row, up to eight rows with the lo halves in the second half of the operand, from an offset of
+    rows on (test_rows_plan.py holds the route)."""
+    shape = synth.HeadShape(d, 4, 2, 128, 1032, max(n for _, n in groups))
+    B = sum(r for r, _ in groups)
+    wl = synth.Workload(f"lists_{d}", 120, shape, B, 0, 0, (64,), 2, 0.5, zipf_subset=False)
+    rng = np.random.default_rng(12)
+    lists = [np.sort(rng.choice(shape.vocab_size, n, replace=False)).astype(np.int32) for _, n in groups]
+    seq_subset = [-1 if n == shape.vocab_size else g for g, (r, n) in enumerate(groups) for _ in range(r)]
+    act = synth.make_activations(wl, ctx=rng.integers(0, 60, B).astype(np.int32), capacity=64)
+    check_lists(gpu, shape, synth.make_weights(wl), lists, act, seq_subset, 2).close()
 
 
 # ------------------------------------------------------------------------------------------ teacher-forced loss
