@@ -14,6 +14,7 @@
 #include "phases.h"
 #include "flow.h"
 #include "batch_launch.h"
+#include "exp_term.h"
 
 using namespace mtp;
 
@@ -154,9 +155,8 @@ __global__ void k_train_begin_step(int n_pos, int *kv_len, int *ext_len) { // a 
     }
 }
 // One workgroup per position: logsumexp(z) - z[label] over the full vocabulary.  A read of the logits, so what counts is requests
-// in flight (two workgroups of sixteen waves per CU, 64 bytes per lane) and few instructions per logit: the exponential of an
-// element is a multiplication and the hardware's exp2 (its argument is off by 2^-23 of at most the spread of the logits, at
-// random over the vocabulary: nothing of it is left in the sum).  512 positions of 151680: 77 us; with expf 93, with four
+// in flight (two workgroups of sixteen waves per CU, 64 bytes per lane) and few instructions per logit: an exponential is
+// two multiplications, an addition and the hardware's exp2 (exp_term.h).  512 positions of 151680: 77 us; with expf 93, with four
 // waves and expf 113.
 constexpr int kCeBlock = 1024, kCeWaves = kCeBlock / kWave;
 __global__ __launch_bounds__(kCeBlock) void k_train_row_ce(const float *__restrict__ logits, int V, const int *labels,
@@ -172,8 +172,7 @@ __global__ __launch_bounds__(kCeBlock) void k_train_row_ce(const float *__restri
             sum *= expf(m - mm); // exp(-inf) = 0 the first time
             m = mm;
         }
-        auto ex = [&](float v) { return __builtin_amdgcn_exp2f((v - m) * 1.44269504088896341f); };
-        sum += (ex(a) + ex(b)) + (ex(c) + ex(d));
+        sum += (exp_term(a - m) + exp_term(b - m)) + (exp_term(c - m) + exp_term(d - m));
     };
     const int head = (int)((4 - (((size_t)blockIdx.x * V) & 3)) & 3); // elements before the first aligned one
     const int nvec = V > head ? (V - head) / 4 : 0;
