@@ -17,28 +17,27 @@
 
 namespace mtp {
 
-// NA: tiles of sixteen rows.  NA = 0: up to eight rows, whose hi and lo halves share one tile (rows 0..7 hi, 8..15 lo): half the
-// activation loads, registers and matrix instructions; the two halves of a result are added at the end.
-template <int NA_>
+// PACKED: up to eight rows, whose hi and lo halves share one operand (rows 0..7 hi, 8..15 lo): half the activation loads,
+// registers and matrix instructions; the two halves of a result are added at the end.
+template <bool PACKED>
 struct FewShape {
-    static constexpr int NA = NA_ ? NA_ : 1, HL = NA_ ? 2 : 1; // tiles, operands per tile
-
-    static constexpr int KB = 8 / NA;          // 32-element blocks of a chunk
-    static constexpr int CK = 32 * KB;         // elements of a chunk
-    static constexpr int L = 8 / NA;           // loads of an item (1 KB each: 2 NA rows)
-    static constexpr int S = 2 * NA;           // items in flight per wave
-    static constexpr int LPR = 32 / NA;        // lanes per row of a load
-    static constexpr int kStep = 1040;         // bytes between the landing places of an item's loads
+    static constexpr int HL = PACKED ? 1 : 2; // operands per tile of sixteen rows
+    static constexpr int KB = 8;              // 32-element blocks of a chunk
+    static constexpr int CK = 32 * KB;        // elements of a chunk
+    static constexpr int L = 8;               // loads of an item (1 KB each: two rows)
+    static constexpr int S = 2;               // items in flight per wave
+    static constexpr int LPR = 32;            // lanes per row of a load
+    static constexpr int kStep = 1040;        // bytes between the landing places of an item's loads
     static constexpr int kSlot = L * kStep;
     static constexpr int kRing = kWaves * S * kSlot;
-    static constexpr int AL = KB * HL * NA;    // activation loads of a chunk
+    static constexpr int AL = KB * HL;        // activation loads of a chunk
 };
 // A listed row that does not exist: behind the end of any matrix (but one within 64 KB of 2 GiB, where it may read what is
 // there: the row's results go nowhere).  Added to the mark of a missing piece it still does not wrap around.
 constexpr uint32_t kFewNoRow = 0x7fff0000u;
 constexpr int kFewMaxTiles = 8;
 __host__ __device__ inline size_t few_lds_bytes() {
-    return (size_t)FewShape<1>::kRing + kBatchMaxSeq * 4 + kFewMaxTiles * 16 * 4;
+    return (size_t)FewShape<false>::kRing + kBatchMaxSeq * 4 + kFewMaxTiles * 16 * 4;
 }
 
 // keeps requests in the order they are written in: the waits below count them
@@ -48,16 +47,13 @@ __device__ __forceinline__ void few_wait() { asm volatile("s_waitcnt vmcnt(%0)" 
 
 // The norm scales s_b = 1/sqrt(mean(u_b^2) + eps) of the pass's rows from the producers' per-tile sums of squares, in two
 // parts: the sums are requested behind the first weights and added up when the rest is on its way.
-template <int NA_>
 struct FewScales {
-    static constexpr int LR = 32 / FewShape<NA_>::NA, N = 16; // lanes per row, values requested at once
+    static constexpr int LR = 32, N = 16; // lanes per row, values per lane (8192 wide: 512 tiles)
     float v[N];
-    __device__ __forceinline__ const float *src(const DraftParams &p, int kind, int row) const {
-        return p.ssq + ((size_t)kind * p.max_batch + p.b0 + row) * (p.d / 16);
-    }
     __device__ __forceinline__ void request(const DraftParams &p, int kind) { // (no branch around a load)
         const int row = threadIdx.x / LR, i0 = threadIdx.x % LR, n = row < p.nb ? p.d / 16 : 0;
-        const row_rsrc r = make_row_rsrc(reinterpret_cast<const uint16_t *>(src(p, kind, 0)), p.nb * (p.d / 16) * 4);
+        const float *src = p.ssq + ((size_t)kind * p.max_batch + p.b0) * (p.d / 16);
+        const row_rsrc r = make_row_rsrc(reinterpret_cast<const uint16_t *>(src), p.nb * (p.d / 16) * 4);
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int i = i0 + LR * u;
@@ -65,26 +61,25 @@ struct FewScales {
                 r, i < n ? (row * (p.d / 16) + i) * 4 : (int)kOobOffset, 0, 0));
         }
     }
-    __device__ __forceinline__ void finish(const DraftParams &p, int kind, float *scale_lds) {
-        const int row = threadIdx.x / LR, i0 = threadIdx.x % LR, n = row < p.nb ? p.d / 16 : 0;
+    __device__ __forceinline__ void finish(const DraftParams &p, float *scale_lds) {
+        const int row = threadIdx.x / LR;
         float s = 0.f;
 #pragma unroll
         for (int u = 0; u < N; ++u) s += v[u];
-        for (int i = i0 + LR * N; i < n; i += LR) s += src(p, kind, row)[i]; // (two tiles, more than 4096 wide)
         s = row16_sum(s);
-        if (LR == 32) s += __shfl_xor(s, 16, kWave);
-        if (i0 == 0) scale_lds[row] = row < p.nb ? 1.0f / sqrtf(s / (float)p.d + p.eps) : 0.f;
+        s += __shfl_xor(s, 16, kWave);
+        if (threadIdx.x % LR == 0) scale_lds[row] = row < p.nb ? 1.0f / sqrtf(s / (float)p.d + p.eps) : 0.f;
     }
 };
 
-// NA tiles of sixteen rows, T weight tiles per group (accumulators per wave).  Ph: as for bgemv_lds.
+// T weight tiles per group (accumulators per wave).  Ph: as for bgemv_lds.
 // Workgroup b of the launch owns `per` units (tiles, or gate/up pairs), the first `rem` workgroups one more.
-template <int NA_, int T, class Ph>
+template <bool PACKED, int T, class Ph>
 __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, int rem, char *smem) {
-    using S_ = FewShape<NA_>;
-    constexpr int NA = S_::NA, HL = S_::HL;
+    using S_ = FewShape<PACKED>;
+    constexpr int HL = S_::HL;
     constexpr int NMAT = Ph::NMAT, KB = S_::KB, CK = S_::CK, L = S_::L, S = S_::S, LPR = S_::LPR;
-    static_assert(T % NMAT == 0 && (size_t)T * NA * kWaves * kWave * 16 <= (size_t)S_::kRing, "tiles of a group");
+    static_assert(T % NMAT == 0 && (size_t)T * kWaves * kWave * 16 <= (size_t)S_::kRing, "tiles of a group");
     const int rg = blockIdx.x;
     const int lane = threadIdx.x & (kWave - 1), j = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -94,7 +89,7 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
     const int ngroups = (nvt + T - 1) / T;
 
     char *ring = smem + (size_t)wave * S * S_::kSlot;
-    f32x4 *red = reinterpret_cast<f32x4 *>(smem); // [kWaves][T * NA][kWave], once the ring is idle
+    f32x4 *red = reinterpret_cast<f32x4 *>(smem); // [kWaves][T][kWave], once the ring is idle
     float *scale_lds = reinterpret_cast<float *>(smem + S_::kRing);
     uint32_t *row_off = reinterpret_cast<uint32_t *>(scale_lds + kBatchMaxSeq); // gathered rows of the group: byte offsets
 
@@ -114,35 +109,32 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
     const row_rsrc ar = make_row_rsrc(ph.in, p.act_bytes);
     const int lo_bytes = (int)(p.a_lo * 2);
     const int a_step = p.act_frag ? p.act_frag * 64 : 64; // bytes per 32 elements
-    int a_lane[NA];
-#pragma unroll
-    for (int at = 0; at < NA; ++at) {
-        const int r = HL == 1 ? j & 7 : at * 16 + j, row = p.b0 + r;
-        int off = p.act_frag ? (g * p.act_frag + row) * 16 : row * p.a_stride * 2 + g * 16;
-        if (HL == 1 && j >= 8) off += lo_bytes;
-        a_lane[at] = r < p.nb ? off : (int)kOobOffset;
+    int a_lane;
+    { // (a mask instead of a branch, which the compiler would put in front of everything: the first requests waited for it)
+        const int r = PACKED ? j & 7 : j, row = p.b0 + r;
+        const int frag = -(int)(p.act_frag != 0);
+        int off = (((g * p.act_frag + row) * 16) & frag) | ((row * p.a_stride * 2 + g * 16) & ~frag);
+        if (PACKED && j >= 8) off += lo_bytes;
+        a_lane = r < p.nb ? off : (int)kOobOffset;
     }
     // Two chunks' operands in registers where a chunk is one item long; with more tiles one, refilled block by block while the
     // chunk's last item is multiplied.
     constexpr int AB = T == 1 ? 2 : 1;
-    u32x4 act[AB][KB][HL][NA];
-    auto issue_block = [&](u32x4(&dst)[KB][HL][NA], int c, int kb) {
+    u32x4 act[AB][KB][HL];
+    auto issue_block = [&](u32x4(&dst)[KB][HL], int c, int kb) {
         const int k = chunk_of(c) * CK + kb * 32, end = c < nc ? K : 0;
         const bool in = k + g * 8 < end;
-#pragma unroll
-        for (int at = 0; at < NA; ++at) {
-            const int off = in ? a_lane[at] + k / 32 * a_step : (int)kOobOffset;
-            dst[kb][0][at] = row_load16<false>(ar, off, 0);
-            if (HL == 2) dst[kb][HL - 1][at] = row_load16<false>(ar, off, lo_bytes);
-        }
+        const int off = in ? a_lane + k / 32 * a_step : (int)kOobOffset;
+        dst[kb][0] = row_load16<false>(ar, off, 0);
+        if (HL == 2) dst[kb][HL - 1] = row_load16<false>(ar, off, lo_bytes);
     };
-    auto issue_act = [&](u32x4(&dst)[KB][HL][NA], int c) {
+    auto issue_act = [&](u32x4(&dst)[KB][HL], int c) {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) issue_block(dst, c, kb);
     };
 
     // weights: lane -> row q L + u of load u, 16-byte piece `piece` of the chunk
-    const int q = lane / LPR, piece = (lane % LPR) ^ (q * (8 / NA));
+    const int q = lane / LPR, piece = (lane % LPR) ^ (q * 8);
     auto issue_w = [&](int grp, int c, int t, int slot) {
         const uint16_t *base;
         int mat_rows, row0, row_end;
@@ -172,13 +164,11 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
     int w_lane[KB]; // where this lane's operand pieces of an item lie
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
-        w_lane[kb] = (j % L) * S_::kStep + (j / L) * (LPR * 16) + (((kb * 4 + g) ^ ((j / L) * (8 / NA))) * 16);
+        w_lane[kb] = (j % L) * S_::kStep + (j / L) * (LPR * 16) + (((kb * 4 + g) ^ ((j / L) * 8)) * 16);
 
-    f32x4 acc[T][NA][HL]; // hi and lo products apart: two chains, and the lo sums keep their low bits
+    f32x4 acc[T][HL]; // hi and lo products apart: two chains, and the lo sums keep their low bits
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int at = 0; at < NA; ++at) acc[t][at][0] = acc[t][at][HL - 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < T; ++t) acc[t][0] = acc[t][HL - 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto set_rows = [&](int grp) { // a group's gathered rows
         if (!Ph::GATHER) return;
@@ -191,7 +181,7 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
         __syncthreads();
     };
     // refill: also ask for the blocks of chunk `next` as this chunk's are used up
-    auto consume = [&](u32x4(&a)[KB][HL][NA], int t, int slot, bool refill, int next) {
+    auto consume = [&](u32x4(&a)[KB][HL], int t, int slot, bool refill, int next) {
         const char *src = ring + slot * S_::kSlot;
 #pragma unroll
         for (int k4 = 0; k4 < KB; k4 += 4) { // four operand reads at a time
@@ -200,11 +190,8 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
             for (int kb = 0; kb < 4; ++kb) w[kb] = *reinterpret_cast<const u32x4 *>(src + w_lane[k4 + kb]);
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) {
-#pragma unroll
-                for (int at = 0; at < NA; ++at) {
-                    acc[t][at][0] = mfma16(a[k4 + kb][0][at], w[kb], acc[t][at][0]);
-                    if (HL == 2) acc[t][at][HL - 1] = mfma16(a[k4 + kb][HL - 1][at], w[kb], acc[t][at][HL - 1]);
-                }
+                acc[t][0] = mfma16(a[k4 + kb][0], w[kb], acc[t][0]);
+                if (HL == 2) acc[t][HL - 1] = mfma16(a[k4 + kb][HL - 1], w[kb], acc[t][HL - 1]);
                 if (refill) issue_block(a, next, k4 + kb);
             }
         }
@@ -214,18 +201,18 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
         set_rows(grp);
         int slot = 0; // of the next item to be multiplied
         issue_w(grp, 0, 0, 0);
-        FewScales<NA_> scales;
+        FewScales scales;
         if (grp == 0 && Ph::SCALE >= 0) scales.request(p, Ph::SCALE);
         issue_act(act[0], 0);
 #pragma unroll
         for (int i = 1; i < S; ++i) issue_w(grp, i / T, i % T, i);
         if (AB == 2) issue_act(act[AB - 1], 1);
-        if (grp == 0 && Ph::SCALE >= 0) scales.finish(p, Ph::SCALE, scale_lds);
+        if (grp == 0 && Ph::SCALE >= 0) scales.finish(p, scale_lds);
         // what the epilogue of this wave's (first) slot reads, asked for now
-        constexpr int NS = T / NMAT * NA;
-        const int s0 = min(wave, NS - 1), t0 = min(grp * T + s0 / NA * NMAT, nvt - 1);
-        const typename Ph::Pre pre = ph.pre(s0 % NA * 16 + g * 4, vt0 + t0, j);
-        auto chunk = [&](u32x4(&a)[KB][HL][NA], int c) {
+        constexpr int NS = T / NMAT;
+        const int t0 = min(grp * T + min(wave, NS - 1) * NMAT, nvt - 1);
+        const typename Ph::Pre pre = ph.pre(g * 4, vt0 + t0, j);
+        auto chunk = [&](u32x4(&a)[KB][HL], int c) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 // Newer requests than this item's: the other items in flight and, near the start of a chunk, one chunk's
@@ -250,29 +237,26 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
         few_wait<0>(); // (requests past the end: zeros on their way to the ring)
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int at = 0; at < NA; ++at) {
-                red[((size_t)wave * (T * NA) + t * NA + at) * kWave + lane] =
-                    HL == 2 ? acc[t][at][0] + acc[t][at][HL - 1] : acc[t][at][0];
-                acc[t][at][0] = acc[t][at][HL - 1] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+        for (int t = 0; t < T; ++t) {
+            red[((size_t)wave * T + t) * kWave + lane] = HL == 2 ? acc[t][0] + acc[t][HL - 1] : acc[t][0];
+            acc[t][0] = acc[t][HL - 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
         __syncthreads();
         static_assert(NS <= kWaves, "one slot per wave");
         if (wave < NS) {
-            const int t = wave / NA * NMAT, at = wave % NA;
+            const int t = wave * NMAT;
             f32x4 sums[NMAT];
 #pragma unroll
             for (int m = 0; m < NMAT; ++m) {
                 f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int w = 0; w < kWaves; ++w) v += red[((size_t)w * (T * NA) + (t + m) * NA + at) * kWave + lane];
-                if (HL == 1) // rows 8..15 hold the lo products of rows 0..7
+                for (int w = 0; w < kWaves; ++w) v += red[((size_t)w * T + t + m) * kWave + lane];
+                if (PACKED) // rows 8..15 hold the lo products of rows 0..7
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], 32, kWave);
                 sums[m] = v;
             }
-            if (grp * T + t < nvt) ph.epi(at * 16 + g * 4, vt0 + grp * T + t, j, sums, scale_lds, pre);
+            if (grp * T + t < nvt) ph.epi(g * 4, vt0 + grp * T + t, j, sums, scale_lds, pre);
         }
         if (grp + 1 < ngroups) __syncthreads(); // the ring is free again
     }

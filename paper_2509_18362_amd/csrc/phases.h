@@ -44,11 +44,7 @@ struct DraftParams {
     int logit_stride;                // floats per (sequence, step) in logits_out: n, or the largest n of the lists
     int fused_gemv_bytes;     // single-launch kernel: bytes of LDS shared by the staged activations and the attention
     long long bar_timeout;    // wall-clock ticks a workgroup may wait for a hand-over before giving up
-    unsigned *admit, *admit_next; // single-launch kernel whose workgroups first wait for all of them (flow_admit): this call's
-                                  // word and the next one's; null: they do not
-    long long admit_ticks;        // the longest that may take
     long long *trace;         // optional wall-clock stamps (100 MHz) of every workgroup of the single-launch kernel
-    int trace_wgs;            // workgroups a section has room for in it (the device's compute units)
     int max_batch;
     // launch plan
     int split_tokens, max_splits; // attention: tokens per split, splits per (sequence, KV head)
@@ -90,6 +86,10 @@ struct DraftParams {
     unsigned tag_base;         // tag of (step, section) = tag_base + 8 * step + section + 1; never 0
     int bg_rg[6], bg_kp[6]; // row groups and reduction parts of the six matrix phases
     int bg_sep[6];          // 1: the phase's epilogue runs as a kernel of its own
+    unsigned *admit, *admit_next; // single-launch kernel whose workgroups first wait for all of them (flow_admit): this call's
+                                  // word and the next one's; null: they do not
+    long long admit_ticks;        // the longest that may take
+    int trace_wgs;            // workgroups a section has room for in it (the device's compute units)
 };
 
 // element e of row b in the hi (or lo) array of split activations; eight elements from a multiple of eight on are neighbours
