@@ -454,7 +454,7 @@ WsLayout ws_layout(const mtp_config &c) {
     if (c.max_batch >= kBatchMinSeq) {
         size_t kmax = std::max({2 * d, qd, (size_t)c.d_ffn});
         l.a_stride = (int)((kmax + 31) / 32 * 32);
-        l.a_lo = std::max(mb, (size_t)kFewRows) * (size_t)l.a_stride;
+        l.a_lo = mb * (size_t)l.a_stride;
         l.act0 = take(2 * l.a_lo * 2);
         l.act1 = take(2 * l.a_lo * 2);
         l.ssq = take((size_t)3 * mb * (d / 16) * 4);

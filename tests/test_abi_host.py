@@ -46,6 +46,20 @@ def test_workspace_holds_length_sized_splits_only_for_calls_that_can_have_them()
     assert size(128, 32768) - size(48, 32768) <= plain + planned_partials
 
 
+def test_workspace_holds_activations_for_the_rows_there_are():
+    """Two buffers of split activations (hi and lo, two bytes each) of the longest reduction for every row: a handle of two sequences
+    pays, and clears at init, for two."""
+
+    def of_d_ffn(rows):  # what 32768 more of d_ffn cost (as long as it is the longest reduction)
+        sizes = [b.mtp_workspace_bytes(b.make_config(synth.HeadShape(4096, 32, 8, 128, f, 32000), rows, 1024, 3))
+                 for f in (32768, 65536)]
+        return sizes[1] - sizes[0]
+
+    a_row = 32768 * (2 * 2 * 2 + 2 * 4)  # split activations; gate and up values
+    for rows in (3, 16, 33):
+        assert abs(of_d_ffn(rows) - of_d_ffn(rows - 1) - a_row) < 256 * 16, rows  # (every part is rounded up to 256 bytes)
+
+
 def test_workspace_bytes_and_config_validation():
     cfg = b.make_config(synth.SEVEN_B, 1, 2112, 3)
     n1 = b.mtp_workspace_bytes(cfg)
