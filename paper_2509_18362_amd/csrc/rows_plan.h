@@ -85,26 +85,23 @@ inline bool rows_gemm_serves(const RowsCall &c, int cus) {
     if (c.K % kRgBK) return false;
     if (c.head && c.n > kRowsTile[1].bn * kMaxHeadCands) return false; // no room for the candidates
     if (c.rows > kRowsFew) return true;
-    // Up to 16 rows (9 to 16 of narrow heads, and the lists of a larger batch: the others take few_rows.h without asking) the
-    // line was drawn against a core whose waves split the reduction, with reduction parts; few_rows.h, which has taken its
-    // place, is the faster one of the two.  That core streamed large matrices as fast as the tiles, and added its
-    // parts by itself; but it takes 10 us (tiny) to 14 us before its workgroups' sums are added up, against 5 us, or 10 with
-    // the launch that adds the parts.  Both kernels go in rounds of one workgroup per CU: this one is ahead while its
-    // workgroups fit one round and where further rounds are nearly full.  Gain of the tiled product over the batched core, us
-    // per step of whole drafts at 2, 5 and 16 rows, K = 512 .. 8192:
-    //   blocks of 128 in one round: K <= 2048 or up to 32 MB +1.3 .. +7; larger heads +1.6 .. +7.6 where nine tenths of the
-    //   round are there, -1.5 .. +4 from half of it (16384 x 3072) on;
-    //   blocks of 256: one round (33000 .. 65536 rows) +0.7 .. +17; two full ones (131072) +5 .. +36; 0.58 of two (75841) +2 at
-    //   K = 512, else -11 .. +4; 0.75 of two (98304) -3 .. +9 up to K = 2048, from 3072 on -14 .. +14; 0.77 of three (151680) -1 ..
-    //   +8 up to K = 2048, -7 .. -25 from 3072 on.
-    const bool small = c.K <= 2048 || (double)c.n * c.K * 2 <= 32e6, half = c.K % 64 != 0;
+    // Up to 16 rows (9 to 16 of narrow heads, and the lists of a larger batch: other calls take few_rows.h without asking) few_rows.h
+    // with row-major activations is the alternative.  Both go in rounds of one workgroup per CU; this kernel is ahead while its
+    // workgroups fit one round, the other, which deals tiles of sixteen rows evenly, beyond.  Gain of the tiled product over
+    // few_rows.h, us per step, heads at 8 and 16 rows, K = 512 .. 4096:
+    //   blocks of 128 in one round (up to 32768 rows): K <= 2048 or up to 32 MB -0.3 .. +4; larger heads +0.5 .. +6 where nine
+    //   tenths of the round are there, -4 .. +3 below;
+    //   blocks of 256: one round (33000 .. 65536 rows) +1.2 .. +6 (65536: -2 .. +6), two full ones (131072) -2.6 .. +5 up to K = 2048,
+    //   -5 .. 0 from 3072 on; 0.58 of two (75841) -2.5 .. -16, 0.75 of two (98304) -2.5 .. -18, 0.77 of three (151680) -5 .. -32;
+    //   reductions of an odd number of 32s, which have no blocks of 256, in two rounds and more: K = 544 and 1056 -1 .. +1, 1568 and 2016
+    //   -1 .. -7 (33000 .. 65536 rows), -1 .. -36 beyond.
+    // The body's phases at 9 and 16 rows, 384 .. 2048 wide: +2.5 .. +11 us per step together.
+    const bool small = c.K <= 2048 || (double)c.n * c.K * 2 <= 32e6;
     if (!small && !c.head) return false;
     const int narrow = (c.n + 127) / 128, wide = (c.n + 255) / 256; // blocks of the two tiles that such calls take
     if (narrow <= cus) return small || 10 * narrow >= 9 * cus;
-    if (half) return small && narrow <= kMaxHeadCands; // (no wide tile: 1056 x 33000 .. 65536 +7 .. +10)
-    if (wide > kMaxHeadCands) return false;
-    const int slots = (wide + cus - 1) / cus * cus;
-    return wide <= cus || (small ? c.K <= 512 || 4 * wide >= 3 * slots : 10 * wide >= 9 * slots);
+    if (c.K % 64 || wide > kMaxHeadCands) return false;
+    return wide <= cus || (small && 10 * wide >= 9 * ((wide + cus - 1) / cus * cus));
 }
 
 // Kernels of the matrix phases of a call of `rows` rows (sequences, or positions of a block) of a head d wide.

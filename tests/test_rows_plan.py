@@ -57,7 +57,7 @@ HEADS = [1024, 4096, 8195, 16384, 24576, 29500, 30336, 32768, 32769, 33000, 3600
 def test_few_rows_take_the_tiles_only_where_their_rounds_are_full(plan, rows, call_rows, K):
     """Up to 16 rows, by themselves or sharing a list in a larger batch, few_rows.h is the alternative.  The tiled product is taken
     in one round of workgroups and where further rounds are nearly full, never in tiles of many times the rows: a head of
-    36000 x 4096 in 282 blocks for 256 units was 7 us slower per step, one of 75841 x 3072 in tiles of 128 rows 18 us."""
+    151680 x 2048 in 593 blocks for 256 units was 23 us slower per step, one of 75841 x 3072 in tiles of 128 rows 18 us."""
     tiles = 0
     for n, p in zip(HEADS, plan([dict(K=K, n=n, rows=rows, head=1, call_rows=call_rows) for n in HEADS])):
         assert p["route"] != CORE
@@ -70,7 +70,7 @@ def test_few_rows_take_the_tiles_only_where_their_rounds_are_full(plan, rows, ca
         assert p["bm"] <= 64, (n, p)
         assert p["parts"] > 1 or blocks <= 1024
         slots = -(-blocks // CUS) * CUS
-        assert blocks <= CUS or K <= 512 or K % 64 or blocks >= 0.75 * slots, (n, p)
+        assert blocks <= CUS or (K <= 2048 and K % 64 == 0 and blocks >= 0.9 * slots), (n, p)
         if K > 2048 and n * K * 2 > 32e6:  # large heads: a nearly full round, in whichever tile
             assert blocks > 0.9 * slots - 1 or (p["bn"] == 256 and blocks > 0.5 * slots), (n, p)
     assert tiles or call_rows <= 16
@@ -78,8 +78,9 @@ def test_few_rows_take_the_tiles_only_where_their_rounds_are_full(plan, rows, ca
 
 @pytest.mark.parametrize("rows,K,n,expect", [
     (16, 4096, 32768, 16), (16, 4096, 30336, 16), (16, 4096, 33000, 64), (5, 4096, 40000, 64), (2, 4096, 65536, 64),
-    (16, 4096, 131072, 64), (16, 4096, 75841, 0), (16, 4096, 98304, 0), (2, 4096, 151680, 0), (16, 3072, 75841, 0),
-    (5, 1024, 75841, 0), (5, 1024, 151680, 64), (5, 512, 75841, 64), (16, 2048, 36000, 64), (5, 1056, 65536, 16)])
+    (16, 4096, 131072, 0), (16, 4096, 75841, 0), (16, 4096, 98304, 0), (2, 4096, 151680, 0), (16, 3072, 75841, 0),
+    (5, 1024, 75841, 0), (5, 1024, 151680, 0), (5, 512, 75841, 0), (16, 2048, 36000, 64), (5, 1056, 65536, 0),
+    (16, 2048, 131072, 64), (8, 2048, 98304, 0), (8, 2016, 32768, 16), (8, 2016, 33000, 0), (16, 3072, 24576, 0)])
 def test_route_of_heads_at_few_rows(plan, rows, K, n, expect):
     """Rows that share a list in a larger batch: the tile's rows, or 0 for few_rows.h, on both sides of the lines."""
     p = plan([dict(K=K, n=n, rows=rows, head=1, call_rows=40)])[0]
