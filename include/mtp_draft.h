@@ -256,7 +256,7 @@ float mtp_last_draft_ms(mtp_handle *h);
  *   2 (default) automatic: mode 1 where it applies, mode 0 otherwise (also when the single launch is refused).
  *   0           one launch per phase.  One sequence: the row-streaming kernels, 7 launches per step plus one to publish
  *               the last draft id.  Two or more (also the rows of a block of positions): the batched kernels (from 17
- *               rows on, and in narrow heads from nine on, a tiled matrix product per phase), one preparation launch
+ *               rows on, and in narrow heads from nine or two on, a tiled matrix product per phase), one preparation launch
  *               per step, and one launch more after a matrix phase whose reduction is split over workgroups and added
  *               up apart.  Matrices of 2 GiB or more: as mode 3.
  *   1           one sequence whose reduction lengths (d_model, n_q_heads * head_dim, d_ffn) are all at least 512, or that has a

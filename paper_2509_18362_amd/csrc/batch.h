@@ -346,7 +346,7 @@ __device__ __forceinline__ void bgemv_lds(const DraftParams &p, Ph &ph, int RG, 
 }
 
 // ---------------------------------------------------------------------------------------------------
-// the phases of a draft step (Sec. 2.1, Fig. 1) on the batched core
+// the phases of a draft step (Sec. 2.1, Fig. 1) over several rows
 // ---------------------------------------------------------------------------------------------------
 struct BgBase {
     static constexpr int NMAT = 1;

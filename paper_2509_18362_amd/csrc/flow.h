@@ -1,5 +1,5 @@
 // Single-launch path for ONE sequence without grid barriers (gfx950): all phases of all K draft steps in one
-// kernel (one workgroup per compute unit, all resident) whose workgroups hand their results over element by element.
+// kernel (one workgroup per compute unit, all resident; narrow heads: a quarter of them, see flow_admit) whose workgroups hand their results over element by element.
 //
 // A draft step at batch 1 is a chain of dependent matrix-vector products (Sec. 2.1) of 30-270 MB each; between two of
 // them every workgroup needs the whole result vector of the phase before.  With a grid barrier that hand-over is a

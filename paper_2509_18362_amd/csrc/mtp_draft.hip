@@ -306,8 +306,9 @@ fused_kernel_t flow_kernel_of(int G, int HD) {
     return nullptr;
 }
 // Loads of 1 KiB per chunk of a row: what one row of most phases fills (half-empty chunks request and multiply zeros).  Three
-// steps, us, with chunks of 2 / 4 / 8: 256 wide 136 / 143 / 166, 2048 wide (d_ffn 6144, 65536 rows) 345 / 305 / 339; 4096 wide
-// takes 8.
+// steps, us, with chunks of 2 / 4 / 8: 256 wide 136 / 143 / 166, 2048 wide (d_ffn 6144, 65536 rows) 345 / 305 / 339.  Against chunks
+// of 8, heads of 1024 to 65536 rows: 512, 768 and 1024 wide 1.16 to 1.30 times as fast in chunks of 2, 1536 and 2048 wide 1.10 to 1.19
+// times in chunks of 4; wider heads take 8.
 fused_kernel_t flow_kernel(const mtp_config &c) {
     const int G = c.n_q_heads / c.n_kv_heads, widest = std::max(c.d_model, c.n_q_heads * c.head_dim);
     if (widest <= 1024) return flow_kernel_of<2>(G, c.head_dim);

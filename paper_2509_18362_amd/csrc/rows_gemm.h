@@ -1,6 +1,6 @@
 // The matrix phases as LDS-tiled matrix products on the matrix cores (gfx950), one per phase: every call of more than 16 rows
 // (a batch, the confirmed positions of one, a prompt, the teacher-forced forward of Sec. 2.1, Eq. (1)) and, from two rows
-// on, phases of narrow heads and lists (rows_gemm_serves in rows_plan.h, the host's route).  The batched core (batch.h)
+// on, phases of narrow heads and lists (rows_route in rows_plan.h).  The batched core (batch.h)
 // streams every weight once per 64 rows; here a weight tile is read once per block of BM rows (16 to 256) and the blocks of one
 // weight tile share an L2.
 //

@@ -53,9 +53,8 @@ inline RowsPlan rows_plan(const RowsCall &c, int cus, size_t part_floats) {
         const RowsTileInfo &ti = kRowsTile[t];
         if (c.K % ti.bk && t < kRowsHalf) continue;
         // Few rows: no tiles of many times as many (their products with rows that are not there cost more than the estimate
-        // says: 75841 x 3072 in tiles of 128 rows 18 us behind the batched core).  Where blocks of 128 weight rows would take a
-        // second round, blocks of 256 (36000 x 4096 at sixteen rows: 5 us ahead of the batched core, in 282 narrow blocks for 256
-        // CUs 7 behind it).
+        // says: 75841 x 3072 in tiles of 128 rows takes 18 us more than without them).  Where blocks of 128 weight rows would take a
+        // second round, blocks of 256 (36000 x 4096 at sixteen rows: 12 us less than in 282 narrow blocks for 256 CUs).
         const int nb = (c.n + ti.bn - 1) / ti.bn;
         if (c.rows <= kRowsFew && (ti.bm > 64 || (ti.bn == 128 && nb > cus && c.K % 64 == 0))) continue;
         const int steps = (c.K + ti.bk - 1) / ti.bk;
