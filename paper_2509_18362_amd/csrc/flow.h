@@ -366,36 +366,36 @@ __host__ __device__ inline size_t flow_tail_bytes(int d, int nvb) {
 // would wait for good.  So every workgroup first counts itself in and waits until all are there: from then on nothing that they
 // wait for depends on another launch.  If that takes too long, ONE workgroup (the one whose flag gets in) does the whole call
 // by itself, as a launch of one workgroup would, and the others leave: no wait depends on more than one resident workgroup.
-// p.admit[0]: arrivals, and kAdmitAlone once the others are to leave; one word decides, so that all of them decide alike.  The
-// calls of a handle take two words in turn and clear each other's (a call's last workgroups may arrive long after its result is
-// complete, but before the next call starts).  Every workgroup arrives exactly once.
+// One 64-bit word decides, so that all of them decide alike: arrivals in its upper half, which only grow - every workgroup of
+// every call arrives exactly once, and a call's place in them follows from what an arrival finds, whoever has called before -
+// and below the mark of the call that one workgroup does alone.  (Nothing has to be cleared or counted on the host.)
 // admit_ticks: the longest wait (100 MHz), 0: never all of them (the first to arrive does the call).
 // ---------------------------------------------------------------------------------------------------
 enum : int { kAdmitLeave = 0, kAdmitAll = 1, kAdmitOne = 2 };
-constexpr unsigned kAdmitAlone = 0x80000000u;
 __device__ __forceinline__ int flow_admit(const DraftParams &p, int *flag) {
     if (threadIdx.x == 0) {
-        auto seen = [&]() { return __hip_atomic_load(p.admit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-        const long long t0 = wall_clock64();
-        const unsigned all = gridDim.x, before = __hip_atomic_fetch_add(p.admit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (blockIdx.x == 0) __hip_atomic_store(p.admit_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const long long t0 = wall_clock64(), limit = p.admit_ticks != 0 ? p.admit_ticks : p.bar_timeout;
+        const unsigned all = gridDim.x;
+        unsigned long long w = __hip_atomic_fetch_add(p.admit, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned before = (unsigned)(w >> 32), place = before % all, first = before - place, mark = first + 1u;
+        w += 1ull << 32; // (as it was right after this arrival)
+        auto put_mark = [&](unsigned m) { // false: w is now what others have made of the word
+            return __hip_atomic_compare_exchange_strong(p.admit, &w, (w & 0xffffffff00000000ull) | m, __ATOMIC_RELAXED,
+                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
         int state = -1;
-        unsigned w = before + 1u;
-        if (p.admit_ticks == 0 && before == 0u) {
-            __hip_atomic_fetch_or(p.admit, kAdmitAlone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            state = kAdmitOne;
-        }
         while (state < 0) {
-            if (w & kAdmitAlone)
+            const bool late = (p.admit_ticks == 0 && place == 0u) || wall_clock64() - t0 > limit;
+            if ((unsigned)w == mark) {
                 state = kAdmitLeave;
-            else if (p.admit_ticks != 0 && w == all)
-                state = kAdmitAll;
-            else if (p.admit_ticks != 0 && wall_clock64() - t0 > p.admit_ticks) {
-                if (__hip_atomic_compare_exchange_strong(p.admit, &w, w | kAdmitAlone, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT))
-                    state = kAdmitOne; // (else w is what another workgroup has made of it)
-            } else
-                w = seen();
+            } else if (p.admit_ticks != 0 && (unsigned)(w >> 32) - first == all) {
+                // (a mark of an earlier call is taken away, long before its number could come round again)
+                if ((unsigned)w == 0u || place != all - 1u || put_mark(0u)) state = kAdmitAll;
+            } else if (late) {
+                if (put_mark(mark)) state = kAdmitOne;
+            } else {
+                w = __hip_atomic_load(p.admit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         *flag = state;
     }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -432,7 +433,7 @@ WsLayout ws_layout(const mtp_config &c) {
     l.gu = take(mb * (size_t)c.d_ffn * 2 * 4);
     l.dn = take(mb * d * 4);
     l.hhat = take(mb * d * 4);
-    l.err = take(192); // (the admission words lie 128 bytes behind the error word)
+    l.err = take(192); // (the admission word lies 128 bytes behind the error word)
     l.admit = l.err + 128;
     l.cand = take((size_t)c.max_draft_steps * mb * kMaxFusedGrid * 8);
     l.rope_inv = take((size_t)c.head_dim / 2 * 8);
@@ -470,6 +471,9 @@ WsLayout ws_layout(const mtp_config &c) {
     return l;
 }
 
+// hand-over tags given to the single-launch calls of all handles (the kernel's tags are the lower half)
+std::atomic<unsigned long long> flow_tags{0};
+
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 } // namespace
@@ -485,9 +489,8 @@ struct mtp_handle {
     size_t lds_limit;
     phase_kernel_t attn_fn;
     fused_kernel_t flow_fn;        // one sequence: all phases of all steps in one launch
-    unsigned long long flow_tags;  // hand-over tags given to earlier calls of that kernel
-    unsigned admit_calls;          // calls of that kernel whose workgroups waited for all of them first
-    long long admit_ticks;         // the longest such wait
+    unsigned long long flow_epoch; // upper half of the tag count at the last call of that kernel
+    long long admit_ticks;         // the longest time its workgroups wait for all of them, where they do
     size_t flow_lds_ok;            // largest LDS size for which a workgroup of that kernel was seen to fit a CU
     int mode;                    // 0: one launch per phase, 1: single launch for the whole call
     long long *trace;             // optional device buffer for phase time stamps
@@ -599,8 +602,7 @@ int32_t mtp_draft_init(mtp_handle **out, const mtp_config *cfg, const mtp_weight
     h->lds_limit = (size_t)lds;
     h->attn_fn = attn_kernel(cfg->n_q_heads / cfg->n_kv_heads, cfg->head_dim);
     h->flow_fn = flow_kernel(*cfg);
-    h->flow_tags = 0;
-    h->admit_calls = 0;
+    h->flow_epoch = flow_tags.load() >> 32; // (the workspace is cleared below)
     h->admit_ticks = kAdmitTicks;
     h->flow_lds_ok = 0;
     h->mode = 2;
@@ -913,20 +915,22 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
                 p.split_tokens = (int)t;
                 p.max_splits = (int)((c.kv_capacity + t - 1) / t);
             }
-            // tags of this call: tag_base + 1 .. tag_base + 8 K, never 0 and never reused: when the 32-bit counter would
-            // wrap, the tagged vectors are cleared and the count starts over
+            // Tags of this call: tag_base + 1 .. tag_base + 8 K, never 0 and never reused, by no handle of the process: handles that
+            // do not run concurrently may share a workspace.  When the 32-bit tags wrap, a handle's next call clears the tagged
+            // vectors first.
             const unsigned long long need = 8ull * (unsigned long long)K + 8ull;
-            if ((h->flow_tags & 0xffffffffull) + need > 0xffffffffull) {
+            unsigned long long tags;
+            do tags = flow_tags.fetch_add(need);
+            while ((tags & 0xffffffffull) + need > 0xffffffffull);
+            if ((tags >> 32) != h->flow_epoch) {
                 const size_t words = (l.tagged_end - l.xt) / 8;
                 hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,
                                    reinterpret_cast<unsigned long long *>(ws + l.xt), (int)words);
-                h->flow_tags = 0;
+                h->flow_epoch = tags >> 32;
             }
-            p.tag_base = (unsigned)h->flow_tags;
+            p.tag_base = (unsigned)tags;
             if (small) {
-                unsigned *word = reinterpret_cast<unsigned *>(ws + l.admit);
-                p.admit = word + 8 * (h->admit_calls & 1);
-                p.admit_next = word + 8 * (~h->admit_calls & 1);
+                p.admit = reinterpret_cast<unsigned long long *>(ws + l.admit);
                 p.admit_ticks = h->admit_ticks;
             }
             void *args[] = {(void *)&p};
@@ -934,8 +938,6 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             const bool launched = hipLaunchKernel((const void *)h->flow_fn, dim3(fgrid), dim3(kBlock), args,
                                                   (unsigned)lds_flow, st) == hipSuccess;
             if (launched) {
-                h->flow_tags += 8ull * (unsigned long long)K;
-                if (small) ++h->admit_calls;
                 if (h->timing == 1) {
                     (void)hipEventRecord(h->ev[1], st);
                     h->ev_recorded = true;

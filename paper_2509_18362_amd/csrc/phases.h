@@ -86,8 +86,8 @@ struct DraftParams {
     unsigned tag_base;         // tag of (step, section) = tag_base + 8 * step + section + 1; never 0
     int bg_rg[6], bg_kp[6]; // row groups and reduction parts of the six matrix phases
     int bg_sep[6];          // 1: the phase's epilogue runs as a kernel of its own
-    unsigned *admit, *admit_next; // single-launch kernel whose workgroups first wait for all of them (flow_admit): this call's
-                                  // word and the next one's; null: they do not
+    unsigned long long *admit;    // single-launch kernel whose workgroups first wait for all of them (flow_admit): the word they
+                                  // do it with; null: they do not
     long long admit_ticks;        // the longest that may take
     int trace_wgs;            // workgroups a section has room for in it (the device's compute units)
 };

@@ -431,9 +431,9 @@ def narrow_engine(gpu, d, hq, hkv, hd, d_ffn, ctx, cap, seed):
     k0, v0 = eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"])
     torch.cuda.synchronize()
 
-    def call(stream=0):
+    def call(stream=0, steps=3):
         kc, vc = k0.clone(), v0.clone()
-        out = eng.draft(3, 0, hid, tok, kc, vc, kv, want_logits=True, want_hidden=True, stream=stream)
+        out = eng.draft(steps, 0, hid, tok, kc, vc, kv, want_logits=True, want_hidden=True, stream=stream)
         return [out["draft"], out["logits"], out["hidden"], kc, vc]
 
     return eng, call
@@ -456,6 +456,30 @@ def test_narrow_single_launch_gives_the_same_bits_alone(gpu, d, hq, hkv, hd, d_f
         assert all(torch.equal(a, b) for a, b in zip(want, got)), ticks
     assert binding.mtp_set_admission_ticks(eng.handle, -1) == -3
     eng.close()
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(256, 4, 2, 64, 688), (1024, 8, 8, 128, 1024), (2048, 16, 8, 128, 8200)])
+def test_single_launches_of_handles_that_share_a_workspace(gpu, d, hq, hkv, hd, d_ffn):
+    """Handles that do not run concurrently may share a workspace: what one call of the single launch leaves in it (tags, arrivals)
+    is not taken for another handle's."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    engines = [narrow_engine(gpu, d, hq, hkv, hd, d_ffn, 300, 768, seed) for seed in (20, 21)]
+    want = [[call(steps=k) for k in (1, 3)] for _, call in engines]
+    torch.cuda.synchronize()
+    shared = engines[0][0].workspace
+    for eng, _ in engines:
+        binding.mtp_draft_destroy(eng.handle)
+        st, eng.handle = binding.mtp_draft_init(eng.cfg, eng.w, eng.subsets, [s.numel() for s in eng.subsets], shared,
+                                                shared.numel())
+        assert st == 0
+    for k, turn in [(k, turn) for k in (0, 1) for turn in (0, 1, 0, 1, 1, 0)]:
+        eng, call = engines[turn]  # (one step first: every vector keeps the tags of the call's only step)
+        got = call(steps=(1, 3)[k])
+        torch.cuda.synchronize()
+        assert eng.poll_error() == 0
+        assert all(torch.equal(a, b) for a, b in zip(want[turn][k], got)), (turn, k)
+    for eng, _ in engines:
+        eng.close()
 
 
 def test_phase_trace_of_a_launch_on_a_quarter_of_the_units(gpu):
