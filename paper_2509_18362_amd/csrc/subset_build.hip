@@ -3,19 +3,23 @@
 // with (Sec. 2.2, which takes the frequent tokens of a language from statistics over a corpus; Eq. (3)).
 //
 // Counting is the only part that touches much memory.  Global atomics on a long-tailed stream would pile up on the
-// few hottest ids (same-address device atomics serialize at ~40 ns each), so every workgroup counts in LDS.  The bins
-// are 16 bits wide, two to a word (an LDS atomic adds 1 or 65536 to the word), so that all the LDS of a CU (160 000
-// bytes) holds 80 000 ids and a 151 680-id vocabulary is two chunks: the stream is read twice (with 32-bit bins it was
-// read four times).  A field cannot overflow: a workgroup scans its slice in blocks of 49 152 tokens, and between two
-// blocks it sweeps its bins (16 bytes per read) and moves every field that has reached 16 384 to the global counts
-// (few fields ever do).  At the end a workgroup stores its bins as they are and a second kernel adds the workgroups'
-// copies up (every workgroup adding its non-zero fields to the global counts with atomics took longer than the counting;
-// the entry point without a workspace still does that).  Every thread keeps the four 16-byte loads of the next round in
-// flight while it counts.
-// Selection: a radix select over the 32-bit counts (three passes of 11, 11 and 10 bits) finds the count T of the n-th
-// most frequent id and how many ids with exactly that count belong to the list; the compaction then walks the ids in
-// ascending order and keeps those with count > T plus the first ties, placing them by prefix sums - the output is
-// born sorted, nothing is sorted.  Both are spread over 64 workgroups (a single compute unit reads memory at
+// few hottest ids (same-address device atomics serialize at ~40 ns each), so every workgroup counts in LDS, in fields so
+// narrow that the 160 KB of a CU hold the whole vocabulary and the stream is read once: 16 bits up to 80 768 ids, 8 up to
+// 155 392, 6 (five to a word) up to 201 920; beyond that the vocabulary is counted in chunks.  Narrow fields wrap, and a
+// wrap carries into the next field of its word.  Both are accounted for exactly: the atomic that adds returns the word as it
+// was, which tells which fields this add wraps, and the number W[j] of wraps of field j is kept in a small table in LDS
+// (hashed by id: only ids that occur more often than a field can hold get there).  A field has had as many increments as it
+// holds plus 2^bits W[j], and W[j-1] of them were carries of the field below, so count[j] = field[j] + 2^bits W[j] - W[j-1],
+// whatever the order of the adds.  (Fields of 16 bits, two passes over the stream and sweeps that moved full fields away in
+// time: 99 us for 2^26 tokens of 151 680 ids; this: 58.)
+// At the end a workgroup stores its bins as they are and a second kernel adds the workgroups' copies up (every workgroup
+// adding its non-zero fields to the global counts with atomics took longer than the counting; the entry point without a
+// workspace still does that).  Every thread keeps the four 16-byte loads of the next round in flight while it counts.
+// Selection: the n-th largest of the counts is at most n_tokens / n, so larger ones are as good as that + 1, and a radix
+// select over the few bits that leaves (digits of up to 12 bits: 2^26 tokens and n = 32 768 take one pass) finds the count T
+// of the n-th most frequent id and how many ids with exactly that count belong to the list; the compaction then walks the
+// ids in ascending order and keeps those with count > T plus the first ties, placing them by prefix sums - the output is
+// born sorted, nothing is sorted.  Both are spread over many workgroups (a single compute unit reads memory at
 // ~20 GB/s: as one workgroup these steps took 0.5 ms, more than the counting); the walk over a pass's buckets is done by
 // every workgroup of the kernel that follows, as a scan (as a kernel of its own with a serial loop it took 13 us a pass).
 #include <hip/hip_runtime.h>
@@ -24,232 +28,285 @@
 #include <cstdint>
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/mtp_draft.h"
+#include "subset_plan.h"
 
 namespace {
 
+using namespace mtp::subset;
+
 constexpr int kHistBlock = 1024;
-constexpr int kChunkIds = 80000;     // ids per chunk: 40 000 words of LDS, two 16-bit bins each
-constexpr int kSweepBlock = 49152;   // tokens a workgroup counts between two sweeps
-constexpr unsigned kSweepAt = 16384; // a sweep moves the fields that have reached this: 16 383 + 49 152 < 65 536
+// Copies of the global counts that the counting kernel's workgroups give the wraps to (where the copies of the bins are there
+// too): in streams of a few hundred ids every workgroup has all of them, and atomics to one cache line go one by one (600 ids
+// of 151 680, 2^26 tokens: 185 us with one copy, 128 with four; a long-tailed stream 85 and 82).
+constexpr int kCountCopies = 4;
+__host__ __device__ constexpr size_t round4(size_t words) { return (words + 3) / 4 * 4; }
 constexpr int kSelBlock = 1024;
 
-__global__ void k_subset_clear(unsigned *counts, int V, unsigned *state, int state_words, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < V) counts[i] = 0u;
-    if (i < state_words) state[i] = i == 2 ? (unsigned)n : 0u; // [2]: ids still to be found by the selection
+// clears `words` words (whole 16-byte pieces), the state among them, and leaves n in the state
+__global__ void k_subset_clear(unsigned *work, size_t words, unsigned *state, int n) {
+    const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+    if (i >= words) return;
+    uint4 zero{0u, 0u, 0u, 0u};
+    if (work + i == state) zero.z = (unsigned)n; // [2]: ids still to be found by the selection
+    *reinterpret_cast<uint4 *>(work + i) = zero;
 }
 
-// grid (slices, chunks): workgroup (s, c) counts the ids of chunk c in slice s of the stream.  The chunks' workgroups of a
-// slice are a multiple of eight apart in the launch order (subset_slices), so they run on the same compute die.
-// What bounds it: reading the stream once per chunk.  Of the second chunk's reads about half find the line in the die's L2
-// (2^26 tokens, 151680 ids: 470 MB from memory for a stream of 268 MB), and the counting hides behind that: the LDS takes
-// a wave's adds in 2 to 6 ns whatever the addresses (19 us for all of a CU's), so the loop over whole rounds does nothing
-// but form an address and an increment: no check for the slice's end, no count of ids outside the vocabulary (that is
-// what is missing from the sum of all counts), no branch around a load.  102 us (111 with those in the loop).
+// The table of wraps: keys (local id, or kNoKey), then as many counts.
+constexpr unsigned kNoKey = 0xffffffffu;
+
+// grid (slices, chunks): workgroup (s, c) counts the ids of chunk c in every (slices)-th piece of the stream, from the s-th on.
+// What bounds it: reading the stream and writing the bins (268 + 39 MB at 2^26 tokens and 151 680 ids: 58 us, 52 with the adds
+// taken out; a stream read twice took 99).
+// The loop over whole rounds has no check for the slice's end, no count of ids outside the vocabulary (that is what is
+// missing from the sum of all counts) and no branch around a load or an add: an id that is not of this chunk adds to a
+// word that its lane alone uses.
+template <int BITS>
 __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restrict__ tokens, long long n_tokens, int V,
-                                                            unsigned *counts, unsigned *partials) {
-    extern __shared__ unsigned bins[]; // word w: ids c0 + 2 w (low half) and c0 + 2 w + 1 (high half)
-    const int c0 = blockIdx.y * kChunkIds;
-    const int nb = min(kChunkIds, V - c0), nw = (nb + 1) / 2, nw4 = (nw + 3) / 4 * 4; // (LDS holds kChunkIds / 2 words)
+                                                            int chunk_ids, unsigned *counts, int copies, unsigned *partials) {
+    constexpr int FPW = 32 / BITS;                    // fields of a word
+    constexpr unsigned kFull = (1u << BITS) - 1u;     // a field that the next add wraps
+    constexpr int kTable = table_entries(BITS);
+    extern __shared__ unsigned bins[]; // word w: local ids FPW w (lowest bits) .. FPW w + FPW - 1
+    const int c0 = blockIdx.y * chunk_ids;
+    const int nb = min(chunk_ids, V - c0), nw4 = bin_words(chunk_ids, BITS);
+    unsigned *keys = bins + nw4, *wraps = keys + kTable, *spare = wraps + kTable; // spare: 64 words, one per lane
     for (int i4 = threadIdx.x * 4; i4 < nw4; i4 += kHistBlock * 4)
         *reinterpret_cast<uint4 *>(bins + i4) = uint4{0u, 0u, 0u, 0u};
+    for (int i = threadIdx.x; i < kTable; i += kHistBlock) {
+        keys[i] = kNoKey;
+        wraps[i] = 0u;
+    }
+    if (threadIdx.x < 64) spare[threadIdx.x] = 0u;
     __syncthreads();
-    // slices of whole 16-byte groups; the last slice also takes the tail
-    const long long groups = n_tokens / 4;
-    const long long per = (groups + gridDim.x - 1) / gridDim.x;
-    const long long g0 = min(groups, per * blockIdx.x), g1 = min(groups, g0 + per);
-    auto one = [&](int t) {
-        const unsigned rel = (unsigned)(t - c0); // (c0 is even)
-        if (rel < (unsigned)nb) atomicAdd(&bins[rel >> 1], 1u << ((rel & 1u) * 16u));
+    counts += (size_t)(blockIdx.x % copies) * round4(V);
+    // `by` wraps of the field of local id `id`: that many carries went into the next field of the word, if there is one
+    auto give = [&](int id, unsigned by) {
+        atomicAdd(&counts[c0 + id], by << BITS);
+        if (id % FPW + 1 < FPW && id + 1 < nb) atomicAdd(&counts[c0 + id + 1], 0u - by);
     };
-    // moves the fields of at least `at` to the global counts (at = 1: all that is left)
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    auto sweep = [&](unsigned at) {
-        __syncthreads();
-        if (at == 1u) { // everything that is left: consecutive lanes take consecutive words (the global atomics of a
-            for (int i = threadIdx.x; i < nw; i += kHistBlock) { // wave then fall into few cache lines)
-                const unsigned w = bins[i], lo = w & 0xffffu, hi = w >> 16;
-                if (lo) atomicAdd(&counts[c0 + 2 * i], lo);
-                if (hi) atomicAdd(&counts[c0 + 2 * i + 1], hi);
+    auto wrapped = [&](int id) {
+        unsigned slot = (unsigned)id * 2654435761u >> (32 - table_bits(BITS));
+        for (int tries = 0; tries < 4; ++tries) {
+            const unsigned key = atomicCAS(&keys[slot], kNoKey, (unsigned)id);
+            if (key == kNoKey || key == (unsigned)id) {
+                atomicAdd(&wraps[slot], 1u);
+                return;
             }
-            return;
+            slot = (slot + 1) % kTable;
         }
-        const unsigned probe = 0xc000c000u; // kSweepAt = 2^14: a field at or above it has one of its two top bits set
-        for (int i4 = threadIdx.x * 4; i4 < nw4; i4 += kHistBlock * 4) {
-            u32x4 w4 = *reinterpret_cast<u32x4 *>(bins + i4);
-            if (((w4.x | w4.y | w4.z | w4.w) & probe) == 0u) continue;
-            unsigned w[4] = {w4.x, w4.y, w4.z, w4.w};
+        give(id, 1u); // no room: straight to the global counts
+    };
+    // place of an id's field in its word (the hardware takes the low five bits of a shift)
+    auto shift_of = [](unsigned rel) { return 32 % BITS == 0 ? rel * BITS & 31u : rel % FPW * BITS; };
+    // Counts N tokens of this thread: all adds first, then (rare) the fields that they wrap: the added one, if it was full, and
+    // those above it as far as they were full too.
+    auto count = [&](auto n, const int *t) {
+        constexpr int N = decltype(n)::value;
+        unsigned rel[N], old[N], full = 0u;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = i4 + q;
-                const unsigned lo = w[q] & 0xffffu, hi = w[q] >> 16;
-                if (lo >= at) {
-                    atomicAdd(&counts[c0 + 2 * i], lo);
-                    w[q] &= 0xffff0000u;
-                }
-                if (hi >= at) {
-                    atomicAdd(&counts[c0 + 2 * i + 1], hi);
-                    w[q] &= 0x0000ffffu;
-                }
-            }
-            *reinterpret_cast<u32x4 *>(bins + i4) = u32x4{w[0], w[1], w[2], w[3]};
+        for (int i = 0; i < N; ++i) {
+            rel[i] = (unsigned)(t[i] - c0);
+            unsigned *at = rel[i] < (unsigned)nb ? bins + rel[i] / FPW : spare + (threadIdx.x & 63);
+            old[i] = atomicAdd(at, 1u << shift_of(rel[i]));
         }
-        __syncthreads();
+        unsigned most = 0u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) most = max(most, __builtin_amdgcn_ubfe(old[i], shift_of(rel[i]), BITS));
+        if (most != kFull) return;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            full |= __builtin_amdgcn_ubfe(old[i], shift_of(rel[i]), BITS) == kFull ? 1u << i : 0u;
+        while (full) {
+            unsigned id = rel[0], word = old[0];
+#pragma unroll
+            for (int i = 1; i < N; ++i)
+                if (full & 1u << i) { // (the last one of them)
+                    id = rel[i];
+                    word = old[i];
+                }
+            full &= ~(1u << (31 - __clz((int)full)));
+            word >>= shift_of(id);
+            int f = (int)(id % FPW);
+            do {
+                if (id < (unsigned)nb) wrapped((int)id); // (not an id of this chunk, or carried into a field without one: nothing)
+                ++id;
+                ++f;
+                word >>= BITS;
+            } while (f < FPW && (word & kFull) == kFull);
+        }
     };
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
     typedef int i32x4 __attribute__((ext_vector_type(4)));
     const i32x4 *t4 = reinterpret_cast<const i32x4 *>(tokens);
-    constexpr int kUnroll = 4;                                      // 16-byte loads per thread and round
-    constexpr long long kIter = (long long)kHistBlock * kUnroll;    // groups per round of the workgroup
-    static_assert(kSweepBlock % (kHistBlock * kUnroll * 4) == 0, "a block of tokens is a whole number of rounds");
-    if (blockIdx.x == gridDim.x - 1) { // the stream's last one to three tokens, while the bins are still empty
+    constexpr int kUnroll = 4; // 16-byte loads per thread and round
+    // Pieces of 16 KB go round the workgroups, so that together they sweep the stream (contiguous slices lie a power of two
+    // apart for such streams, and their reads meet in the same memory channels).
+    const long long groups = n_tokens / 4, stride = (long long)gridDim.x * kHistBlock;
+    const long long first = (long long)blockIdx.x * kHistBlock + threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) { // the stream's last one to three tokens
         const long long i = groups * 4 + threadIdx.x;
-        if (i < n_tokens) one(tokens[i]);
+        if (i < n_tokens) count(std::integral_constant<int, 1>(), tokens + i);
     }
-    if (g0 < g1) {
-        // the loads of round i + 1 are requested before round i is counted; past the slice's end its last group is read
-        // again (and not counted)
-        auto fetch = [&](long long gb, i32x4(&v)[kUnroll]) {
+    if (groups > 0) {
+        // the loads of round i + 1 are requested before round i is counted; past the end the last group is read again
+        auto fetch = [&](long long r, i32x4(&v)[kUnroll]) {
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) v[u] = t4[min(gb + (long long)u * kHistBlock + threadIdx.x, g1 - 1)];
+            for (int u = 0; u < kUnroll; ++u) v[u] = t4[min(first + (r * kUnroll + u) * stride, groups - 1)];
         };
-        const long long rounds = (g1 - g0) / kIter; // whole ones
+        auto count_all = [&](const i32x4(&v)[kUnroll]) {
+            int t[4 * kUnroll];
+#pragma unroll
+            for (int i = 0; i < 4 * kUnroll; ++i) t[i] = v[i / 4][i % 4];
+            count(std::integral_constant<int, 4 * kUnroll>(), t);
+        };
+        const long long rounds = groups / (kUnroll * stride); // whole ones, of all workgroups alike
         i32x4 va[kUnroll], vb[kUnroll];
-        fetch(g0, va);
-        int since_sweep = 0; // tokens counted since the last sweep (uniform)
-        auto round = [&](long long r, const i32x4(&v)[kUnroll], i32x4(&next)[kUnroll]) {
-            fetch(g0 + (r + 1) * kIter, next);
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                one(v[u].x);
-                one(v[u].y);
-                one(v[u].z);
-                one(v[u].w);
-            }
-            since_sweep += (int)kIter * 4;
-            if (since_sweep >= kSweepBlock) {
-                sweep(kSweepAt);
-                since_sweep = 0;
-            }
-        };
+        fetch(0, va);
         long long r = 0;
         for (; r + 1 < rounds; r += 2) {
-            round(r, va, vb);
-            round(r + 1, vb, va);
+            fetch(r + 1, vb);
+            count_all(va);
+            fetch(r + 2, va);
+            count_all(vb);
         }
         if (r < rounds) {
-            round(r, va, vb);
+            fetch(r + 1, vb);
+            count_all(va);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) va[u] = vb[u];
         }
-        // what is left of the slice: less than a round, which fits what the sweeps leave room for
+        // what is left: less than a round
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u)
-            if (g0 + rounds * kIter + (long long)u * kHistBlock + threadIdx.x < g1) {
-                one(va[u].x);
-                one(va[u].y);
-                one(va[u].z);
-                one(va[u].w);
-            }
+            if (first + (rounds * kUnroll + u) * stride >= groups) va[u] = i32x4{-1, -1, -1, -1};
+        count_all(va);
     }
-    // What is left in the bins: with room for it, the workgroup's bins go to memory as they are (k_subset_reduce adds
-    // the workgroups' copies up); without, every non-zero field is added to the global counts (up to 80 000 atomics per
-    // workgroup, 19 M over the grid when every id occurs: slower than the counting itself).
+    __syncthreads();
+    for (int i = threadIdx.x; i < kTable; i += kHistBlock)
+        if (keys[i] != kNoKey) give((int)keys[i], wraps[i]);
+    // What is in the bins: with room for it, the workgroup's bins go to memory as they are (k_subset_reduce adds
+    // the workgroups' copies up); without, every non-zero field is added to the global counts (up to a vocabulary of
+    // atomics per workgroup, 39 M over the grid when every id occurs: slower than the counting itself).
     if (partials) {
-        __syncthreads();
-        unsigned *dst = partials + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (kChunkIds / 2);
+        unsigned *dst = partials + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * nw4;
         for (int i4 = threadIdx.x * 4; i4 < nw4; i4 += kHistBlock * 4)
             *reinterpret_cast<u32x4 *>(dst + i4) = *reinterpret_cast<const u32x4 *>(bins + i4);
     } else {
-        sweep(1u); // (begins with a barrier)
+        for (int i = threadIdx.x; i < nb; i += kHistBlock) { // (consecutive lanes, consecutive ids: few cache lines)
+            const unsigned x = bins[i / FPW] >> (i % FPW * BITS) & kFull;
+            if (x) atomicAdd(&counts[c0 + i], x);
+        }
     }
 }
 
-// counts[id] += the sum over the slices' workgroups of the id's field; thread = one word (two ids) of one chunk.
-// The final counts pass through here, so the first histogram pass of the selection (top digit), their sum and the copy
-// for the caller are taken along.
-constexpr int kSelBuckets0 = 2048;
-constexpr int kSumSlots = 64; // words the sum of all counts is spread over (same-address device atomics: ~40 ns each)
-__device__ __forceinline__ void add_to_sum(unsigned x, unsigned *sums) { // whole waves
+// state: [0] unused, [1] T, [2] n, then r at [3]; [4 + 2 p], [5 + 2 p]: prefix and ids still needed after the walk
+// of pass p; then the bucket counts of the passes, then per-workgroup (above, ties) totals of the compaction, then
+// the slots of the sum of all counts
+constexpr int kCmpGroups = 160; // workgroups of the compaction: one round of 1024 ids each at 151 680 ids
+constexpr int kSumSlots = 64;   // words the sum of all counts is spread over
+constexpr int kHistCopies = 2;  // and the bucket counts of a pass: a few dozen buckets hold most ids
+constexpr int kStateAfter = 4, kStateHist = 16, kStateTotals = kStateHist + kSelPasses * kSelBuckets * kHistCopies,
+              kStateSums = kStateTotals + 2 * kCmpGroups, kStateWordsFull = kStateSums + kSumSlots;
+static_assert(kStateAfter + 2 * kSelPasses <= kStateHist, "state layout");
+
+// The sum over the workgroup's threads, added to one of the slots: one atomic per workgroup (same-address device atomics
+// take ~40 ns each and those to one cache line little less: one per wave, 4752 of them, took 7 of 19 us).  scratch: a word
+// per wave.
+__device__ __forceinline__ void add_to_sum(unsigned x, unsigned *scratch, unsigned *sums) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) x += __shfl_xor(x, off, 64);
-    if ((threadIdx.x & 63) == 0 && x) atomicAdd(&sums[(blockIdx.x * 4 + (threadIdx.x >> 6)) % kSumSlots], x);
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = x;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    x = threadIdx.x < blockDim.x / 64 ? scratch[threadIdx.x] : 0u;
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off, 64);
+    if (threadIdx.x == 0 && x) atomicAdd(&sums[blockIdx.x % kSumSlots], x);
 }
-__global__ __launch_bounds__(256) void k_subset_reduce(const unsigned *__restrict__ partials, int slices, int V,
-                                                       unsigned *counts, unsigned *hist0, unsigned *sums, int *counts_out) {
-    __shared__ unsigned hist[kSelBuckets0];
-    for (int i = threadIdx.x; i < kSelBuckets0; i += 256) hist[i] = 0u;
-    __syncthreads();
-    const int c = blockIdx.y, c0 = c * kChunkIds, nb = min(kChunkIds, V - c0), nw = (nb + 1) / 2;
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool has_lo = w < nw, has_hi = w < nw && 2 * w + 1 < nb;
-    unsigned lo = 0u, hi = 0u;
-    if (has_lo) {
-        const unsigned *src = partials + (size_t)c * slices * (kChunkIds / 2) + w;
-        int sl = 0;
-        for (; sl + 32 <= slices; sl += 32) { // thirty-two loads in flight: the kernel is a chain of strided reads
-            unsigned x[32];
+
+// the workgroup's bucket counts of a pass, from LDS to one of the copies in the state
+__device__ __forceinline__ void put_hist(const unsigned *hist, int buckets, int pass, unsigned *state) {
+    unsigned *dst = state + kStateHist + (pass * kHistCopies + (int)(blockIdx.x % kHistCopies)) * kSelBuckets;
+    for (int i = threadIdx.x; i < buckets; i += blockDim.x)
+        if (hist[i]) atomicAdd(&dst[i], hist[i]);
+}
+
+// counts[id] += the sum over the slices' workgroups of the id's field.  Workgroup: 128 words of one chunk, two waves for
+// each eighth of the slices (all of whose loads are in flight at once: the kernel is a chain of strided reads, 12 us for 256 copies of 152 KB).  The final
+// counts pass through here, so the first histogram pass of the selection, their sum and the copy for the caller are taken along.
+constexpr int kReduceWords = 128;
+template <int BITS>
+__global__ __launch_bounds__(kSelBlock) void k_subset_reduce(const unsigned *__restrict__ partials, int slices, int V,
+                                                             int chunk_ids, SelPlan plan, unsigned *counts,
+                                                             unsigned *state, int *counts_out) {
+    constexpr int FPW = 32 / BITS, kParts = kSelBlock / kReduceWords;
+    __shared__ unsigned hist[kSelBuckets];
+    __shared__ unsigned sums[kParts][kReduceWords * FPW], scratch[kSelBlock / 64];
+    const int buckets = sel_buckets(plan, 0);
+    for (int i = threadIdx.x; i < buckets; i += kSelBlock) hist[i] = 0u;
+    const int c0 = blockIdx.y * chunk_ids, nb = min(chunk_ids, V - c0), nw = bin_words(chunk_ids, BITS);
+    const int part = threadIdx.x / kReduceWords, lw = threadIdx.x % kReduceWords;
+    const int w0 = blockIdx.x * kReduceWords, w = min(w0 + lw, nw - 1);
+    unsigned s[FPW];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) x[u] = src[(size_t)(sl + u) * (kChunkIds / 2)];
+    for (int f = 0; f < FPW; ++f) s[f] = 0u;
+    const unsigned *src = partials + (size_t)blockIdx.y * slices * nw + w;
+    auto take = [&](unsigned x) {
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                lo += x[u] & 0xffffu;
-                hi += x[u] >> 16;
-            }
-        }
-        for (; sl + 16 <= slices; sl += 16) {
-            unsigned x[16];
+        for (int f = 0; f < FPW; ++f) s[f] += x >> (f * BITS) & ((1u << BITS) - 1u);
+    };
+    int sl = part * slices / kParts;
+    const int end = (part + 1) * slices / kParts;
+    for (; sl + 32 <= end; sl += 32) {
+        unsigned x[32];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) x[u] = src[(size_t)(sl + u) * (kChunkIds / 2)];
+        for (int u = 0; u < 32; ++u) x[u] = src[(size_t)(sl + u) * nw];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                lo += x[u] & 0xffffu;
-                hi += x[u] >> 16;
-            }
-        }
-        for (; sl < slices; ++sl) {
-            const unsigned x = src[(size_t)sl * (kChunkIds / 2)];
-            lo += x & 0xffffu;
-            hi += x >> 16;
-        }
-        lo += counts[c0 + 2 * w]; // (the counting kernel, which may have added to these words, has finished)
-        counts[c0 + 2 * w] = lo;
-        if (counts_out) counts_out[c0 + 2 * w] = (int)lo;
+        for (int u = 0; u < 32; ++u) take(x[u]);
     }
-    if (has_hi) {
-        hi += counts[c0 + 2 * w + 1];
-        counts[c0 + 2 * w + 1] = hi;
-        if (counts_out) counts_out[c0 + 2 * w + 1] = (int)hi;
+    for (; sl + 8 <= end; sl += 8) {
+        unsigned x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = src[(size_t)(sl + u) * nw];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) take(x[u]);
     }
-    add_to_sum(lo + (has_hi ? hi : 0u), sums);
-    // top digit: almost every id has a zero there, so those are counted per wave (one LDS atomic instead of up to 128
-    // on the same word)
-    const unsigned dlo = lo >> 21, dhi = hi >> 21;
-    const unsigned zeros = (unsigned)__popcll(__builtin_amdgcn_ballot_w64(has_lo && dlo == 0u)) +
-                           (unsigned)__popcll(__builtin_amdgcn_ballot_w64(has_hi && dhi == 0u));
-    if ((threadIdx.x & 63) == 0 && zeros) atomicAdd(&hist[0], zeros);
-    if (has_lo && dlo) atomicAdd(&hist[dlo], 1u);
-    if (has_hi && dhi) atomicAdd(&hist[dhi], 1u);
+    for (; sl < end; ++sl) take(src[(size_t)sl * nw]);
+#pragma unroll
+    for (int f = 0; f < FPW; ++f) sums[part][lw * FPW + f] = s[f];
     __syncthreads();
-    for (int i = threadIdx.x; i < kSelBuckets0; i += 256)
-        if (hist[i]) atomicAdd(&hist0[i], hist[i]);
+    unsigned total = 0u;
+    for (int base = 0; base < kReduceWords * FPW; base += kSelBlock) { // (whole waves go round together)
+        const int i = base + (int)threadIdx.x, id = w0 * FPW + i;
+        const bool has = i < kReduceWords * FPW && id < nb;
+        unsigned c = 0u;
+        if (has) {
+#pragma unroll
+            for (int q = 0; q < kCountCopies; ++q) c += counts[q * round4(V) + c0 + id]; // (what the counting kernel has given here)
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) c += sums[q][i];
+            counts[c0 + id] = c;
+            if (counts_out) counts_out[c0 + id] = (int)c;
+            total += c;
+        }
+        // ids that do not occur are counted per wave (one LDS atomic instead of up to 64 on the same word)
+        const unsigned digit = sel_key(plan, c) >> plan.shift[0];
+        const unsigned zeros = (unsigned)__popcll(__builtin_amdgcn_ballot_w64(has && digit == 0u));
+        if ((threadIdx.x & 63) == 0 && zeros) atomicAdd(&hist[0], zeros);
+        if (has && digit) atomicAdd(&hist[digit], 1u);
+    }
+    add_to_sum(total, scratch, state + kStateSums); // (a barrier: the bucket counts are complete)
+    if (plan.passes) put_hist(hist, buckets, 0, state);
 }
 
 // ---- selection: T = the n-th largest count, r = how many ids with count == T belong to the n most frequent ----
 // (1 <= r when n >= 1; #(count > T) = n - r).  A radix select, most significant digit first: pass p histograms digit
-// p of the counts that agree with the prefix found so far (kSelGroups workgroups, each in LDS first); the kernel that
+// p of the keys that agree with the prefix found so far (kSelGroups workgroups, each in LDS first); the kernel that
 // follows walks the buckets from the top to the one that holds the n-th largest, every workgroup for itself.
-constexpr int kSelGroups = 64;  // workgroups of a histogram pass of the selection
-constexpr int kCmpGroups = 160; // workgroups of the compaction: one round of 1024 ids each at 151 680 ids
-constexpr int kSelPasses = 3, kSelBuckets = 2048;
-__host__ __device__ constexpr int sel_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
-__host__ __device__ constexpr int sel_bits(int pass) { return pass == 2 ? 10 : 11; }
-// state: [0] unused, [1] T, [2] n, then r at [3]; [4 + 2 p], [5 + 2 p]: prefix and ids still needed after the walk
-// of pass p; then kSelPasses x kSelBuckets bucket counts, then per-workgroup (above, ties) totals of the compaction, then
-// the slots of the sum of all counts
-constexpr int kStateAfter = 4, kStateHist = 16, kStateTotals = kStateHist + kSelPasses * kSelBuckets,
-              kStateSums = kStateTotals + 2 * kCmpGroups, kStateWordsFull = kStateSums + kSumSlots;
+constexpr int kSelGroups = 64; // workgroups of a histogram pass of the selection
 
 // inclusive scan of one value per thread over the workgroup; scratch holds one word per wave; returns the total too
 __device__ __forceinline__ unsigned block_scan(unsigned v, unsigned *scratch, unsigned &total) {
@@ -273,34 +330,47 @@ __device__ __forceinline__ unsigned block_scan(unsigned v, unsigned *scratch, un
 }
 
 // The walk over the buckets of pass `pass`, by the whole workgroup: from the largest digit down to the bucket that
-// holds the need-th largest of the counts that agree with the prefix.  Returns the prefix extended by that digit and
+// holds the need-th largest of the keys that agree with the prefix.  Returns the prefix extended by that digit and
 // the ids still needed from inside the bucket.  Every workgroup of a kernel computes the same values; workgroup 0
 // leaves them in the state for the kernels after this one (kStateAfter).
-__device__ __forceinline__ void sel_walk(unsigned *state, int pass, unsigned *scratch, unsigned *found,
+__device__ __forceinline__ void sel_walk(unsigned *state, const SelPlan &plan, int pass, unsigned *scratch, unsigned *found,
                                          unsigned &prefix, unsigned &need) {
     const unsigned prefix_in = pass == 0 ? 0u : state[kStateAfter + 2 * (pass - 1)];
     const unsigned need_in = pass == 0 ? state[2] : state[kStateAfter + 2 * (pass - 1) + 1];
-    const unsigned *hist = state + kStateHist + pass * kSelBuckets;
-    const int nbuckets = 1 << sel_bits(pass);
-    // thread t holds buckets nbuckets - 1 - 2 t and nbuckets - 2 - 2 t: the scan runs from the top
-    const int hi = nbuckets - 1 - 2 * (int)threadIdx.x, lo = hi - 1;
-    const unsigned a = hi >= 0 ? hist[hi] : 0u, b = lo >= 0 ? hist[lo] : 0u;
+    const unsigned *hist = state + kStateHist + pass * kHistCopies * kSelBuckets;
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kMine = kSelBuckets / kSelBlock; // buckets of a thread, the scan runs from the top
+    static_assert(kMine == 4, "one 16-byte load per copy");
+    const int top = (sel_buckets(plan, pass) + kMine - 1) / kMine * kMine - 1 - kMine * (int)threadIdx.x; // its highest
+    unsigned a[kMine] = {0u, 0u, 0u, 0u};
+    if (top >= 0) {
+        u32x4 x[kHistCopies];
+#pragma unroll
+        for (int c = 0; c < kHistCopies; ++c) x[c] = *reinterpret_cast<const u32x4 *>(hist + c * kSelBuckets + top - (kMine - 1));
+#pragma unroll
+        for (int q = 0; q < kMine; ++q)
+#pragma unroll
+            for (int c = 0; c < kHistCopies; ++c) a[q] += x[c][kMine - 1 - q];
+    }
+    const unsigned mine = a[0] + a[1] + a[2] + a[3];
     unsigned total;
-    const unsigned incl = block_scan(a + b, scratch, total), excl = incl - (a + b);
+    const unsigned incl = block_scan(mine, scratch, total);
     if (threadIdx.x == 0) { // fewer candidates than needed cannot happen (need <= their number); bucket 0 if it did
         found[0] = 0u;
         found[1] = need_in > total ? 0u : need_in;
     }
     __syncthreads();
-    if (hi >= 0 && excl < need_in && need_in <= excl + a) {
-        found[0] = (unsigned)hi;
-        found[1] = need_in - excl;
-    } else if (lo >= 0 && excl + a < need_in && need_in <= incl) {
-        found[0] = (unsigned)lo;
-        found[1] = need_in - excl - a;
+    unsigned above = incl - mine;
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+        if (above < need_in && need_in <= above + a[q]) { // (an empty bucket never)
+            found[0] = (unsigned)(top - q);
+            found[1] = need_in - above;
+        }
+        above += a[q];
     }
     __syncthreads();
-    prefix = prefix_in | (found[0] << sel_shift(pass));
+    prefix = prefix_in | (found[0] << plan.shift[pass]);
     need = found[1];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         state[kStateAfter + 2 * pass] = prefix;
@@ -309,35 +379,35 @@ __device__ __forceinline__ void sel_walk(unsigned *state, int pass, unsigned *sc
     __syncthreads(); // found and scratch may be reused
 }
 
-__global__ __launch_bounds__(kSelBlock) void k_subset_sel_hist(const unsigned *__restrict__ counts, int V, int pass,
-                                                               unsigned *state) {
+__global__ __launch_bounds__(kSelBlock) void k_subset_sel_hist(const unsigned *__restrict__ counts, int V, SelPlan plan,
+                                                               int pass, unsigned *state) {
     __shared__ unsigned hist[kSelBuckets];
     __shared__ unsigned scratch[kSelBlock / 64], found[2];
-    for (int i = threadIdx.x; i < kSelBuckets; i += kSelBlock) hist[i] = 0u;
+    const int buckets = sel_buckets(plan, pass);
+    for (int i = threadIdx.x; i < buckets; i += kSelBlock) hist[i] = 0u;
     unsigned prefix = 0u, need = 0u;
-    if (pass > 0) sel_walk(state, pass - 1, scratch, found, prefix, need);
+    if (pass > 0) sel_walk(state, plan, pass - 1, scratch, found, prefix, need);
     __syncthreads();
-    const int shift = sel_shift(pass);
-    const unsigned digit = (1u << sel_bits(pass)) - 1u;
-    const unsigned mask = pass == 0 ? 0u : 0xffffffffu << sel_shift(pass - 1);
+    const int shift = plan.shift[pass];
+    const unsigned digit = (1u << plan.bits[pass]) - 1u;
+    const unsigned mask = pass == 0 ? 0u : 0xffffffffu << plan.shift[pass - 1];
     const int per = (V + gridDim.x - 1) / gridDim.x, v0 = blockIdx.x * per, v1 = min(V, v0 + per);
     for (int v = v0 + threadIdx.x; v < v1; v += kSelBlock) {
-        const unsigned c = counts[v];
-        if ((c & mask) == prefix) atomicAdd(&hist[(c >> shift) & digit], 1u);
+        const unsigned key = sel_key(plan, counts[v]);
+        if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & digit], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kSelBuckets; i += kSelBlock)
-        if (hist[i]) atomicAdd(&state[kStateHist + pass * kSelBuckets + i], hist[i]);
+    put_hist(hist, buckets, pass, state);
 }
 
 // ---- compaction: the ids in ascending order, those with count > T plus the first r ties ----
 // Workgroup g owns a contiguous range of ids.  First every workgroup counts its (above, ties); then it adds up what the
 // workgroups before it hold (at most kSelGroups pairs) and places its own ids by two workgroup scans.
-__global__ __launch_bounds__(kSelBlock) void k_subset_cmp_count(const unsigned *__restrict__ counts, int V,
+__global__ __launch_bounds__(kSelBlock) void k_subset_cmp_count(const unsigned *__restrict__ counts, int V, SelPlan plan,
                                                                 unsigned *state) {
     __shared__ unsigned scratch[kSelBlock / 64], found[2];
-    unsigned T, r; // the last walk: the prefix is now the whole count
-    sel_walk(state, kSelPasses - 1, scratch, found, T, r);
+    unsigned T, r; // the last walk: the prefix is now the whole key, and T, being a count of a listed id, is its own key
+    sel_walk(state, plan, plan.passes - 1, scratch, found, T, r);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         state[1] = T;
         state[3] = r;
@@ -402,9 +472,10 @@ __global__ __launch_bounds__(kSelBlock) void k_subset_cmp_write(const unsigned *
 
 // the sum of all counts, where k_subset_reduce has not formed it
 __global__ __launch_bounds__(256) void k_subset_sum(const unsigned *__restrict__ counts, int V, unsigned *sums) {
+    __shared__ unsigned scratch[256 / 64];
     unsigned x = 0u;
     for (int v = blockIdx.x * 256 + threadIdx.x; v < V; v += gridDim.x * 256) x += counts[v];
-    add_to_sum(x, sums);
+    add_to_sum(x, scratch, sums);
 }
 __global__ void k_subset_export(const unsigned *counts, int V, const unsigned *state, long long n_tokens, int *counts_out,
                                 int *invalid_out) {
@@ -420,7 +491,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // the library runs on holds its own copy at its own address until the process ends; host code reaches it only through
 // the per-device pointer below (the array's name is a host-side stand-in, not a device address).
 constexpr int kStaticMaxVocab = 262144;
-constexpr int kStateWordsFullStatic = 16 + 3 * 2048 + 2 * 160 + 64; // = kStateWordsFull (spelled out: used in the array bound)
+constexpr int kStateWordsFullStatic = 16 + 3 * 4096 * 2 + 2 * 160 + 64; // = kStateWordsFull (spelled out: used in the array bound)
 __device__ __align__(256) unsigned scratch[kStaticMaxVocab + kStateWordsFullStatic];
 static_assert(kStateWordsFullStatic == kStateWordsFull, "scratch layout");
 constexpr int kMaxDevices = 64;
@@ -428,17 +499,25 @@ unsigned *g_scratch_ptr[kMaxDevices]; // per device: address of that device's co
 bool g_lds_allowed[kMaxDevices];      // per device: the counting kernel may use all the LDS of a CU
 std::mutex g_setup_mutex;
 
+typedef void (*hist_kernel_t)(const int *, long long, int, int, unsigned *, int, unsigned *);
+hist_kernel_t hist_kernel(int bits) { return bits == 16 ? k_subset_hist<16> : bits == 8 ? k_subset_hist<8> : k_subset_hist<6>; }
+typedef void (*reduce_kernel_t)(const unsigned *, int, int, int, SelPlan, unsigned *, unsigned *, int *);
+reduce_kernel_t reduce_kernel(int bits) {
+    return bits == 16 ? k_subset_reduce<16> : bits == 8 ? k_subset_reduce<8> : k_subset_reduce<6>;
+}
+
 // once per device, with that device current: raise the LDS limit of the counting kernel and (for the static entry
 // point) look up the device's copy of the scratch array
 int32_t subset_setup(int dev, bool want_scratch, unsigned **scratch_out) {
     if (dev < 0 || dev >= kMaxDevices) return MTP_ERR_CONFIG;
     std::lock_guard<std::mutex> lock(g_setup_mutex);
     if (!g_lds_allowed[dev]) {
-        if (hipFuncSetAttribute((const void *)k_subset_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kChunkIds * 2) != hipSuccess) {
-            (void)hipGetLastError();
-            return MTP_ERR_HIP;
-        }
+        for (int bits : {16, 8, 6})
+            if (hipFuncSetAttribute((const void *)hist_kernel(bits), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)hist_lds_bytes(chunk_capacity(bits), bits)) != hipSuccess) {
+                (void)hipGetLastError();
+                return MTP_ERR_HIP;
+            }
         g_lds_allowed[dev] = true;
     }
     if (want_scratch) {
@@ -455,37 +534,30 @@ int32_t subset_setup(int dev, bool want_scratch, unsigned **scratch_out) {
     return MTP_OK;
 }
 
-// workgroups per chunk of the counting kernel: 256 workgroups in all (one per CU of the device this is written for),
-// fixed so that the workspace size does not depend on the device
-// (a multiple of eight: the chunks' workgroups of a slice then share a compute die, see k_subset_hist)
-int subset_slices(int V) {
-    const int s = 256 / ((V + kChunkIds - 1) / kChunkIds);
-    return s >= 8 ? s / 8 * 8 : std::max(1, s);
-}
-size_t subset_partial_words(int V) { return (size_t)subset_slices(V) * ((V + kChunkIds - 1) / kChunkIds) * (kChunkIds / 2); }
-
-// everything after the argument checks: `work` holds V counts followed by the selection state and, with_partials, by
-// one copy of the bins per workgroup of the counting kernel
+// everything after the argument checks: `work` holds V counts (with_partials: kCountCopies of them) followed by the selection
+// state and, with_partials, by one copy of the bins per workgroup of the counting kernel
 int32_t subset_build_on(const int32_t *tokens, int64_t n_tokens, int32_t V, int32_t n, unsigned *work, bool with_partials,
                         int32_t *ids_out, int32_t *counts_out, int32_t *invalid_out, hipStream_t st) {
     unsigned *counts = work;
-    unsigned *state = counts + V;
-    unsigned *partials = with_partials ? work + ((size_t)V + kStateWordsFull + 3) / 4 * 4 : nullptr; // 16-byte aligned
-    hipLaunchKernelGGL(k_subset_clear, dim3((V + kStateWordsFull + 255) / 256), dim3(256), 0, st, counts, V, state,
-                       kStateWordsFull, n);
-    const int chunks = (V + kChunkIds - 1) / kChunkIds;
-    const int slices = subset_slices(V);
-    hipLaunchKernelGGL(k_subset_hist, dim3(slices, chunks), dim3(kHistBlock), kChunkIds * 2, st, tokens,
-                       (long long)n_tokens, V, counts, partials);
+    const int copies = with_partials ? kCountCopies : 1;
+    unsigned *state = counts + copies * round4(V);
+    unsigned *partials = with_partials ? state + round4(kStateWordsFull) : nullptr; // (all at multiples of 16 bytes)
+    const size_t clear = copies * round4(V) + round4(kStateWordsFull);
+    hipLaunchKernelGGL(k_subset_clear, dim3((unsigned)((clear / 4 + 255) / 256)), dim3(256), 0, st, work, clear, state, n);
+    const CountPlan cp = count_plan(V);
+    const SelPlan sp = sel_plan(n_tokens, n);
+    const int slices = stream_slices(cp, n_tokens, with_partials);
+    hipLaunchKernelGGL(hist_kernel(cp.bits), dim3(slices, cp.chunks), dim3(kHistBlock), hist_lds_bytes(cp.chunk_ids, cp.bits),
+                       st, tokens, (long long)n_tokens, V, cp.chunk_ids, counts, copies, partials);
     if (partials)
-        hipLaunchKernelGGL(k_subset_reduce, dim3((kChunkIds / 2 + 255) / 256, chunks), dim3(256), 0, st, partials, slices,
-                           V, counts, state + kStateHist, state + kStateSums, counts_out);
+        hipLaunchKernelGGL(reduce_kernel(cp.bits), dim3((bin_words(cp.chunk_ids, cp.bits) + kReduceWords - 1) / kReduceWords, cp.chunks),
+                           dim3(kSelBlock), 0, st, partials, slices, V, cp.chunk_ids, sp, counts, state, counts_out);
     else if (invalid_out)
         hipLaunchKernelGGL(k_subset_sum, dim3(64), dim3(256), 0, st, counts, V, state + kStateSums);
     if (n > 0) {
-        for (int pass = partials ? 1 : 0; pass < kSelPasses; ++pass) // (with partials, pass 0 was taken along above)
-            hipLaunchKernelGGL(k_subset_sel_hist, dim3(kSelGroups), dim3(kSelBlock), 0, st, counts, V, pass, state);
-        hipLaunchKernelGGL(k_subset_cmp_count, dim3(kCmpGroups), dim3(kSelBlock), 0, st, counts, V, state);
+        for (int pass = partials ? 1 : 0; pass < sp.passes; ++pass) // (with partials, pass 0 was taken along above)
+            hipLaunchKernelGGL(k_subset_sel_hist, dim3(kSelGroups), dim3(kSelBlock), 0, st, counts, V, sp, pass, state);
+        hipLaunchKernelGGL(k_subset_cmp_count, dim3(kCmpGroups), dim3(kSelBlock), 0, st, counts, V, sp, state);
         hipLaunchKernelGGL(k_subset_cmp_write, dim3(kCmpGroups), dim3(kSelBlock), 0, st, counts, V, n, state, ids_out,
                            (long long)n_tokens, invalid_out);
     }
@@ -514,7 +586,7 @@ extern "C" {
 
 size_t mtp_subset_workspace_bytes(int32_t vocab_size) {
     if (vocab_size < 1) return 0;
-    return (((size_t)vocab_size + kStateWordsFull + 3) / 4 * 4 + subset_partial_words(vocab_size)) * 4;
+    return (kCountCopies * round4(vocab_size) + round4(kStateWordsFull) + partial_words(count_plan(vocab_size))) * 4;
 }
 
 int32_t mtp_subset_build(const int32_t *tokens, int64_t n_tokens, int32_t vocab_size, int32_t n, void *workspace,

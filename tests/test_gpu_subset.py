@@ -65,3 +65,41 @@ def test_full_vocabulary_and_use_as_output_head_list(gpu):
     eng = binding.DraftEngine(tiny.shape, synth.make_weights(tiny), [lst], 1, 192, 1)
     assert eng.subset_size(0) == 1024
     eng.close()
+
+
+@pytest.mark.parametrize("V", [80768, 80769, 155392, 155393, 201920, 201921])
+def test_every_field_width_and_chunk(gpu, V):
+    """The largest vocabulary of each field width and of a chunk, and one id more: hot ids at both ends and in the middle of the
+    words, a long tail, ids out of range."""
+    rng = np.random.default_rng(V)
+    hot = rng.choice([0, 1, 2, 3, 4, V // 2, V - 2, V - 1], size=1 << 18)
+    toks = np.concatenate([hot, rng.integers(-3, V + 3, size=(1 << 20) + 5)])
+    rng.shuffle(toks)
+    both(gpu, toks, V, V // 7)
+
+
+@pytest.mark.parametrize("V,base,ids,logN", [
+    (4096, 0, 1, 21),          # one id: every add goes to one field, whose wraps carry into a neighbour that never occurs
+    (4096, 8, 2, 24),          # 16-bit fields that wrap together, the second one carried into by the first
+    (100000, 40, 8, 20),       # 8 bits: whole words full at a time, so that a carry runs through several fields
+    (100000, 99996, 4, 20),    # the last word
+    (160000, 155, 400, 23),    # 6 bits, more ids that wrap than the table has room for
+    (100000, 1000, 4000, 24),  # 8 bits: a few wraps each
+    (160001, 159996, 5, 20),   # the last word of the last id has one field in use
+])
+def test_fields_that_wrap(gpu, V, base, ids, logN):
+    """A field narrower than its count: exact counts whatever the order of the adds."""
+    rng = np.random.default_rng(V + ids)
+    toks = base + rng.integers(0, ids, size=(1 << logN) + 1)
+    both(gpu, toks, V, 3)
+    if logN <= 21:  # and in runs: all lanes of a wave at one field
+        both(gpu, np.sort(toks), V, 3)
+
+
+@pytest.mark.parametrize("V,N,n", [(300, (1 << 24) + 64, 1), (300, 1 << 16, 16), (5000, 4095 * 16, 16), (70000, 1 << 20, 60000)])
+def test_selection_in_one_to_three_digits(gpu, V, N, n):
+    """The cut at counts of 25, 13, 12 and few bits: the digits follow from n_tokens / n; ids that occur more often than that
+    all share the last bucket."""
+    rng = np.random.default_rng(N % 1009)
+    toks = np.concatenate([np.zeros(N // 2, dtype=np.int64), rng.integers(0, V, size=N - N // 2)])
+    both(gpu, toks, V, n)
