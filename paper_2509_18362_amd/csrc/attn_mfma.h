@@ -450,13 +450,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
             lsum = lsum * alpha + psum;
             uint32_t ph[4], pl[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                uint16_t h0, l0, h1, l1;
-                split_bf16(pv[2 * e], h0, l0);
-                split_bf16(pv[2 * e + 1], h1, l1);
-                ph[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                pl[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-            }
+            for (int e = 0; e < 4; ++e) split_bf16x2(pv[2 * e], pv[2 * e + 1], ph[e], pl[e]);
             const u32x4 pH = {ph[0], ph[1], ph[2], ph[3]}, pL = {pl[0], pl[1], pl[2], pl[3]};
 
             if constexpr (L::VREG) {

@@ -644,11 +644,10 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     // and barriers on a few CUs, not a bandwidth problem.  The winner's embedding row is asked for as soon as its id is known, and
     // the hidden half is formed while it travels (5 sequences 8.1 us -> 7.3, 16 9.2 -> 8.4).
     auto split_store = [&](uint16_t *dh, uint16_t *dl, size_t e, const float (&o)[4]) {
-        uint16_t h[4], l[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) split_bf16(o[q], h[q], l[q]);
-        *reinterpret_cast<u32x2 *>(dh + e) = u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-        *reinterpret_cast<u32x2 *>(dl + e) = u32x2{(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+        u32x2 h, l;
+        split_bf16x4(o, h, l);
+        *reinterpret_cast<u32x2 *>(dh + e) = h;
+        *reinterpret_cast<u32x2 *>(dl + e) = l;
     };
     auto load_bf16x4 = [&](const uint16_t *src, int e, float (&v)[4]) {
         const u32x2 raw = *reinterpret_cast<const u32x2 *>(src + e);

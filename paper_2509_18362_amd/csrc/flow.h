@@ -324,13 +324,10 @@ __device__ __forceinline__ void flow_norm(float (&v)[kMaxNormIter][4], const u32
             o[1] = hi_half(g.x) * (v[it][1] * inv);
             o[2] = lo_half(g.y) * (v[it][2] * inv);
             o[3] = hi_half(g.y) * (v[it][3] * inv);
-            uint16_t h[4], l[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) split_bf16(o[q], h[q], l[q]);
-            *reinterpret_cast<u32x2 *>(hi + e) =
-                u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-            *reinterpret_cast<u32x2 *>(lo + e) =
-                u32x2{(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+            u32x2 h, l;
+            split_bf16x4(o, h, l);
+            *reinterpret_cast<u32x2 *>(hi + e) = h;
+            *reinterpret_cast<u32x2 *>(lo + e) = l;
             const f32x4 w = {o[0], o[1], o[2], o[3]};
             if (keep_norm) *reinterpret_cast<f32x4 *>(keep_norm + e) = w;
             if (out_global) *reinterpret_cast<f32x4 *>(out_global + e) = w;
@@ -343,11 +340,10 @@ __device__ __forceinline__ void flow_norm(float (&v)[kMaxNormIter][4], const u32
 
 // four floats of this thread -> hi/lo at element e
 __device__ __forceinline__ void flow_split4(const float (&m)[4], uint16_t *hi, uint16_t *lo, int e) {
-    uint16_t h[4], l[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) split_bf16(m[q], h[q], l[q]);
-    *reinterpret_cast<u32x2 *>(hi + e) = u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-    *reinterpret_cast<u32x2 *>(lo + e) = u32x2{(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+    u32x2 h, l;
+    split_bf16x4(m, h, l);
+    *reinterpret_cast<u32x2 *>(hi + e) = h;
+    *reinterpret_cast<u32x2 *>(lo + e) = l;
 }
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return (g / (1.0f + expf(-g))) * u; }

@@ -299,11 +299,8 @@ __device__ __forceinline__ void stage_rmsnorm(const void *src, const uint16_t *g
             o[1] = hi_half(g.x) * (v[it][1] * inv);
             o[2] = lo_half(g.y) * (v[it][2] * inv);
             o[3] = hi_half(g.y) * (v[it][3] * inv);
-            uint16_t h[4], l[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) split_bf16(o[q], h[q], l[q]);
-            u32x2 ph = {(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-            u32x2 pl = {(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+            u32x2 ph, pl;
+            split_bf16x4(o, ph, pl);
             *reinterpret_cast<u32x2 *>(hi + e) = ph;
             *reinterpret_cast<u32x2 *>(lo + e) = pl;
             f32x4 w = {o[0], o[1], o[2], o[3]};
@@ -363,11 +360,8 @@ __device__ __forceinline__ void stage_rmsnorm_wave(const void *src, const uint16
         u32x2 g = *reinterpret_cast<const u32x2 *>(gain + e);
         float o[4] = {lo_half(g.x) * (v[0] * inv), hi_half(g.x) * (v[1] * inv), lo_half(g.y) * (v[2] * inv),
                       hi_half(g.y) * (v[3] * inv)};
-        uint16_t h[4], l[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) split_bf16(o[q], h[q], l[q]);
-        u32x2 ph = {(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-        u32x2 pl = {(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+        u32x2 ph, pl;
+        split_bf16x4(o, ph, pl);
         *reinterpret_cast<u32x2 *>(hi + e) = ph;
         *reinterpret_cast<u32x2 *>(lo + e) = pl;
         f32x4 w = {o[0], o[1], o[2], o[3]};
@@ -410,15 +404,8 @@ __device__ __forceinline__ void stage_plain(const float *src, int K, int kpad, u
         u32x2 ph = {0u, 0u}, pl = {0u, 0u};
         if (e < K) {
             f32x4 raw = ld_f32x4<COH>(src + e);
-            uint16_t h[4], l[4];
-            split_bf16(raw.x, h[0], l[0]);
-            split_bf16(raw.y, h[1], l[1]);
-            split_bf16(raw.z, h[2], l[2]);
-            split_bf16(raw.w, h[3], l[3]);
-            ph.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-            ph.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-            pl.x = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
-            pl.y = (uint32_t)l[2] | ((uint32_t)l[3] << 16);
+            const float v[4] = {raw.x, raw.y, raw.z, raw.w};
+            split_bf16x4(v, ph, pl);
         }
         *reinterpret_cast<u32x2 *>(hi + e) = ph;
         *reinterpret_cast<u32x2 *>(lo + e) = pl;
@@ -436,13 +423,7 @@ __device__ __forceinline__ void stage_swiglu(const float *gu, int F, int kpad, u
             f32x4 u = ld_f32x4<COH>(gu + F + e);
             float m[4] = {(g.x / (1.0f + expf(-g.x))) * u.x, (g.y / (1.0f + expf(-g.y))) * u.y,
                           (g.z / (1.0f + expf(-g.z))) * u.z, (g.w / (1.0f + expf(-g.w))) * u.w};
-            uint16_t h[4], l[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) split_bf16(m[q], h[q], l[q]);
-            ph.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-            ph.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-            pl.x = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
-            pl.y = (uint32_t)l[2] | ((uint32_t)l[3] << 16);
+            split_bf16x4(m, ph, pl);
         }
         *reinterpret_cast<u32x2 *>(hi + e) = ph;
         *reinterpret_cast<u32x2 *>(lo + e) = pl;
