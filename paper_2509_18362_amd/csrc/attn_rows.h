@@ -1,0 +1,274 @@
+// Attention of a long block of new positions (a prompt or a piece of one, the teacher-forced forward) on the matrix cores
+// (gfx950): a workgroup of four or eight waves per (sequence, KV head, 16 / G neighbouring positions).
+//
+// The block's keys and values are in the cache; the sixteen MFMA columns are G query heads of 16 / G positions, which read every
+// key and value together, as in phase_attn_mfma (layouts and arithmetic are that kernel's; there the reasons).  There such an
+// item has a compute unit to itself (eight waves, 127 KB of LDS) and its splits meet in memory: right for few items of
+// thousands of tokens.  With hundreds of positions there are several items for every unit, each of them two rounds of tokens
+// between 5 us of set-up and 5 us until the waves' results have met.  Here an item is small - 33 KB of LDS, the merge in the
+// place of the tiles, results written whole - so that several of them share a unit and one's set-up and merge pass while others
+// multiply.  What bounds it is the chain of a wave's rounds of 32 tokens, 1.2 us each.  509 positions of an
+// empty cache, 32 query and 8 KV heads of 128: 75 us there, 24 here (four waves; eight: 34; with the registers cut for three or four
+// waves per SIMD 26 and 40, with a wave per item and no merge 43).  Where there are fewer items than units, eight waves: 16
+// sequences x 4 behind 512 .. 4096 tokens 52 us there, 49 here (four: 50), one x 4 behind 2048 20 and 17.5 (22).
+#pragma once
+#include "attn_mfma.h"
+
+namespace mtp {
+
+template <int G, int HD, int W>
+struct AttnRowsLds {
+    static constexpr int NC = 16, VS = HD * 2 + 16;
+    static constexpr bool VREG = HD == 128;
+    struct Tiles {
+        alignas(16) uint16_t qs[2][NC][HD + 8];
+        alignas(16) unsigned char k[W][16][VS];
+        alignas(16) unsigned char v[VREG ? 1 : W][VREG ? 1 : 32][VS];
+    };
+    struct Merge { // (columns four banks apart)
+        alignas(16) float acc[W][NC][HD + 4];
+        float ml[W][NC][2];
+    };
+    union {
+        Tiles t;
+        Merge m;
+    };
+};
+
+// W: waves of the workgroup
+template <int G, int HD, int W>
+__device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
+    using L = AttnRowsLds<G, HD, W>;
+    constexpr int kThreads = W * kWave;
+    constexpr int JP = 16 / G, NC = 16, NS = HD / 32, NDB = HD / 16, LPT = HD / 8, TPI = kWave / LPT, NV = 32 / TPI;
+    constexpr float kLog2e = 1.4426950408889634f;
+    const int lane = threadIdx.x & (kWave - 1), i16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    L &lds = *reinterpret_cast<L *>(smem);
+    auto &s = lds.t;
+    const int nseq = p.ext_B, mpos = p.B / nseq, JG = (mpos + JP - 1) / JP;
+    const int kvh = blockIdx.x % p.Hkv, unit = blockIdx.x / p.Hkv;
+    const int b = unit % nseq, jg = JG - 1 - unit / nseq; // the longest first
+    int len = 0, lenj[JP]; // tokens the longest position sees, and each (0: not part of the block)
+#pragma unroll
+    for (int jp = 0; jp < JP; ++jp) lenj[jp] = p.kv_len[min(jg * JP + jp, mpos - 1) * nseq + b];
+#pragma unroll
+    for (int jp = 0; jp < JP; ++jp) {
+        const int L = __builtin_amdgcn_readfirstlane(lenj[jp]);
+        lenj[jp] = jg * JP + jp < mpos && L >= 0 && L + p.K <= p.cap ? L + 1 : 0; // (seq_dead)
+        len = max(len, lenj[jp]);
+    }
+    if (len == 0) return;
+    const uint16_t *kc = p.k_cache + ((size_t)b * p.Hkv + kvh) * p.cap * HD;
+    const uint16_t *vc = p.v_cache + ((size_t)b * p.Hkv + kvh) * p.cap * HD;
+    u32x4 kn[2][NS], vr[NV];
+    auto load_k = [&](int it) { // past the end: the last row again
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                const int tok = min(it * 32 + tl * 16 + u * TPI + lane / LPT, len - 1);
+                kn[tl][u] = ldg16(kc + (size_t)tok * HD + (lane % LPT) * 8);
+            }
+    };
+    auto load_v = [&](int it) {
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int tok = min(it * 32 + u * TPI + lane / LPT, len - 1);
+            vr[u] = ldg16(vc + (size_t)tok * HD + (lane % LPT) * 8);
+        }
+    };
+    // the query: thread -> elements jj and jj + HD/2 of columns c0 .. c0 + NQ - 1, neighbours so that few positions are turned
+    constexpr int CL = kThreads / (HD / 2), NQ = NC / CL;
+    const int jj = threadIdx.x % (HD / 2), c0 = threadIdx.x / (HD / 2) * NQ;
+    const double inv_freq = p.rope_inv[jj];
+    float qa[NQ], qb[NQ];
+    uint16_t ba[NQ], bb[NQ];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+        const int c = c0 + k, hq = kvh * G + c % G;
+        const float *src = p.qkv + (size_t)(min(jg * JP + c / G, mpos - 1) * nseq + b) * p.qkv_dim + (size_t)hq * HD;
+        qa[k] = src[jj];
+        qb[k] = src[jj + HD / 2];
+        ba[k] = p.b_q ? p.b_q[hq * HD + jj] : (uint16_t)0;
+        bb[k] = p.b_q ? p.b_q[hq * HD + jj + HD / 2] : (uint16_t)0;
+    }
+    load_k(wave);
+    load_v(wave);
+    const float scale = 1.0f / sqrtf((float)HD);
+    float cs = 1.f, sn = 0.f;
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+        const int c = c0 + k;
+        if (k % (G < NQ ? G : NQ) == 0) {
+            int pos = 0;
+#pragma unroll
+            for (int u = 0; u < JP; ++u) pos = u == c / G ? max(lenj[u] - 1, 0) : pos;
+            rope_cos_sin(pos, inv_freq, cs, sn);
+        }
+        const float a = qa[k] + bf16_to_f32(ba[k]), e = qb[k] + bf16_to_f32(bb[k]);
+        split_bf16((a * cs - e * sn) * scale * kLog2e, s.qs[0][c][jj], s.qs[1][c][jj]);
+        split_bf16((e * cs + a * sn) * scale * kLog2e, s.qs[0][c][jj + HD / 2], s.qs[1][c][jj + HD / 2]);
+    }
+    lds_barrier();
+    // (a strip is written and read by its wave's own lanes; LDS operations of a wave complete in order)
+    auto ordered = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    u32x4 qh[NS], ql[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const int at = g4 * (HD / 4) + u * 8;
+        qh[u] = *reinterpret_cast<const u32x4 *>(&s.qs[0][i16][at]);
+        ql[u] = *reinterpret_cast<const u32x4 *>(&s.qs[1][i16][at]);
+    }
+    int lim = 0; // tokens this lane's column sees
+#pragma unroll
+    for (int u = 0; u < JP; ++u) lim = u == i16 / G ? lenj[u] : lim;
+    float mx = -INFINITY, lsum = 0.f;
+    f32x4 oacc[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    unsigned char *vrow = &s.v[L::VREG ? 0 : wave][0][0], *krow = &s.k[wave][0][0];
+    const int krd = L::VREG ? (i16 & 3) * 4 + (i16 >> 2) : i16;
+    const int niter = (len + 31) / 32;
+    for (int it = wave; it < niter; it += W) {
+        if constexpr (!L::VREG) {
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                *reinterpret_cast<u32x4 *>(vrow + (size_t)(u * TPI + lane / LPT) * L::VS + (lane % LPT) * 16) = vr[u];
+        }
+        u32x4 kcur[2][NS];
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+#pragma unroll
+            for (int u = 0; u < NS; ++u)
+                *reinterpret_cast<u32x4 *>(krow + (size_t)(u * TPI + lane / LPT) * L::VS + (lane % LPT) * 16) = kn[tl][u];
+            ordered();
+#pragma unroll
+            for (int u = 0; u < NS; ++u)
+                kcur[tl][u] = *reinterpret_cast<const u32x4 *>(krow + (size_t)krd * L::VS + g4 * (HD / 2) + u * 16);
+            ordered();
+        }
+        load_k(it + W);
+        if constexpr (!L::VREG) load_v(it + W);
+        float sv[8];
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                a = mfma16(kcur[tl][u], qh[u], a);
+                a = mfma16(kcur[tl][u], ql[u], a);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sv[4 * tl + e] = a[e];
+        }
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int tok = it * 32 + (L::VREG ? e * 4 + g4 : (e >> 2) * 16 + g4 * 4 + (e & 3));
+            sv[e] = tok < lim ? sv[e] : -INFINITY;
+            tmax = fmaxf(tmax, sv[e]);
+        }
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+        const float mnew = fmaxf(mx, tmax); // finite for a column that has seen a token
+        const float alpha = (mx == mnew) ? 1.0f : __builtin_amdgcn_exp2f(mx - mnew);
+        mx = mnew;
+        float pv[8], psum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            pv[e] = sv[e] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[e] - mnew);
+            psum += pv[e];
+        }
+        lsum = lsum * alpha + psum;
+        uint32_t ph[4], pl[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) split_bf16x2(pv[2 * e], pv[2 * e + 1], ph[e], pl[e]);
+        const u32x4 pH = {ph[0], ph[1], ph[2], ph[3]}, pL = {pl[0], pl[1], pl[2], pl[3]};
+        if constexpr (!L::VREG) ordered();
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+            uint32_t w[4];
+            if constexpr (L::VREG) {
+                const uint32_t sel = (db & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_perm(vr[2 * e + 1][db >> 1], vr[2 * e][db >> 1], sel);
+            } else {
+                const unsigned char *col = vrow + (db * 16 + i16) * 2;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int ta = (e < 2 ? 0 : 16) + g4 * 4 + (2 * e & 3);
+                    w[e] = (uint32_t) * reinterpret_cast<const uint16_t *>(col + (size_t)ta * L::VS) |
+                           ((uint32_t) * reinterpret_cast<const uint16_t *>(col + (size_t)(ta + 1) * L::VS) << 16);
+                }
+            }
+            const u32x4 va = {w[0], w[1], w[2], w[3]};
+            f32x4 o = oacc[db] * alpha;
+            o = mfma16(va, pH, o);
+            o = mfma16(va, pL, o);
+            oacc[db] = o;
+        }
+        if constexpr (L::VREG)
+            load_v(it + W); // the registers are free again
+        else
+            ordered();
+    }
+    lsum += __shfl_xor(lsum, 16, kWave);
+    lsum += __shfl_xor(lsum, 32, kWave);
+    // the waves' results meet in the place of the tiles
+    lds_barrier();
+#pragma unroll
+    for (int db = 0; db < NDB; db += L::VREG ? 4 : 1) // four neighbouring dimensions at a time
+#pragma unroll
+        for (int v = 0; v < (L::VREG ? 4 : 1); ++v) {
+            const f32x4 o = L::VREG ? f32x4{oacc[db][v], oacc[L::VREG ? db + 1 : 0][v], oacc[L::VREG ? db + 2 : 0][v], oacc[L::VREG ? db + 3 : 0][v]}
+                                    : oacc[db];
+            *reinterpret_cast<f32x4 *>(&lds.m.acc[wave][i16][L::VREG ? 8 * (4 * g4 + v) + db : db * 16 + g4 * 4]) = o;
+        }
+    if (g4 == 0) {
+        lds.m.ml[wave][i16][0] = mx;
+        lds.m.ml[wave][i16][1] = lsum;
+    }
+    lds_barrier();
+    // thread -> E neighbouring dimensions of column c
+    constexpr int E = NC * HD / kThreads;
+    static_assert(E == 8 || E == 4 || E == 2, "pieces of a column");
+    const int c = threadIdx.x / (HD / E), e0 = threadIdx.x % (HD / E) * E;
+    int mine = 0;
+#pragma unroll
+    for (int u = 0; u < JP; ++u) mine = u == c / G ? lenj[u] : mine;
+    if (mine == 0) return; // not part of the block
+    float M = -INFINITY, ls = 0.f, r[E];
+#pragma unroll
+    for (int w = 0; w < W; ++w) M = fmaxf(M, lds.m.ml[w][c][0]);
+#pragma unroll
+    for (int i = 0; i < E; ++i) r[i] = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const float f = __builtin_amdgcn_exp2f(lds.m.ml[w][c][0] - M); // (a wave without a token of the column: zero)
+        ls += f * lds.m.ml[w][c][1];
+#pragma unroll
+        for (int i = 0; i < E; ++i) r[i] += f * lds.m.acc[w][c][e0 + i];
+    }
+    const float inv = 1.0f / ls;
+    uint32_t h[E / 2], l[E / 2];
+#pragma unroll
+    for (int i = 0; i < E / 2; ++i) split_bf16x2(r[2 * i] * inv, r[2 * i + 1] * inv, h[i], l[i]);
+    uint16_t *dst = p.attn_split + act_index(p, (jg * JP + c / G) * nseq + b, (kvh * G + c % G) * HD + e0);
+    if constexpr (E == 8) {
+        *reinterpret_cast<u32x4 *>(dst) = u32x4{h[0], h[1], h[2], h[3]};
+        *reinterpret_cast<u32x4 *>(dst + p.a_lo) = u32x4{l[0], l[1], l[2], l[3]};
+    } else if constexpr (E == 4) {
+        *reinterpret_cast<u32x2 *>(dst) = u32x2{h[0], h[1]};
+        *reinterpret_cast<u32x2 *>(dst + p.a_lo) = u32x2{l[0], l[1]};
+    } else {
+        *reinterpret_cast<uint32_t *>(dst) = h[0];
+        *reinterpret_cast<uint32_t *>(dst + p.a_lo) = l[0];
+    }
+}
+
+} // namespace mtp

@@ -43,5 +43,7 @@ void launch_attn_mfma(int G, int HD, const DraftParams &p, int step, int grid, s
 // positions_per_item = 16 / G positions of a sequence share its key/value reads
 size_t attn_mfma_block_lds_bytes(int G, int HD);
 void launch_attn_mfma_block(int G, int HD, const DraftParams &p, int step, int grid, size_t lds, hipStream_t st);
+// a block of new positions whose keys and values are in the cache: a small workgroup per KV head and 16 / G positions (attn_rows.h)
+void launch_attn_rows(const DraftParams &p, int cus, hipStream_t st);
 
 } // namespace mtp

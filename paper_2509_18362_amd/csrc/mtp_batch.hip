@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "attn_mfma.h"
+#include "attn_rows.h"
 #include "batch.h"
 #include "batch_launch.h"
 #include "rows_kernels.h"
@@ -64,7 +65,33 @@ __global__ __launch_bounds__(kBlock) void k_attn_mfma_block(DraftParams p, int s
     phase_attn_mfma<G, HD, false, true, NoHook, true, 16 / G>(p, step, blockIdx.x, gridDim.x, smem);
 }
 
+// a block of positions in small workgroups
+template <int G, int HD, int W>
+__global__ __launch_bounds__(W *kWave, 2) void k_attn_rows(DraftParams p) {
+    extern __shared__ __align__(16) char smem[];
+    attn_rows<G, HD, W>(p, smem);
+}
+
 typedef void (*bg_kernel_t)(DraftParams, int);
+struct AttnRowsKernel {
+    void (*fn)(DraftParams);
+    size_t lds;
+};
+template <int W>
+AttnRowsKernel attn_rows_kernel_of(int G, int HD) {
+    switch (HD * 16 + G) {
+    case 128 * 16 + 1: return {k_attn_rows<1, 128, W>, sizeof(AttnRowsLds<1, 128, W>)};
+    case 128 * 16 + 2: return {k_attn_rows<2, 128, W>, sizeof(AttnRowsLds<2, 128, W>)};
+    case 128 * 16 + 4: return {k_attn_rows<4, 128, W>, sizeof(AttnRowsLds<4, 128, W>)};
+    case 128 * 16 + 8: return {k_attn_rows<8, 128, W>, sizeof(AttnRowsLds<8, 128, W>)};
+    case 64 * 16 + 1: return {k_attn_rows<1, 64, W>, sizeof(AttnRowsLds<1, 64, W>)};
+    case 64 * 16 + 2: return {k_attn_rows<2, 64, W>, sizeof(AttnRowsLds<2, 64, W>)};
+    case 64 * 16 + 4: return {k_attn_rows<4, 64, W>, sizeof(AttnRowsLds<4, 64, W>)};
+    case 64 * 16 + 8: return {k_attn_rows<8, 64, W>, sizeof(AttnRowsLds<8, 64, W>)};
+    }
+    return {nullptr, 0};
+}
+AttnRowsKernel attn_rows_kernel(int G, int HD, int waves) { return waves == 4 ? attn_rows_kernel_of<4>(G, HD) : attn_rows_kernel_of<8>(G, HD); }
 bg_kernel_t attn_mfma_block_kernel(int G, int HD) {
     if (HD == 128) {
         switch (G) {
@@ -199,6 +226,13 @@ void launch_attn_mfma_block(int G, int HD, const DraftParams &p, int step, int g
     hipLaunchKernelGGL(attn_mfma_block_kernel(G, HD), dim3(grid), dim3(kBlock), lds, st, p, step);
 }
 
+void launch_attn_rows(const DraftParams &p, int cus, hipStream_t st) {
+    const int G = p.Hq / p.Hkv, jp = 16 / G, groups = p.ext_B * ((p.B / p.ext_B + jp - 1) / jp) * p.Hkv;
+    const int waves = attn_rows_waves(groups, cus);
+    const AttnRowsKernel k = attn_rows_kernel(G, p.hd, waves);
+    hipLaunchKernelGGL(k.fn, dim3(groups), dim3(waves * kWave), k.lds, st, p);
+}
+
 bool batch_allow_lds(size_t lds_limit, const mtp_config &c) {
     bool ok = true;
     auto allow = [&](const void *kernel) {
@@ -207,6 +241,7 @@ bool batch_allow_lds(size_t lds_limit, const mtp_config &c) {
     const int G = c.n_q_heads / c.n_kv_heads;
     for (bool lpt : {false, true}) allow((const void *)attn_mfma_kernel(G, c.head_dim, lpt));
     allow((const void *)attn_mfma_block_kernel(G, c.head_dim));
+    for (int waves : {4, 8}) allow((const void *)attn_rows_kernel(G, c.head_dim, waves).fn);
     if (c.max_batch < 2) return ok; // one sequence: the row-streaming kernels
     ok = ok && few_allow_lds(lds_limit);
     for (int ph = 0; ph <= kHeadLogits; ++ph)

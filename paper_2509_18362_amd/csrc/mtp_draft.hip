@@ -985,9 +985,12 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             hipLaunchKernelGGL(k_extend_append<128>, dim3(B, p.Hkv), dim3(192), 0, st, pa);
         else
             hipLaunchKernelGGL(k_extend_append<64>, dim3(B, p.Hkv), dim3(96), 0, st, pa);
-        if (mfma_attn && ext->m_max > 1) {
+        const int jp = 16 / (pa.Hq / pa.Hkv), jg = (ext->m_max + jp - 1) / jp; // positions that share reads, groups of them
+        if (p.attn_split && attn_rows_serves(ext->m_max, (long long)ext->B * pa.Hkv * jg, c.kv_capacity, pa.hd)) {
+            launch_attn_rows(pa, h->num_cus, st);
+        } else if (mfma_attn && ext->m_max > 1) {
             // long splits: the positions of a sequence share its key/value reads (16 / G of them per item)
-            const int G = pa.Hq / pa.Hkv, jp = 16 / G, jg = (ext->m_max + jp - 1) / jp;
+            const int G = pa.Hq / pa.Hkv;
             const int items = ext->B * pa.Hkv * pa.max_splits * jg;
             const int grid_b = att_fit ? h->num_cus : std::max(1, std::min(items, h->num_cus * 2));
             pa.attn_queue = items > grid_b ? pa.attn_ticket + (size_t)2 * c.max_batch * c.n_kv_heads : nullptr;

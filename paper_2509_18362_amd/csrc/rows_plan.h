@@ -126,6 +126,23 @@ inline RowsRoute rows_route(const RowsCall &c, bool all_few, int cus) {
     return c.rows <= kFewRows ? kOnFew : kOnCore;
 }
 
+// Attention of a block of new positions (two or more per sequence): attn_rows.h, small workgroups that each serve 16 / G positions
+// of a KV head over all their tokens, or the kernels that split a context over workgroups.  groups: (sequence, KV head, 16 / G
+// positions); the host knows the capacity, not the contexts.  What counts is a wave's rounds of 128 tokens where there are too
+// few groups to fill the chip.  Whole calls, us, splits / attn_rows.h: 509 positions, empty cache (1024 groups of 16 heads, head
+// dimension 128) 773 / 734, of a 2048-wide head 262 / 234, 500 behind 4000 tokens 752 / 610, 16 sequences x 4 behind 100 217 / 201,
+// x 3 behind 2000 235 / 215, 1 x 6 behind 2000 (16 groups, 16 rounds) 166 / 148; 1 x 64 behind 4000 (128 groups, 32 rounds) 235 / 229,
+// 2 x 8 behind 6000 (32 groups, 47 rounds) 187 / 199.  Head dimension 64 (a round takes longer, V is gathered from LDS): 8 x 8 behind
+// 1500 (16 groups, 12 rounds) 90.6 / 82.8, 1 x 6 behind 2000 (2, 16) 66 / 73, 1 x 64 behind 4000 (16, 32) 90 / 96, 16 x 16 behind 2000
+// (64, 16) 141 / 134, 1 x 200 behind 8000 (50, 65) 155 / 172, 1 x 500 behind 4000 (126, 36) 219 / 211.
+inline bool attn_rows_serves(int positions, long long groups, int capacity, int head_dim) {
+    const int rounds = (capacity + 127) / 128;
+    return positions >= 2 && 4 * rounds <= groups + (head_dim == 128 ? 132 : 52);
+}
+
+// waves of its workgroups: eight where there are no more groups than compute units
+inline int attn_rows_waves(long long groups, int cus) { return groups <= cus ? 8 : 4; }
+
 // One sequence of a head with a reduction below 512: the single launch on a quarter of the compute units (flow.h), or one launch
 // per phase on all of them.  step_bytes: weights of a step, kv_bytes: keys and values up to the capacity (the lengths are on the
 // device).  What a launch per phase loses to its gaps a quarter of the units loses to reading more.  Three steps, us, single launch

@@ -1,7 +1,8 @@
 // Prints what the rules of csrc/rows_plan.h say.  Without an argument: reads lines "K n rows head pairs cus part_floats call_rows d"
 // (a matrix phase over `rows` of the call's rows), writes "route tile_rows tile_weight_rows parts microseconds" for each, route 0
 // few_rows.h, 1 the tiles, 2 the batched core; -1 where the whole call takes few_rows.h.  With "narrow": reads "step_bytes
-// kv_bytes", writes 1 where one sequence of a narrow head takes the single launch.
+// kv_bytes", writes 1 where one sequence of a narrow head takes the single launch.  With "block": reads "positions groups capacity
+// head_dim", writes 1 where a block's attention takes attn_rows.h.
 #include <cstdio>
 #include <cstring>
 
@@ -11,6 +12,13 @@ int main(int argc, char **argv) {
     if (argc > 1 && !std::strcmp(argv[1], "narrow")) {
         unsigned long long step, kv;
         while (std::scanf("%llu %llu", &step, &kv) == 2) std::printf("%d\n", mtp::flow_narrow_serves(step, kv) ? 1 : 0);
+        return 0;
+    }
+    if (argc > 1 && !std::strcmp(argv[1], "block")) {
+        int positions, capacity, head_dim;
+        long long groups;
+        while (std::scanf("%d %lld %d %d", &positions, &groups, &capacity, &head_dim) == 4)
+            std::printf("%d\n", mtp::attn_rows_serves(positions, groups, capacity, head_dim) ? 1 : 0);
         return 0;
     }
     int K, n, rows, head, pairs, cus, call_rows, d;

@@ -244,6 +244,39 @@ def test_small_heads_block_of_positions_shared_reads(gpu, hq, hkv, hd):
     check_extend(ref, res, caches, act, ext_len)
 
 
+@pytest.mark.parametrize("hq,hkv,hd", GEOMETRIES)
+@pytest.mark.parametrize("d,ctx,ext,m", [
+    (256, [0, 13, 96, 500], [19, 19, 7, 0], 19),   # row-major activations; rounds of 32 tokens per wave: several, one
+    (256, [31, 109, 255, 125], [1, 19, 1, 4], 19), # or none; lengths on their edges, groups without a position
+    (512, [127, 30], [3, 2], 3),                   # six rows in operand order
+])
+def test_small_heads_block_of_positions_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m):
+    """Blocks in caches of a few hundred slots: the attention whose small workgroups serve 16 / G positions each over all
+    their tokens, on every (group size, head dimension); here with eight waves."""
+    block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m)
+
+
+@pytest.mark.parametrize("hkv,hd", [(2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (4, 128), (8, 128), (16, 128)])
+def test_small_heads_long_blocks_in_smaller_workgroups(gpu, hkv, hd):
+    """More (sequence, KV head, 16 / G positions) than compute units: four waves each."""
+    groups = 7 * hkv * -(-73 * (16 // hkv) // 16)
+    assert groups > 256
+    block_in_small_workgroups(gpu, 16, hkv, hd, 256, [0, 55, 127, 1, 30, 64, 90], [73, 73, 1, 0, 40, 64, 73], 73)
+
+
+def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m):
+    shape = synth.HeadShape(d, hq, hkv, hd, 512, 2048)
+    wl = synth.Workload(f"small_{hq}_{hkv}_{hd}", 70 + hq + 3 * hkv + hd, shape, len(ctx), 0, 0, (512,), 1, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    ext_len = np.array(ext, dtype=np.int32)
+    act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=576)
+    hid, tok = extend_inputs(shape, act, m, 79 + hq + hkv + hd)
+    ref, res, caches = run_extend(gpu, shape, w, w, act, [ids], 0, hid, tok, ext_len)
+    assert res["err"] == 0
+    check_extend(ref, res, caches, act, ext_len)
+
+
 def test_tiny_full_vocab_equals_identity_subset(gpu, tiny):
     """Eq. (3) with the identity list is the full head: same logits bit for bit on the device as well."""
     act = tiny["act"]

@@ -147,3 +147,13 @@ def test_narrow_heads_take_the_single_launch_where_it_is_ahead(driver, d, hq, hk
     step = 2 * (d * (2 * d + (hq + 2 * hkv) * hd + hq * hd + 3 * d_ffn) + n * d)
     out = subprocess.run([driver, "narrow"], input=f"{step} {4 * hkv * hd * cap}", capture_output=True, text=True, check=True)
     assert out.stdout.split() == [str(int(single))], (step, 4 * hkv * hd * cap)
+
+
+@pytest.mark.parametrize("positions,groups,cap,hd,small", [
+    (1, 1024, 512, 128, 0), (2, 8, 64, 128, 1), (509, 1024, 512, 128, 1), (4, 128, 4160, 128, 1), (64, 128, 4096, 128, 1),
+    (8, 32, 6080, 128, 0), (8, 16, 1536, 64, 1), (6, 2, 2048, 64, 0), (64, 16, 4096, 64, 0), (16, 64, 2048, 64, 1),
+    (200, 50, 8256, 64, 0), (500, 126, 4544, 64, 1)])
+def test_attention_of_a_block_by_rounds_and_groups(driver, positions, groups, cap, hd, small):
+    """Small workgroups where the chip is full of them or a wave's rounds are few; one position never."""
+    out = subprocess.run([driver, "block"], input=f"{positions} {groups} {cap} {hd}", capture_output=True, text=True, check=True)
+    assert int(out.stdout) == small
