@@ -137,7 +137,8 @@ struct PollClock {
     __device__ __forceinline__ PollClock() : t0(wall_clock64()), spins(0) {}
     __device__ __forceinline__ bool expired(const DraftParams &p) {
         if ((++spins & 31u) != 0) return false;
-        if (__hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrBarrierTimeout) return true;
+        const int err = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (err & kErrBarrierTimeout) return true;
         if (wall_clock64() - t0 > p.bar_timeout) {
             atomicOr(p.err, kErrBarrierTimeout);
             return true;
@@ -145,30 +146,17 @@ struct PollClock {
         return false;
     }
 };
-// one element, polled until its tag is the wanted one
-__device__ __forceinline__ float ld_tagged(const DraftParams &p, const unsigned long long *src, unsigned tag) {
-    unsigned long long w = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((unsigned)(w >> 32) != tag) {
-        PollClock clk;
-        do {
-            w = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } while ((unsigned)(w >> 32) != tag && !clk.expired(p));
-    }
-    return __uint_as_float((unsigned)w);
-}
-
-// two elements, polled together
+// two elements, polled together until their tags are the wanted one
 __device__ __forceinline__ void ld_tagged2(const DraftParams &p, const unsigned long long *a, const unsigned long long *b,
                                            unsigned tag, float &va, float &vb) {
-    unsigned long long wa = __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned long long wb = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((unsigned)(wa >> 32) != tag || (unsigned)(wb >> 32) != tag) {
-        PollClock clk;
-        do {
-            wa = __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wb = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } while (((unsigned)(wa >> 32) != tag || (unsigned)(wb >> 32) != tag) && !clk.expired(p));
-    }
+    unsigned long long wa, wb;
+    PollClock clk;
+    bool late;
+    do { // (the wave leaves as one, see poll_vec)
+        wa = __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wb = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        late = __any(((unsigned)(wa >> 32) ^ tag) | ((unsigned)(wb >> 32) ^ tag)) != 0;
+    } while (late && !clk.expired(p));
     va = __uint_as_float((unsigned)wa);
     vb = __uint_as_float((unsigned)wb);
 }
