@@ -436,8 +436,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
                 sv[e] = tok < lim ? sv[e] : -INFINITY;
                 tmax = fmaxf(tmax, sv[e]);
             }
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+            tmax = rows_max(tmax);
             const float mnew = fmaxf(mx, tmax); // finite for a column that has seen a token (others: -inf, weights 0)
             const float alpha = (mx == mnew) ? 1.0f : __builtin_amdgcn_exp2f(mx - mnew);
             mx = mnew;
@@ -502,8 +501,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
         }
 
         // ---- merge the waves (and the token being appended) through LDS ----
-        lsum += __shfl_xor(lsum, 16, kWave);
-        lsum += __shfl_xor(lsum, 32, kWave);
+        lsum = rows_sum(lsum);
         if (i16 < NC) {
 #pragma unroll
             for (int db = 0; db < NDB; ++db) {

@@ -173,8 +173,7 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
             sv[e] = tok < lim ? sv[e] : -INFINITY;
             tmax = fmaxf(tmax, sv[e]);
         }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+        tmax = rows_max(tmax);
         const float mnew = fmaxf(mx, tmax); // finite for a column that has seen a token
         const float alpha = (mx == mnew) ? 1.0f : __builtin_amdgcn_exp2f(mx - mnew);
         mx = mnew;
@@ -217,8 +216,7 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
         else
             ordered();
     }
-    lsum += __shfl_xor(lsum, 16, kWave);
-    lsum += __shfl_xor(lsum, 32, kWave);
+    lsum = rows_sum(lsum);
     // the waves' results meet in the place of the tiles
     lds_barrier();
 #pragma unroll

@@ -585,12 +585,7 @@ struct BgHead : BgBase {
         for (int a = 0; a < kBatchMaxSeq / 16; ++a)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                unsigned long long m = best[a][c];
-#pragma unroll
-                for (int off = 1; off < 16; off <<= 1) {
-                    unsigned long long o = __shfl_xor(m, off, kWave);
-                    m = o > m ? o : m;
-                }
+                const unsigned long long m = row16_max_u64(best[a][c]);
                 if ((lane & 15) == 0 && m != 0ull) red[wave * kBatchMaxSeq + a * 16 + (lane >> 4) * 4 + c] = m;
             }
         __syncthreads();
@@ -745,11 +740,7 @@ __device__ __forceinline__ void phase_bprep(const DraftParams &p, int step, char
     sx = wave_sum(sx);
     sg = wave_sum(sg);
     if (early_tok) se = embed_sum();
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const unsigned long long o = __shfl_xor(best, off, kWave);
-        best = o > best ? o : best;
-    }
+    best = wave_max_u64(best);
     if (lane == 0) {
         ra[wave] = sx;
         rb[wave] = sg;

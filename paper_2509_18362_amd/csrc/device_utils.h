@@ -48,7 +48,11 @@ __device__ __forceinline__ void split_bf16x4(const float (&v)[4], u32x2 &hi, u32
     lo = u32x2{l[0], l[1]};
 }
 
-// ---- cross-lane sums -------------------------------------------------------------------------------
+// ---- sums and maxima across lanes --------------------------------------------------------------------
+// All of them in vector instructions: moves within rows of 16 lanes, and swaps of whole rows.  (A shuffle is a trip through LDS,
+// behind whatever the wave has in that queue; two of them ended every row of the single launch and stood in every block of the
+// attention.  K = 3, one sequence: 393 -> 390 us at d = 4096, 123 -> 121 at d = 256; 16 blocks of 4 positions 294 -> 291.)
+// Sums keep the pairing of x[i] + x[i ^ 1], ^ 2, ^ 4 ..: the same bits.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
@@ -68,11 +72,58 @@ __device__ __forceinline__ float oct_sum(float x) {
     x += dpp_f32<0x141>(x);
     return x;
 }
-__device__ __forceinline__ float wave_sum(float x) {
-    x = row16_sum(x);
-    x += __shfl_xor(x, 16, kWave);
-    x += __shfl_xor(x, 32, kWave);
-    return x;
+// x of this lane and of the one 16 (32) lanes away: the lower row's first
+__device__ __forceinline__ u32x2 pair16(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return u32x2{r[0], r[1]};
+}
+__device__ __forceinline__ u32x2 pair32(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return u32x2{r[0], r[1]};
+}
+__device__ __forceinline__ float sum16(float x) {
+    const u32x2 r = pair16(x);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+__device__ __forceinline__ float sum32(float x) {
+    const u32x2 r = pair32(x);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+// over the four rows of 16 lanes: every lane gets the total (the maximum) of the lanes with its place in a row
+__device__ __forceinline__ float rows_sum(float x) { return sum32(sum16(x)); }
+__device__ __forceinline__ float rows_max(float x) {
+    u32x2 r = pair16(x);
+    x = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+    r = pair32(x);
+    return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+__device__ __forceinline__ float wave_sum(float x) { return rows_sum(row16_sum(x)); }
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp_f32<0xB1>(x));
+    x = fmaxf(x, dpp_f32<0x4E>(x));
+    x = fmaxf(x, dpp_f32<0x141>(x));
+    x = fmaxf(x, dpp_f32<0x140>(x));
+    return rows_max(x);
+}
+// maxima of 64-bit keys
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_max_u64(unsigned long long v) {
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, 0xF, 0xF, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, 0xF, 0xF, true);
+    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+    return o > v ? o : v;
+}
+__device__ __forceinline__ unsigned long long row16_max_u64(unsigned long long v) {
+    return dpp_max_u64<0x140>(dpp_max_u64<0x141>(dpp_max_u64<0x4E>(dpp_max_u64<0xB1>(v))));
+}
+__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
+    v = row16_max_u64(v);
+    u32x2 lo = pair16(__uint_as_float((unsigned)v)), hi = pair16(__uint_as_float((unsigned)(v >> 32)));
+    unsigned long long a = ((unsigned long long)hi.x << 32) | lo.x, b = ((unsigned long long)hi.y << 32) | lo.y;
+    v = a > b ? a : b;
+    lo = pair32(__uint_as_float((unsigned)v)), hi = pair32(__uint_as_float((unsigned)(v >> 32)));
+    a = ((unsigned long long)hi.x << 32) | lo.x, b = ((unsigned long long)hi.y << 32) | lo.y;
+    return a > b ? a : b;
 }
 // sum over the whole workgroup; red must hold kWaves floats; contains two barriers
 __device__ __forceinline__ float block_sum(float x, float *red) {

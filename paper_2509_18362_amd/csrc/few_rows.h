@@ -66,8 +66,7 @@ struct FewScales {
         float s = 0.f;
 #pragma unroll
         for (int u = 0; u < N; ++u) s += v[u];
-        s = row16_sum(s);
-        s += __shfl_xor(s, 16, kWave);
+        s = sum16(row16_sum(s));
         if (threadIdx.x % LR == 0) scale_lds[row] = row < p.nb ? 1.0f / sqrtf(s / (float)p.d + p.eps) : 0.f;
     }
 };
@@ -253,7 +252,7 @@ __device__ __forceinline__ void few_rows(const DraftParams &p, Ph &ph, int per, 
                 for (int w = 0; w < kWaves; ++w) v += red[((size_t)w * T + t + m) * kWave + lane];
                 if (PACKED) // rows 8..15 hold the lo products of rows 0..7
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], 32, kWave);
+                    for (int e = 0; e < 4; ++e) v[e] = sum32(v[e]);
                 sums[m] = v;
             }
             if (grp * T + t < nvt) ph.epi(g * 4, vt0 + grp * T + t, j, sums, scale_lds, pre);

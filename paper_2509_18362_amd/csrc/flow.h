@@ -294,11 +294,7 @@ __device__ __forceinline__ float block_sum_lds(float x, float *red) {
     return t;
 }
 __device__ __forceinline__ unsigned long long block_max_u64_lds(unsigned long long v, unsigned long long *red64) {
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        unsigned long long o = __shfl_xor(v, off, kWave);
-        v = o > v ? o : v;
-    }
+    v = wave_max_u64(v);
     flow_barrier();
     if ((threadIdx.x & (kWave - 1)) == 0) red64[threadIdx.x / kWave] = v;
     flow_barrier();

@@ -192,9 +192,7 @@ __global__ __launch_bounds__(kCeBlock) void k_train_row_ce(const float *__restri
     }
     for (int e = threadIdx.x; e < V; e += kCeBlock) // the few elements outside the aligned middle
         if (e < head || e >= head + nvec * 4) take(z[e], -INFINITY, -INFINITY, -INFINITY);
-    float wm = m;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) wm = fmaxf(wm, __shfl_xor(wm, off, kWave));
+    const float wm = wave_max(m);
     sum = wave_sum(wm == -INFINITY ? 0.f : sum * expf(m - wm));
     if ((threadIdx.x & (kWave - 1)) == 0) {
         red_m[threadIdx.x / kWave] = wm;

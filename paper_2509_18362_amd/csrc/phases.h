@@ -175,11 +175,7 @@ __device__ __forceinline__ bool seq_overflows(const DraftParams &p, int b) {
 
 // maximum of a 64-bit key over the workgroup; red64 holds kWaves words; contains two barriers
 __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v, unsigned long long *red64) {
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        unsigned long long o = __shfl_xor(v, off, kWave);
-        v = o > v ? o : v;
-    }
+    v = wave_max_u64(v);
     __syncthreads();
     if ((threadIdx.x & (kWave - 1)) == 0) red64[threadIdx.x / kWave] = v;
     __syncthreads();
@@ -377,12 +373,7 @@ __device__ __forceinline__ unsigned long long winner_key_wave(const DraftParams 
     unsigned long long best = 0ull;
     const int ncand = seq_head(p, b).cands;
     for (int w = threadIdx.x & (kWave - 1); w < ncand; w += kWave) best = cand[w] > best ? cand[w] : best;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        unsigned long long o = __shfl_xor(best, off, kWave);
-        best = o > best ? o : best;
-    }
-    return best;
+    return wave_max_u64(best);
 }
 
 // plain copy of a float vector of length K (multiple of 4) into hi/lo, zero-padded to kpad
@@ -918,9 +909,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
         for (int u = 0; u < NF; ++u)
 #pragma unroll
             for (int k = 0; k < ND; ++k) t[k][u] = u < nsplit ? ld_f32<PCOH>(src + (size_t)u * PW + lane + k * kWave) : 0.f;
-        float M = m;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
+        const float M = wave_max(m);
         const float e = lane < nsplit ? expf(m - M) : 0.f;
         const float inv = 1.0f / wave_sum(l * e);
         float A[ND];
@@ -928,7 +917,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
         for (int k = 0; k < ND; ++k) A[k] = 0.f;
 #pragma unroll
         for (int u = 0; u < NF; ++u) {
-            const float wu = __shfl(e, u, kWave);
+            const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), u));
 #pragma unroll
             for (int k = 0; k < ND; ++k) A[k] += t[k][u] * wu;
         }
@@ -942,8 +931,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
         w[s2] = m;
         M = fmaxf(M, m);
     }
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
+    M = wave_max(M);
     float Ls = 0.f;
     for (int s2 = lane; s2 < nsplit; s2 += kWave) {
         float e = expf(w[s2] - M);
@@ -1233,9 +1221,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
         if (wave < G) {
             const float mm = lane < NSTREAM ? s.ml[lane][wave][0] : -INFINITY;
             const float ll = lane < NSTREAM ? s.ml[lane][wave][1] : 0.f;
-            float M = mm;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
+            const float M = wave_max(mm);
             const float w = mm != -INFINITY ? expf(mm - M) : 0.f;
             const float Ls = wave_sum(ll * w);
             if (lane < NSTREAM) s.ml[lane][wave][0] = w;
@@ -1434,12 +1420,7 @@ __device__ __forceinline__ void phase_lmhead(const DraftParams &p, int step, int
                 p.cand[((size_t)step * p.max_batch + b0 + threadIdx.x) * p.head_grid + vb] = m;
             }
         } else if ((int)threadIdx.x < 16 * nb) { // threads 16*i .. 16*i+15 hold candidates of sequence i
-            unsigned long long m = best[0];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                unsigned long long o = __shfl_xor(m, off, kWave);
-                m = o > m ? o : m;
-            }
+            const unsigned long long m = row16_max_u64(best[0]);
             if ((threadIdx.x & 15) == 0)
                 p.cand[((size_t)step * p.max_batch + b0 + (threadIdx.x >> 4)) * p.head_grid + vb] = m;
         }
@@ -1454,11 +1435,7 @@ __device__ void phase_finalize(const DraftParams &p, int vb, int nvb) {
         unsigned long long best = 0ull;
         const int ncand = seq_head(p, b).cands;
         for (int w = lane; w < ncand; w += kWave) best = cand[w] > best ? cand[w] : best;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            unsigned long long o = __shfl_xor(best, off, kWave);
-            best = o > best ? o : best;
-        }
+        best = wave_max_u64(best);
         if (lane == 0) p.draft_out[(size_t)b * p.K + p.K - 1] = seq_dead(p, b) ? -1 : key_token(p, b, best);
     }
 }

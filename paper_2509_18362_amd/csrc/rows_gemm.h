@@ -392,12 +392,7 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
             if (Ph::CANDS) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    unsigned long long m = best[c];
-#pragma unroll
-                    for (int off = 1; off < 16; off <<= 1) {
-                        const unsigned long long o = __shfl_xor(m, off, kWave);
-                        m = o > m ? o : m;
-                    }
+                    const unsigned long long m = row16_max_u64(best[c]);
                     if (i16 == 0) red[wn * BM + 16 * (TI * wm + ti) + 4 * g + c] = m;
                 }
             }
@@ -460,8 +455,7 @@ __device__ __forceinline__ void rows_epilogue(const DraftParams &pin, Make make_
 #pragma unroll
             for (int u = 0; u < 8; ++u) sum += v[u];
         }
-#pragma unroll
-        for (int off = 1; off < 32; off <<= 1) sum += __shfl_xor(sum, off, kWave);
+        sum = sum16(row16_sum(sum));
         if (sub == 0) scale[tid / 32] = 1.0f / sqrtf(sum / (float)p.d + p.eps);
     }
     __syncthreads();
@@ -493,12 +487,7 @@ __device__ __forceinline__ void rows_epilogue(const DraftParams &pin, Make make_
         unsigned long long *red = reinterpret_cast<unsigned long long *>(scale + 16); // [kWaves][16]
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            unsigned long long m = best[c];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                const unsigned long long o = __shfl_xor(m, off, kWave);
-                m = o > m ? o : m;
-            }
+            const unsigned long long m = row16_max_u64(best[c]);
             if ((lane & 15) == 0) red[wave * 16 + (lane >> 4) * 4 + c] = m;
         }
         __syncthreads();
