@@ -16,9 +16,6 @@ namespace mtp {
 
 constexpr int kBatchAcc = 8;      // accumulators per wave
 constexpr int kBatchMaxSeq = 64;  // sequences per pass
-// A lane offset at or beyond the end of every buffer (the host checks that each matrix is smaller than 2 GiB): such a
-// load returns zeros and moves no data.  Adding the wave-uniform offset (a few MiB at most) cannot wrap it around.
-constexpr uint32_t kOobOffset = 0x80000000u;
 
 // the two activation buffers (and the candidates of the head's workgroup afterwards), the transposition strips, the norm
 // scales, the ids of the row group

@@ -10,6 +10,7 @@ constexpr int kBlock = 512;            // threads per workgroup in every phase
 constexpr int kWaves = kBlock / kWave; // 8
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -21,7 +22,6 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_floa
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 // a in the low half
 __device__ __forceinline__ uint32_t f32_to_bf16x2(float a, float b) {
-    typedef __attribute__((ext_vector_type(2))) float f32x2;
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
@@ -89,6 +89,15 @@ __device__ __forceinline__ float sum32(float x) {
     const u32x2 r = pair32(x);
     return __uint_as_float(r.x) + __uint_as_float(r.y);
 }
+// two such sums in one swap: of a in the lower rows, of b in the upper ones
+__device__ __forceinline__ float sum16_of(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum32_of(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 // over the four rows of 16 lanes: every lane gets the total (the maximum) of the lanes with its place in a row
 __device__ __forceinline__ float rows_sum(float x) { return sum32(sum16(x)); }
 __device__ __forceinline__ float rows_max(float x) {
@@ -98,13 +107,13 @@ __device__ __forceinline__ float rows_max(float x) {
     return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
 }
 __device__ __forceinline__ float wave_sum(float x) { return rows_sum(row16_sum(x)); }
-__device__ __forceinline__ float wave_max(float x) {
+__device__ __forceinline__ float row16_max(float x) {
     x = fmaxf(x, dpp_f32<0xB1>(x));
     x = fmaxf(x, dpp_f32<0x4E>(x));
     x = fmaxf(x, dpp_f32<0x141>(x));
-    x = fmaxf(x, dpp_f32<0x140>(x));
-    return rows_max(x);
+    return fmaxf(x, dpp_f32<0x140>(x));
 }
+__device__ __forceinline__ float wave_max(float x) { return rows_max(row16_max(x)); }
 // maxima of 64-bit keys
 template <int CTRL>
 __device__ __forceinline__ unsigned long long dpp_max_u64(unsigned long long v) {

@@ -205,15 +205,6 @@ template <int CL>
 __device__ __forceinline__ void flow_wait_lds_slot() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CL) : "memory"); }
 
 // ---- polling -----------------------------------------------------------------------------------------------
-__device__ __forceinline__ row_rsrc make_vec_rsrc(const void *base, size_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-}
-// 16 bytes past this compute die's caches (device scope): of a tagged vector two elements, (value, tag, value, tag).  Offsets
-// beyond the buffer read zeros.
-__device__ __forceinline__ u32x4 ld_coherent16(row_rsrc rs, int byte_off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, byte_off, 0, 16));
-}
-
 // This thread's elements e = (it * kBlock + tid) * 4 .. + 3 < n of a tagged vector (n a multiple of 4), polled until
 // all of them carry `tag`.  NIT * kBlock * 4 >= n.
 // A phase is a chain of instructions and round trips, and this is a link of every one.  The wave looks, and leaves, as one:

@@ -317,8 +317,7 @@ fused_kernel_t flow_kernel(const mtp_config &c) {
 // the matrix-core attention's item map: lengths and two orders of the sequences, full splits below each split index
 size_t attn_map_bytes(int B, int max_splits) { return ((size_t)3 * B + max_splits + 2) * 4; }
 size_t attn_lds_bytes(int G, int HD) {
-    int tpi = kWave / (HD / 8), ns = kWaves * tpi;
-    size_t fl = (size_t)G * HD + HD + 2 * HD + (size_t)ns * G * HD + (size_t)ns * G * 2;
+    size_t fl = (size_t)G * HD + 2 * HD + (size_t)kWaves * G * HD + (size_t)kWaves * G * 2; // AttnLds
     return fl * sizeof(float) + 64;
 }
 
@@ -395,7 +394,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
     size_t x, qkv, attn, o, gu, dn, hhat, err, admit, cand, rope_inv, attn_part, total;
-    size_t xt, qkvt, attnt, ot, gut, dnt, candt, tagged_end; // tagged hand-over vectors of the barrier-free kernel
+    size_t xt, qkvt, attnt, ot, gut, dnt, candt, partt, tagged_end; // tagged hand-over vectors of the barrier-free kernel
     // batched path (max_batch above kBatchMinSeq - 1 only)
     size_t act0, act1, ssq, part, part_floats, ticket, a_lo, attn_ticket, row_len, seq_list, list_ids, list_n, list_cands;
     int a_stride;
@@ -436,8 +435,7 @@ WsLayout ws_layout(const mtp_config &c) {
     l.cand = take((size_t)c.max_draft_steps * mb * kMaxFusedGrid * 8);
     l.rope_inv = take((size_t)c.head_dim / 2 * 8);
     l.attn_part = take(attn_part_floats(c) * 4);
-    // two per (sequence, KV head): the single-launch kernel deals a KV head's query heads to two items
-    l.attn_ticket = take(mb * (size_t)c.n_kv_heads * 4 * 2 + 64); // + the attention launch's item counter
+    l.attn_ticket = take(mb * (size_t)c.n_kv_heads * 4 + 64); // one per (sequence, KV head), + the attention launch's item counter
     l.row_len = take(mb * 4);
     l.seq_list = take(mb * 4);
     l.list_ids = take(kMaxListGroups * 8);
@@ -450,6 +448,7 @@ WsLayout ws_layout(const mtp_config &c) {
     l.gut = take((size_t)c.d_ffn * 2 * 8);
     l.dnt = take(d * 8);
     l.candt = take((size_t)c.max_draft_steps * kMaxFusedGrid * 16);
+    l.partt = take((size_t)c.n_q_heads * max_splits_for(c, 1) * (c.head_dim + 2) * 8);
     l.tagged_end = off;
     if (c.max_batch >= kBatchMinSeq) {
         size_t kmax = std::max({2 * d, qd, (size_t)c.d_ffn});
@@ -748,7 +747,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     p.rope_inv = reinterpret_cast<const double *>(ws + l.rope_inv);
     p.attn_part = reinterpret_cast<float *>(ws + l.attn_part);
     p.attn_ticket = reinterpret_cast<int *>(ws + l.attn_ticket); // the vector attention merges its own splits
-    p.attn_queue = p.attn_ticket + (size_t)2 * c.max_batch * c.n_kv_heads;
+    p.attn_queue = p.attn_ticket + (size_t)c.max_batch * c.n_kv_heads;
     p.cand = reinterpret_cast<unsigned long long *>(ws + l.cand);
     p.xt = reinterpret_cast<unsigned long long *>(ws + l.xt);
     p.qkvt = reinterpret_cast<unsigned long long *>(ws + l.qkvt);
@@ -757,6 +756,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     p.gut = reinterpret_cast<unsigned long long *>(ws + l.gut);
     p.dnt = reinterpret_cast<unsigned long long *>(ws + l.dnt);
     p.candt = reinterpret_cast<unsigned long long *>(ws + l.candt);
+    p.partt = reinterpret_cast<unsigned long long *>(ws + l.partt);
     p.bar_timeout = 200000000ll; // 2 s of the 100 MHz wall clock
     p.trace = h->trace;
     p.trace_wgs = std::min(h->num_cus, kMaxFusedGrid);
@@ -991,7 +991,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
             const int G = pa.Hq / pa.Hkv;
             const int items = ext->B * pa.Hkv * pa.max_splits * jg;
             const int grid_b = att_fit ? h->num_cus : std::max(1, std::min(items, h->num_cus * 2));
-            pa.attn_queue = items > grid_b ? pa.attn_ticket + (size_t)2 * c.max_batch * c.n_kv_heads : nullptr;
+            pa.attn_queue = items > grid_b ? pa.attn_ticket + (size_t)c.max_batch * c.n_kv_heads : nullptr;
             launch_attn_mfma_block(G, pa.hd, with_fit(pa), 0, grid_b, lds_attn_block, st);
         } else {
             launch_attention_of(pa, 0);
@@ -1328,7 +1328,7 @@ int32_t mtp_poll_error(mtp_handle *h, void *hip_stream) {
         if (word & kErrBarrierTimeout) {
             // a kernel that gave up may have left arrival counters of the attention splits behind (the hand-over tags
             // need nothing: the next call's tags are larger than any the abandoned call wrote)
-            if (hipMemsetAsync(h->ws + h->lay.attn_ticket, 0, (size_t)h->cfg.max_batch * h->cfg.n_kv_heads * 4 * 2 + 64, st) !=
+            if (hipMemsetAsync(h->ws + h->lay.attn_ticket, 0, (size_t)h->cfg.max_batch * h->cfg.n_kv_heads * 4 + 64, st) !=
                 hipSuccess)
                 return MTP_ERR_HIP;
         }

@@ -6,6 +6,7 @@
 // the current batch chunk), so a 16-row weight tile costs no vector-ALU work besides address arithmetic.
 #pragma once
 #include "device_utils.h"
+#include "exp_term.h"
 #include "rope.h"
 
 namespace mtp {
@@ -83,6 +84,7 @@ struct DraftParams {
     // tag names the (call, step, phase) that produced it, so a consumer that polls an element knows when it is there.
     unsigned long long *xt, *qkvt, *attnt, *ot, *gut, *dnt; // [d], [qkv_dim], [qd], [d], [2F], [d]
     unsigned long long *candt; // [max_draft_steps][head_grid][2]: (orderable logit, tag), (token id, tag)
+    unsigned long long *partt; // [Hq][max_splits][hd + 2]: partials of the attention's splits: sum of p * V, maximum, sum of p
     unsigned tag_base;         // tag of (step, section) = tag_base + 8 * step + section + 1; never 0
     int bg_rg[6], bg_kp[6]; // row groups and reduction parts of the six matrix phases
     int bg_sep[6];          // 1: the phase's epilogue runs as a kernel of its own
@@ -119,7 +121,7 @@ enum : int { SSQ_X = 0, SSQ_X1, SSQ_X2, SSQ_COUNT };
 // tagged hand-over elements
 // ---------------------------------------------------------------------------------------------------
 // sections of a draft step whose results cross to other workgroups, in order; tag = tag_base + 8 * step + section + 1
-enum : int { TS_X = 0, TS_QKV, TS_ATTN, TS_O, TS_GU, TS_DN, TS_CAND };
+enum : int { TS_X = 0, TS_QKV, TS_ATTN, TS_O, TS_GU, TS_DN, TS_CAND, TS_PART };
 __device__ __forceinline__ unsigned step_tag(const DraftParams &p, int step, int section) {
     return p.tag_base + 8u * (unsigned)step + (unsigned)section + 1u;
 }
@@ -146,6 +148,18 @@ struct PollClock {
         return false;
     }
 };
+// A lane offset at or beyond the end of every buffer (the host checks that each matrix is smaller than 2 GiB): such a
+// load returns zeros and moves no data.  Adding the wave-uniform offset (a few MiB at most) cannot wrap it around.
+constexpr uint32_t kOobOffset = 0x80000000u;
+__device__ __forceinline__ row_rsrc make_vec_rsrc(const void *base, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+// 16 bytes past this compute die's caches (device scope): of a tagged vector two elements, (value, tag, value, tag).  Offsets
+// beyond the buffer read zeros.
+__device__ __forceinline__ u32x4 ld_coherent16(row_rsrc rs, int byte_off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, byte_off, 0, 16));
+}
+
 // two elements, polled together until their tags are the wanted one
 __device__ __forceinline__ void ld_tagged2(const DraftParams &p, const unsigned long long *a, const unsigned long long *b,
                                            unsigned tag, float &va, float &vb) {
@@ -855,21 +869,23 @@ __device__ __forceinline__ void phase_qkv(const DraftParams &p, int step, int vb
 // One work item = (sequence, KV head, split of `split_tokens` cache slots).  The G query heads of the group share
 // every key/value they read.  A token's head vector is spread over HD/8 lanes (16 bytes each), so a wave-wide
 // load covers 64/(HD/8) consecutive tokens = 1 KiB of contiguous cache.  Each lane group keeps its own online
-// softmax state; the groups of all 8 waves are merged through LDS.  A sequence that fits one split is finished
-// here; otherwise the item leaves (sum of p*V, max, sum of p) per head in the workspace and the item of the same
-// (sequence, KV head) that finishes last merges them (merge_head).
-// At batch 1 the phase moves little data and is bound by its chain of dependent memory round trips, so the first
-// cache loads are issued before anything else and the rotary table costs no double-precision transcendental.
+// softmax state; a wave's groups are merged in registers, the 8 waves through LDS.  A sequence that fits one split is
+// finished here; otherwise the item leaves (sum of p*V, max, sum of p) per head in the workspace and the item of the same
+// (sequence, KV head) that finishes last merges them (merge_head) - in the single launch every item merges its share of
+// the outputs (flow_merge).
+// At batch 1 the phase moves little data and is bound by its chain of dependent memory round trips and instructions, so
+// the first cache loads are issued before anything else and the rotary table costs no double-precision transcendental.
+// Of the single launch's 11.3 us from the last projected element to the last result (d = 4096, 2112 slots of cache, 16
+// splits) the keys and values took 1.8, the merge of 32 lane groups through LDS 1.7, and the acknowledged partials, the
+// ticket and the merge by whoever came last 5.9: now 8.4, of which 1.3, 1.2 and 3.5.
 template <int G, int HD>
 struct AttnLds {
     static constexpr int LPT = HD / 8;           // lanes per token
     static constexpr int TPI = kWave / LPT;      // tokens per wave-wide load
-    static constexpr int NSTREAM = kWaves * TPI; // independent softmax streams per workgroup
     float q[G][HD];
-    float cs[HD / 2], sn[HD / 2];
     float knew[HD], vnew[HD];
-    float acc[NSTREAM][G][HD];
-    float ml[NSTREAM][G][2];
+    float acc[kWaves][G][HD];
+    float m[G][kWaves], l[G][kWaves];
     // the launch reserves 64 bytes more than the struct: the first word behind it is the "last split to finish" flag
 };
 
@@ -877,16 +893,12 @@ struct AttnLds {
 // are formed once (in the wave-private LDS strip w of max_splits floats), then every lane sums its share of the head
 // dimension with sixteen loads in flight.  PCOH: the partials are read with device-coherent loads; OCOH: the result
 // is written with a device-coherent store.
-template <int HD, bool PCOH, bool OCOH, bool TAGGED = false>
-__device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, int nsplit, float *w, int step = 0) {
+template <int HD, bool PCOH, bool OCOH>
+__device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, int nsplit, float *w) {
     const int lane = threadIdx.x & (kWave - 1);
     const int S = p.max_splits, PW = HD + 2;
     const float *src = p.attn_part + ((size_t)b * p.Hq + hq) * S * PW;
     auto store = [&](int dd, float r) {
-        if (TAGGED) { // one sequence: the consumer polls the element itself
-            st_tagged(p.attnt + (size_t)hq * HD + dd, r, step_tag(p, step, TS_ATTN));
-            return;
-        }
         st_f32<OCOH>(p.attn + (size_t)b * p.qd + (size_t)hq * HD + dd, r);
         if (p.attn_split) {
             uint16_t h, l;
@@ -910,7 +922,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
 #pragma unroll
             for (int k = 0; k < ND; ++k) t[k][u] = u < nsplit ? ld_f32<PCOH>(src + (size_t)u * PW + lane + k * kWave) : 0.f;
         const float M = wave_max(m);
-        const float e = lane < nsplit ? expf(m - M) : 0.f;
+        const float e = lane < nsplit ? exp_term(m - M) : 0.f;
         const float inv = 1.0f / wave_sum(l * e);
         float A[ND];
 #pragma unroll
@@ -934,7 +946,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
     M = wave_max(M);
     float Ls = 0.f;
     for (int s2 = lane; s2 < nsplit; s2 += kWave) {
-        float e = expf(w[s2] - M);
+        float e = exp_term(w[s2] - M);
         w[s2] = e;
         Ls += ld_f32<PCOH>(src + (size_t)s2 * PW + HD + 1) * e;
     }
@@ -956,6 +968,91 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
     }
 }
 
+// The merge of the splits in the single launch, after all of a workgroup's items: nobody waits in the first part, so nobody
+// waits for good here, however few workgroups there are.  Every split's workgroup merges its share of the (KV head, part)'s
+// G * HD outputs: it polls all splits' partials of them.  (A ticket and the merge by whoever draws the last one cost an
+// acknowledgement, the counter's round trip and one wave's walk over all partials: 5.9 us; this 3.5.
+// K = 3, one sequence, d = 4096: 390 -> 385 us, at 8 Ki of context 854 -> 834.)
+// An output belongs to a row of 16 lanes, a split to a lane; with more than 16 splits, a share of fewer outputs, to a wave.
+template <int G, int HD, int GS>
+__device__ __forceinline__ void flow_merge(const DraftParams &p, int step, int vb, int nvb) {
+    constexpr int PW = HD + 2, NO = G * HD, SLOTS = 4;
+    const int T = p.split_tokens, S = p.max_splits;
+    const int Lb = seq_dead(p, 0) ? 0 : __builtin_amdgcn_readfirstlane(p.kv_len[0]);
+    const int nsplit = (Lb + step + T) / T;
+    if (nsplit == 1) return;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const bool wide = nsplit > 16;
+    const int RW = wide ? kWave : 16, NR = kBlock / RW;                   // lanes of an output, outputs at a time
+    const int row = wide ? wave : (int)threadIdx.x >> 4, j = lane & (RW - 1);
+    const int first_row = wide ? wave : wave * 4;                         // the wave's first output
+    const int per = (NO + nsplit - 1) / nsplit;
+    const unsigned tag = step_tag(p, step, TS_PART), out_tag = step_tag(p, step, TS_ATTN);
+    const int n_split_items = p.Hkv * S, n_items = n_split_items * GS;
+    for (int item = vb; item < n_items; item += nvb) {
+        const int part = item / n_split_items, it1 = item % n_split_items, kvh = it1 / S, sp = it1 % S;
+        if (sp >= nsplit) continue;
+        const int h0 = (kvh * GS + part) * G;
+        const row_rsrc rs = make_vec_rsrc(p.partt + (size_t)h0 * S * PW, (size_t)G * S * PW * 8);
+        const int o1 = min((sp + 1) * per, NO);
+        for (int ob = sp * per; ob + first_row < o1; ob += NR * SLOTS) {
+            float A[SLOTS], Ls[SLOTS], M[SLOTS];
+#pragma unroll
+            for (int u = 0; u < SLOTS; ++u) A[u] = Ls[u] = 0.f, M[u] = -INFINITY;
+#pragma unroll 1
+            for (int s0 = 0; s0 < nsplit; s0 += RW) {
+                const int sj = s0 + j;
+                u32x2 a[SLOTS];
+                u32x4 ml[SLOTS];
+                PollClock clk;
+                bool late;
+                do {
+                    unsigned off = 0u;
+#pragma unroll
+                    for (int u = 0; u < SLOTS; ++u)
+                        if (ob + first_row + u * NR < o1) {
+                            const int o = ob + row + u * NR;
+                            const bool mine = o < o1 && sj < nsplit;
+                            const int at = ((o / HD) * S + sj) * PW * 8;
+                            a[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                                rs, mine ? at + (o % HD) * 8 : (int)kOobOffset, 0, 16));
+                            ml[u] = ld_coherent16(rs, mine ? at + HD * 8 : (int)kOobOffset);
+                        }
+#pragma unroll
+                    for (int u = 0; u < SLOTS; ++u)
+                        if (ob + first_row + u * NR < o1) {
+                            const bool mine = ob + row + u * NR < o1 && sj < nsplit;
+                            off |= mine ? (a[u].y ^ tag) | (ml[u].y ^ tag) | (ml[u].w ^ tag) : 0u;
+                        }
+                    late = __any((int)off) != 0;
+                } while (late && !clk.expired(p));
+#pragma unroll
+                for (int u = 0; u < SLOTS; ++u)
+                    if (ob + first_row + u * NR < o1) {
+                        const bool mine = ob + row + u * NR < o1 && sj < nsplit;
+                        const float m = mine ? __uint_as_float(ml[u].x) : -INFINITY, mn = fmaxf(M[u], m);
+                        const float mz = mn == -INFINITY ? 0.f : mn;
+                        const float f = exp_term(M[u] - mz), w = exp_term(m - mz);
+                        A[u] = A[u] * f + __uint_as_float(a[u].x) * w;
+                        Ls[u] = Ls[u] * f + __uint_as_float(ml[u].z) * w;
+                        M[u] = mn;
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < SLOTS; ++u)
+                if (ob + first_row + u * NR < o1) {
+                    float mm = row16_max(M[u]);
+                    if (wide) mm = rows_max(mm);
+                    const float w = M[u] == -INFINITY ? 0.f : exp_term(M[u] - mm);
+                    float r = row16_sum(A[u] * w), t = row16_sum(Ls[u] * w);
+                    if (wide) r = rows_sum(r), t = rows_sum(t);
+                    const int o = ob + row + u * NR;
+                    if (j == 0 && o < o1) st_tagged(p.attnt + (size_t)h0 * HD + o, r / t, out_tag);
+                }
+        }
+    }
+}
+
 // COH: q/k/v are read, and the appended cache entries, the result and the split partials written, with
 // device-coherent accesses (the phases of a step run inside one kernel)
 struct NoHook {
@@ -969,11 +1066,12 @@ struct NoHook {
 template <int GT, int HD, bool COH = false, bool TICKET = false, class Hook = NoHook, bool TAGGED = false, int GS = 1>
 __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int vb, int nvb, char *smem, Hook before_q = Hook()) {
     static_assert(GT % GS == 0, "whole heads per part");
+    static_assert(TAGGED || GS == 1, "one ticket per (sequence, KV head)");
     constexpr int G = GT / GS; // query heads per item
     using L = AttnLds<G, HD>;
     // U blocks of TPI tokens per wave and round: one round covers kWaves * U * TPI tokens (with half the heads per
     // item the registers allow a fifth block, and the single-launch kernel's splits of up to 160 tokens need one round)
-    constexpr int LPT = L::LPT, TPI = L::TPI, NSTREAM = L::NSTREAM, U = GS > 1 ? 5 : 4;
+    constexpr int LPT = L::LPT, TPI = L::TPI, U = GS > 1 ? 5 : 4;
     L &s = *reinterpret_cast<L *>(smem);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int c = lane % LPT, tq = lane / LPT;
@@ -991,7 +1089,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
         const int h0 = kvh * GT + part * G; // the item's first query head
         const bool dead = seq_dead(p, b);
         if (p.kv_appended && dead) continue; // a row that is not part of the block (uniform for the workgroup)
-        const int Lb = dead ? 0 : p.kv_len[b];
+        const int Lb = dead ? 0 : __builtin_amdgcn_readfirstlane(p.kv_len[b]);
         const int len = Lb + step + 1, pnew = len - 1;
         const int nsplit = (len + T - 1) / T;
         if (sp >= nsplit) continue; // uniform for the workgroup
@@ -1006,16 +1104,16 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
         const float *qkv = p.qkv + (size_t)b * p.qkv_dim;
         const int nblk = (ntok + TPI - 1) / TPI;
 
+        // (past the split's last token the loads return zeros and move no data; the scores are masked)
+        const row_rsrc k_rs = make_vec_rsrc(kc + (size_t)t0 * HD, (size_t)ntok * HD * 2);
+        const row_rsrc v_rs = make_vec_rsrc(vc + (size_t)t0 * HD, (size_t)ntok * HD * 2);
         u32x4 kr[U], vr[U];
-        bool ok[U];
         auto load_blocks = [&](int base) {
+            const int at = base * 1024 + lane * 16; // a block of TPI tokens is 1 KiB
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                int t = (base + u * kWaves) * TPI + tq;
-                ok[u] = t < ntok;
-                size_t off = (size_t)(t0 + (ok[u] ? t : 0)) * HD + c * 8; // slot t0 is always inside the cache
-                kr[u] = ldg16(kc + off);
-                vr[u] = ldg16(vc + off);
+                kr[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(k_rs, at + u * kWaves * 1024, 0, 0));
+                vr[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(v_rs, at + u * kWaves * 1024, 0, 0));
             }
         };
         load_blocks(wave); // in flight while q, the rotary table and the new key/value are prepared
@@ -1117,126 +1215,122 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
             for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
         }
 
-        // nl: blocks of this round that exist for the wave (uniform): the others are skipped, not masked
-        auto absorb = [&](const float(&sc)[U][G], const float(&vv)[U][8], const bool(&okk)[U], int nl) {
+        // n more tokens for this lane's group: scores sc (-inf: no such token, its value reads as zeros)
+        auto absorb = [&](const auto &sc, const auto &vr, int nl) {
+            constexpr int N = sizeof(vr) / sizeof(vr[0]);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float mb = mx[g];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (u < nl && okk[u]) mb = fmaxf(mb, sc[u][g]);
-                if (mb == -INFINITY) continue;
-                float alpha = expf(mx[g] - mb); // 0 when nothing was absorbed before
-                float sm = sum[g] * alpha;
+                for (int u = 0; u < N; ++u)
+                    if (u < nl) mb = fmaxf(mb, sc[u][g]);
+                const float mz = mb == -INFINITY ? 0.f : mb; // nothing so far: weights of exp(-inf)
+                const float alpha = exp_term(mx[g] - mz);
+                mx[g] = mb;
+                sum[g] *= alpha;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[g][e] *= alpha;
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (u < nl && okk[u]) {
-                        float pr = expf(sc[u][g] - mb);
-                        sm += pr;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) acc[g][e] += pr * vv[u][e];
+                for (int u = 0; u < N; ++u)
+                    if (u < nl) {
+                        const float pr = exp_term(sc[u][g] - mz);
+                        sum[g] += pr;
+                        acc[g][0] += pr * lo_half(vr[u].x);
+                        acc[g][1] += pr * hi_half(vr[u].x);
+                        acc[g][2] += pr * lo_half(vr[u].y);
+                        acc[g][3] += pr * hi_half(vr[u].y);
+                        acc[g][4] += pr * lo_half(vr[u].z);
+                        acc[g][5] += pr * hi_half(vr[u].z);
+                        acc[g][6] += pr * lo_half(vr[u].w);
+                        acc[g][7] += pr * hi_half(vr[u].w);
                     }
-                mx[g] = mb;
-                sum[g] = sm;
             }
         };
 
         for (int base = wave; base < nblk; base += kWaves * U) {
             if (base != wave) load_blocks(base);
+            // blocks of this round that exist for the wave (uniform): the others are skipped, not masked
             const int nl = __builtin_amdgcn_readfirstlane(min(U, (nblk - base + kWaves - 1) / kWaves));
-            float sc[U][G], vv[U][8];
+            float sc[U][G];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (u >= nl) { // no such block: nothing of it is used
-#pragma unroll
-                    for (int g = 0; g < G; ++g) sc[u][g] = 0.f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) vv[u][e] = 0.f;
-                    continue;
-                }
-                float kf[8] = {lo_half(kr[u].x), hi_half(kr[u].x), lo_half(kr[u].y), hi_half(kr[u].y),
-                               lo_half(kr[u].z), hi_half(kr[u].z), lo_half(kr[u].w), hi_half(kr[u].w)};
-                vv[u][0] = lo_half(vr[u].x);
-                vv[u][1] = hi_half(vr[u].x);
-                vv[u][2] = lo_half(vr[u].y);
-                vv[u][3] = hi_half(vr[u].y);
-                vv[u][4] = lo_half(vr[u].z);
-                vv[u][5] = hi_half(vr[u].z);
-                vv[u][6] = lo_half(vr[u].w);
-                vv[u][7] = hi_half(vr[u].w);
+                if (u >= nl) continue;
+                const float kf[8] = {lo_half(kr[u].x), hi_half(kr[u].x), lo_half(kr[u].y), hi_half(kr[u].y),
+                                     lo_half(kr[u].z), hi_half(kr[u].z), lo_half(kr[u].w), hi_half(kr[u].w)};
+                const bool there = (base + u * kWaves) * TPI + tq < ntok;
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     float a = 0.f;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) a += q[g][e] * kf[e];
-                    sc[u][g] = (LPT == 16) ? row16_sum(a) : oct_sum(a);
+                    a = (LPT == 16) ? row16_sum(a) : oct_sum(a);
+                    sc[u][g] = there ? a : -INFINITY;
                 }
             }
-            absorb(sc, vv, ok, nl);
+            absorb(sc, vr, nl);
         }
-        if (last && wave == 0) { // the token being appended, from LDS; every lane group computes it, group 0 keeps it
-            float sc[U][G], vv[U][8];
-            bool okn[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                okn[u] = (u == 0) && (tq == 0);
-#pragma unroll
-                for (int g = 0; g < G; ++g) sc[u][g] = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) vv[u][e] = 0.f;
+        if (last && wave == kWaves - 1) { // the token being appended, from LDS, for the wave with the fewest blocks
+            float sc[1][G];
+            u32x4 vn[1] = {u32x4{0u, 0u, 0u, 0u}}; // (bf16 values: the halves are exact)
+            if (tq == 0) {
+                const float *v = s.vnew + c * 8;
+                vn[0] = u32x4{f32_to_bf16x2(v[0], v[1]), f32_to_bf16x2(v[2], v[3]), f32_to_bf16x2(v[4], v[5]),
+                              f32_to_bf16x2(v[6], v[7])};
             }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) vv[0][e] = s.vnew[c * 8 + e];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float a = 0.f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) a += q[g][e] * s.knew[c * 8 + e];
-                sc[0][g] = (LPT == 16) ? row16_sum(a) : oct_sum(a);
+                a = (LPT == 16) ? row16_sum(a) : oct_sum(a);
+                sc[0][g] = tq == 0 ? a : -INFINITY; // every lane group computes it, group 0 keeps it
             }
-            absorb(sc, vv, okn, 1);
+            absorb(sc, vn, 1);
         }
-        // merge the lane groups of the workgroup
-        // (a single split publishes its result as tagged elements that other workgroups act on at once: the appended
-        // cache entry, written by waves of this workgroup above, is acknowledged first; the barriers below order it
-        // before every wave's result stores)
-        if (TAGGED && nsplit == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const int stream = wave * TPI + tq;
+        // Merge the wave's lane groups: the weights exp(max - maximum of the wave), then sums over the groups in which each
+        // row of 16 lanes ends up with two of the eight elements (a swap and an addition halve two registers' worth at once)
+        const int row = lane >> 4;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
+            float mw = mx[g];
+            if (LPT == 8) mw = fmaxf(mw, dpp_f32<0x128>(mw)); // row_ror:8
+            mw = rows_max(mw);
+            const float w = mx[g] == -INFINITY ? 0.f : exp_term(mx[g] - mw);
+            float sw = sum[g] * w;
+            if (LPT == 8) sw += dpp_f32<0x128>(sw);
+            sw = rows_sum(sw);
+            float a[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s.acc[stream][g][c * 8 + e] = acc[g][e];
-            if (c == 0) {
-                s.ml[stream][g][0] = mx[g];
-                s.ml[stream][g][1] = sum[g];
+            for (int e = 0; e < 8; ++e) {
+                a[e] = acc[g][e] * w;
+                if (LPT == 8) a[e] += dpp_f32<0x128>(a[e]);
             }
-        }
-        lds_barrier();
-        // wave g forms the weights of head g's streams once (lane = stream): exp(max_stream - max), zero for a stream
-        // that saw no token; they replace the stream maxima in LDS, and the head's maximum and weighted sum go where
-        // the rotary table used to be
-        static_assert(NSTREAM <= kWave && G <= kWaves && G <= HD / 2, "one wave per head, one lane per stream");
-        if (wave < G) {
-            const float mm = lane < NSTREAM ? s.ml[lane][wave][0] : -INFINITY;
-            const float ll = lane < NSTREAM ? s.ml[lane][wave][1] : 0.f;
-            const float M = wave_max(mm);
-            const float w = mm != -INFINITY ? expf(mm - M) : 0.f;
-            const float Ls = wave_sum(ll * w);
-            if (lane < NSTREAM) s.ml[lane][wave][0] = w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = sum32_of(a[e], a[e + 4]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) a[e] = sum16_of(a[e], a[e + 2]);
+            if ((lane & 15) < LPT)
+                *reinterpret_cast<f32x2 *>(&s.acc[wave][g][c * 8 + row * 2]) = f32x2{a[0], a[1]};
             if (lane == 0) {
-                s.cs[wave] = M;
-                s.sn[wave] = Ls;
+                s.m[g][wave] = mw;
+                s.l[g][wave] = sw;
             }
         }
+        // (what is published below other workgroups act on: the appended cache entry, written by waves of this workgroup
+        // above, is acknowledged first; the barrier orders it before every wave's stores)
+        if (TAGGED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lds_barrier();
         for (int o = tid; o < G * HD; o += kBlock) {
-            int g = o / HD, dd = o % HD;
-            const float M = s.cs[g], Ls = s.sn[g];
-            float A = 0.f;
-#pragma unroll 8
-            for (int st = 0; st < NSTREAM; ++st) A += s.acc[st][g][dd] * s.ml[st][g][0];
+            const int g = o / HD, dd = o % HD;
+            float M = s.m[g][0], Ls = 0.f, A = 0.f;
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, s.m[g][w]);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float f = s.m[g][w] == -INFINITY ? 0.f : exp_term(s.m[g][w] - M); // (a wave without a token)
+                Ls += s.l[g][w] * f;
+                A += s.acc[w][g][dd] * f;
+            }
             int hq = h0 + g;
             if (nsplit == 1) {
                 const float r = A / Ls;
@@ -1251,6 +1345,11 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
                     p.attn_split[at] = h;
                     p.attn_split[p.a_lo + at] = l;
                 }
+            } else if (TAGGED) {
+                const unsigned tag = step_tag(p, step, TS_PART);
+                unsigned long long *dst = p.partt + ((size_t)hq * S + sp) * PW;
+                st_tagged(dst + dd, A, tag);
+                if (dd < 2) st_tagged(dst + HD + dd, dd == 0 ? M : Ls, tag);
             } else {
                 float *dst = p.attn_part + (((size_t)b * p.Hq + hq) * S + sp) * PW;
                 st_f32<COH || TICKET>(dst + dd, A);
@@ -1260,7 +1359,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
                 }
             }
         }
-        if (TICKET && nsplit > 1) {
+        if (TICKET && !TAGGED && nsplit > 1) {
             // The workgroup whose split of this (sequence, KV head) is the last to finish merges the splits, one
             // query head per wave.  The partials above were written through to memory and have been acknowledged
             // (the wait below) before this workgroup draws its ticket, and the merging workgroup reads them past its
@@ -1269,7 +1368,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (tid == 0) {
-                int *ticket = p.attn_ticket + ((size_t)b * p.Hkv + kvh) * GS + part; // (GS > 1: one sequence)
+                int *ticket = p.attn_ticket + (size_t)b * p.Hkv + kvh;
                 const int old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (old == nsplit - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 last_to_arrive = (old == nsplit - 1) ? 1 : 0;
@@ -1277,11 +1376,11 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
             __syncthreads();
             const bool merges = last_to_arrive != 0;
             if (merges && wave < G)
-                merge_head<HD, true, COH, TAGGED>(p, b, h0 + wave, nsplit,
-                                                  reinterpret_cast<float *>(smem) + (size_t)wave * S, step);
+                merge_head<HD, true, COH>(p, b, h0 + wave, nsplit, reinterpret_cast<float *>(smem) + (size_t)wave * S);
         }
     }
     if (first_item) before_q();
+    if constexpr (TAGGED) flow_merge<G, HD, GS>(p, step, vb, nvb);
 }
 
 // ---------------------------------------------------------------------------------------------------

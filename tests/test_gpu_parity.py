@@ -418,6 +418,27 @@ def test_single_launch_one_sequence_row_streaming(gpu, hq, hkv, hd):
         eng.close()
 
 
+@pytest.mark.parametrize("hq,hkv,hd", [(8, 1, 64), (8, 1, 128), (4, 2, 128), (8, 8, 64)])
+@pytest.mark.parametrize("splits", [1, 2, 16, 33, 63])
+def test_single_launch_merges_of_many_splits(gpu, hq, hkv, hd, splits):
+    """The first step's context fills its splits of 128 tokens, the second one's last split is the new token alone; an
+    output's partials then lie in one row of lanes (up to 16 splits), in a wave, or beyond one."""
+    binding = gpu["binding"]
+    cap = 128 * 64 // hkv
+    ctx = min(128 * splits, cap - 128) - 1
+    shape = synth.HeadShape(512, hq, hkv, hd, 688, 2048)
+    wl = synth.Workload(f"splits_{hq}_{hkv}_{hd}", 170 + hq + hd + splits, shape, 1, 0, 0, (512,), 3, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=np.array([ctx], dtype=np.int32), capacity=cap)
+    eng = binding.DraftEngine(shape, w, [ids], 1, cap, 3)
+    assert binding.mtp_set_launch_mode(eng.handle, binding.LAUNCH_SINGLE) == 0
+    for _ in range(2):
+        ref, res, caches = run_both(gpu, shape, w, w, act, [ids], 0, 3, engine=eng)
+        check_chain(ref, res, caches, act["kv_len"], 3, need_clear=False)
+    eng.close()
+
+
 @pytest.mark.parametrize("d_ffn", [1288, 3400])
 def test_single_launch_gate_and_up_rows_left_over(gpu, d_ffn):
     """The gate and up rows beyond whole rounds of the grid's 2048 waves are dealt singly; where more than 1024 of each
