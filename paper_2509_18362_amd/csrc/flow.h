@@ -47,133 +47,148 @@ __host__ __device__ inline size_t flow_gemv_region(int d, int qd, int F) {
 
 enum FlowPhase : int { FL_PROJH = 0, FL_PROJE, FL_QKV, FL_O, FL_GATEUP, FL_DOWN, FL_HEAD, FL_NONE };
 
-// One matrix phase as a list of rows (run-time description): up to three matrices stacked row-wise.  PAIRED: the
-// rows of [w_gate; w_up] dealt so that a wave gets row q of both, one after the other (its j-th row is gate or up row
-// (j / 2) * nw + w for j < 2 * pair_rounds; the rem = F % nw rows of each matrix that are left over are dealt singly:
+// One matrix phase as a list of rows: up to three matrices stacked row-wise, wave w takes the virtual rows w, w + nw, ...
+// Gate and up: the rows of [w_gate; w_up] dealt so that a wave gets row q of both, one after the other (its j-th row is gate or
+// up row (j / 2) * nw + w for j < 2 * pair_rounds; the rem = F % nw rows of each matrix that are left over are dealt singly:
 // rem gate rows, then rem up rows, numbered on from the pairs - 2 rem may exceed nw, the waves then get a second
 // round of them).  Virtual row v = w + j * nw, as in every other phase.
-struct FlowJob {
-    const uint16_t *base[3];
-    int seg1, seg2; // first row of the second and of the third matrix
-    int pitch;      // elements between consecutive rows of a matrix
-    int K, rows;
-    const int *ids; // optional row indirection (the compressed output head)
-    int paired, pair_rounds, rem, nw;
-    // The id list is read-only during the call and row indices are wave-uniform: a scalar load (a vector load would make
-    // the wave wait for every weight chunk in flight before it can form the row's address).
-    __device__ __forceinline__ int row_id(int v) const {
-        typedef const int __attribute__((address_space(4))) *const_int_ptr;
-        return ids ? *((const_int_ptr)(ids + min(v, rows - 1))) : 0;
-    }
-    // rid: the row's entry of the id list (ids jobs), fetched by the caller one chunk ahead
-    __device__ __forceinline__ const uint16_t *rowptr(int v, int j, int rid) const {
-        if (paired) {
-            const int w = v - j * nw;
-            int mat, r;
-            if (j < 2 * pair_rounds) {
-                mat = j & 1;
-                r = (j >> 1) * nw + w;
-            } else {
-                const int i = v - 2 * pair_rounds * nw; // 0 .. 2 rem - 1
-                mat = i < rem ? 0 : 1;
-                r = pair_rounds * nw + (i < rem ? i : i - rem);
-            }
-            return (mat ? base[1] : base[0]) + (size_t)r * pitch; // (no run-time index: the struct stays in registers)
-        }
-        const int r = ids ? rid : v;
-        const uint16_t *b = r < seg1 ? base[0] : r < seg2 ? base[1] : base[2];
-        const int o = r < seg1 ? r : r < seg2 ? r - seg1 : r - seg2;
-        return b + (size_t)o * pitch;
-    }
+// A wave's share comes in chunks of CL 1 KiB loads (eight, or four or two where rows are shorter: a half-empty chunk requests,
+// reads and multiplies zeros); a chunk never straddles rows; the chunk count is padded to an odd number of at least three (a
+// phase's first three chunks sit in register slot 0, register slot 1 and the LDS slot, the rest alternate between the register
+// slots).
+//
+// All of it stands in three registers for the whole call: lane 8 * phase + field.  A field is one instruction away, where
+// forming it anew (a division, a choice between the phases and loads of the arguments, twice per phase) stood in every phase's
+// chain, and keeping it in scalar registers pushed others out into vector lanes.  K = 3, one sequence, d = 256: 121 -> 108 us, d = 4096:
+// 386 -> 384 (its chains hide behind the weights on their way).
+struct FlowTab {
+    int num, ptr, io;
 };
-
-__device__ __forceinline__ FlowJob flow_job(const DraftParams &p, int ph, int nw) {
-    constexpr int kNone = 0x7fffffff;
-    FlowJob j;
-    j.base[1] = j.base[2] = nullptr;
-    j.seg1 = j.seg2 = kNone;
-    j.ids = nullptr;
-    j.paired = 0;
-    j.pair_rounds = j.rem = 0;
-    j.nw = nw;
-    switch (ph) {
-    case FL_PROJH: j.base[0] = p.w_proj; j.pitch = 2 * p.d; j.K = p.d; j.rows = p.d; break;
-    case FL_PROJE: j.base[0] = p.w_proj + p.d; j.pitch = 2 * p.d; j.K = p.d; j.rows = p.d; break;
-    case FL_QKV:
-        j.base[0] = p.w_q; j.base[1] = p.w_k; j.base[2] = p.w_v;
-        j.seg1 = p.qd; j.seg2 = p.qd + p.kvd;
-        j.pitch = p.d; j.K = p.d; j.rows = p.qkv_dim;
-        break;
-    case FL_O: j.base[0] = p.w_o; j.pitch = p.qd; j.K = p.qd; j.rows = p.d; break;
-    case FL_GATEUP:
-        j.base[0] = p.w_gate; j.base[1] = p.w_up;
-        j.pitch = p.d; j.K = p.d; j.rows = 2 * p.F;
-        j.paired = 1; j.pair_rounds = p.F / nw; j.rem = p.F % nw;
-        break;
-    case FL_DOWN: j.base[0] = p.w_down; j.pitch = p.F; j.K = p.F; j.rows = p.d; break;
-    default: j.base[0] = p.lm_head; j.ids = p.ids; j.pitch = p.d; j.K = p.d; j.rows = p.n; break;
-    }
-    return j;
+enum FlowNum : int { FN_K = 0, FN_PITCH, FN_ROWS, FN_NREAL, FN_CPR, FN_LAST, FN_A, FN_B }; // LAST: the wave's last row;
+                                                         // A, B: first rows of w_k, w_v; pair_rounds, rem of gate and up
+enum FlowPtr : int { FP_MAT = 0, FP_IDS = 6 };           // up to three matrices; the row list of the output head
+enum FlowIo : int { FI_GAIN = 0, FI_OUT = 2, FI_IN = 4 }; // gains of the phase's norm, vector it writes, vector it polls
+__device__ __forceinline__ int flow_num(const FlowTab &t, int ph, int f) { return __builtin_amdgcn_readlane(t.num, ph * 8 + f); }
+__device__ __forceinline__ unsigned long long flow_word2(int v, int ph, int f) {
+    return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane(v, ph * 8 + f + 1) << 32) |
+           (unsigned)__builtin_amdgcn_readlane(v, ph * 8 + f);
 }
+template <class T>
+__device__ __forceinline__ T *flow_ptr(int v, int ph, int f) { return reinterpret_cast<T *>(flow_word2(v, ph, f)); }
 
-// a wave's share of a job: rows wr0, wr0 + nw, ...; chunks of CL 1 KiB loads (eight, or four or two where rows are shorter:
-// a half-empty chunk requests, reads and multiplies zeros), a chunk never straddles rows; the
-// chunk count is padded to an odd number of at least three (a phase's first three chunks sit in register slot 0,
-// register slot 1 and the LDS slot, the rest alternate between the register slots)
-struct FlowGeom {
-    int nblk, cpr, nrows, nreal, nchunks, wr_last;
-};
 template <int CL>
-__device__ __forceinline__ FlowGeom flow_geom(const FlowJob &j, int wr0, int nw) {
-    FlowGeom g;
-    g.nblk = (j.K + 511) / 512;
-    g.cpr = (g.nblk + CL - 1) / CL;
-    g.nrows = wr0 < j.rows ? (j.rows - wr0 + nw - 1) / nw : 0;
-    g.nreal = g.nrows * g.cpr;
-    g.nchunks = max(3, g.nreal | 1);
-    g.wr_last = wr0 + max(g.nrows - 1, 0) * nw;
-    return g;
+__device__ __forceinline__ int flow_chunks(int K) { return ((K + 511) / 512 + CL - 1) / CL; } // of a row
+__device__ __forceinline__ int flow_rows(int rows, int wr0, int nw) { return wr0 < rows ? (rows - wr0 + nw - 1) / nw : 0; }
+template <int CL>
+__device__ __forceinline__ FlowTab flow_tab(const DraftParams &p, int wr0, int nw) {
+    const int lane = threadIdx.x & (kWave - 1), ph = lane >> 3, f = lane & 7; // (FL_NONE: no rows)
+    const int K = ph == FL_O ? p.qd : ph == FL_DOWN ? p.F : p.d;
+    const int rows = ph == FL_QKV ? p.qkv_dim : ph == FL_GATEUP ? 2 * p.F : ph == FL_HEAD ? p.n : ph == FL_NONE ? 0 : p.d;
+    const int pitch = ph <= FL_PROJE ? 2 * p.d : K;
+    const int cpr = flow_chunks<CL>(K), nrows = flow_rows(rows, wr0, nw);
+    const int rounds = p.F / nw;
+    FlowTab t;
+    t.num = f == FN_K ? K : f == FN_PITCH ? pitch : f == FN_ROWS ? rows : f == FN_NREAL ? nrows * cpr : f == FN_CPR ? cpr
+            : f == FN_LAST ? wr0 + max(nrows - 1, 0) * nw
+            : f == FN_A ? (ph == FL_QKV ? p.qd : rounds) : (ph == FL_QKV ? p.qd + p.kvd : p.F - rounds * nw);
+    const void *m = nullptr, *v = nullptr;
+    const int mat = f >> 1;
+    if (mat == 0)
+        m = ph == FL_PROJH ? p.w_proj : ph == FL_PROJE ? p.w_proj + p.d : ph == FL_QKV ? p.w_q : ph == FL_O ? p.w_o
+            : ph == FL_GATEUP ? p.w_gate : ph == FL_DOWN ? p.w_down : p.lm_head;
+    if (mat == 1) m = ph == FL_QKV ? p.w_k : p.w_up;
+    if (mat == 2) m = p.w_v;
+    if (mat == 3 && ph == FL_HEAD) m = p.ids;
+    if (mat == 0)
+        v = ph == FL_PROJH ? p.g_h : ph == FL_PROJE ? p.g_e : ph == FL_QKV ? p.g_attn : ph == FL_GATEUP ? p.g_mlp : p.g_final;
+    if (mat == 1)
+        v = ph == FL_PROJE ? p.xt : ph == FL_QKV ? p.qkvt : ph == FL_O ? p.ot : ph == FL_GATEUP ? p.gut : p.dnt;
+    if (mat == 2)
+        v = ph == FL_QKV ? p.xt : ph == FL_O ? p.attnt : ph == FL_GATEUP ? p.ot : ph == FL_DOWN ? p.gut : p.dnt;
+    const unsigned long long mw = reinterpret_cast<unsigned long long>(m), vw = reinterpret_cast<unsigned long long>(v);
+    t.ptr = (int)(f & 1 ? mw >> 32 : mw);
+    t.io = (int)(f & 1 ? vw >> 32 : vw);
+    return t;
 }
 
-// load cursor of a wave: which job it is requesting chunks of, and where in the wave's share it stands
+// load cursor of a wave: which phase it is requesting chunks of, and where in the wave's share it stands
 struct FlowLoad {
-    FlowJob j;
-    FlowGeom g;
-    int id;           // FlowPhase the cursor is in
+    int id;            // FlowPhase the cursor is in
+    const uint16_t *base;           // its first matrix
+    int K, pitch, nreal, cpr, last;
     int row, jr, c, n; // next chunk: virtual row, its round, chunk within the row, chunks requested so far
     int rid;           // id-list entry of `row` (requested when the cursor moved there, used at the next request)
 };
-__device__ __forceinline__ void flow_load_begin(FlowLoad &L, const FlowJob &j, const FlowGeom &g, int id, int wr0) {
-    L.j = j;
-    L.g = g;
+// The id list is read-only during the call and row indices are wave-uniform: a scalar load (a vector load would make
+// the wave wait for every weight chunk in flight before it can form the row's address).
+__device__ __forceinline__ int flow_row_id(const FlowTab &t, int id, int v) {
+    typedef const int __attribute__((address_space(4))) *const_int_ptr;
+    if (id != FL_HEAD) return 0;
+    const int *ids = flow_ptr<const int>(t.ptr, FL_HEAD, FP_IDS);
+    return ids ? *((const_int_ptr)(ids + min(v, flow_num(t, FL_HEAD, FN_ROWS) - 1))) : v;
+}
+__device__ __forceinline__ void flow_load_begin(FlowLoad &L, const FlowTab &t, int id, int wr0) {
     L.id = id;
+    L.base = flow_ptr<const uint16_t>(t.ptr, id, FP_MAT);
+    L.K = flow_num(t, id, FN_K);
+    L.pitch = flow_num(t, id, FN_PITCH);
+    L.nreal = flow_num(t, id, FN_NREAL);
+    L.cpr = flow_num(t, id, FN_CPR);
+    L.last = flow_num(t, id, FN_LAST);
     L.row = wr0;
     L.jr = 0;
     L.c = 0;
     L.n = 0;
-    L.rid = j.row_id(wr0);
+    L.rid = flow_row_id(t, id, wr0);
+}
+// the row the cursor stands in (past the wave's last chunk a zero-length buffer), then the cursor moves on by a chunk; voff: the
+// lane's offset of the chunk in the row
+template <int CL>
+__device__ __forceinline__ row_rsrc flow_next(FlowLoad &L, const FlowTab &t, int nw, int lane, int &voff) {
+    const bool live = L.n < L.nreal;
+    int v = min(L.row, L.last), mat = 0;
+    if (L.id == FL_GATEUP) {
+        const int pairs = flow_num(t, FL_GATEUP, FN_A), rem = flow_num(t, FL_GATEUP, FN_B);
+        if (L.jr < 2 * pairs) {
+            mat = L.jr & 1;
+            v = (L.jr >> 1) * nw + v - L.jr * nw;
+        } else {
+            const int i = v - 2 * pairs * nw; // 0 .. 2 rem - 1
+            mat = i < rem ? 0 : 1;
+            v = pairs * nw + (i < rem ? i : i - rem);
+        }
+    } else if (L.id == FL_QKV) {
+        const int k0 = flow_num(t, FL_QKV, FN_A), v0 = flow_num(t, FL_QKV, FN_B);
+        mat = v < k0 ? 0 : v < v0 ? 1 : 2;
+        v -= v < k0 ? 0 : v < v0 ? k0 : v0;
+    } else if (L.id == FL_HEAD) {
+        v = L.rid;
+    }
+    const uint16_t *base = L.base;
+    if (mat != 0) base = flow_ptr<const uint16_t>(t.ptr, L.id, FP_MAT + 2 * mat);
+    const uint16_t *row = base + (size_t)(live ? v : 0) * L.pitch;
+    const row_rsrc rs = make_row_rsrc(row, live ? L.K * 2 : 0); // wave-uniform
+    // The block's offset travels in the per-lane offset, which the buffer's range check covers: whatever lies beyond the
+    // row (the tail of its last block, the empty slots of its last chunk) reads as zeros and moves no data.
+    voff = lane * 16 + L.c * (CL * 1024);
+    ++L.n;
+    if (++L.c == L.cpr) {
+        L.c = 0;
+        L.row += nw;
+        ++L.jr;
+        L.rid = flow_row_id(t, L.id, L.row);
+    }
+    return rs;
 }
 // Request the cursor's next chunk into a ring slot.  Past the wave's last chunk (padding, or no next phase) the
 // request goes to a zero-length buffer: it returns zeros and moves no data, so the ring is refilled without a branch
 // around any load and the compiler can count the loads in flight.
 template <int CL>
-__device__ __forceinline__ void flow_issue(FlowLoad &L, u32x4 (&buf)[CL], int lane) {
-    const bool live = L.n < L.g.nreal;
-    const int v = live ? min(L.row, L.g.wr_last) : 0;
-    const int jr = live ? L.jr : 0;
-    const row_rsrc rs = make_row_rsrc(L.j.rowptr(v, jr, L.rid), live ? L.j.K * 2 : 0); // wave-uniform
-    // The block's offset travels in the per-lane offset, which the buffer's range check covers: whatever lies beyond the
-    // row (the tail of its last block, the empty slots of its last chunk) reads as zeros and moves no data.
-    const int voff = lane * 16 + L.c * (CL * 1024);
+__device__ __forceinline__ void flow_issue(FlowLoad &L, const FlowTab &t, int nw, u32x4 (&buf)[CL], int lane) {
+    int voff;
+    const row_rsrc rs = flow_next<CL>(L, t, nw, lane, voff);
 #pragma unroll
     for (int u = 0; u < CL; ++u) buf[u] = row_load16<true>(rs, voff + u * 1024, 0);
-    ++L.n;
-    if (++L.c == L.g.cpr) {
-        L.c = 0;
-        L.row += L.j.nw;
-        ++L.jr;
-        L.rid = L.j.row_id(L.row);
-    }
 }
 
 // The same request into the wave's LDS slot (8 KiB: up to eight loads of 1 KiB, each lane's 16 bytes where a register load
@@ -181,23 +196,13 @@ __device__ __forceinline__ void flow_issue(FlowLoad &L, u32x4 (&buf)[CL], int la
 // the reader does (flow_wait_lds_slot).
 constexpr int kLdsSlotBytes = kChunkLoads * 1024;
 template <int CL>
-__device__ __forceinline__ void flow_issue_lds(FlowLoad &L, char *slot, int lane) {
-    const bool live = L.n < L.g.nreal;
-    const int v = live ? min(L.row, L.g.wr_last) : 0;
-    const int jr = live ? L.jr : 0;
-    const row_rsrc rs = make_row_rsrc(L.j.rowptr(v, jr, L.rid), live ? L.j.K * 2 : 0); // wave-uniform
-    const int voff = lane * 16 + L.c * (CL * 1024);
+__device__ __forceinline__ void flow_issue_lds(FlowLoad &L, const FlowTab &t, int nw, char *slot, int lane) {
+    int voff;
+    const row_rsrc rs = flow_next<CL>(L, t, nw, lane, voff);
 #pragma unroll
     for (int u = 0; u < CL; ++u)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(slot + u * 1024), 16,
                                                  voff + u * 1024, 0, 0, 2);
-    ++L.n;
-    if (++L.c == L.g.cpr) {
-        L.c = 0;
-        L.row += L.j.nw;
-        ++L.jr;
-        L.rid = L.j.row_id(L.row);
-    }
 }
 // The LDS slot's chunk was requested before the two register chunks that follow it in the stream and
 // loads complete in order: once at most those (2 CL) requests are outstanding it has landed.
@@ -445,24 +450,31 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
     };
 
     u32x4 ring[2][CL];
+    // The call's first requests go out before the table is formed, which waits for all of the arguments.
+    FlowTab tab = {0, 0, 0};
     FlowLoad L;
-    L.id = FL_NONE;
+    L.id = FL_PROJH;
+    L.base = p.w_proj;
+    L.K = d;
+    L.pitch = 2 * d;
+    L.cpr = flow_chunks<CL>(d);
+    L.nreal = flow_rows(d, wr0, nw) * L.cpr;
+    L.last = wr0 + max(flow_rows(d, wr0, nw) - 1, 0) * nw;
+    L.row = wr0;
+    L.jr = L.c = L.n = L.rid = 0;
+    flow_issue(L, tab, nw, ring[0], lane);
+    flow_issue(L, tab, nw, ring[1], lane);
+    flow_issue_lds<CL>(L, tab, nw, slot, lane);
+    tab = flow_tab<CL>(p, wr0, nw);
     bool slot_late = false; // the LDS slot's chunk of the phase that begins has not been requested yet
 
     for (int step = 0; step < p.K; ++step) {
 #pragma unroll 1
         for (int ph = FL_PROJH; ph <= FL_HEAD; ++ph) {
-            const FlowJob job = flow_job(p, ph, nw);
-            const FlowGeom g = flow_geom<CL>(job, wr0, nw);
-            const int kpad = flow_kpad(job.K);
+            const int K = flow_num(tab, ph, FN_K), nblk = (K + 511) / 512, kpad = nblk * 512;
+            const int nreal = flow_num(tab, ph, FN_NREAL), cpr = flow_num(tab, ph, FN_CPR), nchunks = max(3, nreal | 1);
             uint16_t *act_hi = reinterpret_cast<uint16_t *>(smem), *act_lo = act_hi + kpad;
             const int sec = ph == FL_PROJH ? 7 : ph == FL_PROJE ? 0 : ph == FL_QKV ? 1 : ph + 0; // O..HEAD are 3..6
-            if (L.id != ph) { // first phase of the call, or the phase after the attention: nothing was requested ahead
-                flow_load_begin(L, job, g, ph, wr0);
-                flow_issue(L, ring[0], lane);
-                flow_issue(L, ring[1], lane);
-                flow_issue_lds<CL>(L, slot, lane);
-            }
             stamp(step, sec, kTraceRequested);
             flow_barrier(); // every wave has finished with the activations of the phase before
 
@@ -471,8 +483,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                 float v[kMaxNormIter][4];
                 // The gains of this phase's norm are requested before anything is polled: they do not depend on it, and a
                 // load issued after the poll would add its own trip through the (busy) memory system to the hand-over.
-                const uint16_t *gain = ph == FL_PROJH ? p.g_h : ph == FL_PROJE ? p.g_e : ph == FL_QKV ? p.g_attn
-                                       : ph == FL_GATEUP ? p.g_mlp : p.g_final;
+                const uint16_t *gain = flow_ptr<const uint16_t>(tab.io, ph, FI_GAIN);
                 u32x2 gq[kMaxNormIter];
 #pragma unroll
                 for (int it = 0; it < kMaxNormIter; ++it) {
@@ -548,12 +559,12 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                     break;
                 }
                 case FL_QKV:
-                    poll_vec<kMaxNormIter>(p, p.xt, d, step_tag(p, step, TS_X), v);
+                    poll_vec<kMaxNormIter>(p, flow_ptr<const unsigned long long>(tab.io, FL_QKV, FI_IN), d, step_tag(p, step, TS_X), v);
                     stamp(step, sec, kTraceReleased);
                     flow_norm(v, gq, d, kpad, p.eps, act_hi, act_lo, red, resid, nullptr, nullptr);
                     break;
                 case FL_GATEUP: { // x1 = x + w_o a
-                    poll_vec<kMaxNormIter>(p, p.ot, d, step_tag(p, step, TS_O), v);
+                    poll_vec<kMaxNormIter>(p, flow_ptr<const unsigned long long>(tab.io, FL_GATEUP, FI_IN), d, step_tag(p, step, TS_O), v);
                     stamp(step, sec, kTraceReleased);
 #pragma unroll
                     for (int it = 0; it < kMaxNormIter; ++it) {
@@ -570,7 +581,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                     break;
                 }
                 case FL_HEAD: { // x2 = x1 + w_down m; the step's output hidden state
-                    poll_vec<kMaxNormIter>(p, p.dnt, d, step_tag(p, step, TS_DN), v);
+                    poll_vec<kMaxNormIter>(p, flow_ptr<const unsigned long long>(tab.io, FL_HEAD, FI_IN), d, step_tag(p, step, TS_DN), v);
                     stamp(step, sec, kTraceReleased);
 #pragma unroll
                     for (int it = 0; it < kMaxNormIter; ++it) {
@@ -634,7 +645,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                 }
             }
             if (slot_late) { // the third chunk requested ahead for this phase (see the end of a phase)
-                flow_issue_lds<CL>(L, slot, lane);
+                flow_issue_lds<CL>(L, tab, nw, slot, lane);
                 slot_late = false;
             }
             flow_barrier();
@@ -644,13 +655,12 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
             const int next = ph == FL_QKV ? FL_NONE : ph == FL_HEAD ? (step + 1 < p.K ? FL_PROJH : FL_NONE) : ph + 1;
             const unsigned out_tag = step_tag(p, step, ph == FL_PROJE ? TS_X : ph == FL_QKV ? TS_QKV : ph == FL_O ? TS_O
                                                        : ph == FL_GATEUP ? TS_GU : TS_DN);
-            unsigned long long *out_t = ph == FL_PROJE ? p.xt : ph == FL_QKV ? p.qkvt : ph == FL_O ? p.ot
-                                        : ph == FL_GATEUP ? p.gut : ph == FL_DOWN ? p.dnt : nullptr;
+            unsigned long long *out_t = flow_ptr<unsigned long long>(tab.io, ph, FI_OUT); // (of the phases that have one)
             float *logits = (ph == FL_HEAD && p.logits_out) ? p.logits_out + (size_t)step * p.n : nullptr;
             unsigned long long best = 0ull; // output head: best (logit, row) this wave has seen (lane 0)
             float gate_saved = 0.f;
-            const int pair_rows = 2 * job.pair_rounds;
-            const bool throttle = g.nchunks >= 8;
+            const int pair_rounds = flow_num(tab, FL_GATEUP, FN_A), pair_rows = 2 * pair_rounds;
+            const bool throttle = nchunks >= 8;
 
             f32x4 acc_h = {0.f, 0.f, 0.f, 0.f}, acc_l = {0.f, 0.f, 0.f, 0.f};
             const int dv = (lane & 15) - 4 * (lane >> 4); // which of this lane's four results lies on the diagonal
@@ -660,7 +670,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
 #pragma unroll
                 for (int u = 0; u < CL; ++u) {
                     // slots past the row's last block hold zero weights: they re-read the last block's activations
-                    const int e0 = min(c_c * CL + u, g.nblk - 1) * 512 + lane * 8;
+                    const int e0 = min(c_c * CL + u, nblk - 1) * 512 + lane * 8;
                     const u32x4 ah = *reinterpret_cast<const u32x4 *>(act_hi + e0);
                     const u32x4 al = *reinterpret_cast<const u32x4 *>(act_lo + e0);
                     const u32x4 wv = w(u);
@@ -670,13 +680,10 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
             };
             // the cursor moves on to the phase that follows once this phase's share is exhausted
             auto advance_cursor = [&]() {
-                if (L.n >= L.g.nchunks && L.id == ph && next != FL_NONE) {
-                    const FlowJob nj = flow_job(p, next, nw);
-                    flow_load_begin(L, nj, flow_geom<CL>(nj, wr0, nw), next, wr0);
-                }
+                if (L.n >= nchunks && L.id == ph && next != FL_NONE) flow_load_begin(L, tab, next, wr0);
             };
             auto row_end = [&](int n) {
-                if (n < g.nreal && ++c_c == g.cpr) { // end of a row: sum the diagonal
+                if (n < nreal && ++c_c == cpr) { // end of a row: sum the diagonal
                     c_c = 0;
                     const f32x4 t = acc_h + acc_l;
                     float val = dv == 0 ? t.x : dv == 1 ? t.y : dv == 2 ? t.z : dv == 3 ? t.w : 0.f;
@@ -696,7 +703,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                                 else
                                     st_tagged(out_t + (c_j >> 1) * nw + w, silu_mul(gate_saved, val), out_tag);
                             } else { // dealt singly: gate values, then up values, behind the pairs
-                                st_tagged(out_t + c_row - job.pair_rounds * nw, val, out_tag);
+                                st_tagged(out_t + c_row - pair_rounds * nw, val, out_tag);
                             }
                             break;
                         }
@@ -717,7 +724,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
             // after the first two.  Every register slot is refilled as soon as it is free; the LDS slot is refilled once,
             // at the end of the phase, with the third chunk of the phase that follows.
             int pend = 0; // register slots whose refill waits for the end of the phase
-            for (int n0 = 0; n0 < g.nchunks; n0 += (n0 == 0 ? 3 : 2)) {
+            for (int n0 = 0; n0 < nchunks; n0 += (n0 == 0 ? 3 : 2)) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
                     consume([&](int u) { return ring[s][u]; });
@@ -736,7 +743,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                         pend |= 1 << s;
                     } else {
                         if (throttle) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                        flow_issue(L, ring[s], lane);
+                        flow_issue(L, tab, nw, ring[s], lane);
                         row_end(n0 + s);
                     }
                 }
@@ -746,8 +753,8 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                     row_end(2);
                 }
             }
-            if (pend & 1) flow_issue(L, ring[0], lane);
-            if (pend & 2) flow_issue(L, ring[1], lane);
+            if (pend & 1) flow_issue(L, tab, nw, ring[0], lane);
+            if (pend & 2) flow_issue(L, tab, nw, ring[1], lane);
             // The LDS slot's chunk of the next phase is requested by that phase, behind its polls (a wave's loads
             // complete in order, and a poll behind three chunks per wave returns 2 us later than behind two; with one
             // chunk or none in front of them the polls gain less than the memory system loses: 141.7 and 149.5 us per
@@ -781,6 +788,12 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                 stamp(step, 2, kTraceStaged);
                 call_attn<G, HD, true, true, true, kFlowAttnParts<G>>(p, step, vb, nvb, smem);
                 stamp(step, 2, kTraceDone);
+                // Nothing was requested ahead: the attention has the registers.  (Requested here, not where the phase begins:
+                // there the ring would count as in use all through the attention.)
+                flow_load_begin(L, tab, FL_O, wr0);
+                flow_issue(L, tab, nw, ring[0], lane);
+                flow_issue(L, tab, nw, ring[1], lane);
+                flow_issue_lds<CL>(L, tab, nw, slot, lane);
             }
         }
     }
