@@ -160,13 +160,14 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     const int k1 = __builtin_amdgcn_readfirstlane((kp + 1) * nk / KP); // k1 > k0: KP <= nk
     // Workgroups of a call with one block of rows start at different places of their rows (and come back to the beginning):
     // rows lie a power of two apart, and while all of them read the same 128 bytes of their rows only some of the memory
-    // channels have work (64 rows, 32768 weight rows of 8 KB: 71 us without, 63 with).  With several blocks of rows the
+    // channels have work (64 rows, 32768 weight rows of 8 KB: 71 us without, 63 with).  The workgroups of a die are spread evenly
+    // over the reduction (five steps on from one to the next left some of 32 close together: 2 % more).  With several blocks of rows the
     // workgroups of a die stay together instead, so that the activations they read come from their L2.
     // (HALF: a reduction of an odd number of 32s in steps of 64.  The half step keeps its place at the end, kw ends the whole
     // ones; what its second half brings lies behind the rows' ends and is not multiplied.  Kernels of its own, because the
     // few instructions cost every other width 1 to 2 % of a short step.)
     const int kw = T::HALF && k1 == nk ? k1 - 1 : k1;
-    const int rot = MB == 1 && (!T::HALF || kw > k0) ? __builtin_amdgcn_readfirstlane(nblk * 5 % (kw - k0)) : 0;
+    const int rot = MB == 1 ? ((unit >> 3) & 31) * (kw - k0) >> 5 : 0;
     p.b0 = pin.seq_lo + mblk * BM;
     p.nb = min(BM, pin.seq_hi - p.b0);
 
