@@ -541,16 +541,19 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
                 if (len_c == 0 || sp >= nsplit_c) continue; // not part of the block, or this split is past its end
                 row = (jg * JP + jp) * nseq + b;
             }
+            // (no branch per stream: all of a thread's reads are on their way together.  Three id lists at 24 sequences, 3 steps:
+            // 874 -> 866 us; 16 sequences 643 -> 640)
             float M = -INFINITY;
+#pragma unroll
             for (int st = 0; st < NSTREAM; ++st) M = fmaxf(M, s.ml[st][c][0]);
             float Ls = 0.f, A = 0.f;
+#pragma unroll
             for (int st = 0; st < NSTREAM; ++st) {
-                float mm = s.ml[st][c][0];
-                if (mm != -INFINITY) {
-                    float w = expf(mm - M);
-                    Ls += s.ml[st][c][1] * w;
-                    A += s.acc[st][c][dd] * w;
-                }
+                const float mm = s.ml[st][c][0], l = s.ml[st][c][1], a = s.acc[st][c][dd];
+                const bool seen = mm != -INFINITY; // (a stream without a token of the column adds nothing, whatever it holds)
+                const float w = seen ? exp_term(mm - M) : 0.f;
+                Ls += l * w;
+                A += (seen ? a : 0.f) * w;
             }
             int hq = kvh * G + g;
             if (nsplit_c == 1) {
