@@ -11,7 +11,7 @@
 //                 registers as bf16 hi + lo, pre-multiplied by log2(e)/sqrt(HD).
 //   online softmax in the MFMA result layout: a lane holds 2 x 4 tokens of ONE head column, so the running maximum,
 //                 the rescale factor and the running sum are per-lane scalars; the maximum of a step is combined
-//                 over the four lane groups of a column with two shuffles.
+//                 over the four lane groups of a column with two swaps of rows of lanes.
 //   O^T += V^T P  with the 16 dimensions of a block as rows and the heads as columns, contraction over the 32 tokens.
 //                 The eight probabilities a lane just computed are exactly the eight contraction elements the P
 //                 operand wants from it (tokens 4g..4g+3 of both tiles: the assignment of tokens to MFMA depth slots

@@ -906,9 +906,8 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
                 const int parts = p.Hq / p.Hkv >= 2 ? 2 : 1; // kFlowAttnParts
                 const long long want = ((long long)c.kv_capacity * p.Hkv * parts + fgrid - 1) / fgrid;
                 long long t = std::min<long long>(std::max<long long>(plan_tokens, (want + 31) / 32 * 32), kMaxSplitTokens);
-                // A capacity of at most two rounds is one split: nothing to merge saves 2 us per step (capacity 192 at head
-                // dimension 64: 136 -> 128 us per three steps, 640: 136 -> 134, 960: 136 -> 140; 256 at 128: 189 -> 183, 512:
-                // 190 -> 191).
+                // A capacity of at most two rounds is one split: nothing to merge (600 tokens at head dimension 64, three steps: 112.7 us,
+                // split 112.2: since every workgroup merges its share the two are the same, and one split writes no partials).
                 if (c.kv_capacity <= 2 * kFlowRoundBytes / p.hd) t = (c.kv_capacity + 31) / 32 * 32;
                 p.split_tokens = (int)t;
                 p.max_splits = (int)((c.kv_capacity + t - 1) / t);

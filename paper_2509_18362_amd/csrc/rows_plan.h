@@ -148,7 +148,8 @@ inline int attn_rows_waves(long long groups, int cus) { return groups <= cus ? 8
 // device).  What a launch per phase loses to its gaps a quarter of the units loses to reading more.  Three steps, us, single launch
 // / launch per phase: 2.6 MiB of weights 131 / 159, 3.8 146-158 / 152-161, 4.6 161 / 169, 5.3 157-166 / 156-164, 5.8 165-176 /
 // 160-168, 7.8 175-181 / 165-169; with 3.8 MiB of weights and 8 MiB of keys and values 166 / 174, 16 MiB 180 / 190 or (4.5 MiB,
-// 16 query heads) 194 / 188, 32 MiB 344 / 212.
+// 16 query heads) 194 / 188, 32 MiB 344 / 212.  (The lines were drawn with these; the single launch has since become 20 us shorter,
+// the first of them 108.)
 constexpr size_t kFlowNarrowBytes = 5 << 20, kFlowNarrowKvBytes = 8 << 20;
 inline bool flow_narrow_serves(size_t step_bytes, size_t kv_bytes) {
     return step_bytes <= kFlowNarrowBytes && kv_bytes <= kFlowNarrowKvBytes;
