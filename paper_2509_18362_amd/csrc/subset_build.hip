@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "../../include/mtp_draft.h"
+#include "subset_fields.h"
 #include "subset_plan.h"
 
 namespace {
@@ -66,8 +67,8 @@ constexpr unsigned kNoKey = 0xffffffffu;
 template <int BITS>
 __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restrict__ tokens, long long n_tokens, int V,
                                                             int chunk_ids, unsigned *counts, int copies, unsigned *partials) {
-    constexpr int FPW = 32 / BITS;                    // fields of a word
-    constexpr unsigned kFull = (1u << BITS) - 1u;     // a field that the next add wraps
+    constexpr int FPW = Fields<BITS>::kPerWord;
+    constexpr unsigned kFull = Fields<BITS>::kFull;
     constexpr int kTable = table_entries(BITS);
     extern __shared__ unsigned bins[]; // word w: local ids FPW w (lowest bits) .. FPW w + FPW - 1
     const int c0 = blockIdx.y * chunk_ids;
@@ -99,44 +100,12 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
         }
         give(id, 1u); // no room: straight to the global counts
     };
-    // place of an id's field in its word (the hardware takes the low five bits of a shift)
-    auto shift_of = [](unsigned rel) { return 32 % BITS == 0 ? rel * BITS & 31u : rel % FPW * BITS; };
-    // Counts N tokens of this thread: all adds first, then (rare) the fields that they wrap: the added one, if it was full, and
-    // those above it as far as they were full too.
+    // (an id that is not of this chunk adds to a word that its lane alone uses)
     auto count = [&](auto n, const int *t) {
-        constexpr int N = decltype(n)::value;
-        unsigned rel[N], old[N], full = 0u;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            rel[i] = (unsigned)(t[i] - c0);
-            unsigned *at = rel[i] < (unsigned)nb ? bins + rel[i] / FPW : spare + (threadIdx.x & 63);
-            old[i] = atomicAdd(at, 1u << shift_of(rel[i]));
-        }
-        unsigned most = 0u;
-#pragma unroll
-        for (int i = 0; i < N; ++i) most = max(most, __builtin_amdgcn_ubfe(old[i], shift_of(rel[i]), BITS));
-        if (most != kFull) return;
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-            full |= __builtin_amdgcn_ubfe(old[i], shift_of(rel[i]), BITS) == kFull ? 1u << i : 0u;
-        while (full) {
-            unsigned id = rel[0], word = old[0];
-#pragma unroll
-            for (int i = 1; i < N; ++i)
-                if (full & 1u << i) { // (the last one of them)
-                    id = rel[i];
-                    word = old[i];
-                }
-            full &= ~(1u << (31 - __clz((int)full)));
-            word >>= shift_of(id);
-            int f = (int)(id % FPW);
-            do {
-                if (id < (unsigned)nb) wrapped((int)id); // (not an id of this chunk, or carried into a field without one: nothing)
-                ++id;
-                ++f;
-                word >>= BITS;
-            } while (f < FPW && (word & kFull) == kFull);
-        }
+        Fields<BITS>::template count<decltype(n)::value>(
+            t, c0, (unsigned)nb,
+            [&](unsigned rel, bool inside, unsigned by) { return atomicAdd(inside ? bins + rel / FPW : spare + (threadIdx.x & 63), by); },
+            wrapped);
     };
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
     typedef int i32x4 __attribute__((ext_vector_type(4)));

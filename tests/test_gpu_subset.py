@@ -29,6 +29,22 @@ def both(gpu, tokens, V, n):
     return want
 
 
+def both_entry_points(gpu, tokens, V, n):
+    """And the entry point without a workspace, as far as its vocabularies go."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    want = both(gpu, tokens, V, n)
+    if V > binding.mtp_subset_static_max_vocab():
+        return
+    dev = torch.from_numpy(np.ascontiguousarray(tokens, dtype=np.int32)).to("cuda:0")
+    ids, counts, invalid = (torch.full((size,), -7, dtype=torch.int32, device="cuda:0") for size in (n, V, 4))
+    torch.cuda.synchronize()
+    assert binding.mtp_subset_build_static(dev, dev.numel(), V, n, ids, counts, invalid, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(counts.cpu().numpy().astype(np.int64), want["counts"])
+    assert int(invalid.cpu().numpy()[0]) == want["invalid"]
+    np.testing.assert_array_equal(ids.cpu().numpy(), want["ids"])
+
+
 @pytest.mark.parametrize("V,N,n", [(7, 40, 3), (16, 10, 12), (50, 2001, 50), (50, 2003, 0), (33, 500, 5), (5, 0, 2),
                                    (1, 9, 1), (300, 7, 299)])
 def test_small_streams_with_ties_and_invalid_ids(gpu, V, N, n):
@@ -103,3 +119,33 @@ def test_selection_in_one_to_three_digits(gpu, V, N, n):
     rng = np.random.default_rng(N % 1009)
     toks = np.concatenate([np.zeros(N // 2, dtype=np.int64), rng.integers(0, V, size=N - N // 2)])
     both(gpu, toks, V, n)
+
+
+@pytest.mark.parametrize("V", [100000, 155393, 200001, 250000, 400000])
+@pytest.mark.parametrize("kind", ["padded", "out of range", "before a chunk"])
+def test_tokens_that_are_not_ids_of_the_chunk(gpu, V, kind):
+    """Rows half of padding, other numbers out of range, and ids that are frequent and lie right before a chunk's first (of two or
+    three chunks), in vocabularies of every field width, one chunk and several: none of them may end up in another id's count."""
+    rng = np.random.default_rng(V)
+    n = 1 << 22
+    toks = rng.integers(0, V, size=n)
+    if kind == "padded":
+        toks.reshape(-1, 256)[:, 128:] = -1
+    elif kind == "out of range":
+        toks[rng.random(n) < 0.4] = -1
+        toks[rng.random(n) < 0.3] = -5
+        toks[rng.random(n) < 0.1] = V
+    else:
+        first = [c * (-(-V // parts // piece) * piece) for parts in (2, 3) for c in range(1, parts) for piece in (16, 20)]
+        hot = rng.random(n) < 0.6
+        toks[hot] = rng.choice(np.array(first) - 1, size=int(hot.sum()))
+    both_entry_points(gpu, toks, V, V // 7)
+
+
+@pytest.mark.parametrize("V,ids", [(60000, 3), (100000, 700), (151680, 3000), (200001, 700), (250000, 3000)])
+def test_fields_that_wrap_without_a_workspace(gpu, V, ids):
+    """One copy of the counts, fields added one by one: ids side by side and scattered, more of them than the table of wraps holds."""
+    rng = np.random.default_rng(V + ids)
+    n = (1 << 23) + 3
+    some = np.concatenate([V // 3 + np.arange(ids), rng.choice(V, ids)])
+    both_entry_points(gpu, rng.choice(some, n), V, min(V, 2 * ids + 5))

@@ -2,6 +2,7 @@
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -46,3 +47,33 @@ def test_the_digits_cover_every_count_the_cut_can_fall_on(plan):
         assert 1 <= passes <= 3 and all(1 <= b <= 12 for b, _ in used)
         assert used[-1][1] == 0 and all(hi[1] == lo[0] + lo[1] for hi, lo in zip(used, used[1:]))
         assert cap < 1 << (used[0][0] + used[0][1])
+
+
+@pytest.fixture(scope="module")
+def fields(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("fields") / "subset_fields")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wno-unknown-pragmas", "-Werror",
+                    os.path.join(ROOT, "tests", "plan", "subset_fields_driver.cpp"), "-o", exe], check=True)
+    return lambda bits, V, chunk, toks: subprocess.run([exe, str(bits), str(V), str(chunk)], input=toks.astype(np.int32).tobytes(),
+                                                       capture_output=True, check=True).stdout.decode()
+
+
+@pytest.mark.parametrize("bits", [6, 8, 16])
+@pytest.mark.parametrize("V,chunk", [(1000, 1000), (1003, 1003), (1003, 340)])
+@pytest.mark.parametrize("kind", ["padded", "out of range", "neighbour", "hot", "all"])
+def test_fields_that_wrap_are_counted_exactly(fields, bits, V, chunk, kind):
+    """Every width, one chunk and several, a last word with fields that have no id; tokens that are not ids of the chunk (padding
+    of -1, numbers on both sides of the vocabulary, the id below a chunk's first) wrap nothing that is counted."""
+    rng = np.random.default_rng(bits + V + chunk)
+    n = 1 << (21 if bits == 16 else 18)
+    t = rng.integers(0, V, n)
+    if kind == "padded":
+        t.reshape(-1, 256)[:, 128:] = -1
+    elif kind == "out of range":  # a field of the word that nobody reads and the one above it
+        t[rng.random(n) < 0.5] = -1
+        t[rng.random(n) < 0.4] = rng.choice([-5, -4, -3, -2, V, V + 1, V + 2, -(1 << 31), (1 << 31) - 1])
+    elif kind == "neighbour":
+        t[rng.random(n) < 0.9] = min(chunk, V) - 1
+    elif kind == "hot":           # whole words full at a time: carries run through several fields
+        t[:] = rng.choice([0, 1, 2, 3, 4, 5, 6, 7, V - 3, V - 2, V - 1], n)
+    assert fields(bits, V, chunk, t) == ""
