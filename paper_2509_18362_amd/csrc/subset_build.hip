@@ -5,7 +5,7 @@
 // Counting is the only part that touches much memory.  Global atomics on a long-tailed stream would pile up on the
 // few hottest ids (same-address device atomics serialize at ~40 ns each), so every workgroup counts in LDS, in fields so
 // narrow that the 160 KB of a CU hold the whole vocabulary and the stream is read once: 16 bits up to 80 768 ids, 8 up to
-// 155 392, 6 (five to a word) up to 201 920; beyond that the vocabulary is counted in chunks.  Narrow fields wrap, and a
+// 155 392; beyond that the vocabulary is counted in chunks.  Narrow fields wrap, and a
 // wrap carries into the next field of its word.  Both are accounted for exactly: the atomic that adds returns the word as it
 // was, which tells which fields this add wraps, and the number W[j] of wraps of field j is kept in a small table in LDS
 // (hashed by id: only ids that occur more often than a field can hold get there).  A field has had as many increments as it
@@ -469,11 +469,9 @@ bool g_lds_allowed[kMaxDevices];      // per device: the counting kernel may use
 std::mutex g_setup_mutex;
 
 typedef void (*hist_kernel_t)(const int *, long long, int, int, unsigned *, int, unsigned *);
-hist_kernel_t hist_kernel(int bits) { return bits == 16 ? k_subset_hist<16> : bits == 8 ? k_subset_hist<8> : k_subset_hist<6>; }
+hist_kernel_t hist_kernel(int bits) { return bits == 16 ? k_subset_hist<16> : k_subset_hist<8>; }
 typedef void (*reduce_kernel_t)(const unsigned *, int, int, int, SelPlan, unsigned *, unsigned *, int *);
-reduce_kernel_t reduce_kernel(int bits) {
-    return bits == 16 ? k_subset_reduce<16> : bits == 8 ? k_subset_reduce<8> : k_subset_reduce<6>;
-}
+reduce_kernel_t reduce_kernel(int bits) { return bits == 16 ? k_subset_reduce<16> : k_subset_reduce<8>; }
 
 // once per device, with that device current: raise the LDS limit of the counting kernel and (for the static entry
 // point) look up the device's copy of the scratch array
@@ -481,7 +479,7 @@ int32_t subset_setup(int dev, bool want_scratch, unsigned **scratch_out) {
     if (dev < 0 || dev >= kMaxDevices) return MTP_ERR_CONFIG;
     std::lock_guard<std::mutex> lock(g_setup_mutex);
     if (!g_lds_allowed[dev]) {
-        for (int bits : {16, 8, 6})
+        for (int bits : {16, 8})
             if (hipFuncSetAttribute((const void *)hist_kernel(bits), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)hist_lds_bytes(chunk_capacity(bits), bits)) != hipSuccess) {
                 (void)hipGetLastError();

@@ -12,8 +12,8 @@ namespace subset {
 constexpr int kLdsWords = 160 * 1024 / 4; // of a CU, all of them the counting workgroup's
 constexpr int kSpareWords = 64;
 
-// entries of the table of wraps: ids that occur more often in a slice than a field can hold (64 times in 2^18 tokens is
-// one in 4096: a few hundred ids of a long tail)
+// entries of the table of wraps: ids that occur more often in a slice than a field can hold (256 times in 2^18 tokens is
+// one in 1024: a few hundred ids of a long tail)
 constexpr int table_bits(int bits) { return bits == 8 ? 10 : 8; }
 constexpr int table_entries(int bits) { return 1 << table_bits(bits); }
 // words of the bins of `ids` ids, whole 16-byte pieces
@@ -23,18 +23,20 @@ constexpr int chunk_capacity(int bits) { return (kLdsWords - 2 * table_entries(b
 constexpr size_t hist_lds_bytes(int ids, int bits) {
     return ((size_t)bin_words(ids, bits) + 2 * table_entries(bits) + kSpareWords) * 4;
 }
-static_assert(chunk_capacity(16) == 80768 && chunk_capacity(8) == 155392 && chunk_capacity(6) == 201920, "said elsewhere");
+static_assert(chunk_capacity(16) == 80768 && chunk_capacity(8) == 155392, "said elsewhere");
 
 struct CountPlan {
     int bits, chunks, chunk_ids, slices; // width of a field, passes over the stream, ids of each, workgroups of each
 };
 
-// The widest fields with which the stream is read the fewest times (wide fields wrap less often, narrow ones hold more
-// ids).  256 workgroups in all, one per CU of the device this is written for (232 with 6-bit fields, whose copies of the bins
-// are the largest), a multiple of eight per chunk: the chunks' workgroups of a slice then share a compute die.
+// The wider fields unless the narrower ones read the stream fewer times (wide fields wrap less often, narrow ones hold more
+// ids).  256 workgroups in all, one per CU of the device this is written for, a multiple of eight per chunk: the chunks' workgroups of
+// a slice then share a compute die.  (Fields of 6 bits would hold 201 920 ids in one chunk, but leave no room for the wraps of a stream of
+// a few hundred ids: 2^26 tokens of 200 001 ids, 600 of which occur, side by side / a long tail: 418 / 103 us, in two chunks of
+// 8 bits 135 / 113, in three of 16 bits 151 / 165.)
 inline CountPlan count_plan(int V) {
     CountPlan p{};
-    for (int bits : {16, 8, 6}) {
+    for (int bits : {16, 8}) {
         const int chunks = (V - 1) / chunk_capacity(bits) + 1;
         if (p.bits && chunks >= p.chunks) continue;
         p.bits = bits;
@@ -43,7 +45,7 @@ inline CountPlan count_plan(int V) {
     const int per_word = 32 / p.bits, piece = 4 * per_word; // chunks begin at whole 16-byte pieces of words
     p.chunk_ids = ((V - 1) / p.chunks / piece + 1) * piece;
     p.chunks = (V - 1) / p.chunk_ids + 1; // (rounding up may have emptied the last of very many)
-    const int s = (p.bits == 6 ? 232 : 256) / p.chunks;
+    const int s = 256 / p.chunks;
     p.slices = s >= 8 ? s / 8 * 8 : std::max(1, s);
     return p;
 }

@@ -85,7 +85,7 @@ def test_full_vocabulary_and_use_as_output_head_list(gpu):
 
 @pytest.mark.parametrize("V", [80768, 80769, 155392, 155393, 201920, 201921])
 def test_every_field_width_and_chunk(gpu, V):
-    """The largest vocabulary of each field width and of a chunk, and one id more: hot ids at both ends and in the middle of the
+    """The largest vocabulary of each field width and of a chunk, and larger ones: hot ids at both ends and in the middle of the
     words, a long tail, ids out of range."""
     rng = np.random.default_rng(V)
     hot = rng.choice([0, 1, 2, 3, 4, V // 2, V - 2, V - 1], size=1 << 18)
@@ -99,8 +99,9 @@ def test_every_field_width_and_chunk(gpu, V):
     (4096, 8, 2, 24),          # 16-bit fields that wrap together, the second one carried into by the first
     (100000, 40, 8, 20),       # 8 bits: whole words full at a time, so that a carry runs through several fields
     (100000, 99996, 4, 20),    # the last word
-    (160000, 155, 400, 23),    # 6 bits, more ids that wrap than the table has room for
-    (100000, 1000, 4000, 24),  # 8 bits: a few wraps each
+    (160000, 155, 100, 23),    # two chunks
+    (100000, 1000, 4000, 24),  # many ids, none of which wraps
+    (400000, 1000, 1500, 25),  # three chunks; more ids that wrap than the table of wraps has room for
     (160001, 159996, 5, 20),   # the last word of the last id has one field in use
 ])
 def test_fields_that_wrap(gpu, V, base, ids, logN):
@@ -142,10 +143,11 @@ def test_tokens_that_are_not_ids_of_the_chunk(gpu, V, kind):
     both_entry_points(gpu, toks, V, V // 7)
 
 
-@pytest.mark.parametrize("V,ids", [(60000, 3), (100000, 700), (151680, 3000), (200001, 700), (250000, 3000)])
-def test_fields_that_wrap_without_a_workspace(gpu, V, ids):
-    """One copy of the counts, fields added one by one: ids side by side and scattered, more of them than the table of wraps holds."""
+@pytest.mark.parametrize("V,ids,logN", [(60000, 3, 23), (100000, 40, 23), (151680, 60, 23), (200001, 60, 23), (250000, 700, 26)])
+def test_fields_that_wrap_without_a_workspace(gpu, V, ids, logN):
+    """One copy of the counts, fields added one by one: as many ids side by side as scattered, one chunk and two, in the last case
+    more of them than the table of wraps holds."""
     rng = np.random.default_rng(V + ids)
-    n = (1 << 23) + 3
+    n = (1 << logN) + 3
     some = np.concatenate([V // 3 + np.arange(ids), rng.choice(V, ids)])
     both_entry_points(gpu, rng.choice(some, n), V, min(V, 2 * ids + 5))

@@ -32,7 +32,7 @@ def test_chunks_cover_the_vocabulary_and_fit_a_compute_unit(plan):
         assert chunks * ids >= V and (chunks - 1) * ids < V, (V, r)       # the last chunk is not empty
         assert ids % (4 * (32 // bits)) == 0 and lds <= 160 * 1024, (V, r)
         assert 1 <= slices and slices * chunks <= max(256, chunks) and 1 <= stream <= slices, (V, r)
-    assert [r[0] for r in plan([(80768, 1, 1), (80769, 1, 1), (155392, 1, 1), (155393, 1, 1), (201920, 1, 1)])] == [16, 8, 8, 6, 6]
+    assert [r[0] for r in plan([(80768, 1, 1), (80769, 1, 1), (155392, 1, 1), (155393, 1, 1), (201920, 1, 1)])] == [16, 8, 8, 16, 8]
 
 
 def test_the_digits_cover_every_count_the_cut_can_fall_on(plan):
@@ -62,7 +62,7 @@ def fields(tmp_path_factory):
 @pytest.mark.parametrize("V,chunk", [(1000, 1000), (1003, 1003), (1003, 340)])
 @pytest.mark.parametrize("kind", ["padded", "out of range", "neighbour", "hot", "all"])
 def test_fields_that_wrap_are_counted_exactly(fields, bits, V, chunk, kind):
-    """Every width, one chunk and several, a last word with fields that have no id; tokens that are not ids of the chunk (padding
+    """Several widths (also one that leaves bits of a word over), one chunk and several, a last word with fields that have no id; tokens that are not ids of the chunk (padding
     of -1, numbers on both sides of the vocabulary, the id below a chunk's first) wrap nothing that is counted."""
     rng = np.random.default_rng(bits + V + chunk)
     n = 1 << (21 if bits == 16 else 18)
