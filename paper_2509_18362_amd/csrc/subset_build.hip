@@ -88,17 +88,30 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
         atomicAdd(&counts[c0 + id], by << BITS);
         if (id % FPW + 1 < FPW && id + 1 < nb) atomicAdd(&counts[c0 + id + 1], 0u - by);
     };
+    // the first place of an id in the table; the others are a block of sixteen apart
+    auto slot_of = [](int id) {
+        return ((unsigned)(id >> 4) * 2654435761u >> (36 - table_bits(BITS))) * 16 + (unsigned)(id & 15);
+    };
     auto wrapped = [&](int id) {
-        unsigned slot = (unsigned)id * 2654435761u >> (32 - table_bits(BITS));
+        unsigned slot = slot_of(id);
         for (int tries = 0; tries < 4; ++tries) {
             const unsigned key = atomicCAS(&keys[slot], kNoKey, (unsigned)id);
             if (key == kNoKey || key == (unsigned)id) {
                 atomicAdd(&wraps[slot], 1u);
                 return;
             }
-            slot = (slot + 1) % kTable;
+            slot = (slot + 16) % kTable;
         }
         give(id, 1u); // no room: straight to the global counts
+    };
+    // an id's wraps in the table (an id in it always has some), once no more are added
+    auto booked = [&](int id) {
+        unsigned slot = slot_of(id);
+        for (int tries = 0; tries < 4; ++tries) {
+            if (keys[slot] == (unsigned)id) return wraps[slot];
+            slot = (slot + 16) % kTable;
+        }
+        return 0u;
     };
     // (an id that is not of this chunk adds to a word that its lane alone uses)
     auto count = [&](auto n, const int *t) {
@@ -154,8 +167,13 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
         count_all(va);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kTable; i += kHistBlock)
-        if (keys[i] != kNoKey) give((int)keys[i], wraps[i]);
+    for (int i = threadIdx.x; i < kTable; i += kHistBlock) {
+        if (keys[i] == kNoKey) continue;
+        const int id = (int)keys[i];
+        const unsigned w = wraps[i], below = id % FPW ? booked(id - 1) : 0u;
+        atomicAdd(&counts[c0 + id], (w << BITS) - below);
+        if (id % FPW + 1 < FPW && id + 1 < nb && booked(id + 1) == 0u) atomicAdd(&counts[c0 + id + 1], 0u - w);
+    }
     // What is in the bins: with room for it, the workgroup's bins go to memory as they are (k_subset_reduce adds
     // the workgroups' copies up); without, every non-zero field is added to the global counts (up to a vocabulary of
     // atomics per workgroup, 39 M over the grid when every id occurs: slower than the counting itself).
