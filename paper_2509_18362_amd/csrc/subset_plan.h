@@ -52,12 +52,15 @@ inline CountPlan count_plan(int V) {
 inline size_t partial_words(const CountPlan &p) { return (size_t)p.slices * p.chunks * bin_words(p.chunk_ids, p.bits); }
 // Slices of a stream of n_tokens: a workgroup clears and stores its bins however few tokens it counts, and the kernel after
 // it reads them all (151 680 ids, 2^22 tokens: 50 us in 256 slices, 41 in 128; 2^18: 52 and 30 in 8).
-// Without the copies of the bins (stored: false) only ids that occur cost anything afterwards.
-constexpr int kSliceTokens = 32768, kSliceTokensAdded = 4096;
+// Without the copies of the bins (stored: false) only ids that occur cost anything afterwards: an add of every slice that has one,
+// and those of one id go one by one.  Half as many slices are ahead until the reading counts for more (151 680 ids, 256 slices
+// / 128: 2^23 tokens of a long tail 108 us / 93, of 2500 ids 70 / 55).
+constexpr int kSliceTokens = 32768, kSliceTokensAdded = 4096, kSliceTokensAll = 65536;
 inline int stream_slices(const CountPlan &p, int64_t n_tokens, bool stored) {
     const int per = stored ? kSliceTokens : kSliceTokensAdded;
+    const int most = stored || n_tokens >= (int64_t)kSliceTokensAll * p.slices ? p.slices : (p.slices + 1) / 2;
     const int64_t want = (n_tokens + per - 1) / per;
-    return (int)std::min<int64_t>(p.slices, std::max<int64_t>(8, (want + 7) / 8 * 8));
+    return (int)std::min<int64_t>(most, std::max<int64_t>(8, (want + 7) / 8 * 8));
 }
 
 // The selection's digits, most significant first.  The n-th largest count T is at most n_tokens / n, so the keys are the
