@@ -40,8 +40,8 @@ using namespace mtp::subset;
 
 constexpr int kHistBlock = 1024;
 // Copies of the global counts that the counting kernel's workgroups give the wraps to (where the copies of the bins are there
-// too): in streams of a few hundred ids every workgroup has all of them, and atomics to one cache line go one by one (600 ids
-// of 151 680, 2^26 tokens: 185 us with one copy, 128 with four; a long-tailed stream 85 and 82).
+// too): in streams of a few hundred ids every workgroup has all of them, and atomics to one cache line go one by one (600
+// scattered ids of 151 680, 2^26 tokens: 93 us with one copy, 86 with four; a long-tailed stream 86 and 85).
 constexpr int kCountCopies = 4;
 __host__ __device__ constexpr size_t round4(size_t words) { return (words + 3) / 4 * 4; }
 constexpr int kSelBlock = 1024;
@@ -55,7 +55,10 @@ __global__ void k_subset_clear(unsigned *work, size_t words, unsigned *state, in
     *reinterpret_cast<uint4 *>(work + i) = zero;
 }
 
-// The table of wraps: keys (local id, or kNoKey), then as many counts.
+// The table of wraps: keys (local id, or kNoKey), then as many counts.  Ids that differ in their last four bits only are neighbours in
+// it, so that the wave that hands them to the global counts has few cache lines to go to, each once (an atomic per id, what the
+// field below carried in taken off: 600 ids side by side of 151 680, 2^26 tokens: places scattered by id and two atomics per id 128 us,
+// without a workspace 190; so 80 and 78).
 constexpr unsigned kNoKey = 0xffffffffu;
 
 // grid (slices, chunks): workgroup (s, c) counts the ids of chunk c in every (slices)-th piece of the stream, from the s-th on.
@@ -88,7 +91,7 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
         atomicAdd(&counts[c0 + id], by << BITS);
         if (id % FPW + 1 < FPW && id + 1 < nb) atomicAdd(&counts[c0 + id + 1], 0u - by);
     };
-    // the first place of an id in the table; the others are a block of sixteen apart
+    // the first place of an id; the others it can have are sixteen apart
     auto slot_of = [](int id) {
         return ((unsigned)(id >> 4) * 2654435761u >> (36 - table_bits(BITS))) * 16 + (unsigned)(id & 15);
     };

@@ -49,6 +49,13 @@ def test_the_digits_cover_every_count_the_cut_can_fall_on(plan):
         assert cap < 1 << (used[0][0] + used[0][1])
 
 
+def test_slices_without_a_workspace(plan):
+    """Half of the workgroups until each of all of them has 65536 tokens; never more than count the stream with a workspace, never none."""
+    calls = [(151680, t, 1) for t in (0, 1, 1 << 15, 1 << 18, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)] + [(250000, (1 << 23) - 1, 1)]
+    assert [r[14] for r in plan(calls)] == [8, 8, 8, 64, 128, 128, 256, 256, 64]
+    assert all(1 <= r[14] <= r[3] for r in plan([(V, 1 << 20, 1) for V in VOCABS]))
+
+
 @pytest.fixture(scope="module")
 def fields(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("fields") / "subset_fields")
