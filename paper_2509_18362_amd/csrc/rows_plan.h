@@ -127,7 +127,9 @@ inline RowsRoute rows_route(const RowsCall &c, bool all_few, int cus) {
 }
 
 // Attention of a block of new positions (two or more per sequence): attn_rows.h, small workgroups that each serve 16 / G positions
-// of a KV head over all their tokens, or the kernels that split a context over workgroups.  groups: (sequence, KV head, 16 / G
+// of a KV head over all their tokens, or the kernels that split a context over workgroups.  matrix_cores: the splits are long enough
+// for the matrix cores there.  Shorter ones stay with the vector attention, whose query and probabilities are 32-bit (here as there they
+// are pairs of bf16) and which a value that is not finite at a later position does not reach.  groups: (sequence, KV head, 16 / G
 // positions); the host knows the capacity, not the contexts.  What counts is a wave's rounds of 128 tokens where there are too
 // few groups to fill the chip.  Whole calls, us, splits / attn_rows.h: 509 positions, empty cache (1024 groups of 16 heads, head
 // dimension 128) 773 / 734, of a 2048-wide head 262 / 234, 500 behind 4000 tokens 752 / 610, 16 sequences x 4 behind 100 217 / 201,
@@ -135,9 +137,9 @@ inline RowsRoute rows_route(const RowsCall &c, bool all_few, int cus) {
 // 2 x 8 behind 6000 (32 groups, 47 rounds) 187 / 199.  Head dimension 64 (a round takes longer, V is gathered from LDS): 8 x 8 behind
 // 1500 (16 groups, 12 rounds) 90.6 / 82.8, 1 x 6 behind 2000 (2, 16) 66 / 73, 1 x 64 behind 4000 (16, 32) 90 / 96, 16 x 16 behind 2000
 // (64, 16) 141 / 134, 1 x 200 behind 8000 (50, 65) 155 / 172, 1 x 500 behind 4000 (126, 36) 219 / 211.
-inline bool attn_rows_serves(int positions, long long groups, int capacity, int head_dim) {
+inline bool attn_rows_serves(int positions, bool matrix_cores, long long groups, int capacity, int head_dim) {
     const int rounds = (capacity + 127) / 128;
-    return positions >= 2 && 4 * rounds <= groups + (head_dim == 128 ? 132 : 52);
+    return positions >= 2 && matrix_cores && 4 * rounds <= groups + (head_dim == 128 ? 132 : 52);
 }
 
 // waves of its workgroups: eight where there are no more groups than compute units

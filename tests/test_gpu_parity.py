@@ -248,12 +248,48 @@ def test_small_heads_block_of_positions_shared_reads(gpu, hq, hkv, hd):
 @pytest.mark.parametrize("d,ctx,ext,m", [
     (256, [0, 13, 96, 500], [19, 19, 7, 0], 19),   # row-major activations; rounds of 32 tokens per wave: several, one
     (256, [31, 109, 255, 125], [1, 19, 1, 4], 19), # or none; lengths on their edges, groups without a position
-    (512, [127, 30], [3, 2], 3),                   # six rows in operand order
+    (512, [127, 30], [3, 2], 3),                   # six rows in operand order (the vector attention)
 ])
 def test_small_heads_block_of_positions_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m):
-    """Blocks in caches of a few hundred slots: the attention whose small workgroups serve 16 / G positions each over all
+    """Blocks in caches of 2048 slots: the attention whose small workgroups serve 16 / G positions each over all
     their tokens, on every (group size, head dimension); here with eight waves."""
     block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m)
+
+
+@pytest.mark.parametrize("hq,hkv,hd,ctx,ext,m", [
+    (8, 8, 64, [127, 30], [4, 3], 4), (16, 8, 128, [127, 0], [4, 1], 4), (32, 8, 64, [700], [8], 8),     # up to eight rows, packed
+    (4, 4, 64, [127, 30, 0, 900], [4, 4, 2, 0], 4), (16, 4, 128, [500, 64], [8, 5], 8),                  # up to sixteen
+])
+def test_blocks_of_few_rows_in_small_workgroups(gpu, hq, hkv, hd, ctx, ext, m):
+    """The same attention, its results in the operand order of the kernel of up to sixteen rows."""
+    block_in_small_workgroups(gpu, hq, hkv, hd, 512, ctx, ext, m)
+
+
+@pytest.mark.parametrize("hq,hkv,hd,ctx,m,cap", [
+    (8, 2, 64, [100], 4, 2112), (8, 1, 128, [2000], 6, 2112), (32, 8, 128, [511], 4, 2112), (4, 4, 64, [60, 0, 130], 2, 192)])
+def test_a_later_position_that_is_not_finite_leaves_the_earlier_ones_alone(gpu, hq, hkv, hd, ctx, m, cap):
+    """Blocks with short splits: the earlier positions' outputs are the same bits whatever stands at the last one."""
+    binding = gpu["binding"]
+    shape = synth.HeadShape(512, hq, hkv, hd, 512, 2048)
+    wl = synth.Workload(f"finite_{hq}_{hkv}_{hd}", 90 + hq + hd, shape, len(ctx), 0, 0, (512,), 1, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=cap)
+    hid, tok = extend_inputs(shape, act, m, 91)
+    eng = binding.DraftEngine(shape, w, [ids], len(ctx) * m, cap, 1)
+    got = []
+    for last in (None, 0x7fc0, 0x7f80):  # as drawn, NaN, infinity
+        if last is not None:
+            hid[m - 1] = last
+        out = eng.extend(0, eng.to_device_bits(hid), eng.to_device_i32(tok), eng.to_device_i32(np.full(len(ctx), m, np.int32)),
+                         eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"]), eng.to_device_i32(act["kv_len"]),
+                         want_logits=True, want_hidden=True)
+        got.append({k: out[k].cpu().numpy()[: m - 1] for k in ("logits", "hidden", "draft")})
+    eng.close()
+    assert np.isfinite(got[0]["logits"]).all()
+    for other in got[1:]:
+        for k in got[0]:
+            np.testing.assert_array_equal(got[0][k], other[k])
 
 
 @pytest.mark.parametrize("hkv,hd", [(2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (4, 128), (8, 128), (16, 128)])
@@ -270,7 +306,8 @@ def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m):
     w = synth.make_weights(wl)
     ids = synth.make_subsets(wl)[0]
     ext_len = np.array(ext, dtype=np.int32)
-    act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=576)
+    # (splits of capacity * rows * hkv / 256 tokens: the matrix cores from 449 on, up to the next 64)
+    act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=2048)
     hid, tok = extend_inputs(shape, act, m, 79 + hq + hkv + hd)
     ref, res, caches = run_extend(gpu, shape, w, w, act, [ids], 0, hid, tok, ext_len)
     assert res["err"] == 0

@@ -154,6 +154,8 @@ def test_narrow_heads_take_the_single_launch_where_it_is_ahead(driver, d, hq, hk
     (8, 32, 6080, 128, 0), (8, 16, 1536, 64, 1), (6, 2, 2048, 64, 0), (64, 16, 4096, 64, 0), (16, 64, 2048, 64, 1),
     (200, 50, 8256, 64, 0), (500, 126, 4544, 64, 1)])
 def test_attention_of_a_block_by_rounds_and_groups(driver, positions, groups, cap, hd, small):
-    """Small workgroups where the chip is full of them or a wave's rounds are few; one position never."""
-    out = subprocess.run([driver, "block"], input=f"{positions} {groups} {cap} {hd}", capture_output=True, text=True, check=True)
-    assert int(out.stdout) == small
+    """Small workgroups where the chip is full of them or a wave's rounds are few; one position never, and no block whose splits
+    the vector attention serves."""
+    out = subprocess.run([driver, "block"], input="".join(f"{positions} {mc} {groups} {cap} {hd}\n" for mc in (1, 0)),
+                         capture_output=True, text=True, check=True)
+    assert out.stdout.split() == [str(small), "0"]
