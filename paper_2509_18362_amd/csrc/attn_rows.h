@@ -247,10 +247,11 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
     for (int i = 0; i < E; ++i) r[i] = 0.f;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        const float f = __builtin_amdgcn_exp2f(lds.m.ml[w][c][0] - M); // (a wave without a token of the column: zero)
+        const bool seen = lds.m.ml[w][c][0] != -INFINITY; // (a wave without a token of the column adds nothing, whatever it holds)
+        const float f = seen ? __builtin_amdgcn_exp2f(lds.m.ml[w][c][0] - M) : 0.f;
         ls += f * lds.m.ml[w][c][1];
 #pragma unroll
-        for (int i = 0; i < E; ++i) r[i] += f * lds.m.acc[w][c][e0 + i];
+        for (int i = 0; i < E; ++i) r[i] += f * (seen ? lds.m.acc[w][c][e0 + i] : 0.f);
     }
     const float inv = 1.0f / ls;
     uint32_t h[E / 2], l[E / 2];

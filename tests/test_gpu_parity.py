@@ -269,6 +269,17 @@ def test_blocks_of_few_rows_in_small_workgroups(gpu, hq, hkv, hd, ctx, ext, m):
     (8, 2, 64, [100], 4, 2112), (8, 1, 128, [2000], 6, 2112), (32, 8, 128, [511], 4, 2112), (4, 4, 64, [60, 0, 130], 2, 192)])
 def test_a_later_position_that_is_not_finite_leaves_the_earlier_ones_alone(gpu, hq, hkv, hd, ctx, m, cap):
     """Blocks with short splits: the earlier positions' outputs are the same bits whatever stands at the last one."""
+    last_position_not_finite(gpu, hq, hkv, hd, ctx, m, cap, m - 1)
+
+
+@pytest.mark.parametrize("hq,hkv,hd", [(8, 8, 64), (8, 8, 128)])
+def test_a_position_that_is_not_finite_stays_in_its_round(gpu, hq, hkv, hd):
+    """On the matrix cores sixteen positions share the rounds of 32 tokens they read: what is not finite reaches those with tokens
+    in the same round (0 x infinity), and no other.  The sixteenth position is the fourth token of the second round."""
+    last_position_not_finite(gpu, hq, hkv, hd, [20], 16, 2048, 12)
+
+
+def last_position_not_finite(gpu, hq, hkv, hd, ctx, m, cap, same):
     binding = gpu["binding"]
     shape = synth.HeadShape(512, hq, hkv, hd, 512, 2048)
     wl = synth.Workload(f"finite_{hq}_{hkv}_{hd}", 90 + hq + hd, shape, len(ctx), 0, 0, (512,), 1, 0.5, zipf_subset=False)
@@ -284,7 +295,7 @@ def test_a_later_position_that_is_not_finite_leaves_the_earlier_ones_alone(gpu, 
         out = eng.extend(0, eng.to_device_bits(hid), eng.to_device_i32(tok), eng.to_device_i32(np.full(len(ctx), m, np.int32)),
                          eng.to_device_bits(act["k_cache"]), eng.to_device_bits(act["v_cache"]), eng.to_device_i32(act["kv_len"]),
                          want_logits=True, want_hidden=True)
-        got.append({k: out[k].cpu().numpy()[: m - 1] for k in ("logits", "hidden", "draft")})
+        got.append({k: out[k].cpu().numpy()[:same] for k in ("logits", "hidden", "draft")})
     eng.close()
     assert np.isfinite(got[0]["logits"]).all()
     for other in got[1:]:
