@@ -983,7 +983,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
         else
             hipLaunchKernelGGL(k_extend_append<64>, dim3(B, p.Hkv), dim3(96), 0, st, pa);
         const int jp = 16 / (pa.Hq / pa.Hkv), jg = (ext->m_max + jp - 1) / jp; // positions that share reads, groups of them
-        if (p.attn_split && attn_rows_serves(ext->m_max, mfma_attn, (long long)ext->B * pa.Hkv * jg, c.kv_capacity, pa.hd)) {
+        if (p.attn_split && attn_rows_serves(ext->m_max, mfma_attn, ext->B, (long long)ext->B * pa.Hkv * jg, att_fit, c.kv_capacity)) {
             launch_attn_rows(pa, h->num_cus, st);
         } else if (mfma_attn && ext->m_max > 1) {
             // long splits: the positions of a sequence share its key/value reads (16 / G of them per item)

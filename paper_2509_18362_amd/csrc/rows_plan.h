@@ -129,17 +129,21 @@ inline RowsRoute rows_route(const RowsCall &c, bool all_few, int cus) {
 // Attention of a block of new positions (two or more per sequence): attn_rows.h, small workgroups that each serve 16 / G positions
 // of a KV head over all their tokens, or the kernels that split a context over workgroups.  matrix_cores: the splits are long enough
 // for the matrix cores there.  Shorter ones stay with the vector attention, whose query and probabilities are 32-bit (here as there they
-// are pairs of bf16) and which a value that is not finite at a later position does not reach.  groups: (sequence, KV head, 16 / G
-// positions); the host knows the capacity, not the contexts.  What counts is a wave's rounds of 128 tokens where there are too
-// few groups to fill the chip.  Whole calls, us, splits / attn_rows.h: 509 positions, empty cache (1024 groups of 16 heads, head
-// dimension 128) 773 / 734, of a 2048-wide head 262 / 234, 500 behind 4000 tokens 752 / 610, 16 sequences x 4 behind 100 217 / 201,
-// x 3 behind 2000 235 / 215, 1 x 6 behind 2000 (16 groups, 16 rounds) 166 / 148; 1 x 64 behind 4000 (128 groups, 32 rounds) 235 / 229,
-// 2 x 8 behind 6000 (32 groups, 47 rounds) 187 / 199.  Head dimension 64 (a round takes longer, V is gathered from LDS): 8 x 8 behind
-// 1500 (16 groups, 12 rounds) 90.6 / 82.8, 1 x 6 behind 2000 (2, 16) 66 / 73, 1 x 64 behind 4000 (16, 32) 90 / 96, 16 x 16 behind 2000
-// (64, 16) 141 / 134, 1 x 200 behind 8000 (50, 65) 155 / 172, 1 x 500 behind 4000 (126, 36) 219 / 211.
-inline bool attn_rows_serves(int positions, bool matrix_cores, long long groups, int capacity, int head_dim) {
+// are pairs of bf16) and which a value that is not finite at a later position does not reach.
+//
+// The host knows the capacity, not the contexts, so the rule has to hold where one sequence fills its cache and the others are short: the
+// chain of that one's rounds of 128 tokens then decides, as it does where there are few groups (sequence, KV head, 16 / G positions).
+// sized: the splits are sized by the lengths found on the device (few groups), which shortens just that.  Splits / attn_rows.h, whole
+// calls of heads 512 wide, least and mean of a set of 1863 (all contexts at the capacity; one of them, the others at 60):
+//   5 and 9 rounds                               1.04, 1.12;  1.04, 1.13
+//   sized:      17, 25, 33, 65 rounds            1.02, 1.11;  0.97, 1.06     0.99, 1.08;  0.93, 1.01     0.95, 1.04;  0.88, 0.95     0.82, 0.94;  0.75, 0.81
+//   not sized:  25, 33, 49, 129 rounds           1.02, 1.07;  1.00, 1.10     1.11, 1.18;  1.07, 1.18     1.02, 1.14;  0.93, 1.08     0.88, 1.17;  0.67, 0.87
+//               (fewer than 64 groups: 25, 33    0.98, 1.00;  0.98, 1.00     0.92;  0.93)
+//   one sequence, more than 16 rounds: two groups per round or more 1.03, 1.25; fewer 0.43, 0.87
+inline bool attn_rows_serves(int positions, bool matrix_cores, int sequences, long long groups, bool sized, int capacity) {
     const int rounds = (capacity + 127) / 128;
-    return positions >= 2 && matrix_cores && 4 * rounds <= groups + (head_dim == 128 ? 132 : 52);
+    if (positions < 2 || !matrix_cores) return false;
+    return rounds <= 16 || (!sized && groups >= 64 && rounds <= 40) || (sequences == 1 && 2ll * rounds <= groups);
 }
 
 // waves of its workgroups: eight where there are no more groups than compute units

@@ -2,7 +2,7 @@
 // (a matrix phase over `rows` of the call's rows), writes "route tile_rows tile_weight_rows parts microseconds" for each, route 0
 // few_rows.h, 1 the tiles, 2 the batched core; -1 where the whole call takes few_rows.h.  With "narrow": reads "step_bytes
 // kv_bytes", writes 1 where one sequence of a narrow head takes the single launch.  With "block": reads "positions matrix_cores
-// groups capacity head_dim", writes 1 where a block's attention takes attn_rows.h.
+// sequences groups sized capacity", writes 1 where a block's attention takes attn_rows.h.
 #include <cstdio>
 #include <cstring>
 
@@ -15,10 +15,10 @@ int main(int argc, char **argv) {
         return 0;
     }
     if (argc > 1 && !std::strcmp(argv[1], "block")) {
-        int positions, matrix_cores, capacity, head_dim;
+        int positions, matrix_cores, sequences, sized, capacity;
         long long groups;
-        while (std::scanf("%d %d %lld %d %d", &positions, &matrix_cores, &groups, &capacity, &head_dim) == 5)
-            std::printf("%d\n", mtp::attn_rows_serves(positions, matrix_cores != 0, groups, capacity, head_dim) ? 1 : 0);
+        while (std::scanf("%d %d %d %lld %d %d", &positions, &matrix_cores, &sequences, &groups, &sized, &capacity) == 6)
+            std::printf("%d\n", mtp::attn_rows_serves(positions, matrix_cores != 0, sequences, groups, sized != 0, capacity) ? 1 : 0);
         return 0;
     }
     int K, n, rows, head, pairs, cus, call_rows, d;

@@ -311,14 +311,19 @@ def test_small_heads_long_blocks_in_smaller_workgroups(gpu, hkv, hd):
     block_in_small_workgroups(gpu, 16, hkv, hd, 256, [0, 55, 127, 1, 30, 64, 90], [73, 73, 1, 0, 40, 64, 73], 73)
 
 
-def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m):
+def test_more_rounds_in_small_workgroups(gpu):
+    """Up to 40 rounds of 128 tokens where the splits are not sized by the lengths found: one context fills the cache."""
+    block_in_small_workgroups(gpu, 8, 8, 64, 256, [5102, 0, 127, 3000] * 5, [18, 19, 1, 4] * 5, 19, cap=5120)
+
+
+def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m, cap=2048):
     shape = synth.HeadShape(d, hq, hkv, hd, 512, 2048)
     wl = synth.Workload(f"small_{hq}_{hkv}_{hd}", 70 + hq + 3 * hkv + hd, shape, len(ctx), 0, 0, (512,), 1, 0.5, zipf_subset=False)
     w = synth.make_weights(wl)
     ids = synth.make_subsets(wl)[0]
     ext_len = np.array(ext, dtype=np.int32)
     # (splits of capacity * rows * hkv / 256 tokens: the matrix cores from 449 on, up to the next 64)
-    act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=2048)
+    act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=cap)
     hid, tok = extend_inputs(shape, act, m, 79 + hq + hkv + hd)
     ref, res, caches = run_extend(gpu, shape, w, w, act, [ids], 0, hid, tok, ext_len)
     assert res["err"] == 0

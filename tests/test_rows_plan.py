@@ -149,13 +149,17 @@ def test_narrow_heads_take_the_single_launch_where_it_is_ahead(driver, d, hq, hk
     assert out.stdout.split() == [str(int(single))], (step, 4 * hkv * hd * cap)
 
 
-@pytest.mark.parametrize("positions,groups,cap,hd,small", [
-    (1, 1024, 512, 128, 0), (2, 8, 64, 128, 1), (509, 1024, 512, 128, 1), (4, 128, 4160, 128, 1), (64, 128, 4096, 128, 1),
-    (8, 32, 6080, 128, 0), (8, 16, 1536, 64, 1), (6, 2, 2048, 64, 0), (64, 16, 4096, 64, 0), (16, 64, 2048, 64, 1),
-    (200, 50, 8256, 64, 0), (500, 126, 4544, 64, 1)])
-def test_attention_of_a_block_by_rounds_and_groups(driver, positions, groups, cap, hd, small):
-    """Small workgroups where the chip is full of them or a wave's rounds are few; one position never, and no block whose splits
-    the vector attention serves."""
-    out = subprocess.run([driver, "block"], input="".join(f"{positions} {mc} {groups} {cap} {hd}\n" for mc in (1, 0)),
+@pytest.mark.parametrize("positions,sequences,groups,sized,cap,small", [
+    (1, 512, 1024, 0, 512, 0),                                                       # one position: never
+    (509, 1, 1024, 0, 512, 1), (2, 4, 8, 1, 2048, 1), (64, 8, 512, 0, 1088, 1),      # up to 16 rounds of 128 tokens: always
+    (4, 16, 128, 1, 2049, 0), (4, 16, 128, 1, 4160, 0), (4, 16, 128, 1, 32832, 0),   # more, and splits by the lengths that are there
+    (8, 64, 512, 0, 4160, 1), (8, 64, 512, 0, 5120, 1), (8, 64, 512, 0, 5121, 0),    # more, and contexts that may differ
+    (8, 64, 1024, 0, 32832, 0), (4, 8, 32, 0, 4160, 0),
+    (500, 1, 1000, 0, 32832, 1), (64, 1, 128, 1, 8256, 0), (64, 1, 130, 1, 8256, 1), # one sequence
+])
+def test_attention_of_a_block_by_rounds_and_groups(driver, positions, sequences, groups, sized, cap, small):
+    """Small workgroups where no context can be long enough to keep the chip waiting for one wave's rounds; never in a block whose
+    splits the vector attention serves."""
+    out = subprocess.run([driver, "block"], input="".join(f"{positions} {mc} {sequences} {groups} {sized} {cap}\n" for mc in (1, 0)),
                          capture_output=True, text=True, check=True)
     assert out.stdout.split() == [str(small), "0"]
