@@ -551,7 +551,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
             for (int st = 0; st < NSTREAM; ++st) {
                 const float mm = s.ml[st][c][0], l = s.ml[st][c][1], a = s.acc[st][c][dd];
                 const bool seen = mm != -INFINITY; // (a stream without a token of the column adds nothing, whatever it holds)
-                const float w = seen ? exp_term(mm - M) : 0.f;
+                const float w = seen ? exp_weight(mm - M) : 0.f;
                 Ls += l * w;
                 A += (seen ? a : 0.f) * w;
             }

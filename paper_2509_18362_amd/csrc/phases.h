@@ -922,7 +922,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
 #pragma unroll
             for (int k = 0; k < ND; ++k) t[k][u] = u < nsplit ? ld_f32<PCOH>(src + (size_t)u * PW + lane + k * kWave) : 0.f;
         const float M = wave_max(m);
-        const float e = lane < nsplit ? exp_term(m - M) : 0.f;
+        const float e = lane < nsplit ? exp_weight(m - M) : 0.f;
         const float inv = 1.0f / wave_sum(l * e);
         float A[ND];
 #pragma unroll
@@ -946,7 +946,7 @@ __device__ __forceinline__ void merge_head(const DraftParams &p, int b, int hq, 
     M = wave_max(M);
     float Ls = 0.f;
     for (int s2 = lane; s2 < nsplit; s2 += kWave) {
-        float e = exp_term(w[s2] - M);
+        float e = exp_weight(w[s2] - M);
         w[s2] = e;
         Ls += ld_f32<PCOH>(src + (size_t)s2 * PW + HD + 1) * e;
     }
@@ -1032,7 +1032,7 @@ __device__ __forceinline__ void flow_merge(const DraftParams &p, int step, int v
                         const bool mine = ob + row + u * NR < o1 && sj < nsplit;
                         const float m = mine ? __uint_as_float(ml[u].x) : -INFINITY, mn = fmaxf(M[u], m);
                         const float mz = mn == -INFINITY ? 0.f : mn;
-                        const float f = exp_term(M[u] - mz), w = exp_term(m - mz);
+                        const float f = exp_weight(M[u] - mz), w = exp_weight(m - mz);
                         A[u] = A[u] * f + __uint_as_float(a[u].x) * w;
                         Ls[u] = Ls[u] * f + __uint_as_float(ml[u].z) * w;
                         M[u] = mn;
@@ -1043,7 +1043,7 @@ __device__ __forceinline__ void flow_merge(const DraftParams &p, int step, int v
                 if (ob + first_row + u * NR < o1) {
                     float mm = row16_max(M[u]);
                     if (wide) mm = rows_max(mm);
-                    const float w = M[u] == -INFINITY ? 0.f : exp_term(M[u] - mm);
+                    const float w = M[u] == -INFINITY ? 0.f : exp_weight(M[u] - mm);
                     float r = row16_sum(A[u] * w), t = row16_sum(Ls[u] * w);
                     if (wide) r = rows_sum(r), t = rows_sum(t);
                     const int o = ob + row + u * NR;
@@ -1225,7 +1225,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
                 for (int u = 0; u < N; ++u)
                     if (u < nl) mb = fmaxf(mb, sc[u][g]);
                 const float mz = mb == -INFINITY ? 0.f : mb; // nothing so far: weights of exp(-inf)
-                const float alpha = exp_term(mx[g] - mz);
+                const float alpha = exp_weight(mx[g] - mz);
                 mx[g] = mb;
                 sum[g] *= alpha;
 #pragma unroll
@@ -1233,7 +1233,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
 #pragma unroll
                 for (int u = 0; u < N; ++u)
                     if (u < nl) {
-                        const float pr = exp_term(sc[u][g] - mz);
+                        const float pr = exp_weight(sc[u][g] - mz);
                         sum[g] += pr;
                         acc[g][0] += pr * lo_half(vr[u].x);
                         acc[g][1] += pr * hi_half(vr[u].x);
@@ -1295,7 +1295,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
             float mw = mx[g];
             if (LPT == 8) mw = fmaxf(mw, dpp_f32<0x128>(mw)); // row_ror:8
             mw = rows_max(mw);
-            const float w = mx[g] == -INFINITY ? 0.f : exp_term(mx[g] - mw);
+            const float w = mx[g] == -INFINITY ? 0.f : exp_weight(mx[g] - mw);
             float sw = sum[g] * w;
             if (LPT == 8) sw += dpp_f32<0x128>(sw);
             sw = rows_sum(sw);
@@ -1327,7 +1327,7 @@ __device__ __forceinline__ void phase_attn(const DraftParams &p, int step, int v
             for (int w = 1; w < kWaves; ++w) M = fmaxf(M, s.m[g][w]);
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
-                const float f = s.m[g][w] == -INFINITY ? 0.f : exp_term(s.m[g][w] - M); // (a wave without a token)
+                const float f = s.m[g][w] == -INFINITY ? 0.f : exp_weight(s.m[g][w] - M); // (a wave without a token)
                 Ls += s.l[g][w] * f;
                 A += s.acc[w][g][dd] * f;
             }

@@ -1,5 +1,6 @@
 // Sums of csrc/exp_term.h over a vocabulary: reads lines "seed spread", writes the sum's relative error (terms as the kernel forms
-// them, added up in double) for normally distributed logits.
+// them, added up in double) for normally distributed logits.  With "weight": writes the largest relative error of a single weight
+// with an exponent of -80 to 0, and what it makes of 0 and -inf.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -12,7 +13,16 @@
 using std::fmaf;
 #include "../../paper_2509_18362_amd/csrc/exp_term.h"
 
-int main() {
+int main(int argc, char **) {
+    if (argc > 1) {
+        double worst = 0;
+        for (int i = 0; i <= 800000; ++i) {
+            const float t = -1e-4f * i;
+            worst = std::max(worst, std::fabs(mtp::exp_weight(t) / std::exp((double)t) - 1));
+        }
+        std::printf("%.6g %g %g\n", worst, mtp::exp_weight(0.f), mtp::exp_weight(-INFINITY));
+        return 0;
+    }
     unsigned seed;
     double spread;
     while (std::scanf("%u %lf", &seed, &spread) == 2) {
