@@ -204,10 +204,10 @@ __device__ __forceinline__ void flow_issue_lds(FlowLoad &L, const FlowTab &t, in
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(slot + u * 1024), 16,
                                                  voff + u * 1024, 0, 0, 2);
 }
-// The LDS slot's chunk was requested before the two register chunks that follow it in the stream and
-// loads complete in order: once at most those (2 CL) requests are outstanding it has landed.
-template <int CL>
-__device__ __forceinline__ void flow_wait_lds_slot() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CL) : "memory"); }
+// Every load that the wave has asked for has landed, the LDS slot's chunk among them.  (Not just all but the two register chunks that are
+// requested behind it: a phase of three chunks puts those off until its end, and the slot's is the last there is.  The compiler waits
+// like this before every pass of the loop over the chunks as it is, but for the registers' sake: it does not know of the slot.)
+__device__ __forceinline__ void flow_wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---- polling -----------------------------------------------------------------------------------------------
 // This thread's elements e = (it * kBlock + tid) * 4 .. + 3 < n of a tagged vector (n a multiple of 4), polled until
@@ -724,6 +724,7 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
             // after the first two.  Every register slot is refilled as soon as it is free; the LDS slot is refilled once,
             // at the end of the phase, with the third chunk of the phase that follows.
             int pend = 0; // register slots whose refill waits for the end of the phase
+            flow_wait_loads();
             for (int n0 = 0; n0 < nchunks; n0 += (n0 == 0 ? 3 : 2)) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
@@ -748,7 +749,6 @@ __device__ __forceinline__ void flow_steps(const DraftParams &p, char *smem, int
                     }
                 }
                 if (n0 == 0) {
-                    flow_wait_lds_slot<CL>();
                     consume([&](int u) { return *reinterpret_cast<const u32x4 *>(slot + u * 1024 + lane * 16); });
                     row_end(2);
                 }

@@ -508,6 +508,25 @@ def test_single_launch_gate_and_up_rows_left_over(gpu, d_ffn):
     eng.close()
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(1024, 8, 4, 128, 3072), (1024, 8, 8, 64, 2600), (2048, 16, 8, 128, 6144), (2080, 16, 4, 128, 11008),
+                                               (1536, 4, 1, 64, 256)])
+def test_single_launch_phases_of_three_chunks(gpu, d, hq, hkv, hd, d_ffn):
+    """Waves with three rows of one chunk (gate and up of 1024 wide heads; the narrow head's every 1536-row phase) or one row of three
+    (their down projections, in chunks of two, four and eight blocks): the third chunk, in the LDS slot, has nothing requested behind it."""
+    binding = gpu["binding"]
+    shape = synth.HeadShape(d, hq, hkv, hd, d_ffn, 2048)
+    wl = synth.Workload(f"three_{d}", 130 + d % 89, shape, 1, 0, 0, (512,), 3, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=np.array([70], dtype=np.int32), capacity=192)
+    eng = binding.DraftEngine(shape, w, [ids], 1, 192, 3)
+    assert binding.mtp_set_launch_mode(eng.handle, binding.LAUNCH_SINGLE) == 0
+    for _ in range(2):
+        ref, res, caches = run_both(gpu, shape, w, w, act, [ids], 0, 3, engine=eng)
+        check_chain(ref, res, caches, act["kv_len"], 3, need_clear=False)
+    eng.close()
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,d_ffn", [(256, 4, 4, 64, 256), (288, 2, 1, 128, 1000), (480, 8, 2, 64, 2048),
                                                (1024, 8, 4, 128, 520), (1056, 10, 5, 128, 4104), (2048, 16, 8, 128, 2600)])
 @pytest.mark.parametrize("ctx,cap", [(0, 64), (250, 256), (300, 320), (317, 352), (700, 768)])
