@@ -152,11 +152,11 @@ inline int attn_rows_waves(long long groups, int cus) { return groups <= cus ? 8
 // One sequence of a head with a reduction below 512: the single launch on a quarter of the compute units (flow.h), or one launch
 // per phase on all of them.  step_bytes: weights of a step, kv_bytes: keys and values up to the capacity (the lengths are on the
 // device).  What a launch per phase loses to its gaps a quarter of the units loses to reading more.  Three steps, us, single launch
-// / launch per phase: 2.6 MiB of weights 131 / 159, 3.8 146-158 / 152-161, 4.6 161 / 169, 5.3 157-166 / 156-164, 5.8 165-176 /
-// 160-168, 7.8 175-181 / 165-169; with 3.8 MiB of weights and 8 MiB of keys and values 166 / 174, 16 MiB 180 / 190 or (4.5 MiB,
-// 16 query heads) 194 / 188, 32 MiB 344 / 212.  (The lines were drawn with these; the single launch has since become 20 us shorter,
-// the first of them 108.)
-constexpr size_t kFlowNarrowBytes = 5 << 20, kFlowNarrowKvBytes = 8 << 20;
+// / launch per phase: 256 wide, 3.6 MiB of weights 122 / 151, 4.6 131 / 158, 5.6 140 / 160, 7.1 155 / 169, 8.6 169 / 173, 9.6 178 / 177
+// (wider ones meet later: 480 wide, 9.3 132 / 162, 18.7 185 / 185); with 4.5 MiB of weights, 16 query heads and 8 MiB of keys and values
+// 149 / 180, 16 MiB 168 / 177 (6.5 MiB of weights: 185 / 183), 32 MiB 303 / 193.  Of 317 heads within the lines none is below 1.04
+// times as fast so.
+constexpr size_t kFlowNarrowBytes = 8 << 20, kFlowNarrowKvBytes = 16 << 20;
 inline bool flow_narrow_serves(size_t step_bytes, size_t kv_bytes) {
     return step_bytes <= kFlowNarrowBytes && kv_bytes <= kFlowNarrowKvBytes;
 }

@@ -196,6 +196,7 @@ __global__ __launch_bounds__(kHistBlock) void k_subset_hist(const int *__restric
 // of pass p; then the bucket counts of the passes, then per-workgroup (above, ties) totals of the compaction, then
 // the slots of the sum of all counts
 constexpr int kCmpGroups = 160; // workgroups of the compaction: one round of 1024 ids each at 151 680 ids
+static_assert(kCmpGroups <= kSelBlock, "a thread for each workgroup's totals");
 constexpr int kSumSlots = 64;   // words the sum of all counts is spread over
 constexpr int kHistCopies = 2;  // and the bucket counts of a pass: a few dozen buckets hold most ids
 constexpr int kStateAfter = 4, kStateHist = 16, kStateTotals = kStateHist + kSelPasses * kSelBuckets * kHistCopies,
@@ -392,7 +393,7 @@ __global__ __launch_bounds__(kSelBlock) void k_subset_sel_hist(const unsigned *_
 
 // ---- compaction: the ids in ascending order, those with count > T plus the first r ties ----
 // Workgroup g owns a contiguous range of ids.  First every workgroup counts its (above, ties); then it adds up what the
-// workgroups before it hold (at most kSelGroups pairs) and places its own ids by two workgroup scans.
+// workgroups before it hold (one pair per thread) and places its own ids by two workgroup scans.
 __global__ __launch_bounds__(kSelBlock) void k_subset_cmp_count(const unsigned *__restrict__ counts, int V, SelPlan plan,
                                                                 unsigned *state) {
     __shared__ unsigned scratch[kSelBlock / 64], found[2];
