@@ -50,6 +50,130 @@ struct AttnMfmaLds {
     int len[JP], last[JP];                       // JP > 1: the positions' lengths, and whose splits this item completed
 };
 
+// One round of a wave: 32 tokens, of which the caller's K and V rows are in kn and vr (a lane group of HD / 8 lanes per row), against the
+// wave's sixteen columns.  tok0: the first of them, lim: how many tokens this lane's column sees; krow, vrow: the wave's strips in LDS (rows
+// of HD * 2 + 16 bytes; vrow where V does not stay in registers).  load_k and load_v request the next round's rows as soon as the
+// registers are free.  mx, lsum, oacc: the column's online softmax (in units of log2) and output.
+template <int HD, class LoadK, class LoadV>
+__device__ __forceinline__ void attn_round(int tok0, int lim, unsigned char *krow, unsigned char *vrow, const u32x4 (&kn)[2][HD / 32],
+                                           const u32x4 (&vr)[HD / 16], const u32x4 (&qh)[HD / 32], const u32x4 (&ql)[HD / 32],
+                                           const LoadK &load_k, const LoadV &load_v, float &mx, float &lsum, f32x4 (&oacc)[HD / 16]) {
+    constexpr bool VREG = HD == 128;
+    constexpr int NS = HD / 32, NDB = HD / 16, LPT = HD / 8, TPI = kWave / LPT, NV = 32 / TPI, VS = HD * 2 + 16;
+    static_assert(NV == HD / 16, "V rows of a lane");
+    const int lane = threadIdx.x & (kWave - 1), i16 = lane & 15, g4 = lane >> 4;
+    // which parked K row becomes row i16 of a score tile: with V in registers, row 4 g + e is token 4 e + g of the
+    // tile, so that a lane's eight scores belong to the eight tokens whose V rows it loaded
+    const int krd = VREG ? (i16 & 3) * 4 + (i16 >> 2) : i16;
+    // park the V rows, then request the next iteration's rows into the same registers
+    if constexpr (!VREG) {
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+            *reinterpret_cast<u32x4 *>(vrow + (size_t)(u * TPI + lane / LPT) * VS + (lane % LPT) * 16) = vr[u];
+    }
+    // K through the wave's strip into the operand layout: row i16, elements g4*HD/4 + 8u .. +8 for step u
+    u32x4 kcur[2][NS];
+#pragma unroll
+    for (int tl = 0; tl < 2; ++tl) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u)
+            *reinterpret_cast<u32x4 *>(krow + (size_t)(u * TPI + lane / LPT) * VS + (lane % LPT) * 16) = kn[tl][u];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int u = 0; u < NS; ++u)
+            kcur[tl][u] = *reinterpret_cast<const u32x4 *>(krow + (size_t)krd * VS + g4 * (HD / 2) + u * 16);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    load_k();
+    if constexpr (!VREG) load_v();
+
+    // scores of 2 x 16 tokens against the columns
+    f32x4 sc[2];
+#pragma unroll
+    for (int tl = 0; tl < 2; ++tl) {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            a = mfma16(kcur[tl][u], qh[u], a);
+            a = mfma16(kcur[tl][u], ql[u], a);
+        }
+        sc[tl] = a;
+    }
+    float sv[8] = {sc[0].x, sc[0].y, sc[0].z, sc[0].w, sc[1].x, sc[1].y, sc[1].z, sc[1].w};
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int tok = tok0 + (VREG ? e * 4 + g4 : (e >> 2) * 16 + g4 * 4 + (e & 3));
+        sv[e] = tok < lim ? sv[e] : -INFINITY;
+        tmax = fmaxf(tmax, sv[e]);
+    }
+    tmax = rows_max(tmax);
+    const float mnew = fmaxf(mx, tmax); // finite for a column that has seen a token (others: -inf, weights 0)
+    const float alpha = (mx == mnew) ? 1.0f : __builtin_amdgcn_exp2f(mx - mnew);
+    mx = mnew;
+    float pv[8], psum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        pv[e] = sv[e] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[e] - mnew);
+        psum += pv[e];
+    }
+    lsum = lsum * alpha + psum;
+    uint32_t ph[4], pl[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split_bf16x2(pv[2 * e], pv[2 * e + 1], ph[e], pl[e]);
+    const u32x4 pH = {ph[0], ph[1], ph[2], ph[3]}, pL = {pl[0], pl[1], pl[2], pl[3]};
+
+    if constexpr (VREG) {
+        // the lane's load u holds dimensions 8 i16 .. +8 of token 4 u + g4, the token whose probability sits in
+        // pv[u]: output block db takes dimension 8 i16 + db as its row i16, its eight depth elements are
+        // element db of the eight loads (a byte permute per pair), no LDS in between
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+            const uint32_t sel = (db & 1) ? 0x07060302u : 0x05040100u;
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t a = vr[2 * e][db >> 1], c = vr[2 * e + 1][db >> 1];
+                w[e] = __builtin_amdgcn_perm(c, a, sel);
+            }
+            const u32x4 va = {w[0], w[1], w[2], w[3]};
+            f32x4 o = oacc[db] * alpha;
+            o = mfma16(va, pH, o);
+            o = mfma16(va, pL, o);
+            oacc[db] = o;
+        }
+        load_v(); // the registers are free again
+    } else {
+    // the parked rows were written by this wave's own lanes; LDS operations of a wave complete in order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) {
+        // rows = dimensions db*16 + i16; depth slot g4, element e = token 4 g4 + e (e < 4) or 16 + 4 g4 + e - 4
+        const unsigned char *col = vrow + (db * 16 + i16) * 2;
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int ta = (e < 2 ? 0 : 16) + g4 * 4 + (2 * e & 3), tb = ta + 1;
+            const uint32_t a = *reinterpret_cast<const uint16_t *>(col + (size_t)ta * VS);
+            const uint32_t c = *reinterpret_cast<const uint16_t *>(col + (size_t)tb * VS);
+            w[e] = a | (c << 16);
+        }
+        const u32x4 va = {w[0], w[1], w[2], w[3]};
+        f32x4 o = oacc[db] * alpha;
+        o = mfma16(va, pH, o);
+        o = mfma16(va, pL, o);
+        oacc[db] = o;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // TICKET: as in phase_attn, the workgroup whose split of a (sequence, KV head) finishes last merges the splits.
 // QUEUE (and p.attn_queue set): the workgroups draw their items from one counter (p.attn_queue[0]) instead of taking
 // every nvb-th: contexts of a batch differ in length, the host does not know them, and a fixed assignment leaves the
@@ -386,119 +510,8 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
 #pragma unroll
         for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
         unsigned char *vrow = &s.v[L::VREG ? 0 : wave][0][0], *krow = &s.k[wave][0][0];
-        // which parked K row becomes row i16 of a score tile: with V in registers, row 4 g + e is token 4 e + g of the
-        // tile, so that a lane's eight scores belong to the eight tokens whose V rows it loaded
-        const int krd = L::VREG ? (i16 & 3) * 4 + (i16 >> 2) : i16;
-
-        for (int it = wave; it < niter; it += kWaves) {
-            // park the V rows, then request the next iteration's rows into the same registers
-            if constexpr (!L::VREG) {
-#pragma unroll
-                for (int u = 0; u < NV; ++u)
-                    *reinterpret_cast<u32x4 *>(vrow + (size_t)(u * TPI + lane / LPT) * L::VS + (lane % LPT) * 16) = vr[u];
-            }
-            // K through the wave's strip into the operand layout: row i16, elements g4*HD/4 + 8u .. +8 for step u
-            u32x4 kcur[2][NS];
-#pragma unroll
-            for (int tl = 0; tl < 2; ++tl) {
-#pragma unroll
-                for (int u = 0; u < NS; ++u)
-                    *reinterpret_cast<u32x4 *>(krow + (size_t)(u * TPI + lane / LPT) * L::VS + (lane % LPT) * 16) = kn[tl][u];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                for (int u = 0; u < NS; ++u)
-                    kcur[tl][u] = *reinterpret_cast<const u32x4 *>(krow + (size_t)krd * L::VS + g4 * (HD / 2) + u * 16);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
-            load_k(it + kWaves);
-            if constexpr (!L::VREG) load_v(it + kWaves);
-
-            // scores of 2 x 16 tokens against the G heads
-            f32x4 sc[2];
-#pragma unroll
-            for (int tl = 0; tl < 2; ++tl) {
-                f32x4 a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int u = 0; u < NS; ++u) {
-                    a = mfma16(kcur[tl][u], qh[u], a);
-                    a = mfma16(kcur[tl][u], ql[u], a);
-                }
-                sc[tl] = a;
-            }
-            float sv[8] = {sc[0].x, sc[0].y, sc[0].z, sc[0].w, sc[1].x, sc[1].y, sc[1].z, sc[1].w};
-            float tmax = -INFINITY;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int tok = it * 32 + (L::VREG ? e * 4 + g4 : (e >> 2) * 16 + g4 * 4 + (e & 3));
-                sv[e] = tok < lim ? sv[e] : -INFINITY;
-                tmax = fmaxf(tmax, sv[e]);
-            }
-            tmax = rows_max(tmax);
-            const float mnew = fmaxf(mx, tmax); // finite for a column that has seen a token (others: -inf, weights 0)
-            const float alpha = (mx == mnew) ? 1.0f : __builtin_amdgcn_exp2f(mx - mnew);
-            mx = mnew;
-            float pv[8], psum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                pv[e] = sv[e] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[e] - mnew);
-                psum += pv[e];
-            }
-            lsum = lsum * alpha + psum;
-            uint32_t ph[4], pl[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) split_bf16x2(pv[2 * e], pv[2 * e + 1], ph[e], pl[e]);
-            const u32x4 pH = {ph[0], ph[1], ph[2], ph[3]}, pL = {pl[0], pl[1], pl[2], pl[3]};
-
-            if constexpr (L::VREG) {
-                // the lane's load u holds dimensions 8 i16 .. +8 of token 4 u + g4, the token whose probability sits in
-                // pv[u]: output block db takes dimension 8 i16 + db as its row i16, its eight depth elements are
-                // element db of the eight loads (a byte permute per pair), no LDS in between
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) {
-                    const uint32_t sel = (db & 1) ? 0x07060302u : 0x05040100u;
-                    uint32_t w[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t a = vr[2 * e][db >> 1], c = vr[2 * e + 1][db >> 1];
-                        w[e] = __builtin_amdgcn_perm(c, a, sel);
-                    }
-                    const u32x4 va = {w[0], w[1], w[2], w[3]};
-                    f32x4 o = oacc[db] * alpha;
-                    o = mfma16(va, pH, o);
-                    o = mfma16(va, pL, o);
-                    oacc[db] = o;
-                }
-                load_v(it + kWaves); // the registers are free again
-            } else {
-            // the parked rows were written by this wave's own lanes; LDS operations of a wave complete in order
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-            for (int db = 0; db < NDB; ++db) {
-                // rows = dimensions db*16 + i16; depth slot g4, element e = token 4 g4 + e (e < 4) or 16 + 4 g4 + e - 4
-                const unsigned char *col = vrow + (db * 16 + i16) * 2;
-                uint32_t w[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int ta = (e < 2 ? 0 : 16) + g4 * 4 + (2 * e & 3), tb = ta + 1;
-                    const uint32_t a = *reinterpret_cast<const uint16_t *>(col + (size_t)ta * L::VS);
-                    const uint32_t c = *reinterpret_cast<const uint16_t *>(col + (size_t)tb * L::VS);
-                    w[e] = a | (c << 16);
-                }
-                const u32x4 va = {w[0], w[1], w[2], w[3]};
-                f32x4 o = oacc[db] * alpha;
-                o = mfma16(va, pH, o);
-                o = mfma16(va, pL, o);
-                oacc[db] = o;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            }
-        }
+        for (int it = wave; it < niter; it += kWaves)
+            attn_round<HD>(it * 32, lim, krow, vrow, kn, vr, qh, ql, [&] { load_k(it + kWaves); }, [&] { load_v(it + kWaves); }, mx, lsum, oacc);
 
         // ---- merge the waves (and the token being appended) through LDS ----
         lsum = rows_sum(lsum);

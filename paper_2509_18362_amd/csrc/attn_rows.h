@@ -111,12 +111,6 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
         split_bf16((e * cs + a * sn) * scale * kLog2e, s.qs[0][c][jj + HD / 2], s.qs[1][c][jj + HD / 2]);
     }
     lds_barrier();
-    // (a strip is written and read by its wave's own lanes; LDS operations of a wave complete in order)
-    auto ordered = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     u32x4 qh[NS], ql[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
@@ -132,90 +126,9 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     unsigned char *vrow = &s.v[L::VREG ? 0 : wave][0][0], *krow = &s.k[wave][0][0];
-    const int krd = L::VREG ? (i16 & 3) * 4 + (i16 >> 2) : i16;
     const int niter = (len + 31) / 32;
-    for (int it = wave; it < niter; it += W) {
-        if constexpr (!L::VREG) {
-#pragma unroll
-            for (int u = 0; u < NV; ++u)
-                *reinterpret_cast<u32x4 *>(vrow + (size_t)(u * TPI + lane / LPT) * L::VS + (lane % LPT) * 16) = vr[u];
-        }
-        u32x4 kcur[2][NS];
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-#pragma unroll
-            for (int u = 0; u < NS; ++u)
-                *reinterpret_cast<u32x4 *>(krow + (size_t)(u * TPI + lane / LPT) * L::VS + (lane % LPT) * 16) = kn[tl][u];
-            ordered();
-#pragma unroll
-            for (int u = 0; u < NS; ++u)
-                kcur[tl][u] = *reinterpret_cast<const u32x4 *>(krow + (size_t)krd * L::VS + g4 * (HD / 2) + u * 16);
-            ordered();
-        }
-        load_k(it + W);
-        if constexpr (!L::VREG) load_v(it + W);
-        float sv[8];
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int u = 0; u < NS; ++u) {
-                a = mfma16(kcur[tl][u], qh[u], a);
-                a = mfma16(kcur[tl][u], ql[u], a);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sv[4 * tl + e] = a[e];
-        }
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int tok = it * 32 + (L::VREG ? e * 4 + g4 : (e >> 2) * 16 + g4 * 4 + (e & 3));
-            sv[e] = tok < lim ? sv[e] : -INFINITY;
-            tmax = fmaxf(tmax, sv[e]);
-        }
-        tmax = rows_max(tmax);
-        const float mnew = fmaxf(mx, tmax); // finite for a column that has seen a token
-        const float alpha = (mx == mnew) ? 1.0f : __builtin_amdgcn_exp2f(mx - mnew);
-        mx = mnew;
-        float pv[8], psum = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            pv[e] = sv[e] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[e] - mnew);
-            psum += pv[e];
-        }
-        lsum = lsum * alpha + psum;
-        uint32_t ph[4], pl[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) split_bf16x2(pv[2 * e], pv[2 * e + 1], ph[e], pl[e]);
-        const u32x4 pH = {ph[0], ph[1], ph[2], ph[3]}, pL = {pl[0], pl[1], pl[2], pl[3]};
-        if constexpr (!L::VREG) ordered();
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            uint32_t w[4];
-            if constexpr (L::VREG) {
-                const uint32_t sel = (db & 1) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_perm(vr[2 * e + 1][db >> 1], vr[2 * e][db >> 1], sel);
-            } else {
-                const unsigned char *col = vrow + (db * 16 + i16) * 2;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int ta = (e < 2 ? 0 : 16) + g4 * 4 + (2 * e & 3);
-                    w[e] = (uint32_t) * reinterpret_cast<const uint16_t *>(col + (size_t)ta * L::VS) |
-                           ((uint32_t) * reinterpret_cast<const uint16_t *>(col + (size_t)(ta + 1) * L::VS) << 16);
-                }
-            }
-            const u32x4 va = {w[0], w[1], w[2], w[3]};
-            f32x4 o = oacc[db] * alpha;
-            o = mfma16(va, pH, o);
-            o = mfma16(va, pL, o);
-            oacc[db] = o;
-        }
-        if constexpr (L::VREG)
-            load_v(it + W); // the registers are free again
-        else
-            ordered();
-    }
+    for (int it = wave; it < niter; it += W)
+        attn_round<HD>(it * 32, lim, krow, vrow, kn, vr, qh, ql, [&] { load_k(it + W); }, [&] { load_v(it + W); }, mx, lsum, oacc);
     lsum = rows_sum(lsum);
     // the waves' results meet in the place of the tiles
     lds_barrier();
