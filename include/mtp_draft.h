@@ -175,7 +175,9 @@ int32_t mtp_accept(mtp_handle *h, int32_t B, int32_t K, const int32_t *draft, co
  *                positions >= ext_len[b] are unspecified)
  * A sequence whose block does not fit its cache (kv_len[b] + ext_len[b] > kv_capacity), or with a negative kv_len
  * or an ext_len outside 0 .. m_max, is left alone: drafts -1, cache and kv_len untouched, MTP_ERR_KV_OVERFLOW from
- * mtp_poll_error.  Always one launch per phase, whatever the launch mode.
+ * mtp_poll_error.  A position's outputs do not depend on later positions, as long as all values are finite: on the matrix cores
+ * positions share the rounds of 32 tokens they read, and a key or value that is not finite can make NaN of earlier positions of its
+ * sequence that read the same round.  Always one launch per phase, whatever the launch mode.
  */
 int32_t mtp_draft_extend(mtp_handle *h, int32_t B, int32_t m_max, int32_t subset_index, const void *hidden_in,
                          const int32_t *tokens, const int32_t *ext_len, void *k_cache, void *v_cache, int32_t *kv_len,
@@ -260,7 +262,7 @@ float mtp_last_draft_ms(mtp_handle *h);
  *               per step, and one launch more after a matrix phase whose reduction is split over workgroups and added
  *               up apart.  Matrices of 2 GiB or more: as mode 3.
  *   1           one sequence whose reduction lengths (d_model, n_q_heads * head_dim, d_ffn) are all at least 512, or that has a
- *               shorter one and reads at most 5 MiB of weights per step, with at most 8 MiB of keys and values up to
+ *               shorter one and reads at most 8 MiB of weights per step, with at most 16 MiB of keys and values up to
  *               kv_capacity: one launch runs all phases of all K steps, on one workgroup per compute unit in the first case, on
  *               a quarter of the units in the second; its workgroups hand
  *               their results over element by element (every element carries a tag naming the call, step and phase that
