@@ -248,12 +248,20 @@ def test_small_heads_block_of_positions_shared_reads(gpu, hq, hkv, hd):
 @pytest.mark.parametrize("d,ctx,ext,m", [
     (256, [0, 13, 96, 500], [19, 19, 7, 0], 19),   # row-major activations; rounds of 32 tokens per wave: several, one
     (256, [31, 109, 255, 125], [1, 19, 1, 4], 19), # or none; lengths on their edges, groups without a position
-    (512, [127, 30], [3, 2], 3),                   # six rows in operand order (the vector attention)
+    (512, [127, 30], [3, 2], 3),                   # six rows in operand order
 ])
 def test_small_heads_block_of_positions_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m):
-    """Blocks in caches of 2048 slots: the attention whose small workgroups serve 16 / G positions each over all
+    """Blocks in caches of a few hundred slots: the attention whose small workgroups serve 16 / G positions each over all
     their tokens, on every (group size, head dimension); here with eight waves."""
     block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m)
+
+
+@pytest.mark.parametrize("hq,hkv,hd", GEOMETRIES)
+@pytest.mark.parametrize("ctx,ext,m", [([0, 13, 96, 500], [19, 19, 7, 0], 19), ([31, 109, 255, 125], [1, 19, 1, 4], 19)])
+def test_blocks_of_positions_in_small_workgroups(gpu, hq, hkv, hd, ctx, ext, m):
+    """The same blocks in caches of 2048 slots: with fewer, splits are short and the vector attention serves most of them (splits of
+    capacity * rows * hkv / 256 tokens: the matrix cores from 449 on, up to the next 64)."""
+    block_in_small_workgroups(gpu, hq, hkv, hd, 256, ctx, ext, m, cap=2048)
 
 
 @pytest.mark.parametrize("hq,hkv,hd,ctx,ext,m", [
@@ -262,7 +270,7 @@ def test_small_heads_block_of_positions_in_small_workgroups(gpu, hq, hkv, hd, d,
 ])
 def test_blocks_of_few_rows_in_small_workgroups(gpu, hq, hkv, hd, ctx, ext, m):
     """The same attention, its results in the operand order of the kernel of up to sixteen rows."""
-    block_in_small_workgroups(gpu, hq, hkv, hd, 512, ctx, ext, m)
+    block_in_small_workgroups(gpu, hq, hkv, hd, 512, ctx, ext, m, cap=2048)
 
 
 @pytest.mark.parametrize("hq,hkv,hd,ctx,m,cap", [
@@ -311,18 +319,23 @@ def test_small_heads_long_blocks_in_smaller_workgroups(gpu, hkv, hd):
     block_in_small_workgroups(gpu, 16, hkv, hd, 256, [0, 55, 127, 1, 30, 64, 90], [73, 73, 1, 0, 40, 64, 73], 73)
 
 
+@pytest.mark.parametrize("hkv,hd", [(2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (4, 128), (8, 128), (16, 128)])
+def test_long_blocks_in_smaller_workgroups(gpu, hkv, hd):
+    """The same in caches of 2048 slots."""
+    block_in_small_workgroups(gpu, 16, hkv, hd, 256, [0, 55, 127, 1, 30, 64, 90], [73, 73, 1, 0, 40, 64, 73], 73, cap=2048)
+
+
 def test_more_rounds_in_small_workgroups(gpu):
     """Up to 40 rounds of 128 tokens where the splits are not sized by the lengths found: one context fills the cache."""
     block_in_small_workgroups(gpu, 8, 8, 64, 256, [5102, 0, 127, 3000] * 5, [18, 19, 1, 4] * 5, 19, cap=5120)
 
 
-def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m, cap=2048):
+def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m, cap=576):
     shape = synth.HeadShape(d, hq, hkv, hd, 512, 2048)
     wl = synth.Workload(f"small_{hq}_{hkv}_{hd}", 70 + hq + 3 * hkv + hd, shape, len(ctx), 0, 0, (512,), 1, 0.5, zipf_subset=False)
     w = synth.make_weights(wl)
     ids = synth.make_subsets(wl)[0]
     ext_len = np.array(ext, dtype=np.int32)
-    # (splits of capacity * rows * hkv / 256 tokens: the matrix cores from 449 on, up to the next 64)
     act = synth.make_activations(wl, ctx=np.array(ctx, dtype=np.int32), capacity=cap)
     hid, tok = extend_inputs(shape, act, m, 79 + hq + hkv + hd)
     ref, res, caches = run_extend(gpu, shape, w, w, act, [ids], 0, hid, tok, ext_len)

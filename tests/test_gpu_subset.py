@@ -68,7 +68,7 @@ def test_long_tailed_streams(gpu, V, logN, n):
 
 
 def test_full_vocabulary_and_use_as_output_head_list(gpu):
-    """The 7B vocabulary (151680 ids, four counting chunks) with the paper's list sizes; the built list is accepted
+    """The 7B vocabulary (151680 ids, one counting chunk) with the paper's list sizes; the built list is accepted
     as a compressed-head id list by mtp_draft_init (ascending, unique, in range)."""
     binding = gpu["binding"]
     V = synth.SEVEN_B.vocab_size
@@ -85,7 +85,7 @@ def test_full_vocabulary_and_use_as_output_head_list(gpu):
 
 @pytest.mark.parametrize("V", [80768, 80769, 155392, 155393, 201920, 201921])
 def test_every_field_width_and_chunk(gpu, V):
-    """The largest vocabulary of each field width and of a chunk, and larger ones: hot ids at both ends and in the middle of the
+    """The largest vocabulary of each field width and of a chunk, and one id more: hot ids at both ends and in the middle of the
     words, a long tail, ids out of range."""
     rng = np.random.default_rng(V)
     hot = rng.choice([0, 1, 2, 3, 4, V // 2, V - 2, V - 1], size=1 << 18)
@@ -99,10 +99,11 @@ def test_every_field_width_and_chunk(gpu, V):
     (4096, 8, 2, 24),          # 16-bit fields that wrap together, the second one carried into by the first
     (100000, 40, 8, 20),       # 8 bits: whole words full at a time, so that a carry runs through several fields
     (100000, 99996, 4, 20),    # the last word
-    (160000, 155, 100, 23),    # two chunks
-    (100000, 1000, 4000, 24),  # many ids, none of which wraps
-    (400000, 1000, 1500, 25),  # three chunks; more ids that wrap than the table of wraps has room for
+    (160000, 155, 400, 23),    # 6 bits, more ids that wrap than the table has room for
+    (100000, 1000, 4000, 24),  # 8 bits: a few wraps each
     (160001, 159996, 5, 20),   # the last word of the last id has one field in use
+    (160000, 155, 100, 23),    # two chunks (there are no fields of 6 bits any more: 160000 ids are two chunks of 16)
+    (400000, 1000, 1500, 25),  # three chunks; more ids that wrap than the table of wraps has room for
 ])
 def test_fields_that_wrap(gpu, V, base, ids, logN):
     """A field narrower than its count: exact counts whatever the order of the adds."""
