@@ -29,13 +29,17 @@ __device__ __forceinline__ uint32_t f32_to_bf16x2(float a, float b) {
 __device__ __forceinline__ float lo_half(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float hi_half(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }
 
-// x ~= hi + lo with hi, lo bf16: keeps 16 mantissa bits of a float activation through a bf16 MFMA
+// x ~= hi + lo with hi, lo bf16: keeps 16 mantissa bits of a float activation through a bf16 MFMA.  The halves are those of the float x
+// (contracted with the product that x often is, the difference would be of a number that is nowhere else: a lo half in some hundreds
+// rounds the other way, and then entries of the caches of a prompt or a training forward).
 __device__ __forceinline__ void split_bf16(float x, uint16_t &hi, uint16_t &lo) {
+#pragma clang fp contract(off)
     hi = f32_to_bf16(x);
     lo = f32_to_bf16(x - bf16_to_f32(hi));
 }
 // two of them (a in the low halves)
 __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t &hi, uint32_t &lo) {
+#pragma clang fp contract(off)
     hi = f32_to_bf16x2(a, b);
     lo = f32_to_bf16x2(a - lo_half(hi), b - hi_half(hi));
 }

@@ -343,6 +343,39 @@ def block_in_small_workgroups(gpu, hq, hkv, hd, d, ctx, ext, m, cap=576):
     check_extend(ref, res, caches, act, ext_len)
 
 
+@pytest.mark.parametrize("B", [1, 3, 12, 40])
+def test_activations_are_split_after_they_are_rounded(gpu, B):
+    """A normalised input x = g * (h * inv) goes through the products as bf16(x) + bf16(x - bf16(x)) of the float x.  The projection picks its
+    elements one by one and all else is zero, so that the step's output is that sum times one number; inputs are multiples of 1/16,
+    whose squares add up exactly in any order, so inv is known to the bit.  The output's scale and two roundings stay within 2^-22;
+    a lo half that rounds the other way is off by up to 2^-16."""
+    binding = gpu["binding"]
+    d = 1024
+    shape = synth.HeadShape(d, 8, 8, 128, 512, 2048)
+    rng = np.random.default_rng(600 + B)
+    w = {k: np.zeros(s, np.float32) for k, s in synth.weight_shapes(shape).items()}
+    for k in w:
+        if k.startswith("g_"):
+            w[k][:] = 1.0
+    w["g_hnorm"] = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(rng.uniform(0.5, 2.0, d).astype(np.float32)))
+    w["w_proj"][np.arange(d), np.arange(d)] = 1.0
+    w["embed"][:] = 1.0
+    eng = binding.DraftEngine(shape, {k: synth.f32_to_bf16_bits(v) for k, v in w.items()}, [np.arange(512, dtype=np.int32)], B, 64, 1)
+    zero = eng.to_device_bits(np.zeros((B, 8, 64, 128), np.uint16))
+    for _ in range(1 + 40 // B):
+        h = (rng.integers(1, 64, (B, d)) * rng.choice([-1, 1], (B, d)) / 16).astype(np.float32)
+        mean = ((h.astype(np.float64) ** 2).sum(-1) / d).astype(np.float32)
+        inv = np.float32(1) / np.sqrt(mean + np.float32(shape.rms_eps))
+        x = w["g_hnorm"] * (h * inv[:, None])
+        hi = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(x))
+        want = (hi + synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(x - hi))).astype(np.float64)
+        out = eng.draft(1, 0, eng.to_device_bits(synth.f32_to_bf16_bits(h)), eng.to_device_i32(np.zeros(B)), zero.clone(), zero.clone(),
+                        eng.to_device_i32(np.zeros(B)), want_hidden=True)
+        ratio = out["hidden"].cpu().numpy()[:, 0].astype(np.float64) / want
+        assert np.abs(ratio / np.median(ratio, axis=-1, keepdims=True) - 1).max() <= 2.0 ** -22
+    eng.close()
+
+
 def test_tiny_full_vocab_equals_identity_subset(gpu, tiny):
     """Eq. (3) with the identity list is the full head: same logits bit for bit on the device as well."""
     act = tiny["act"]
