@@ -50,6 +50,10 @@ struct AttnMfmaLds {
     int len[JP], last[JP];                       // JP > 1: the positions' lengths, and whose splits this item completed
 };
 
+// A query's pair of elements, turned: which of the two products is rounded by itself is said, so that all kernels give the same bits.
+__device__ __forceinline__ float rope_lower(float a, float b, float cs, float sn) { return fmaf(cs, a, -(sn * b)); }
+__device__ __forceinline__ float rope_upper(float a, float b, float cs, float sn) { return fmaf(cs, b, sn * a); }
+
 // One round of a wave: 32 tokens, of which the caller's K and V rows are in kn and vr (a lane group of HD / 8 lanes per row), against the
 // wave's sixteen columns.  tok0: the first of them, lim: how many tokens this lane's column sees; krow, vrow: the wave's strips in LDS (rows
 // of HD * 2 + 16 bytes; vrow where V does not stay in registers).  load_k and load_v request the next round's rows as soon as the
@@ -463,7 +467,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
             }
             if (c < NC) {
                 const float a = qa[r] + bf16_to_f32(bqa[r]), bb = qb[r] + bf16_to_f32(bqb[r]);
-                const float q0 = (a * cs - bb * sn) * scale, q1 = (bb * cs + a * sn) * scale;
+                const float q0 = rope_lower(a, bb, cs, sn) * scale, q1 = rope_upper(a, bb, cs, sn) * scale;
                 s.q[c][jj] = q0;
                 s.q[c][jj + HD / 2] = q1;
                 split_bf16(q0 * kLog2e, s.qs[0][c][jj], s.qs[1][c][jj]);

@@ -27,7 +27,7 @@ struct AttnRowsLds {
     };
     struct Merge { // (columns four banks apart)
         alignas(16) float acc[W][NC][HD + 4];
-        float ml[W][NC][2];
+        float ml[kWaves][NC][2];
     };
     union {
         Tiles t;
@@ -35,13 +35,17 @@ struct AttnRowsLds {
     };
 };
 
-// W: waves of the workgroup
+// W: waves of the workgroup.  Round r of 32 tokens belongs to stream r % 8, as in phase_attn_mfma, whose wave r % 8 has it: with four waves
+// each has two streams, in turn.  A context that is one split there gives the same bits here, with four waves as with eight (four
+// streams of twice the rounds are another order of the sums: 8e-5 of a prompt's logits, 3e-4 of a training forward's, through
+// cache entries that round to the neighbouring bf16 value).
 template <int G, int HD, int W>
 __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
     using L = AttnRowsLds<G, HD, W>;
     constexpr int kThreads = W * kWave;
     constexpr int JP = 16 / G, NC = 16, NS = HD / 32, NDB = HD / 16, LPT = HD / 8, TPI = kWave / LPT, NV = 32 / TPI;
-    constexpr float kLog2e = 1.4426950408889634f;
+    constexpr int PER = kWaves / W; // streams of a wave
+    constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
     const int lane = threadIdx.x & (kWave - 1), i16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     L &lds = *reinterpret_cast<L *>(smem);
@@ -107,8 +111,8 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
             rope_cos_sin(pos, inv_freq, cs, sn);
         }
         const float a = qa[k] + bf16_to_f32(ba[k]), e = qb[k] + bf16_to_f32(bb[k]);
-        split_bf16((a * cs - e * sn) * scale * kLog2e, s.qs[0][c][jj], s.qs[1][c][jj]);
-        split_bf16((e * cs + a * sn) * scale * kLog2e, s.qs[0][c][jj + HD / 2], s.qs[1][c][jj + HD / 2]);
+        split_bf16(rope_lower(a, e, cs, sn) * scale * kLog2e, s.qs[0][c][jj], s.qs[1][c][jj]);
+        split_bf16(rope_upper(a, e, cs, sn) * scale * kLog2e, s.qs[0][c][jj + HD / 2], s.qs[1][c][jj + HD / 2]);
     }
     lds_barrier();
     u32x4 qh[NS], ql[NS];
@@ -121,55 +125,76 @@ __device__ __forceinline__ void attn_rows(const DraftParams &p, char *smem) {
     int lim = 0; // tokens this lane's column sees
 #pragma unroll
     for (int u = 0; u < JP; ++u) lim = u == i16 / G ? lenj[u] : lim;
-    float mx = -INFINITY, lsum = 0.f;
-    f32x4 oacc[NDB];
+    float mx[PER], lsum[PER];
+    f32x4 oacc[PER][NDB];
 #pragma unroll
-    for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int v = 0; v < PER; ++v) {
+        mx[v] = -INFINITY;
+        lsum[v] = 0.f;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) oacc[v][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     unsigned char *vrow = &s.v[L::VREG ? 0 : wave][0][0], *krow = &s.k[wave][0][0];
     const int niter = (len + 31) / 32;
-    for (int it = wave; it < niter; it += W)
-        attn_round<HD>(it * 32, lim, krow, vrow, kn, vr, qh, ql, [&] { load_k(it + W); }, [&] { load_v(it + W); }, mx, lsum, oacc);
-    lsum = rows_sum(lsum);
-    // the waves' results meet in the place of the tiles
-    lds_barrier();
+    for (int it = wave; it < niter;) {
 #pragma unroll
-    for (int db = 0; db < NDB; db += L::VREG ? 4 : 1) // four neighbouring dimensions at a time
-#pragma unroll
-        for (int v = 0; v < (L::VREG ? 4 : 1); ++v) {
-            const f32x4 o = L::VREG ? f32x4{oacc[db][v], oacc[L::VREG ? db + 1 : 0][v], oacc[L::VREG ? db + 2 : 0][v], oacc[L::VREG ? db + 3 : 0][v]}
-                                    : oacc[db];
-            *reinterpret_cast<f32x4 *>(&lds.m.acc[wave][i16][L::VREG ? 8 * (4 * g4 + v) + db : db * 16 + g4 * 4]) = o;
+        for (int v = 0; v < PER; ++v) {
+            attn_round<HD>(it * 32, lim, krow, vrow, kn, vr, qh, ql, [&] { load_k(it + W); }, [&] { load_v(it + W); }, mx[v], lsum[v],
+                           oacc[v]);
+            it += W;
+            if (it >= niter) break;
         }
-    if (g4 == 0) {
-        lds.m.ml[wave][i16][0] = mx;
-        lds.m.ml[wave][i16][1] = lsum;
     }
-    lds_barrier();
-    // thread -> E neighbouring dimensions of column c
+    // The streams' results meet in the place of the tiles, one of every wave at a time, in order.  Thread -> E neighbouring
+    // dimensions of column c
     constexpr int E = NC * HD / kThreads;
     static_assert(E == 8 || E == 4 || E == 2, "pieces of a column");
     const int c = threadIdx.x / (HD / E), e0 = threadIdx.x % (HD / E) * E;
     int mine = 0;
 #pragma unroll
     for (int u = 0; u < JP; ++u) mine = u == c / G ? lenj[u] : mine;
-    if (mine == 0) return; // not part of the block
     float M = -INFINITY, ls = 0.f, r[E];
-#pragma unroll
-    for (int w = 0; w < W; ++w) M = fmaxf(M, lds.m.ml[w][c][0]);
 #pragma unroll
     for (int i = 0; i < E; ++i) r[i] = 0.f;
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const bool seen = lds.m.ml[w][c][0] != -INFINITY; // (a wave without a token of the column adds nothing, whatever it holds)
-        const float f = seen ? __builtin_amdgcn_exp2f(lds.m.ml[w][c][0] - M) : 0.f;
-        ls += f * lds.m.ml[w][c][1];
+    for (int v = 0; v < PER; ++v) {
+        lds_barrier();
 #pragma unroll
-        for (int i = 0; i < E; ++i) r[i] += f * (seen ? lds.m.acc[w][c][e0 + i] : 0.f);
+        for (int db = 0; db < NDB; db += L::VREG ? 4 : 1) // four neighbouring dimensions at a time
+#pragma unroll
+            for (int e = 0; e < (L::VREG ? 4 : 1); ++e) {
+                const f32x4 o = L::VREG ? f32x4{oacc[v][db][e], oacc[v][L::VREG ? db + 1 : 0][e], oacc[v][L::VREG ? db + 2 : 0][e],
+                                                oacc[v][L::VREG ? db + 3 : 0][e]}
+                                        : oacc[v][db];
+                *reinterpret_cast<f32x4 *>(&lds.m.acc[wave][i16][L::VREG ? 8 * (4 * g4 + e) + db : db * 16 + g4 * 4]) = o;
+            }
+        if (v == 0)
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const float l = rows_sum(lsum[u]);
+                if (g4 == 0) {
+                    lds.m.ml[u * W + wave][i16][0] = mx[u] * kLn2;
+                    lds.m.ml[u * W + wave][i16][1] = l;
+                }
+            }
+        lds_barrier();
+        if (v == 0)
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) M = fmaxf(M, lds.m.ml[w][c][0]);
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float mm = lds.m.ml[v * W + w][c][0];
+            const bool seen = mm != -INFINITY; // (a stream without a token of the column adds nothing, whatever it holds)
+            const float f = seen ? exp_weight(mm - M) : 0.f;
+            ls += lds.m.ml[v * W + w][c][1] * f;
+#pragma unroll
+            for (int i = 0; i < E; ++i) r[i] += (seen ? lds.m.acc[w][c][e0 + i] : 0.f) * f;
+        }
     }
-    const float inv = 1.0f / ls;
+    if (mine == 0) return; // not part of the block
     uint32_t h[E / 2], l[E / 2];
 #pragma unroll
-    for (int i = 0; i < E / 2; ++i) split_bf16x2(r[2 * i] * inv, r[2 * i + 1] * inv, h[i], l[i]);
+    for (int i = 0; i < E / 2; ++i) split_bf16x2(r[2 * i] / ls, r[2 * i + 1] / ls, h[i], l[i]);
     uint16_t *dst = p.attn_split + act_index(p, (jg * JP + c / G) * nseq + b, (kvh * G + c % G) * HD + e0);
     if constexpr (E == 8) {
         *reinterpret_cast<u32x4 *>(dst) = u32x4{h[0], h[1], h[2], h[3]};

@@ -325,6 +325,40 @@ def test_long_blocks_in_smaller_workgroups(gpu, hkv, hd):
     block_in_small_workgroups(gpu, 16, hkv, hd, 256, [0, 55, 127, 1, 30, 64, 90], [73, 73, 1, 0, 40, 64, 73], 73, cap=2048)
 
 
+@pytest.mark.parametrize("hq,hkv,hd", GEOMETRIES + [(16, 8, 64), (16, 16, 128)])
+def test_small_workgroups_give_the_bits_of_the_splits(gpu, hq, hkv, hd):
+    """A cache of 1024 slots (small workgroups: of eight waves, in the last two cases of four) and one of 16448 (splits of 4096
+    tokens, each of these contexts is one): the same tokens in eight sums, so the same bits."""
+    torch, binding = gpu["torch"], gpu["binding"]
+    m, short, long = 73, 1024, 16448
+    ctx = np.array([0, 55, 127, 1, 950, 300][:6 if hkv >= 8 else 3] + [900], dtype=np.int32)
+    groups = len(ctx) * hkv * -(-m * (hq // hkv) // 16)
+    assert len(ctx) * m > 128 and (groups > 256) == (hkv >= 8)  # splits not sized by the lengths; waves of a workgroup
+    shape = synth.HeadShape(256, hq, hkv, hd, 512, 2048)
+    wl = synth.Workload(f"bits_{hq}_{hkv}_{hd}", 170 + hq + 3 * hkv + hd, shape, len(ctx), 0, 0, (512,), 1, 0.5, zipf_subset=False)
+    w = synth.make_weights(wl)
+    ids = synth.make_subsets(wl)[0]
+    act = synth.make_activations(wl, ctx=ctx, capacity=short)
+    hid, tok = extend_inputs(shape, act, m, 171)
+    ext_len = np.array([m, 60, m, 0, m, 19][:len(ctx) - 1] + [40], dtype=np.int32)
+    got = []
+    for cap in (short, long):
+        eng = binding.DraftEngine(shape, w, [ids], len(ctx) * m, cap, 1)
+        caches = []
+        for name in ("k_cache", "v_cache"):
+            c = torch.zeros((len(ctx), hkv, cap, hd), dtype=torch.int16, device="cuda:0")
+            c[:, :, :short] = eng.to_device_bits(act[name])
+            caches.append(c)
+        out = eng.extend(0, eng.to_device_bits(hid), eng.to_device_i32(tok), eng.to_device_i32(ext_len), *caches,
+                         eng.to_device_i32(act["kv_len"]), want_logits=True, want_hidden=True)
+        live = np.arange(m)[:, None] < ext_len[None, :]
+        got.append([out[k].cpu().numpy()[live] for k in ("logits", "hidden", "draft")])
+        eng.close()
+    assert np.isfinite(got[0][0]).all()
+    for small, split in zip(*got):
+        np.testing.assert_array_equal(small, split)
+
+
 def test_more_rounds_in_small_workgroups(gpu):
     """Up to 40 rounds of 128 tokens where the splits are not sized by the lengths found: one context fills the cache."""
     block_in_small_workgroups(gpu, 8, 8, 64, 256, [5102, 0, 127, 3000] * 5, [18, 19, 1, 4] * 5, 19, cap=5120)
