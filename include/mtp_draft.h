@@ -338,7 +338,7 @@ int32_t mtp_subset_build(const int32_t *tokens, int64_t n_tokens, int32_t vocab_
  *   vocab_size   at most mtp_subset_static_max_vocab() (262144 ids: the array is 1 MiB + 98 KB per GPU, held until
  *                the process ends); larger vocabularies return MTP_ERR_WORKSPACE with a message on stderr
  * The array has no room for the per-workgroup copies of the bins, so the counting kernel adds its bins to the counts
- * with atomics instead: about twice the time (191 us against 88) of mtp_subset_build on a stream of 2^26 tokens.
+ * with atomics instead: about twice the time (195 us against 83) of mtp_subset_build on a stream of 2^26 tokens.
  * Every call on a GPU uses that GPU's one array (its contents are cleared at the start of each call): calls that
  * overlap on one GPU - different streams, or graphs replayed concurrently - race and must be serialised by the
  * caller.  The first call on a device looks the array's address up (a host-side query, no allocation).

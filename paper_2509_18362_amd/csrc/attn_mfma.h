@@ -151,30 +151,30 @@ __device__ __forceinline__ void attn_round(int tok0, int lim, unsigned char *kro
         }
         load_v(); // the registers are free again
     } else {
-    // the parked rows were written by this wave's own lanes; LDS operations of a wave complete in order
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // the parked rows were written by this wave's own lanes; LDS operations of a wave complete in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-        // rows = dimensions db*16 + i16; depth slot g4, element e = token 4 g4 + e (e < 4) or 16 + 4 g4 + e - 4
-        const unsigned char *col = vrow + (db * 16 + i16) * 2;
-        uint32_t w[4];
+        for (int db = 0; db < NDB; ++db) {
+            // rows = dimensions db*16 + i16; depth slot g4, element e = token 4 g4 + e (e < 4) or 16 + 4 g4 + e - 4
+            const unsigned char *col = vrow + (db * 16 + i16) * 2;
+            uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int ta = (e < 2 ? 0 : 16) + g4 * 4 + (2 * e & 3), tb = ta + 1;
-            const uint32_t a = *reinterpret_cast<const uint16_t *>(col + (size_t)ta * VS);
-            const uint32_t c = *reinterpret_cast<const uint16_t *>(col + (size_t)tb * VS);
-            w[e] = a | (c << 16);
+            for (int e = 0; e < 4; ++e) {
+                const int ta = (e < 2 ? 0 : 16) + g4 * 4 + (2 * e & 3), tb = ta + 1;
+                const uint32_t a = *reinterpret_cast<const uint16_t *>(col + (size_t)ta * VS);
+                const uint32_t c = *reinterpret_cast<const uint16_t *>(col + (size_t)tb * VS);
+                w[e] = a | (c << 16);
+            }
+            const u32x4 va = {w[0], w[1], w[2], w[3]};
+            f32x4 o = oacc[db] * alpha;
+            o = mfma16(va, pH, o);
+            o = mfma16(va, pL, o);
+            oacc[db] = o;
         }
-        const u32x4 va = {w[0], w[1], w[2], w[3]};
-        f32x4 o = oacc[db] * alpha;
-        o = mfma16(va, pH, o);
-        o = mfma16(va, pL, o);
-        oacc[db] = o;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -558,8 +558,7 @@ __device__ void phase_attn_mfma(const DraftParams &p, int step, int vb, int nvb,
                 if (len_c == 0 || sp >= nsplit_c) continue; // not part of the block, or this split is past its end
                 row = (jg * JP + jp) * nseq + b;
             }
-            // (no branch per stream: all of a thread's reads are on their way together.  Three id lists at 24 sequences, 3 steps:
-            // 874 -> 866 us; 16 sequences 643 -> 640)
+            // (no branch per stream: all of a thread's reads are on their way together)
             float M = -INFINITY;
 #pragma unroll
             for (int st = 0; st < NSTREAM; ++st) M = fmaxf(M, s.ml[st][c][0]);

@@ -8,9 +8,9 @@
 // between 5 us of set-up and 5 us until the waves' results have met.  Here an item is small - 33 KB of LDS, the merge in the
 // place of the tiles, results written whole - so that several of them share a unit and one's set-up and merge pass while others
 // multiply.  What bounds it is the chain of a wave's rounds of 32 tokens, 1.2 us each.  509 positions of an
-// empty cache, 32 query and 8 KV heads of 128: 75 us there, 24 here (four waves; eight: 34; with the registers cut for three or four
-// waves per SIMD 26 and 40, with a wave per item and no merge 43).  Where there are fewer items than units, eight waves: 16
-// sequences x 4 behind 512 .. 4096 tokens 52 us there, 49 here (four: 50), one x 4 behind 2048 20 and 17.5 (22).
+// empty cache, 32 query and 8 KV heads of 128: 75 us there, 30 here with four waves, 34 with eight.  (24 with four sums of a column's
+// tokens instead of eight, see below; of those: 26 and 40 with the registers cut for three or four waves per SIMD, 43 with a wave per
+// item and no merge.)  Where there are fewer items than units, eight waves.
 #pragma once
 #include "attn_mfma.h"
 

@@ -862,7 +862,7 @@ int32_t run_draft(mtp_handle *h, int32_t B, int32_t K, int32_t subset_index, con
     // carry the tags of the captured call - takes one launch per phase instead (those kernels keep no state across
     // calls on the host).
     // Heads with shorter reductions take a quarter of the units, where that is enough to read their weights (256 wide, 4096 rows,
-    // three steps: 129 us with 64 workgroups, 128 with 256, 159 with a launch per phase).  Their calls may overlap others, so
+    // three steps: 122 us with 64 workgroups, 151 with a launch per phase).  Their calls may overlap others, so
     // their workgroups make sure that all of them are there before they wait for one another's results (flow_admit).
     const bool wide = p.d >= 512 && p.qd >= 512 && p.F >= 512;
     const size_t step_bytes = 2 * ((size_t)p.d * (2 * p.d + p.qkv_dim + p.qd + 3 * (size_t)p.F) + (size_t)p.n * p.d);

@@ -140,6 +140,8 @@ inline RowsRoute rows_route(const RowsCall &c, bool all_few, int cus) {
 //   not sized:  25, 33, 49, 129 rounds           1.02, 1.07;  1.00, 1.10     1.11, 1.18;  1.07, 1.18     1.02, 1.14;  0.93, 1.08     0.88, 1.17;  0.67, 0.87
 //               (fewer than 64 groups: 25, 33    0.98, 1.00;  0.98, 1.00     0.92;  0.93)
 //   one sequence, more than 16 rounds: two groups per round or more 1.03, 1.25; fewer 0.43, 0.87
+// (Those with workgroups of four waves had four sums of a column's tokens then.  With eight, 264 blocks of 5 to 40 rounds that are served:
+// mean 1.18; least 0.975 with all contexts at the capacity, 17 rounds, 289 us / 296, and 0.988 with one, 40 rounds, 114 / 116.)
 inline bool attn_rows_serves(int positions, bool matrix_cores, int sequences, long long groups, bool sized, int capacity) {
     const int rounds = (capacity + 127) / 128;
     if (positions < 2 || !matrix_cores) return false;
