@@ -161,7 +161,8 @@ __device__ __forceinline__ void rows_gemm(const DraftParams &pin, Make make_phas
     // Workgroups of a call with one block of rows start at different places of their rows (and come back to the beginning):
     // rows lie a power of two apart, and while all of them read the same 128 bytes of their rows only some of the memory
     // channels have work (64 rows, 32768 weight rows of 8 KB: 71 us without, 63 with).  The workgroups of a die are spread evenly
-    // over the reduction (five steps on from one to the next left some of 32 close together: 2 % more).  With several blocks of rows the
+    // over the reduction (five steps on from one to the next left some of 32 close together; three id lists at 24 sequences, whole call:
+    // within what runs differ by).  With several blocks of rows the
     // workgroups of a die stay together instead, so that the activations they read come from their L2.
     // (HALF: a reduction of an odd number of 32s in steps of 64.  The half step keeps its place at the end, kw ends the whole
     // ones; what its second half brings lies behind the rows' ends and is not multiplied.  Kernels of its own, because the
